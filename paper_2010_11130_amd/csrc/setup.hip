@@ -1329,42 +1329,63 @@ __global__ __launch_bounds__(1024) void k_inv_lds(int n, const double* __restric
   }
 }
 
-// CSR transpose: counts, offsets, scatter with an atomic cursor, then each
-// row sorted by column so the result does not depend on scheduling.
-__global__ void k_tcount(int64_t n, const int64_t* __restrict__ rp, const int32_t* __restrict__ ci,
-                         int32_t* __restrict__ cnt) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+// CSR transpose: counts, offsets, scatter with an atomic cursor into scratch,
+// then each row placed in column order so the result does not depend on
+// scheduling.
+__global__ __launch_bounds__(256) void k_tcount(int64_t n, const int64_t* __restrict__ rp,
+                                                const int32_t* __restrict__ ci, int32_t* __restrict__ cnt) {
+  const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t i = gid / PG;
   if (i >= n) return;
-  for (int64_t k = rp[i]; k < rp[i + 1]; ++k) atomicAdd(&cnt[ci[k]], 1);
+  for (int64_t k = rp[i] + gid % PG; k < rp[i + 1]; k += PG) atomicAdd(&cnt[ci[k]], 1);
 }
 
-__global__ void k_tscatter(int64_t n, const int64_t* __restrict__ rp, const int32_t* __restrict__ ci,
-                           const double* __restrict__ v, const int64_t* __restrict__ tp, int32_t* __restrict__ cur,
-                           int32_t* __restrict__ tc, double* __restrict__ tv) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+__global__ __launch_bounds__(256) void k_tscatter(int64_t n, const int64_t* __restrict__ rp,
+                                                  const int32_t* __restrict__ ci, const double* __restrict__ v,
+                                                  const int64_t* __restrict__ tp, int32_t* __restrict__ cur,
+                                                  int32_t* __restrict__ tc, double* __restrict__ tv) {
+  const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t i = gid / PG;
   if (i >= n) return;
-  for (int64_t k = rp[i]; k < rp[i + 1]; ++k) {
-    int32_t j = ci[k];
-    int64_t pos = tp[j] + atomicAdd(&cur[j], 1);
+  for (int64_t k = rp[i] + gid % PG; k < rp[i + 1]; k += PG) {
+    const int32_t j = ci[k];
+    const int64_t pos = tp[j] + atomicAdd(&cur[j], 1);
     tc[pos] = (int32_t)i;
     if (tv) tv[pos] = v ? v[k] : 1.0;
   }
 }
 
-__global__ void k_rowsort(int64_t n, const int64_t* __restrict__ tp, int32_t* __restrict__ tc, double* __restrict__ tv) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  for (int64_t a = tp[i] + 1; a < tp[i + 1]; ++a) {
-    int32_t kc = tc[a];
-    double kv = tv ? tv[a] : 0.0;
-    int64_t b = a - 1;
-    while (b >= tp[i] && tc[b] > kc) {
-      tc[b + 1] = tc[b];
-      if (tv) tv[b + 1] = tv[b];
-      --b;
+// Place the scattered entries of each transposed row by rank: G lanes per
+// row, each counts the row's smaller columns (all distinct) against its own,
+// which the lanes of the group pass round by shuffles.  Latency bound: a row
+// costs one dependent load per G entries and ceil(len/G)^2 G compares.  It
+// replaced an insertion sort by one thread per row in global memory, a serial
+// chain of loads and stores quadratic in the row (2+1-D, p = 2, mapped 16^3
+// mesh with adjoint operators: 20 launches of 1097 us on average, the longest
+// rows of the coarse levels deciding each; now 40 us a wave per row, 7 us 16 lanes per row).
+template <int G>
+__global__ __launch_bounds__(256) void k_rowrank(int64_t n, const int64_t* __restrict__ tp,
+                                                 const int32_t* __restrict__ sc, const double* __restrict__ sv,
+                                                 int32_t* __restrict__ tc, double* __restrict__ tv) {
+  const int g = threadIdx.x % G;
+  for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / G; i < n;
+       i += (int64_t)gridDim.x * blockDim.x / G) {
+    const int64_t a = tp[i];
+    const int len = (int)(tp[i + 1] - a);
+    for (int k0 = 0; k0 < len; k0 += G) {
+      const int k = k0 + g;
+      const int32_t own = k < len ? sc[a + k] : INT32_MAX;
+      int rank = 0;
+      for (int q0 = 0; q0 < len; q0 += G) {
+        const int32_t other = q0 == k0 ? own : q0 + g < len ? sc[a + q0 + g] : INT32_MAX;
+#pragma unroll
+        for (int q = 0; q < G; ++q) rank += __shfl(other, q, G) < own;
+      }
+      if (k < len) {
+        tc[a + rank] = own;
+        if (tv) tv[a + rank] = sv[a + k];
+      }
     }
-    tc[b + 1] = kc;
-    if (tv) tv[b + 1] = kv;
   }
 }
 
@@ -1417,16 +1438,27 @@ static ah_status transpose(int64_t nrow, int64_t ncol, const int64_t* rp, const 
   int32_t* cnt = nullptr;
   AH_TRY(tmp.get(&cnt, ncol + 1));
   AH_HIP(hipMemsetAsync(cnt, 0, (ncol + 1) * sizeof(int32_t), st));
-  hipLaunchKernelGGL(k_tcount, g1(nrow), dim3(256), 0, st, nrow, rp, ci, cnt);
+  hipLaunchKernelGGL(k_tcount, g1(nrow * PG), dim3(256), 0, st, nrow, rp, ci, cnt);
   AH_LAUNCHED();
   AH_TRY(ar.get(tp, ncol + 1));
   AH_TRY(scan_i32_to_i64(cnt, *tp, ncol, st, tmp));
   AH_TRY(ar.get(tc, nnz));
   if (tv) AH_TRY(ar.get(tv, nnz));
   AH_HIP(hipMemsetAsync(cnt, 0, (ncol + 1) * sizeof(int32_t), st));
-  hipLaunchKernelGGL(k_tscatter, g1(nrow), dim3(256), 0, st, nrow, rp, ci, v, *tp, cnt, *tc, tv ? *tv : nullptr);
+  int32_t* sc = nullptr;
+  double* sv = nullptr;
+  AH_TRY(tmp.get(&sc, nnz));
+  if (tv) AH_TRY(tmp.get(&sv, nnz));
+  hipLaunchKernelGGL(k_tscatter, g1(nrow * PG), dim3(256), 0, st, nrow, rp, ci, v, *tp, cnt, sc, sv);
   AH_LAUNCHED();
-  hipLaunchKernelGGL(k_rowsort, g1(ncol), dim3(256), 0, st, ncol, *tp, *tc, tv ? *tv : nullptr);
+  // a wave per row from 24 entries a row on (coarse operators, whose longest
+  // rows have several hundred); 16 lanes below (restrictions, P)
+  if (nnz > 24 * ncol)
+    hipLaunchKernelGGL(k_rowrank<64>, dim3((unsigned)std::min<int64_t>(cdiv(ncol, 4), 1 << 22)), dim3(256), 0, st,
+                       ncol, *tp, sc, sv, *tc, tv ? *tv : nullptr);
+  else
+    hipLaunchKernelGGL(k_rowrank<16>, dim3((unsigned)std::min<int64_t>(cdiv(ncol, 16), 1 << 22)), dim3(256), 0, st,
+                       ncol, *tp, sc, sv, *tc, tv ? *tv : nullptr);
   AH_LAUNCHED();
   return AH_OK;
 }
