@@ -99,51 +99,215 @@ __global__ void k_sum_final(int nb, const double* __restrict__ partial, double* 
   }
 }
 
-// f(X) = sum_k c_k exp(-|X - X_k|^2 / (2 w^2))
-__global__ void k_gauss(int64_t npts, int D, const double* __restrict__ X, int K, const double* __restrict__ C,
-                        double inv2w2, const double* __restrict__ c, double* __restrict__ f) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= npts) return;
-  double x[3] = {0, 0, 0};
-  for (int a = 0; a < D; ++a) x[a] = X[i * D + a];
-  double s = 0.0;
-  for (int k = 0; k < K; ++k) {
-    double r2 = 0.0;
-    for (int a = 0; a < D; ++a) { double d = x[a] - C[k * D + a]; r2 += d * d; }
-    s += c[k] * exp(-r2 * inv2w2);
-  }
-  f[i] = s;
+// 2^(j/32) rounded to double, and what the rounding left out.
+__constant__ const double EXP_HI[32] = {
+    0x1.0000000000000p+0, 0x1.059b0d3158574p+0, 0x1.0b5586cf9890fp+0, 0x1.11301d0125b51p+0,
+    0x1.172b83c7d517bp+0, 0x1.1d4873168b9aap+0, 0x1.2387a6e756238p+0, 0x1.29e9df51fdee1p+0,
+    0x1.306fe0a31b715p+0, 0x1.371a7373aa9cbp+0, 0x1.3dea64c123422p+0, 0x1.44e086061892dp+0,
+    0x1.4bfdad5362a27p+0, 0x1.5342b569d4f82p+0, 0x1.5ab07dd485429p+0, 0x1.6247eb03a5585p+0,
+    0x1.6a09e667f3bcdp+0, 0x1.71f75e8ec5f74p+0, 0x1.7a11473eb0187p+0, 0x1.82589994cce13p+0,
+    0x1.8ace5422aa0dbp+0, 0x1.93737b0cdc5e5p+0, 0x1.9c49182a3f090p+0, 0x1.a5503b23e255dp+0,
+    0x1.ae89f995ad3adp+0, 0x1.b7f76f2fb5e47p+0, 0x1.c199bdd85529cp+0, 0x1.cb720dcef9069p+0,
+    0x1.d5818dcfba487p+0, 0x1.dfc97337b9b5fp+0, 0x1.ea4afa2a490dap+0, 0x1.f50765b6e4540p+0};
+__constant__ const float EXP_LO[32] = {
+    0.0f, 5.109225029e-17f, 8.551889706e-17f, -7.899853967e-17f, -3.046782080e-17f, 1.041027846e-16f,
+    8.912812676e-17f, 3.829204837e-17f, 3.982015231e-17f, -7.712630693e-17f, 4.658027592e-17f, 2.667932131e-18f,
+    2.538250279e-17f, -2.858731210e-17f, 7.700948380e-17f, -6.770511659e-17f, -9.667293313e-17f, -3.023758135e-17f,
+    -3.483994557e-17f, -1.016455328e-16f, 7.949834810e-17f, -1.013691647e-17f, 2.470719257e-17f, -1.012567991e-16f,
+    8.199010021e-17f, -1.851380418e-17f, 2.960140695e-17f, 1.822745843e-17f, 3.283107224e-17f, -6.122763413e-17f,
+    -1.061994606e-16f, 8.960767791e-17f};
+
+// exp(x) for x <= 0 (NaN stays NaN), by the table-driven method of P. T. P.
+// Tang (ACM TOMS 15, 1989): x = (32 e + j) ln2/32 + r with |r| <= ln2/64,
+// exp(x) = 2^e 2^(j/32) (1 + p(r)), p the Taylor series to r^6 (next term
+// below 4e-18), the table with its rounding error, in LDS (its 32 doubles
+// fill the 64 banks once).  14 FP64 operations instead of the general
+// function's about 25.
+__device__ inline double exp_neg(double x, const double* hi, const float* lo) {
+  x = x < -746.0 ? -746.0 : x;   // 0 either way
+  const double magic = 6755399441055744.0;   // 1.5 * 2^52: rounds to an integer in the low bits
+  const double t = fma(x, 0x1.71547652b82fep+5, magic);
+  const double k = t - magic;
+  const int n = __double2loint(t);
+  double r = fma(k, -0x1.62e42fefa39efp-6, x);   // exact: both are multiples of 2^-58
+  r = fma(k, -0x1.abc9e3b39803fp-61, r);
+  double q = fma(r, 1.0 / 720.0, 1.0 / 120.0);
+  q = fma(r, q, 1.0 / 24.0);
+  q = fma(r, q, 1.0 / 6.0);
+  q = fma(r, q, 0.5);
+  const double p = fma(r * r, q, r);
+  const double h = hi[n & 31];
+  return ldexp(h + fma(h, p, (double)lo[n & 31]), n >> 5);
 }
 
-// partial[k][blk] = sum over the block's points of y(X) phi_k(X)
-__global__ __launch_bounds__(256) void k_gauss_t(int64_t npts, int D, const double* __restrict__ X, int K,
-                                                 const double* __restrict__ C, double inv2w2,
-                                                 const double* __restrict__ y, double* __restrict__ partial, int nblk) {
-  __shared__ double red[256];
-  const int k = blockIdx.y;
-  double ck[3] = {0, 0, 0};
-  for (int a = 0; a < D; ++a) ck[a] = C[k * D + a];
-  double s = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < npts; i += (int64_t)nblk * 256) {
-    double r2 = 0.0;
-    for (int a = 0; a < D; ++a) { double d = X[i * D + a] - ck[a]; r2 += d * d; }
-    s += y[i] * exp(-r2 * inv2w2);
+__device__ inline void exp_table(double* hi, float* lo) {
+  if (threadIdx.x < 32) {
+    hi[threadIdx.x] = EXP_HI[threadIdx.x];
+    lo[threadIdx.x] = EXP_LO[threadIdx.x];
   }
+  __syncthreads();
+}
+
+// -|x - X_k|^2 / (2 w^2)
+template <int D>
+__device__ inline double gauss_arg(const double* x, const double* __restrict__ c, double inv2w2) {
+  double r2 = 0.0;
+#pragma unroll
+  for (int a = 0; a < D; ++a) { const double d = x[a] - c[a]; r2 += d * d; }
+  return -r2 * inv2w2;
+}
+
+// f(X) = sum_k c_k exp(-|X - X_k|^2 / (2 w^2)): S waves share 64 P points, each
+// with every S-th centre, whose coordinates are wave-uniform (scalar) loads.
+// Bound by the FP64 vector units: about 24 operations per (point, centre)
+// pair against 8 (D + 1) bytes per point.  5.3M points x 256 centres: 1997 us
+// with the general exponential and a point per thread, 1278 us now.
+template <int D, int P, int S>
+__global__ __launch_bounds__(256) void k_gauss(int64_t npts, const double* __restrict__ X, int K,
+                                               const double* __restrict__ C, double inv2w2,
+                                               const double* __restrict__ c, double* __restrict__ f) {
+  __shared__ double hi[32];
+  __shared__ float lo[32];
+  __shared__ double red[S > 1 ? S * 64 * P : 1];
+  exp_table(hi, lo);
+  const int lane = threadIdx.x & 63;
+  const int wv = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int64_t i0 = ((int64_t)blockIdx.x * (4 / S) + wv / S) * (64 * P) + lane;
+  double x[P][D], s[P];
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    const int64_t i = i0 + 64 * p;
+    s[p] = 0.0;
+#pragma unroll
+    for (int a = 0; a < D; ++a) x[p][a] = i < npts ? X[i * D + a] : 0.0;
+  }
+  for (int k = wv % S; k < K; k += S) {
+    const double ck = c[k];
+#pragma unroll
+    for (int p = 0; p < P; ++p) s[p] = fma(ck, exp_neg(gauss_arg<D>(x[p], C + (int64_t)k * D, inv2w2), hi, lo), s[p]);
+  }
+  if (S > 1) {
+#pragma unroll
+    for (int p = 0; p < P; ++p) red[(wv * P + p) * 64 + lane] = s[p];
+    __syncthreads();
+    for (int t = threadIdx.x; t < 64 * P; t += 256) {
+      const int64_t i = (int64_t)blockIdx.x * (64 * P) + t;
+      double v = 0.0;
+#pragma unroll
+      for (int w = 0; w < S; ++w) v += red[w * 64 * P + t];
+      if (i < npts) f[i] = v;
+    }
+    return;
+  }
+#pragma unroll
+  for (int p = 0; p < P; ++p)
+    if (i0 + 64 * p < npts) f[i0 + 64 * p] = s[p];
+}
+
+// partial[blk][k] = sum over the block's 256 P points of y(X) phi_k(X), for
+// the block's kc centres from blockIdx.y kc on (kc <= 64, a multiple of 8).
+// A thread keeps its P points in registers and walks the centres eight at a
+// time; the eight sums of a wave are reduced together, each exchange step
+// halving the number of values a lane still carries (10 exchanges for eight
+// sums, not 48).  Bound like k_gauss.  One centre per block row instead read
+// X and y once per centre: 5567 us at 5.3M points x 256 centres (44 GB of
+// cache reads, 7.9 TB/s), 1431 us now.
+template <int D, int P>
+__global__ __launch_bounds__(256) void k_gauss_t(int64_t npts, const double* __restrict__ X, int K,
+                                                 const double* __restrict__ C, double inv2w2,
+                                                 const double* __restrict__ y, double* __restrict__ partial, int kc) {
+  __shared__ double hi[32];
+  __shared__ float lo[32];
+  __shared__ double red[4][64];
+  exp_table(hi, lo);
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  const int64_t i0 = (int64_t)blockIdx.x * (256 * P) + threadIdx.x;
+  double x[P][D], yv[P];
+#pragma unroll
+  for (int p = 0; p < P; ++p) {
+    const int64_t i = i0 + 256 * p;
+    yv[p] = i < npts ? y[i] : 0.0;
+#pragma unroll
+    for (int a = 0; a < D; ++a) x[p][a] = i < npts ? X[i * D + a] : 0.0;
+  }
+  const int k0 = blockIdx.y * kc, k1 = min(K, k0 + kc);
+  for (int kb = k0; kb < k1; kb += 8) {
+    double v[8];
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const double* ck = C + (int64_t)min(kb + q, K - 1) * D;
+      double s = 0.0;
+#pragma unroll
+      for (int p = 0; p < P; ++p) s = fma(yv[p], exp_neg(gauss_arg<D>(x[p], ck, inv2w2), hi, lo), s);
+      v[q] = s;
+    }
+#pragma unroll
+    for (int h = 4; h >= 1; h >>= 1) {
+      const bool up = lane & (8 * h);
+#pragma unroll
+      for (int q = 0; q < h; ++q) {
+        const double keep = up ? v[q + h] : v[q], send = up ? v[q] : v[q + h];
+        v[q] = keep + __shfl_xor(send, 8 * h, 64);
+      }
+    }
+    for (int o = 4; o > 0; o >>= 1) v[0] += __shfl_xor(v[0], o, 64);
+    if ((lane & 7) == 0) red[wv][kb - k0 + (lane >> 3)] = v[0];
+  }
+  __syncthreads();
+  const int t = threadIdx.x;
+  if (t < k1 - k0) partial[(int64_t)blockIdx.x * K + k0 + t] = red[0][t] + red[1][t] + red[2][t] + red[3][t];
+}
+
+// out[k] = sum over blocks of partial[blk][k], eight k per workgroup.
+__global__ __launch_bounds__(256) void k_cols_sum(int K, int nblk, const double* __restrict__ partial,
+                                                  double* __restrict__ out) {
+  __shared__ double red[256];
+  const int k = blockIdx.x * 8 + (threadIdx.x & 7);
+  double s = 0.0;
+  if (k < K)
+    for (int b = threadIdx.x >> 3; b < nblk; b += 32) s += partial[(int64_t)b * K + k];
   red[threadIdx.x] = s;
   __syncthreads();
-  for (int o = 128; o > 0; o >>= 1) {
-    if (threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
+  for (int o = 128; o >= 8; o >>= 1) {
+    if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
     __syncthreads();
   }
-  if (threadIdx.x == 0) partial[(int64_t)k * nblk + blockIdx.x] = red[0];
+  if (threadIdx.x < 8 && k < K) out[k] = red[threadIdx.x];
 }
 
-__global__ void k_rows_sum(int K, int nblk, const double* __restrict__ partial, double* __restrict__ out) {
-  int k = blockIdx.x * blockDim.x + threadIdx.x;
-  if (k >= K) return;
-  double s = 0.0;
-  for (int b = 0; b < nblk; ++b) s += partial[(int64_t)k * nblk + b];
-  out[k] = s;
+// A few points per SIMD make the kernels latency bound: from 2^19 points on
+// a wave carries several points per lane (four forward, eight transposed, the
+// centres' scalar loads and the reductions shared between them), below that
+// four waves share the centres of 64 points.
+constexpr int64_t GAUSS_MANY = (int64_t)1 << 19;
+
+template <int D>
+static void gauss_launch(int64_t npts, const double* X, int K, const double* C, double inv2w2, const double* c,
+                         double* f, hipStream_t st) {
+  if (npts >= GAUSS_MANY)
+    hipLaunchKernelGGL((k_gauss<D, 4, 1>), dim3((unsigned)cdiv(npts, 1024)), dim3(256), 0, st, npts, X, K, C, inv2w2,
+                       c, f);
+  else
+    hipLaunchKernelGGL((k_gauss<D, 1, 4>), dim3((unsigned)cdiv(npts, 64)), dim3(256), 0, st, npts, X, K, C, inv2w2,
+                       c, f);
+}
+
+template <int D>
+static ah_status gauss_t_launch(int64_t npts, const double* X, int K, const double* C, double inv2w2,
+                                const double* y, double* dc, Arena& tmp, hipStream_t st) {
+  const bool many = npts >= GAUSS_MANY;
+  const int nblk = (int)std::max<int64_t>(1, cdiv(npts, many ? 2048 : 256));
+  const int kc = many ? 64 : 8;
+  double* part = nullptr;
+  AH_TRY(tmp.get(&part, (int64_t)K * nblk));
+  const dim3 grid(nblk, (unsigned)cdiv(K, kc));
+  if (many)
+    hipLaunchKernelGGL((k_gauss_t<D, 8>), grid, dim3(256), 0, st, npts, X, K, C, inv2w2, y, part, kc);
+  else
+    hipLaunchKernelGGL((k_gauss_t<D, 1>), grid, dim3(256), 0, st, npts, X, K, C, inv2w2, y, part, kc);
+  hipLaunchKernelGGL(k_cols_sum, dim3((unsigned)cdiv(K, 8)), dim3(256), 0, st, K, nblk, part, dc);
+  AH_LAUNCHED();
+  return AH_OK;
 }
 
 ah_status grad_dispatch(const ah_system* s, const double* a_vert, const double* lam_fwd, const double* lam_adj,
@@ -222,8 +386,10 @@ extern "C" ah_status ah_source_gauss(int D, int64_t npts, const double* X, int K
   }
   if (npts == 0) return AH_OK;
   hipStream_t st = as_stream(stream);
-  hipLaunchKernelGGL(k_gauss, dim3((unsigned)cdiv(npts, 256)), dim3(256), 0, st, npts, D, X, K, centers,
-                     1.0 / (2.0 * width * width), c, f);
+  const double s = 1.0 / (2.0 * width * width);
+  if (D == 1) gauss_launch<1>(npts, X, K, centers, s, c, f, st);
+  else if (D == 2) gauss_launch<2>(npts, X, K, centers, s, c, f, st);
+  else gauss_launch<3>(npts, X, K, centers, s, c, f, st);
   AH_LAUNCHED();
   return AH_OK;
 }
@@ -235,15 +401,13 @@ extern "C" ah_status ah_source_gauss_T(int D, int64_t npts, const double* X, int
     return AH_EINVAL;
   }
   hipStream_t st = as_stream(stream);
-  int nblk = (int)std::min<int64_t>(512, std::max<int64_t>(1, cdiv(npts, 256 * 8)));
   Arena tmp;
   tmp.stream = st;
-  double* part = nullptr;
-  AH_TRY(tmp.get(&part, (int64_t)K * nblk));
-  hipLaunchKernelGGL(k_gauss_t, dim3(nblk, K), dim3(256), 0, st, npts, D, X, K, centers, 1.0 / (2.0 * width * width),
-                     y, part, nblk);
-  hipLaunchKernelGGL(k_rows_sum, dim3((unsigned)cdiv(K, 256)), dim3(256), 0, st, K, nblk, part, dc);
-  AH_LAUNCHED();
+  const double s = 1.0 / (2.0 * width * width);
+  ah_status rc = D == 1 ? gauss_t_launch<1>(npts, X, K, centers, s, y, dc, tmp, st)
+               : D == 2 ? gauss_t_launch<2>(npts, X, K, centers, s, y, dc, tmp, st)
+                        : gauss_t_launch<3>(npts, X, K, centers, s, y, dc, tmp, st);
+  if (rc < 0) { tmp.release(); return rc; }
   AH_HIP(hipStreamSynchronize(st));
   tmp.release();
   return AH_OK;
