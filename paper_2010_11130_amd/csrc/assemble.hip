@@ -5,10 +5,10 @@
 // scalar CSR matrix used by AIR.  Also reconstruction, slab coupling and
 // the adjoint gradient kernel.
 //
-// One workgroup (one wave) per element.  The element basis is the monomial
-// basis xi^alpha on the reference simplex of the cell; facet unknowns use the
-// nodal Lagrange basis on the sorted-vertex facet simplex.  Rows = test
-// functions, columns = trial functions:
+// A wave assembles one element or, where its matrices are small, four.  The
+// element basis is the nodal Lagrange basis on the reference simplex of the
+// cell; facet unknowns use the nodal Lagrange basis on the sorted-vertex facet
+// simplex.  Rows = test functions, columns = trial functions:
 //   A(u,v) = int_K (-u a_hat.grad_hat v + nu grad u.grad v)
 //            + sum_F int_F [(a+ + tau) u v - nu (grad u.n) v - nu u (grad v.n)]
 //   B(l,v) = sum_F int_F [(a- - tau) l v + nu l (grad v.n)]
@@ -33,7 +33,11 @@ struct Sz {
   static constexpr int N1 = P + 2;
   static constexpr int NQ = D == 2 ? N1 * N1 : N1 * N1 * N1;
   static constexpr int NQF = D == 2 ? N1 : N1 * N1;
-  static constexpr int NR = NL + 1 + NU;   // right-hand sides of the element solve
+  static constexpr int BS = B * (B + 1) / 2;   // packed symmetric facet matrices
+  static constexpr int DS = D * (D + 1) / 2;
+  // lanes per element: 16 where a lane can hold the whole of A_K, else a wave
+  static constexpr int G = NU <= 6 ? 16 : 64;
+  static constexpr int EPB = 64 / G;           // elements per (one-wave) workgroup
 };
 
 struct ElemArgs {
@@ -59,11 +63,16 @@ struct ElemArgs {
   const double* fac_mu;
   const double* fac_psi;
   const double* fac_proj;
+  const double* fac_pp;    // [nqf][b(b+1)/2] products of facet basis functions
+  const double* fac_mass;  // [b(b+1)/2] facet mass matrix over |F|
   const double* ten_adv;   // [(D+1) D][nu nu] reference advection tensor
-  const double* ten_dif;   // [D D][nu nu] reference diffusion tensor
+  const double* ten_dif;   // [D(D+1)/2][nu nu] reference diffusion tensor
+  const double* ten_dn;    // [D+1][D][nu nu] facet normal-derivative tensors
   double nu, alpha;
-  double* bval;
-  double* H;
+  double* bval;            // off-diagonal blocks of S
+  double* Dg;              // [ne][D+1][b][b] the elements' parts of its diagonal blocks
+  double* Hk;              // [ne][nl] the elements' parts of H
+  int add_off;             // off-diagonal blocks may get two parts (a cell given twice): add to zeros
   double* lamD;
   double* Ainv;
   double* Bm;
@@ -75,9 +84,18 @@ struct ElemArgs {
   const double* lam_adj;   // [n_free] adjoint solution (zero on Dirichlet facets)
   double* dJdf_q;          // [ne][nq]
   double* dnu_elem;        // [ne]
-  int8_t mono[20][3];
+  int8_t node[64];         // element node at lattice indices (i_1, ..): sum i_k (p+1)^(k-1)
+  int8_t fnode[10][3];     // barycentric indices of the facet nodes
 };
 
+// The element's matrices in LDS.  With a nodal element basis the trace of
+// basis function i on facet F is the facet function of node i, or zero where
+// node i is not on F, so every facet term comes from three facet matrices
+//   MA = int (a+ + tau) psi psi,  MB = int (a- - tau) psi psi,
+//   Z  = nu int (d phi_i/dn) psi  (from ten_dn, no quadrature)
+// by scattering: A gets MA - Z - Z^T, B_F = MB + Z, C_F = Z^T - MA and
+// D_F = -MB (+ int a+ psi psi on Neumann facets).  Only the upwind weights
+// a+ and a- need points: two packed b x b sums per facet.
 template <int D, int P>
 struct ElemSmem {
   using S = Sz<D, P>;
@@ -88,52 +106,67 @@ struct ElemSmem {
   double nrm[(D + 1) * D];
   double area[D + 1];
   double eta[(D + 1) * D];
-  int fid[D + 1], kindf[D + 1], bidx[D + 1], loc[(D + 1) * D];
-  double A[S::NU * S::NU];
-  double Bm[S::NU * S::NL];
-  double Cm[S::NL * S::NU];
-  double Dd[(D + 1) * S::B * S::B];
-  double F[S::NU];
-  double LD[S::NL];
-  double vcoef[(D + 1) * D + D * D];   // beta_kr, then G_rs
-  // quadrature scratch of the integration phase
-  struct Quad {
-    double q_wf[S::NQ];             // W_q f_q at the element points
-    union {
-      struct {
-        double f_phi[S::NQF * S::NU];
-        double f_dn[S::NQF * S::NU];
-      };
-      double beta[S::NQ * D];       // J^-1 (1, a(x_q)) of the volume phase (velocity at points)
-    };
-    double f_cA[S::NQF], f_cB[S::NQF], f_cD[S::NQF], f_W[S::NQF], f_g[S::NQF];
-    double f_psi[S::NQF * S::B];    // facet basis at the facet points (staged)
-    double f_proj[S::B * S::NQF];   // facet L2 projection weights (staged)
+  double vcoef[(D + 1) * D + S::DS];   // beta_kr, then G_rs (r <= s)
+  int fid[D + 1], kindf[D + 1], bidx[D + 1];
+  int8_t loc[(D + 1) * D];
+  int8_t fnode[(D + 1) * S::B];        // element node of facet node m
+  int8_t pos[(D + 1) * S::NU];         // facet node of element node i, or -1
+  double MA[(D + 1) * S::BS], MB[(D + 1) * S::BS], DD[(D + 1) * S::BS];
+  double F[S::NU], y[S::NU], LD[S::NL];
+  union {
+    double A[S::NU * S::NU];
+    struct {
+      double wf[S::NQ];                // W_q f_q at the element points
+      double cap[(D + 1) * S::NQF], cam[(D + 1) * S::NQF];   // W a+, W a- at the facet points
+      double Fp[S::G];
+    } q;
   };
-  Quad qd;
+  union {
+    double ZC[S::NL * S::NU];          // Z by (facet, facet node; element node), then C
+    double beta[S::NQ * D];            // J^-1 (1, a(x_q)) (velocity at the points)
+  };
 };
 
-// Element geometry: inverse Jacobian, penalty, facet normals/areas.
+// Packed index of a symmetric entry.
+__device__ inline int sym(int m, int n) { return m >= n ? m * (m + 1) / 2 + n : n * (n + 1) / 2 + m; }
+
+// Element geometry: inverse Jacobian, penalty, facet normals and areas, and
+// which element nodes lie on which facet.  g: lane of the element's S::G.
 template <int D, int P>
-__device__ void elem_geometry(const ElemArgs& a, ElemSmem<D, P>& sm, int64_t e, double nu_eff, double alpha) {
-  const int t = threadIdx.x;
-  if (t < (D + 1) * D) {
-    int k = t / D, c = t % D;
-    sm.X[t] = a.vert[(int64_t)a.cell[e * (D + 1) + k] * D + c];
+__device__ void elem_geometry(const ElemArgs& a, ElemSmem<D, P>& sm, int64_t e, int g, double nu_eff, double alpha,
+                              bool live) {
+  using S = Sz<D, P>;
+  constexpr int G = S::G;
+  for (int t = g; t < (D + 1) * D; t += G) {
+    sm.X[t] = a.vert[(int64_t)a.cell[e * (D + 1) + t / D] * D + t % D];
     sm.loc[t] = a.facet_loc[e * (D + 1) * D + t];
   }
-  if (t < (D + 1) * (D - 1)) {
-    int k = t / (D - 1), c = t % (D - 1);
-    sm.av[t] = a.a_vert ? a.a_vert[(int64_t)a.cell[e * (D + 1) + k] * (D - 1) + c] : 0.0;
+  for (int t = g; t < (D + 1) * (D - 1); t += G)
+    sm.av[t] = a.a_vert ? a.a_vert[(int64_t)a.cell[e * (D + 1) + t / (D - 1)] * (D - 1) + t % (D - 1)] : 0.0;
+  if (g < D + 1) {
+    const int f = a.elem_facet[e * (D + 1) + g];
+    sm.fid[g] = f;
+    sm.kindf[g] = a.kind[f];
+    sm.bidx[g] = a.bf_index[f];
   }
-  if (t < D + 1) {
-    int f = a.elem_facet[e * (D + 1) + t];
-    sm.fid[t] = f;
-    sm.kindf[t] = a.kind[f];
-    sm.bidx[t] = a.bf_index[f];
-  }
+  for (int t = g; t < (D + 1) * S::NU; t += G) sm.pos[t] = -1;
+  for (int k = g; k < S::NL; k += G) sm.LD[k] = 0.0;
   __syncthreads();
-  if (t == 0) {
+  for (int t = g; t < (D + 1) * S::B; t += G) {
+    const int f = t / S::B, m = t % S::B;
+    int at = 0;
+#pragma unroll
+    for (int s = 0; s < D; ++s) {
+      const int v = sm.loc[f * D + s];   // local vertex; its lattice index is coordinate v (v > 0)
+      int w = a.fnode[m][s];
+      for (int c = 1; c < v; ++c) w *= P + 1;
+      at += v > 0 ? w : 0;
+    }
+    const int i = a.node[at];
+    sm.fnode[t] = (int8_t)i;
+    sm.pos[f * S::NU + i] = (int8_t)m;
+  }
+  if (g == 0) {
     double J[D * D];   // J[r][c] = X[c+1][r] - X[0][r]
     for (int r = 0; r < D; ++r)
       for (int c = 0; c < D; ++c) J[r * D + c] = sm.X[(c + 1) * D + r] - sm.X[r];
@@ -150,224 +183,203 @@ __device__ void elem_geometry(const ElemArgs& a, ElemSmem<D, P>& sm, int64_t e, 
       Ji[6] = c02 / det; Ji[7] = (J[1] * J[6] - J[0] * J[7]) / det; Ji[8] = (J[0] * J[4] - J[1] * J[3]) / det;
     }
     for (int k = 0; k < D * D; ++k) sm.Jinv[k] = Ji[k];
-    double ad = fabs(det);
+    const double ad = fabs(det);
     sm.absdet = ad;
-    double h = pow(ad, 1.0 / D);
-    sm.tau = nu_eff * alpha / h;
-    double fact = D == 2 ? 2.0 : 6.0;
-    for (int lf = 0; lf <= D; ++lf) {
-      double g[D];
-      for (int c = 0; c < D; ++c) {
-        double v = 0.0;
-        if (lf == 0)
-          for (int r = 0; r < D; ++r) v -= Ji[r * D + c];
-        else
-          v = Ji[(lf - 1) * D + c];
-        g[c] = v;
-      }
-      double gn = 0.0;
-      for (int c = 0; c < D; ++c) gn += g[c] * g[c];
-      gn = sqrt(gn);
-      for (int c = 0; c < D; ++c) sm.nrm[lf * D + c] = -g[c] / gn;
-      sm.area[lf] = D * (ad / fact) * gn;
-      for (int r = 0; r < D; ++r) {
-        double v = 0.0;
-        for (int c = 1; c < D; ++c) v += Ji[r * D + c] * sm.nrm[lf * D + c];
-        sm.eta[lf * D + r] = v;
-      }
+    sm.tau = nu_eff * alpha / (D == 2 ? sqrt(ad) : cbrt(ad));
+    if (live && (!(ad > 0.0) || !isfinite(ad))) atomicOr(a.err, 2);
+  }
+  __syncthreads();
+  if (g < D + 1) {
+    const double fact = D == 2 ? 2.0 : 6.0;
+    double gr[D], gn = 0.0;
+#pragma unroll
+    for (int c = 0; c < D; ++c) {
+      double v = 0.0;
+      if (g == 0)
+        for (int r = 0; r < D; ++r) v -= sm.Jinv[r * D + c];
+      else
+        v = sm.Jinv[(g - 1) * D + c];
+      gr[c] = v;
+      gn += v * v;
     }
-    if (!(ad > 0.0) || !isfinite(ad)) atomicOr(a.err, 2);
+    gn = sqrt(gn);
+#pragma unroll
+    for (int c = 0; c < D; ++c) { gr[c] = -gr[c] / gn; sm.nrm[g * D + c] = gr[c]; }
+    sm.area[g] = D * (sm.absdet / fact) * gn;
+#pragma unroll
+    for (int r = 0; r < D; ++r) {
+      double v = 0.0;
+#pragma unroll
+      for (int c = 1; c < D; ++c) v += sm.Jinv[r * D + c] * gr[c];
+      sm.eta[g * D + r] = v;
+    }
   }
   __syncthreads();
 }
 
-// Monomial xi^alpha and its reference gradient.
-template <int D>
-__device__ inline double mono_eval(const int8_t* ex, const double* xi, double* dv) {
-  double pw[D][4];
-  for (int c = 0; c < D; ++c) {
-    pw[c][0] = 1.0;
-    for (int k = 1; k < 4; ++k) pw[c][k] = pw[c][k - 1] * xi[c];
-  }
-  double v = 1.0;
-  for (int c = 0; c < D; ++c) v *= pw[c][ex[c]];
-  for (int c = 0; c < D; ++c) {
-    if (ex[c] == 0) { dv[c] = 0.0; continue; }
-    double d = (double)ex[c] * pw[c][ex[c] - 1];
-    for (int o = 0; o < D; ++o)
-      if (o != c) d *= pw[o][ex[o]];
-    dv[c] = d;
-  }
-  return v;
-}
-
-// Integrate A, B, C, D (diagonal facet blocks), F, G and the Dirichlet traces.
-// advect = false and nu_eff = 1 gives the nu-derivative of the blocks.
+// A, MA, MB, DD, Z, F and the Dirichlet traces.  advect = false and nu_eff = 1
+// gives the nu-derivative of the blocks.
 template <int D, int P>
-__device__ void elem_integrate(const ElemArgs& a, ElemSmem<D, P>& sm, int64_t e, double nu_eff, bool advect,
+__device__ void elem_integrate(const ElemArgs& a, ElemSmem<D, P>& sm, int64_t e, int g, double nu_eff, bool advect,
                                bool data) {
   using S = Sz<D, P>;
-  constexpr int NU = S::NU, NL = S::NL, B = S::B, NQ = S::NQ, NQF = S::NQF;
-  const int t = threadIdx.x;
-  const int NT = blockDim.x;
-  for (int k = t; k < NL; k += NT) sm.LD[k] = 0.0;
-  // ---- volume terms from the reference tensors (the element map and the
-  // velocity are affine on K): with a_k = (1, a at vertex k),
-  // beta_kr = (J^-1 a_k)_r and G_rs = sum over the spatial c of
-  // Jinv[r][c] Jinv[s][c],
-  //   A_ij = |det J| (nu sum_rs G_rs M^rs_ij - sum_kr beta_kr T^kr_ij),
-  //   F_i  = sum_q w_q |det J| f(x_q) phi_i(x_q).
-  if (t < (D + 1) * D) {
-    const int k = t / D, r = t % D;
+  constexpr int NU = S::NU, B = S::B, BS = S::BS, NQ = S::NQ, NQF = S::NQF, G = S::G, DS = S::DS;
+  // volume coefficients: with a_k = (1, a at vertex k), beta_kr = (J^-1 a_k)_r
+  // and G_rs = sum over the spatial c of Jinv[r][c] Jinv[s][c],
+  //   A_ij = |det J| (nu sum_{r<=s} G_rs M^rs_ij - sum_kr beta_kr T^kr_ij)
+  for (int t = g; t < (D + 1) * D + DS; t += G) {
     double v = 0.0;
-    if (advect) {
-      v = sm.Jinv[r * D];
-      for (int c = 1; c < D; ++c) v += sm.Jinv[r * D + c] * sm.av[k * (D - 1) + c - 1];
+    if (t < (D + 1) * D) {
+      const int k = t / D, r = t % D;
+      if (advect) {
+        v = sm.Jinv[r * D];
+        for (int c = 1; c < D; ++c) v += sm.Jinv[r * D + c] * sm.av[k * (D - 1) + c - 1];
+      }
+    } else {
+      int u = t - (D + 1) * D, r = 0;
+      while (u >= D - r) { u -= D - r; ++r; }
+      for (int c = 1; c < D; ++c) v += sm.Jinv[r * D + c] * sm.Jinv[(r + u) * D + c];
     }
     sm.vcoef[t] = v;
-  } else if (t < (D + 1) * D + D * D) {
-    const int u = t - (D + 1) * D, r = u / D, s2 = u % D;
-    double g = 0.0;
-    for (int c = 1; c < D; ++c) g += sm.Jinv[r * D + c] * sm.Jinv[s2 * D + c];
-    sm.vcoef[t] = g;
   }
   const bool has_f = data && a.f_q;
   if (has_f)
-    for (int q = t; q < NQ; q += NT) sm.qd.q_wf[q] = a.vol_w[q] * sm.absdet * a.f_q[e * NQ + q];
-  // velocity given at the quadrature points: beta_q = J^-1 (1, a(x_q)), and
-  // the advective part of A_ij is sum_q w_q phi_j(x_q) beta_q . grad phi_i(x_q)
-  const bool aq = advect && a.a_qe;
-  if (aq)
-    for (int k = t; k < NQ * D; k += NT) {
-      const int q = k / D, r = k % D;
-      double v = sm.Jinv[r * D];
-      for (int c = 1; c < D; ++c) v += sm.Jinv[r * D + c] * a.a_qe[((int64_t)e * NQ + q) * (D - 1) + c - 1];
-      sm.qd.beta[k] = v;
+    for (int q = g; q < NQ; q += G) sm.q.wf[q] = a.vol_w[q] * sm.absdet * a.f_q[e * NQ + q];
+  // upwind weights at the facet points
+  if (advect)
+    for (int t = g; t < (D + 1) * NQF; t += G) {
+      const int f = t / NQF, q = t % NQF;
+      double an = sm.nrm[f * D];
+#pragma unroll
+      for (int c = 1; c < D; ++c) {
+        double v = 0.0;
+        if (a.a_qf)
+          v = a.a_qf[((int64_t)sm.fid[f] * NQF + q) * (D - 1) + c - 1];
+        else
+          for (int s = 0; s < D; ++s) v += a.fac_mu[q * D + s] * sm.av[sm.loc[f * D + s] * (D - 1) + c - 1];
+        an += v * sm.nrm[f * D + c];
+      }
+      const double W = a.fac_w[q] * sm.area[f];
+      sm.q.cap[t] = W * (0.5 * (an + fabs(an)));
+      sm.q.cam[t] = W * (0.5 * (an - fabs(an)));
+    }
+  if (data && a.g_q)
+    for (int t = g; t < (D + 1) * B; t += G) {
+      const int f = t / B, m = t % B;
+      if (sm.kindf[f] != 1) continue;
+      const double* gq = a.g_q + (int64_t)sm.bidx[f] * NQF;
+      double acc = 0.0;
+      for (int q = 0; q < NQF; ++q) acc += a.fac_proj[m * NQF + q] * gq[q];
+      sm.LD[t] = acc;
     }
   __syncthreads();
-  for (int idx = t; idx < NU * NU; idx += NT) {
-    double adv = 0.0, dif = 0.0;
-    if (aq) {
-      const int i = idx / NU, j = idx % NU;
-      for (int q = 0; q < NQ; ++q) {
-        double g = 0.0;
-        _Pragma("unroll") for (int r = 0; r < D; ++r) g += sm.qd.beta[q * D + r] * a.vol_dphi[(q * NU + i) * D + r];
-        adv += a.vol_w[q] * a.vol_phi[q * NU + j] * g;
+  for (int t = g; t < (D + 1) * BS; t += G) {
+    const int f = t / BS, mn = t % BS;
+    double ap = 0.0, am = 0.0;
+    if (advect) {
+#pragma unroll 5
+      for (int q = 0; q < NQF; ++q) {
+        const double pp = a.fac_pp[q * BS + mn];
+        ap += sm.q.cap[f * NQF + q] * pp;
+        am += sm.q.cam[f * NQF + q] * pp;
       }
-    } else {
-      _Pragma("unroll") for (int kr = 0; kr < (D + 1) * D; ++kr)
-        adv += sm.vcoef[kr] * a.ten_adv[(size_t)kr * NU * NU + idx];
     }
-    _Pragma("unroll") for (int rs = 0; rs < D * D; ++rs)
-      dif += sm.vcoef[(D + 1) * D + rs] * a.ten_dif[(size_t)rs * NU * NU + idx];
-    sm.A[idx] = sm.absdet * (nu_eff * dif - adv);
+    const double w = sm.tau * sm.area[f] * a.fac_mass[mn];
+    sm.MA[t] = ap + w;
+    sm.MB[t] = am - w;
+    sm.DD[t] = w - am + ((sm.kindf[f] == 2) ? ap : 0.0);
+  }
+  // F_i = sum_q W_q f_q phi_i(x_q), the points dealt to G / NU lanes per i
+  constexpr int PARTS = G / NU;
+  if (has_f && g < PARTS * NU) {
+    const int i = g % NU;
+    double acc = 0.0;
+    for (int q = g / NU; q < NQ; q += PARTS) acc += sm.q.wf[q] * a.vol_phi[q * NU + i];
+    sm.q.Fp[g] = acc;
   }
   __syncthreads();
-  for (int i = t; i < NU; i += NT) {
+  for (int i = g; i < NU; i += G) {
     double acc = 0.0;
     if (has_f)
-      for (int q = 0; q < NQ; ++q) acc += sm.qd.q_wf[q] * a.vol_phi[q * NU + i];
+#pragma unroll
+      for (int k = 0; k < PARTS; ++k) acc += sm.q.Fp[k * NU + i];
     sm.F[i] = acc;
   }
   __syncthreads();
-  // ---- facet terms
-  for (int k = t; k < NQF * B; k += NT) {
-    sm.qd.f_psi[k] = a.fac_psi[k];
-    sm.qd.f_proj[k] = a.fac_proj[k];
+  // velocity given at the quadrature points: the advective part of A_ij is
+  // sum_q w_q phi_j(x_q) beta_q . grad phi_i(x_q), beta_q = J^-1 (1, a(x_q))
+  const bool aq = advect && a.a_qe;
+  if (aq) {
+    for (int k = g; k < NQ * D; k += G) {
+      const int q = k / D, r = k % D;
+      double v = sm.Jinv[r * D];
+      for (int c = 1; c < D; ++c) v += sm.Jinv[r * D + c] * a.a_qe[((int64_t)e * NQ + q) * (D - 1) + c - 1];
+      sm.beta[k] = v;
+    }
+    __syncthreads();
+    for (int idx = g; idx < NU * NU; idx += G) {
+      const int i = idx / NU, j = idx % NU;
+      double adv = 0.0;
+      for (int q = 0; q < NQ; ++q) {
+        double gr = 0.0;
+#pragma unroll
+        for (int r = 0; r < D; ++r) gr += sm.beta[q * D + r] * a.vol_dphi[(q * NU + i) * D + r];
+        adv += a.vol_w[q] * a.vol_phi[q * NU + j] * gr;
+      }
+      sm.A[idx] = adv;
+    }
+    __syncthreads();
   }
-  for (int lf = 0; lf <= D; ++lf) {
-    const bool isN = sm.kindf[lf] == 2;
-    const bool isD = sm.kindf[lf] == 1;
-    {
-      constexpr int FPART = (NQF * 4 <= 64) ? 4 : (NQF * 2 <= 64 ? 2 : 1);
-      constexpr int FIPP = (NU + FPART - 1) / FPART;
-      for (int idx = t; idx < NQF * FPART; idx += NT) {
-        const int q = idx % NQF, part = idx / NQF;
-        double lam[D + 1];
-        for (int k = 0; k <= D; ++k) lam[k] = 0.0;
-        for (int s2 = 0; s2 < D; ++s2) lam[sm.loc[lf * D + s2]] = a.fac_mu[q * D + s2];
-        double xi[D];
-        for (int c = 0; c < D; ++c) xi[c] = lam[c + 1];
-        for (int ii = 0; ii < FIPP; ++ii) {
-          const int i = part * FIPP + ii;
-          if (i >= NU) break;
-          double dv[D];
-          double v = mono_eval<D>(a.mono[i], xi, dv);
-          double dn = 0.0;
-          for (int c = 0; c < D; ++c) dn += dv[c] * sm.eta[lf * D + c];
-          sm.qd.f_phi[q * NU + i] = v;
-          sm.qd.f_dn[q * NU + i] = dn;
-        }
-      }
+  for (int t = g; t < S::NL * NU; t += G) {
+    const int fm = t / NU, i = t % NU, f = fm / B;
+    const int j = sm.fnode[fm];
+    double v = 0.0;
+#pragma unroll
+    for (int r = 0; r < D; ++r) v += sm.eta[f * D + r] * a.ten_dn[((f * D + r) * NU + j) * NU + i];
+    sm.ZC[t] = nu_eff * sm.area[f] * v;
+  }
+  __syncthreads();
+  for (int idx = g; idx < NU * NU; idx += G) {
+    const int i = idx / NU, j = idx % NU;
+    double adv = 0.0, dif = 0.0;
+    if (aq) {
+      adv = sm.A[idx];
+    } else {
+#pragma unroll
+      for (int kr = 0; kr < (D + 1) * D; ++kr) adv += sm.vcoef[kr] * a.ten_adv[kr * NU * NU + idx];
     }
-    for (int q = t; q < NQF; q += NT) {
-      double lam[D + 1];
-      for (int k = 0; k <= D; ++k) lam[k] = 0.0;
-      for (int s = 0; s < D; ++s) lam[sm.loc[lf * D + s]] = a.fac_mu[q * D + s];
-      double an = 0.0;
-      if (advect) {
-        an = sm.nrm[lf * D];
-        for (int c = 1; c < D; ++c) {
-          double v = 0.0;
-          if (a.a_qf)
-            v = a.a_qf[((int64_t)sm.fid[lf] * NQF + q) * (D - 1) + c - 1];
-          else
-            for (int k = 0; k <= D; ++k) v += lam[k] * sm.av[k * (D - 1) + c - 1];
-          an += v * sm.nrm[lf * D + c];
-        }
-      }
-      double ap = 0.5 * (an + fabs(an)), am = 0.5 * (an - fabs(an));
-      double W = a.fac_w[q] * sm.area[lf];
-      sm.qd.f_W[q] = W;
-      sm.qd.f_cA[q] = W * (ap + sm.tau);
-      sm.qd.f_cB[q] = W * (am - sm.tau);
-      sm.qd.f_cD[q] = -W * (am - sm.tau) + ((isN && advect) ? W * ap : 0.0);
-      sm.qd.f_g[q] = (data && a.g_q && sm.bidx[lf] >= 0) ? a.g_q[(int64_t)sm.bidx[lf] * NQF + q] : 0.0;
+#pragma unroll
+    for (int rs = 0; rs < DS; ++rs) dif += sm.vcoef[(D + 1) * D + rs] * a.ten_dif[rs * NU * NU + idx];
+    double v = sm.absdet * (nu_eff * dif - adv);
+#pragma unroll
+    for (int f = 0; f <= D; ++f) {
+      const int mi = sm.pos[f * NU + i], mj = sm.pos[f * NU + j];
+      if (mj >= 0) v -= sm.ZC[(f * B + mj) * NU + i];
+      if (mi >= 0) v -= sm.ZC[(f * B + mi) * NU + j];
+      if (mi >= 0 && mj >= 0) v += sm.MA[f * BS + sym(mi, mj)];
     }
-    __syncthreads();
-    for (int idx = t; idx < NU * NU; idx += NT) {
-      int i = idx / NU, j = idx % NU;
-      double acc = 0.0;
-      _Pragma("unroll 4") for (int q = 0; q < NQF; ++q) {
-        double pi = sm.qd.f_phi[q * NU + i], pj = sm.qd.f_phi[q * NU + j];
-        acc += sm.qd.f_cA[q] * pj * pi - nu_eff * sm.qd.f_W[q] * (sm.qd.f_dn[q * NU + j] * pi + pj * sm.qd.f_dn[q * NU + i]);
-      }
-      sm.A[idx] += acc;
-    }
-    for (int idx = t; idx < NU * B; idx += NT) {
-      int i = idx / B, m = idx % B;
-      double acc = 0.0;
-      _Pragma("unroll 4") for (int q = 0; q < NQF; ++q) {
-        double psi = sm.qd.f_psi[q * B + m];
-        acc += sm.qd.f_cB[q] * psi * sm.qd.f_phi[q * NU + i] + nu_eff * sm.qd.f_W[q] * psi * sm.qd.f_dn[q * NU + i];
-      }
-      sm.Bm[i * NL + lf * B + m] = acc;
-    }
-    for (int idx = t; idx < B * NU; idx += NT) {
-      int m = idx / NU, j = idx % NU;
-      double acc = 0.0;
-      _Pragma("unroll 4") for (int q = 0; q < NQF; ++q) {
-        double psi = sm.qd.f_psi[q * B + m];
-        acc += -sm.qd.f_cA[q] * sm.qd.f_phi[q * NU + j] * psi + nu_eff * sm.qd.f_W[q] * sm.qd.f_dn[q * NU + j] * psi;
-      }
-      sm.Cm[(lf * B + m) * NU + j] = acc;
-    }
-    for (int idx = t; idx < B * B; idx += NT) {
-      int m = idx / B, n = idx % B;
-      double acc = 0.0;
-      _Pragma("unroll 4") for (int q = 0; q < NQF; ++q) acc += sm.qd.f_cD[q] * sm.qd.f_psi[q * B + m] * sm.qd.f_psi[q * B + n];
-      sm.Dd[lf * B * B + idx] = acc;
-    }
-    if (data) {
-      for (int m = t; m < B; m += NT) {
-        if (isD) {
-          double acc = 0.0;
-          _Pragma("unroll 4") for (int q = 0; q < NQF; ++q) acc += sm.qd.f_proj[m * NQF + q] * sm.qd.f_g[q];
-          sm.LD[lf * B + m] = acc;
-        }
-      }
-    }
-    __syncthreads();
+    sm.A[idx] = v;
+  }
+  __syncthreads();
+}
+
+// Entry r of column (facet lf, node m) of B_K.
+template <int D, int P>
+__device__ inline double elem_b(const ElemSmem<D, P>& sm, int r, int lf, int m) {
+  using S = Sz<D, P>;
+  const int q = sm.pos[lf * S::NU + r];
+  const double z = sm.ZC[(lf * S::B + m) * S::NU + r];
+  return q >= 0 ? z + sm.MB[lf * S::BS + sym(q, m)] : z;
+}
+
+// Z -> C_K in place: C = Z^T - MA at the facet's nodes.
+template <int D, int P>
+__device__ inline void elem_z_to_c(ElemSmem<D, P>& sm, int g) {
+  using S = Sz<D, P>;
+  for (int t = g; t < S::NL * S::NU; t += S::G) {
+    const int fm = t / S::NU, lf = fm / S::B;
+    const int q = sm.pos[lf * S::NU + t % S::NU];
+    if (q >= 0) sm.ZC[t] -= sm.MA[lf * S::BS + sym(q, fm % S::B)];
   }
 }
 
@@ -380,181 +392,249 @@ __device__ inline double wave_bcast(double v, int src) {
 
 __device__ inline int wave_bcast(int v, int src) { return __builtin_amdgcn_readlane(v, src); }
 
+// Element blocks, X = A^-1 [B | I] by Gauss-Jordan with partial pivoting in
+// registers, and the condensed block S_K = D_K - C_K A_K^-1 B_K with its
+// right-hand side.  Each off-diagonal block of S belongs to one element and is
+// stored plainly; the diagonal blocks and H have up to two parts, kept per
+// element and summed per facet afterwards, so nothing is zeroed or added
+// atomically.
+//
+// Bound by the FP64 vector and LDS pipes, not by HBM (2-D + time, p = 2: 24,576
+// elements take 199 us; p = 1, 5.3M elements 10.4 ms; before, with a monomial
+// basis, every facet term by quadrature and one element per wave: 616 us and
+// 48.5 ms).  Small elements (nu <= 6): 16 lanes each, a lane holding all of A
+// and one column, four elements to a wave; larger ones: a wave each, a lane a
+// column of [A | B | F | I], the pivot column broadcast by readlane.
 template <int D, int P>
 __global__ __launch_bounds__(64) void k_element(ElemArgs a) {
   using S = Sz<D, P>;
-  constexpr int NU = S::NU, NL = S::NL, B = S::B, NR = S::NR;
-  // columns of [A | B F I], lane l holds columns l + 64 u
-  constexpr int NC = NU + NR;
-  constexpr int CPL = (NC + 63) / 64;
-  __shared__ ElemSmem<D, P> sm;
-  const int64_t e = blockIdx.x;
-  const int t = threadIdx.x;
-  const int NT = blockDim.x;
-  elem_geometry<D, P>(a, sm, e, a.nu, a.alpha);
-  elem_integrate<D, P>(a, sm, e, a.nu, true, true);
-  // keep the unfactored blocks
-  if (a.Bm) {
-    for (int k = t; k < NU * NL; k += NT) a.Bm[e * NU * NL + k] = sm.Bm[k];
-    for (int k = t; k < NL * NU; k += NT) a.Cm[e * NL * NU + k] = sm.Cm[k];
-    for (int k = t; k < NU; k += NT) a.Fv[e * NU + k] = sm.F[k];
-  }
-  // Gauss-Jordan with partial pivoting on [A | B F I] in registers: the
-  // pivot row and the pivot column are broadcast from the lane holding
-  // column k; no barriers.  Afterwards the columns right of A hold
-  // X = A^-1 [B | F | I].
-  double col[CPL][NU];
-#pragma unroll
-  for (int u = 0; u < CPL; ++u) {
-    const int c = t + 64 * u;
-#pragma unroll
-    for (int r = 0; r < NU; ++r) {
-      double v = 0.0;
-      if (c < NU) v = sm.A[r * NU + c];
-      else if (c < NU + NL) v = sm.Bm[r * NL + (c - NU)];
-      else if (c == NU + NL) v = sm.F[r];
-      else if (c < NC) v = (r == c - NU - NL - 1) ? 1.0 : 0.0;
-      col[u][r] = v;
-    }
-  }
+  constexpr int NU = S::NU, NL = S::NL, B = S::B, G = S::G;
+  __shared__ ElemSmem<D, P> sm_[S::EPB];
+  const int g = threadIdx.x % G;
+  ElemSmem<D, P>& sm = sm_[G == 64 ? 0 : threadIdx.x / G];
+  const int64_t e0 = (int64_t)blockIdx.x * S::EPB + (G == 64 ? 0 : threadIdx.x / G);
+  const bool live = e0 < a.ne;
+  const int64_t e = live ? e0 : a.ne - 1;
+  elem_geometry<D, P>(a, sm, e, g, a.nu, a.alpha, live);
+  elem_integrate<D, P>(a, sm, e, g, a.nu, true, true);
   bool singular = false;
-  for (int k = 0; k < NU; ++k) {
-    // pivot search in column k (lane k, slot 0): first largest |a_rk|, r >= k
-    double best = -1.0;
-    int p = k;
+  // this lane's column of A^-1 [B | I]: xs; its column of B_K (or -1), and of
+  // the identity (or -1)
+  double xs[NU];
+  int cc = -1, ci = -1;
+  if constexpr (G == 16) {
+    static_assert(G != 16 || NL + NU <= 16, "a lane per column");
+    cc = g < NL ? g : -1;
+    ci = g >= NL && g < NL + NU ? g - NL : -1;
+    double M[NU][NU];
 #pragma unroll
     for (int r = 0; r < NU; ++r) {
-      const double v = fabs(col[0][r]);
-      if (r >= k && v > best) { best = v; p = r; }
-    }
-    p = wave_bcast(p, k);
-    best = wave_bcast(best, k);
-    if (!(best > 0.0) || !isfinite(best)) singular = true;
-    // swap rows k and p (selects keep the register indices static)
+      xs[r] = cc >= 0 ? elem_b<D, P>(sm, r, cc / B, cc % B) : r == ci ? 1.0 : 0.0;
 #pragma unroll
-    for (int u = 0; u < CPL; ++u) {
-      double vk = 0.0, vp = 0.0;
+      for (int c = 0; c < NU; ++c) M[r][c] = sm.A[r * NU + c];
+    }
+    if (a.Bm && live && cc >= 0)
+#pragma unroll
+      for (int r = 0; r < NU; ++r) a.Bm[(e * NU + r) * NL + cc] = xs[r];
+#pragma unroll
+    for (int k = 0; k < NU; ++k) {
+#pragma unroll
+      for (int r = k + 1; r < NU; ++r) {
+        const bool sw = fabs(M[r][k]) > fabs(M[k][k]);
+#pragma unroll
+        for (int c = k; c < NU; ++c) {
+          const double u = M[k][c], v = M[r][c];
+          M[k][c] = sw ? v : u;
+          M[r][c] = sw ? u : v;
+        }
+        const double u = xs[k], v = xs[r];
+        xs[k] = sw ? v : u;
+        xs[r] = sw ? u : v;
+      }
+      if (!(fabs(M[k][k]) > 0.0) || !isfinite(M[k][k])) singular = true;
+      const double inv = 1.0 / M[k][k];
+#pragma unroll
+      for (int c = k + 1; c < NU; ++c) M[k][c] *= inv;
+      xs[k] *= inv;
 #pragma unroll
       for (int r = 0; r < NU; ++r) {
-        vk = (r == k) ? col[u][r] : vk;
-        vp = (r == p) ? col[u][r] : vp;
+        if (r == k) continue;
+#pragma unroll
+        for (int c = k + 1; c < NU; ++c) M[r][c] -= M[r][k] * M[k][c];
+        xs[r] -= M[r][k] * xs[k];
       }
-#pragma unroll
-      for (int r = 0; r < NU; ++r) col[u][r] = (r == k) ? vp : ((r == p) ? vk : col[u][r]);
     }
-    // the pivot column, now in lane k
-    double f[NU];
-#pragma unroll
-    for (int r = 0; r < NU; ++r) f[r] = wave_bcast(col[0][r], k);
-    double piv = 0.0;
-#pragma unroll
-    for (int r = 0; r < NU; ++r) piv = (r == k) ? f[r] : piv;
-    const double inv = 1.0 / piv;
-#pragma unroll
-    for (int u = 0; u < CPL; ++u) {
-      double xk = 0.0;
-#pragma unroll
-      for (int r = 0; r < NU; ++r) xk = (r == k) ? col[u][r] : xk;
-      xk *= inv;
-#pragma unroll
-      for (int r = 0; r < NU; ++r) col[u][r] = (r == k) ? xk : col[u][r] - f[r] * xk;
-    }
-  }
-  if (singular && t == 0) atomicOr(a.err, 1);
-  // Dirichlet part: w = A^-1 B[:, Dir] lambda_D (broadcast from the lanes of
-  // the Dirichlet columns), then y = A^-1 F - w
-  double w[NU];
-#pragma unroll
-  for (int r = 0; r < NU; ++r) w[r] = 0.0;
-  for (int lf = 0; lf <= D; ++lf) {
-    if (sm.kindf[lf] != 1) continue;
-    for (int m = 0; m < B; ++m) {
-      const int c = NU + lf * B + m;
-      const int src = c & 63, us = c >> 6;
-      const double ld = sm.LD[lf * B + m];
+    __syncthreads();
+    // A^-1 F from the identity columns, through A's place
+    if (ci >= 0)
 #pragma unroll
       for (int r = 0; r < NU; ++r) {
-        double v = col[0][r];
+        sm.A[r * NU + ci] = xs[r];
+        if (a.Ainv && live) a.Ainv[(e * NU + r) * NU + ci] = xs[r];
+      }
+    __syncthreads();
+    if (g < NU) {
+      double v = 0.0;
 #pragma unroll
-        for (int u = 1; u < CPL; ++u) v = (us == u) ? col[u][r] : v;
-        w[r] += wave_bcast(v, src) * ld;
+      for (int c = 0; c < NU; ++c) v += sm.A[g * NU + c] * sm.F[c];
+      sm.y[g] = v;
+    }
+  } else {
+    // columns of [A | B F I], lane l holds columns l + 64 u
+    constexpr int NC = NU + NL + 1 + NU;
+    constexpr int CPL = (NC + 63) / 64;
+    static_assert(NU + NL + 1 <= 64, "the columns of A, B and F in the first slot");
+    double col[CPL][NU];
+#pragma unroll
+    for (int u = 0; u < CPL; ++u) {
+      const int c = g + 64 * u;
+#pragma unroll
+      for (int r = 0; r < NU; ++r) {
+        double v = 0.0;
+        if (c < NU) v = sm.A[r * NU + c];
+        else if (c < NU + NL) v = elem_b<D, P>(sm, r, (c - NU) / B, (c - NU) % B);
+        else if (c == NU + NL) v = sm.F[r];
+        else if (c < NC) v = (r == c - NU - NL - 1) ? 1.0 : 0.0;
+        col[u][r] = v;
       }
     }
-  }
-  double y[NU];
-  {
-    const int c = NU + NL;
-    const int src = c & 63, us = c >> 6;
+    cc = g >= NU && g < NU + NL ? g - NU : -1;
+    if (a.Bm && cc >= 0)
 #pragma unroll
-    for (int r = 0; r < NU; ++r) {
-      double v = col[0][r];
+      for (int r = 0; r < NU; ++r) a.Bm[(e * NU + r) * NL + cc] = col[0][r];
 #pragma unroll
-      for (int u = 1; u < CPL; ++u) v = (us == u) ? col[u][r] : v;
-      y[r] = wave_bcast(v, src) - w[r];
+    for (int k = 0; k < NU; ++k) {
+      // pivot search in column k (lane k, slot 0): first largest |a_rk|, r >= k
+      double best = fabs(col[0][k]);
+      int p = k;
+#pragma unroll
+      for (int r = k + 1; r < NU; ++r) {
+        const double v = fabs(col[0][r]);
+        if (v > best) { best = v; p = r; }
+      }
+      p = wave_bcast(p, k);
+      if (p != k) {
+#pragma unroll
+        for (int r = k + 1; r < NU; ++r)
+          if (p == r)   // uniform
+#pragma unroll
+            for (int u = 0; u < CPL; ++u) {
+              const double v = col[u][k];
+              col[u][k] = col[u][r];
+              col[u][r] = v;
+            }
+      }
+      // the pivot column, now in lane k
+      double f[NU];
+#pragma unroll
+      for (int r = 0; r < NU; ++r) f[r] = wave_bcast(col[0][r], k);
+      if (!(fabs(f[k]) > 0.0) || !isfinite(f[k])) singular = true;
+      const double inv = 1.0 / f[k];
+#pragma unroll
+      for (int u = 0; u < CPL; ++u) {
+        const double xk = col[u][k] * inv;
+#pragma unroll
+        for (int r = 0; r < NU; ++r) col[u][r] = r == k ? xk : col[u][r] - f[r] * xk;
+      }
     }
-  }
-  // S_K = D_K - C_K A^-1 B_K column by column (lane of column NU + cc),
-  // scattered at once: <= 2 contributions per entry, so the atomic sums are
-  // order-independent
-  const int32_t* slot = a.elem_slot + e * (D + 1) * (D + 1);
+    // kept element inverse: the identity columns now hold A^-1
+    if (a.Ainv) {
 #pragma unroll
-  for (int u = 0; u < CPL; ++u) {
-    const int cc = t + 64 * u - NU;
-    if (cc < 0 || cc >= NL) continue;
+      for (int u = 0; u < CPL; ++u) {
+        const int c = g + 64 * u - NU - NL - 1;
+        if (c < 0 || c >= NU) continue;
+#pragma unroll
+        for (int r = 0; r < NU; ++r) a.Ainv[(e * NU + r) * NU + c] = col[u][r];
+      }
+    }
+    if (g == NU + NL)
+#pragma unroll
+      for (int r = 0; r < NU; ++r) sm.y[r] = col[0][r];
+#pragma unroll
+    for (int r = 0; r < NU; ++r) xs[r] = col[0][r];
+  }
+  if (singular && live && g == 0) atomicOr(a.err, 1);
+  __syncthreads();
+  // keep C and F; y = A^-1 (F - B[:, Dir] lambda_D)
+  elem_z_to_c<D, P>(sm, g);
+  bool dir = false;
+#pragma unroll
+  for (int lf = 0; lf <= D; ++lf) dir |= sm.kindf[lf] == 1;
+  if (__any(dir)) {
+    for (int lf = 0; lf <= D; ++lf)
+      for (int m = 0; m < B; ++m) {
+        if (dir && sm.kindf[lf] == 1 && cc == lf * B + m)
+#pragma unroll
+          for (int r = 0; r < NU; ++r) sm.y[r] -= xs[r] * sm.LD[cc];
+        __syncthreads();
+      }
+  }
+  __syncthreads();
+  if (a.Cm && live) {
+    for (int k = g; k < NL * NU; k += G) a.Cm[e * NL * NU + k] = sm.ZC[k];
+    for (int k = g; k < NU; k += G) a.Fv[e * NU + k] = sm.F[k];
+  }
+  // S_K = D_K - C_K X column by column
+  if (cc >= 0 && live) {
     const int cb = cc / B, cm = cc % B;
-    for (int r = 0; r < NL; ++r) {
-      const int rb = r / B, rm = r % B;
-      double v = (rb == cb) ? sm.Dd[rb * B * B + rm * B + cm] : 0.0;
+    const int32_t* slot = a.elem_slot + e * (D + 1) * (D + 1);
 #pragma unroll
-      for (int k = 0; k < NU; ++k) v -= sm.Cm[r * NU + k] * col[u][k];
+    for (int rb = 0; rb <= D; ++rb) {
       const int sl = slot[rb * (D + 1) + cb];
-      if (sl >= 0) unsafeAtomicAdd(&a.bval[(int64_t)sl * B * B + rm * B + cm], v);
+      const bool on = rb == cb;
+      double* out = on ? a.Dg + (e * (D + 1) + rb) * B * B + cm : a.bval + (int64_t)sl * B * B + cm;
+      if (!on && sl < 0) continue;
+#pragma unroll 2
+      for (int rm = 0; rm < B; ++rm) {
+        double v = on ? sm.DD[rb * S::BS + sym(rm, cm)] : 0.0;
+        const double* C = sm.ZC + (rb * B + rm) * NU;
+#pragma unroll
+        for (int k = 0; k < NU; ++k) v -= C[k] * xs[k];
+        if (!on && a.add_off) unsafeAtomicAdd(out + rm * B, v);
+        else out[rm * B] = v;
+      }
     }
   }
-  // H_K = -C_K (A^-1 F - A^-1 B[:,Dir] lambda_D) - D_K[:,Dir] lambda_D
-  for (int r = t; r < NL; r += NT) {
+  // H_K = -C_K y - D_K[:, Dir] lambda_D
+  for (int r = g; r < NL; r += G) {
     const int lf = r / B, rm = r % B;
     double v = 0.0;
 #pragma unroll
-    for (int k = 0; k < NU; ++k) v -= sm.Cm[r * NU + k] * y[k];
-    if (sm.kindf[lf] == 1)
-      for (int n = 0; n < B; ++n) v -= sm.Dd[lf * B * B + rm * B + n] * sm.LD[lf * B + n];
-    const int f = sm.fid[lf];
-    const int fr = a.free_rank[f];
-    if (fr >= 0) unsafeAtomicAdd(&a.H[(int64_t)fr * B + rm], v);
-    if (sm.kindf[lf] == 1) a.lamD[(int64_t)f * B + rm] = sm.LD[r];
-  }
-  // kept element inverse: the identity columns now hold A^-1
-  if (a.Ainv) {
-#pragma unroll
-    for (int u = 0; u < CPL; ++u) {
-      const int ci = t + 64 * u - NU - NL - 1;
-      if (ci < 0 || ci >= NU) continue;
-#pragma unroll
-      for (int r = 0; r < NU; ++r) a.Ainv[e * NU * NU + r * NU + ci] = col[u][r];
+    for (int k = 0; k < NU; ++k) v -= sm.ZC[r * NU + k] * sm.y[k];
+    if (sm.kindf[lf] == 1) {
+      for (int n = 0; n < B; ++n) v -= sm.DD[lf * S::BS + sym(rm, n)] * sm.LD[lf * B + n];
+      if (live) a.lamD[(int64_t)sm.fid[lf] * B + rm] = sm.LD[r];
     }
+    if (live) a.Hk[e * NL + r] = v;
   }
 }
 
 // Inverse of each free facet's diagonal block (Gauss-Jordan, partial
 // pivoting).  All register arrays are indexed with compile-time indices
 // (unrolled loops, predicated row swaps) so they stay in registers.
+//
+// The diagonal block and H of a facet are the sums of its at most two elements'
+// parts (slots e (D+1) + lf, in element order).
 template <int B>
-__global__ __launch_bounds__(64) void k_diag_inv(int64_t nfree, const int64_t* __restrict__ bptr, const int32_t* __restrict__ bcol,
-                           const double* __restrict__ bval, double* __restrict__ dinv, int* err) {
+__global__ __launch_bounds__(64) void k_diag_inv(int64_t nfree, const int32_t* __restrict__ fslot,
+                                                 const double* __restrict__ Dg, double* __restrict__ dinv, int* err) {
   int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (r >= nfree) return;
-  int64_t s = -1;
-  for (int64_t k = bptr[r]; k < bptr[r + 1]; ++k)
-    if (bcol[k] == r) { s = k; break; }
+  const int64_t s0 = fslot[2 * r], s1 = fslot[2 * r + 1];
   double M[B][B], I[B][B];
 #pragma unroll
   for (int i = 0; i < B; ++i)
 #pragma unroll
     for (int j = 0; j < B; ++j) {
-      M[i][j] = s >= 0 ? bval[s * B * B + i * B + j] : 0.0;
+      M[i][j] = Dg[s0 * B * B + i * B + j];
       I[i][j] = i == j ? 1.0 : 0.0;
     }
+  if (s1 >= 0) {
+#pragma unroll
+    for (int i = 0; i < B; ++i)
+#pragma unroll
+      for (int j = 0; j < B; ++j) M[i][j] += Dg[s1 * B * B + i * B + j];
+  }
   double scale = 0.0;
 #pragma unroll
   for (int i = 0; i < B; ++i)
@@ -597,6 +677,29 @@ __global__ __launch_bounds__(64) void k_diag_inv(int64_t nfree, const int64_t* _
   for (int i = 0; i < B; ++i)
 #pragma unroll
     for (int j = 0; j < B; ++j) dinv[r * B * B + i * B + j] = I[i][j];
+}
+
+// H0 of every free facet unknown: the sum of its elements' parts.
+__global__ void k_h_sum(int64_t n, int B, const int32_t* __restrict__ fslot, const double* __restrict__ Hk,
+                        double* __restrict__ H) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  const int64_t R = i / B;
+  const int m = (int)(i - R * B);
+  const int64_t s0 = fslot[2 * R], s1 = fslot[2 * R + 1];
+  H[i] = s1 >= 0 ? Hk[s0 * B + m] + Hk[s1 * B + m] : Hk[s0 * B + m];
+}
+
+// Unscaled systems keep the diagonal blocks of S in its block pattern.
+__global__ void k_diag_store(int64_t nfree, int B, const int64_t* __restrict__ bptr,
+                             const int32_t* __restrict__ bcol, const int32_t* __restrict__ fslot,
+                             const double* __restrict__ Dg, double* __restrict__ bval) {
+  const int64_t r = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (r >= nfree) return;
+  int64_t s = bptr[r];
+  while (bcol[s] != r) ++s;
+  const int64_t s0 = fslot[2 * r], s1 = fslot[2 * r + 1];
+  for (int k = 0; k < B * B; ++k) bval[s * B * B + k] = Dg[s0 * B * B + k] + (s1 >= 0 ? Dg[s1 * B * B + k] : 0.0);
 }
 
 // Scalar CSR of the level-0 operator on the structural pattern of the free
@@ -773,71 +876,73 @@ __global__ void k_quad_points_bfacet(int64_t nbf, int D, int nqf, const double* 
 template <int D, int P>
 __global__ __launch_bounds__(64) void k_grad(ElemArgs a) {
   using S = Sz<D, P>;
-  constexpr int NU = S::NU, NL = S::NL, B = S::B, NQ = S::NQ;
-  __shared__ ElemSmem<D, P> sm;
-  __shared__ double sL[NL], sLa[NL], sR[NU], sU[NU], sT[NU], sW[NU], sred[64];
-  const int64_t e = blockIdx.x;
-  const int t = threadIdx.x;
-  const int NT = blockDim.x;
-  elem_geometry<D, P>(a, sm, e, 1.0, a.alpha);
-  elem_integrate<D, P>(a, sm, e, 1.0, false, false);
+  constexpr int NU = S::NU, NL = S::NL, B = S::B, NQ = S::NQ, G = S::G;
+  struct Vec { double L[NL], La[NL], R[NU], T[NU], U[NU], W[NU]; };
+  __shared__ ElemSmem<D, P> sm_[S::EPB];
+  __shared__ Vec sv_[S::EPB];
+  const int g = threadIdx.x % G;
+  ElemSmem<D, P>& sm = sm_[G == 64 ? 0 : threadIdx.x / G];
+  Vec& sv = sv_[G == 64 ? 0 : threadIdx.x / G];
+  const int64_t e0 = (int64_t)blockIdx.x * S::EPB + (G == 64 ? 0 : threadIdx.x / G);
+  const bool live = e0 < a.ne;
+  const int64_t e = live ? e0 : a.ne - 1;
+  elem_geometry<D, P>(a, sm, e, g, 1.0, a.alpha, live);
+  elem_integrate<D, P>(a, sm, e, g, 1.0, false, false);
   const double* Ai = a.Ainv + e * NU * NU;
   const double* Bo = a.Bm + e * NU * NL;
   const double* Co = a.Cm + e * NL * NU;
   const double* Fo = a.Fv + e * NU;
-  for (int r = t; r < NL; r += NT) {
+  for (int r = g; r < NL; r += G) {
     int lf = r / B, m = r % B, f = sm.fid[lf];
     int fr = a.free_rank[f];
-    sL[r] = fr >= 0 ? a.lam_fwd[(int64_t)fr * B + m] : a.lamD[(int64_t)f * B + m];
-    sLa[r] = fr >= 0 ? a.lam_adj[(int64_t)fr * B + m] : 0.0;
+    sv.L[r] = fr >= 0 ? a.lam_fwd[(int64_t)fr * B + m] : a.lamD[(int64_t)f * B + m];
+    sv.La[r] = fr >= 0 ? a.lam_adj[(int64_t)fr * B + m] : 0.0;
   }
   __syncthreads();
-  for (int i = t; i < NU; i += NT) {
+  for (int i = g; i < NU; i += G) {
     double r = Fo[i];
-    for (int c = 0; c < NL; ++c) r -= Bo[i * NL + c] * sL[c];
-    sR[i] = r;
+    for (int c = 0; c < NL; ++c) r -= Bo[i * NL + c] * sv.L[c];
+    sv.R[i] = r;
     double tt = 0.0;
-    for (int c = 0; c < NL; ++c) tt += Co[c * NU + i] * sLa[c];
-    sT[i] = tt;
+    for (int c = 0; c < NL; ++c) tt += Co[c * NU + i] * sv.La[c];
+    sv.T[i] = tt;
   }
   __syncthreads();
-  for (int i = t; i < NU; i += NT) {
+  for (int i = g; i < NU; i += G) {
     double u = 0.0, w = 0.0;
     for (int k = 0; k < NU; ++k) {
-      u += Ai[i * NU + k] * sR[k];
-      w -= Ai[k * NU + i] * sT[k];
+      u += Ai[i * NU + k] * sv.R[k];
+      w -= Ai[k * NU + i] * sv.T[k];
     }
-    sU[i] = u;
-    sW[i] = w;
+    sv.U[i] = u;
+    sv.W[i] = w;
   }
   __syncthreads();
-  if (a.dJdf_q)
-    for (int q = t; q < NQ; q += NT) {
+  if (a.dJdf_q && live)
+    for (int q = g; q < NQ; q += G) {
       double v = 0.0;
-      for (int i = 0; i < NU; ++i) v += sW[i] * a.vol_phi[q * NU + i];
+      for (int i = 0; i < NU; ++i) v += sv.W[i] * a.vol_phi[q * NU + i];
       a.dJdf_q[e * NQ + q] = a.vol_w[q] * sm.absdet * v;
     }
   double acc = 0.0;
-  for (int i = t; i < NU; i += NT) {
+  for (int i = g; i < NU; i += G) {
     double v = 0.0;
-    for (int j = 0; j < NU; ++j) v += sm.A[i * NU + j] * sU[j];
-    for (int c = 0; c < NL; ++c) v += sm.Bm[i * NL + c] * sL[c];
-    acc -= sW[i] * v;
+    for (int j = 0; j < NU; ++j) v += sm.A[i * NU + j] * sv.U[j];
+    for (int c = 0; c < NL; ++c) v += elem_b<D, P>(sm, i, c / B, c % B) * sv.L[c];
+    acc -= sv.W[i] * v;
   }
-  for (int r = t; r < NL; r += NT) {
-    double v = 0.0;
-    for (int j = 0; j < NU; ++j) v += sm.Cm[r * NU + j] * sU[j];
-    int lf = r / B, m = r % B;
-    for (int n = 0; n < B; ++n) v += sm.Dd[lf * B * B + m * B + n] * sL[lf * B + n];
-    acc -= sLa[r] * v;
-  }
-  sred[t] = acc;
   __syncthreads();
-  if (t == 0) {
-    double s2 = 0.0;
-    for (int k = 0; k < NT; ++k) s2 += sred[k];
-    a.dnu_elem[e] = s2;
+  elem_z_to_c<D, P>(sm, g);
+  __syncthreads();
+  for (int r = g; r < NL; r += G) {
+    double v = 0.0;
+    for (int j = 0; j < NU; ++j) v += sm.ZC[r * NU + j] * sv.U[j];
+    int lf = r / B, m = r % B;
+    for (int n = 0; n < B; ++n) v += sm.DD[lf * S::BS + sym(m, n)] * sv.L[lf * B + n];
+    acc -= sv.La[r] * v;
   }
+  for (int o = G / 2; o > 0; o >>= 1) acc += __shfl_xor(acc, o, G);
+  if (g == 0 && live) a.dnu_elem[e] = acc;
 }
 
 // ------------------------------------------------------------ dispatch
@@ -853,7 +958,7 @@ static ah_status launch_element(const ElemArgs& a, hipStream_t st) {
                      (a.Ainv ? (S::NU * S::NU + 2.0 * S::NU * S::NL + S::NU) * 8.0 : 0.0);
   ProfScope ps;
   prof_begin(ps, "element", st, per * (double)a.ne);
-  hipLaunchKernelGGL((k_element<D, P>), dim3(a.ne), dim3(64), 0, st, a);
+  hipLaunchKernelGGL((k_element<D, P>), dim3((unsigned)cdiv(a.ne, S::EPB)), dim3(64), 0, st, a);
   prof_end(ps);
   AH_LAUNCHED();
   return AH_OK;
@@ -871,16 +976,18 @@ static ah_status element_dispatch(int D, int p, const ElemArgs& a, hipStream_t s
 }
 
 template <int B>
-static ah_status scale_to_csr(ah_system* s, const ah_mesh* m, hipStream_t st, int* d_err) {
+static ah_status scale_to_csr(ah_system* s, const ah_mesh* m, const double* Dg, hipStream_t st, int* d_err) {
   const int64_t nfree = s->nfree;
   const int64_t n = nfree * B;
   Arena& ar = s->arena;
-  if (s->unscaled)
+  if (s->unscaled) {
+    hipLaunchKernelGGL(k_diag_store, dim3(cdiv(std::max<int64_t>(nfree, 1), 256)), dim3(256), 0, st, nfree, B,
+                       m->d_bsr_ptr, m->d_bsr_col, m->d_facet_slot, Dg, s->d_bval);
     hipLaunchKernelGGL(k_ident_blocks<B>, dim3(cdiv(std::max<int64_t>(nfree * B * B, 1), 256)), dim3(256), 0, st,
                        nfree, s->d_Dinv);
-  else
+  } else
     hipLaunchKernelGGL(k_diag_inv<B>, dim3(cdiv(std::max<int64_t>(nfree, 1), 64)), dim3(64), 0, st, nfree,
-                       m->d_bsr_ptr, m->d_bsr_col, s->d_bval, s->d_Dinv, d_err);
+                       m->d_facet_slot, Dg, s->d_Dinv, d_err);
   AH_LAUNCHED();
   const int64_t nob = (int64_t)m->odb_col.size();
   s->nnz = s->unscaled ? (int64_t)B * B * s->nnzb : n + (int64_t)B * B * nob;
@@ -934,13 +1041,14 @@ static ah_status rhs_dispatch(int b, ah_system* s, const double* g_q, hipStream_
   return AH_EUNSUPPORTED;
 }
 
-static ah_status scale_dispatch(int b, ah_system* s, const ah_mesh* m, hipStream_t st, int* d_err) {
+static ah_status scale_dispatch(int b, ah_system* s, const ah_mesh* m, const double* Dg, hipStream_t st,
+                                int* d_err) {
   switch (b) {
-    case 2: return scale_to_csr<2>(s, m, st, d_err);
-    case 3: return scale_to_csr<3>(s, m, st, d_err);
-    case 4: return scale_to_csr<4>(s, m, st, d_err);
-    case 6: return scale_to_csr<6>(s, m, st, d_err);
-    case 10: return scale_to_csr<10>(s, m, st, d_err);
+    case 2: return scale_to_csr<2>(s, m, Dg, st, d_err);
+    case 3: return scale_to_csr<3>(s, m, Dg, st, d_err);
+    case 4: return scale_to_csr<4>(s, m, Dg, st, d_err);
+    case 6: return scale_to_csr<6>(s, m, Dg, st, d_err);
+    case 10: return scale_to_csr<10>(s, m, Dg, st, d_err);
   }
   set_error("unsupported facet block size %d", b);
   return AH_EUNSUPPORTED;
@@ -964,16 +1072,24 @@ static void fill_common(ElemArgs& a, const ah_mesh* m, const RefTables& t) {
   a.fac_mu = t.d_fac_mu;
   a.fac_psi = t.d_fac_psi;
   a.fac_proj = t.d_fac_proj;
+  a.fac_pp = t.d_fac_pp;
+  a.fac_mass = t.d_fac_mass;
   a.ten_adv = t.d_ten_adv;
   a.ten_dif = t.d_ten_dif;
-  for (int i = 0; i < 20; ++i)
-    for (int c = 0; c < 3; ++c) a.mono[i][c] = (i < t.nu && c < t.D) ? (int8_t)t.mono[i * t.D + c] : 0;
+  a.ten_dn = t.d_ten_dn;
+  for (int i = 0; i < t.nu; ++i) {
+    int at = 0;
+    for (int c = t.D - 1; c >= 0; --c) at = at * (t.p + 1) + t.node[i * t.D + c];
+    a.node[at] = (int8_t)i;
+  }
+  for (int m = 0; m < t.b; ++m)
+    for (int c = 0; c < t.D; ++c) a.fnode[m][c] = (int8_t)t.fnode[m * t.D + c];
 }
 
 template <int D, int P>
 static ah_status launch_grad(const ElemArgs& a, hipStream_t st) {
   if (a.ne == 0) return AH_OK;
-  hipLaunchKernelGGL((k_grad<D, P>), dim3(a.ne), dim3(64), 0, st, a);
+  hipLaunchKernelGGL((k_grad<D, P>), dim3((unsigned)cdiv(a.ne, Sz<D, P>::EPB)), dim3(64), 0, st, a);
   AH_LAUNCHED();
   return AH_OK;
 }
@@ -1092,12 +1208,19 @@ static ah_status assemble_impl(const ah_mesh* mc, const ah_hdg_params* prm, doub
   }
   int* d_err = nullptr;
   if ((rc = ar.get(&d_err, 1))) return fail(rc);
+  // the elements' parts of the diagonal blocks and of H, summed per facet
+  Arena tmp;
+  tmp.stream = st;
+  auto fail_tmp = [&](ah_status code) { tmp.release(); return fail(code); };
+  double *Dg = nullptr, *Hk = nullptr;
+  if ((rc = tmp.get(&Dg, m->ne * (m->D + 1) * t.b * t.b))) return fail_tmp(rc);
+  if ((rc = tmp.get(&Hk, m->ne * s->nl))) return fail_tmp(rc);
   if (hipMemsetAsync(d_err, 0, sizeof(int), st) != hipSuccess ||
-      hipMemsetAsync(s->d_bval, 0, s->nnzb * t.b * t.b * sizeof(double), st) != hipSuccess ||
-      hipMemsetAsync(s->d_H0, 0, s->n * sizeof(double), st) != hipSuccess ||
+      (m->shared_pairs &&
+       hipMemsetAsync(s->d_bval, 0, s->nnzb * t.b * t.b * sizeof(double), st) != hipSuccess) ||
       hipMemsetAsync(s->d_lamD, 0, m->nf * t.b * sizeof(double), st) != hipSuccess) {
     set_error("hdg_assemble: memset failed");
-    return fail(AH_EHIP);
+    return fail_tmp(AH_EHIP);
   }
   ElemArgs a{};
   fill_common(a, m, t);
@@ -1109,15 +1232,21 @@ static ah_status assemble_impl(const ah_mesh* mc, const ah_hdg_params* prm, doub
   a.nu = nu;
   a.alpha = s->alpha;
   a.bval = s->d_bval;
-  a.H = s->d_H0;
+  a.Dg = Dg;
+  a.Hk = Hk;
+  a.add_off = m->shared_pairs;
   a.lamD = s->d_lamD;
   a.Ainv = s->d_Ainv;
   a.Bm = s->d_Bm;
   a.Cm = s->d_Cm;
   a.Fv = s->d_Fv;
   a.err = d_err;
-  if ((rc = element_dispatch(m->D, prm->p, a, st))) return fail(rc);
-  if ((rc = scale_dispatch(t.b, s, m, st, d_err))) return fail(rc);
+  if ((rc = element_dispatch(m->D, prm->p, a, st))) return fail_tmp(rc);
+  if (s->n > 0)
+    hipLaunchKernelGGL(k_h_sum, dim3((unsigned)cdiv(s->n, 256)), dim3(256), 0, st, s->n, t.b, m->d_facet_slot, Hk,
+                       s->d_H0);
+  if ((rc = scale_dispatch(t.b, s, m, Dg, st, d_err))) return fail_tmp(rc);
+  tmp.release();
   if ((rc = rhs_dispatch(t.b, s, g_q, st))) return fail(rc);
   int herr = 0;
   if ((rc = read_bytes(d_err, &herr, sizeof(int), st))) return fail(rc);

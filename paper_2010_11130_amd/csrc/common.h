@@ -83,21 +83,28 @@ inline int dim_p(int D, int p) {  // dim P_p on a D-simplex
 }
 
 // Host reference data of (D, p): quadrature and basis tables uploaded once.
+// Element basis: Lagrange on the equispaced lattice (lattice order).
 struct RefTables {
   int D = 0, p = 0, nq = 0, nqf = 0, nu = 0, b = 0;
   // host copies
   std::vector<double> vol_w, vol_lam;         // [nq], [nq][D+1]
-  std::vector<double> vol_phi, vol_dphi;      // [nq][nu], [nq][nu][D]  (monomial basis)
+  std::vector<double> vol_phi, vol_dphi;      // [nq][nu], [nq][nu][D]
   std::vector<double> fac_w, fac_mu;          // [nqf] (sum 1), [nqf][D]
   std::vector<double> fac_psi;                // [nqf][b]
   std::vector<double> fac_proj;               // [b][nqf]  L2 projection onto P_p(F)
-  std::vector<int> mono;                      // [nu][D] exponents of the element basis
-  std::vector<double> lat_phi;                // [nu lattice nodes][nu] basis at element lattice
+  std::vector<double> fac_pp;                 // [nqf][b(b+1)/2]  psi_m psi_n, (m, n <= m) at m(m+1)/2 + n
+  std::vector<double> fac_mass;               // [b(b+1)/2]  facet mass matrix over |F|
+  std::vector<int> node;                      // [nu][D] lattice indices of the element nodes
+  std::vector<int> fnode;                     // [b][D]  barycentric indices of the facet nodes
   // reference tensors of the volume terms (affine element, velocity linear
   // in each element), by the element rule:
   //   ten_adv[k][r][i][j] = sum_q w_q lam_k phi_j d_r phi_i   (k <= D, r < D)
-  //   ten_dif[r][s][i][j] = sum_q w_q d_r phi_j d_s phi_i     (r, s < D)
+  //   ten_dif[rs][i][j] = sum_q w_q d_r phi_j d_s phi_i, plus the same with r
+  //     and s exchanged where r < s   (rs over r <= s)
   std::vector<double> ten_adv, ten_dif;
+  // normal-derivative tensor of facet f (the one opposite local vertex f):
+  //   ten_dn[f][r][j][i] = (1/|F|) int_F d_r phi_i phi_j
+  std::vector<double> ten_dn;
   // device copies
   double* d_vol_w = nullptr;
   double* d_vol_lam = nullptr;
@@ -107,9 +114,11 @@ struct RefTables {
   double* d_fac_mu = nullptr;
   double* d_fac_psi = nullptr;
   double* d_fac_proj = nullptr;
-  double* d_lat_phi = nullptr;
+  double* d_fac_pp = nullptr;
+  double* d_fac_mass = nullptr;
   double* d_ten_adv = nullptr;
   double* d_ten_dif = nullptr;
+  double* d_ten_dn = nullptr;
 };
 
 ah_status build_ref_tables(int D, int p, RefTables& t);
@@ -142,6 +151,8 @@ struct ah_mesh {
   std::vector<int64_t> odb_ptr;      // [nfree+1] the same pattern without the diagonal block
   std::vector<int32_t> odb_col;      // [nnzb - nfree]
   std::vector<int32_t> elem_slot;    // [ne][(D+1)^2] block index or -1
+  std::vector<int32_t> facet_slot;   // [nfree][2] its element facets e (D+1) + lf, -1 when absent
+  bool shared_pairs = false;         // two cells share more than one facet (a cell given twice)
   // time planes and the pairing used for slab coupling: boundary facets of
   // this mesh on t_min matched (by spatial vertex coordinates) with facets on
   // t_max of the mesh pair_src
@@ -163,6 +174,7 @@ struct ah_mesh {
   int32_t* d_facet_vert = nullptr;
   int32_t* d_free_rank = nullptr;
   int32_t* d_elem_slot = nullptr;
+  int32_t* d_facet_slot = nullptr;
   int64_t* d_bsr_ptr = nullptr;
   int32_t* d_bsr_col = nullptr;
   int64_t* d_odb_ptr = nullptr;

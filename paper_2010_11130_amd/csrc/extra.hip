@@ -20,16 +20,16 @@ __device__ inline double trace_at(const int32_t* free_rank, const double* lam, c
   return dir_zero ? 0.0 : lamD[(int64_t)f * b + m];
 }
 
-// U_K = A_K^-1 (F_K - B_K Lambda_K), then the values at the element lattice.
+// U_K = A_K^-1 (F_K - B_K Lambda_K): values at the element lattice (nodal basis).
 __global__ void k_reconstruct(int64_t ne, int D, int nu, int b, const int32_t* __restrict__ elem_facet,
                               const int32_t* __restrict__ free_rank, const double* __restrict__ lam,
                               const double* __restrict__ lamD, const double* __restrict__ Ainv,
                               const double* __restrict__ Bm, const double* __restrict__ Fv,
-                              const double* __restrict__ lat_phi, double* __restrict__ U) {
+                              double* __restrict__ U) {
   int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (e >= ne) return;
   const int nl = (D + 1) * b;
-  double L[40], r[20], u[20];
+  double L[40], r[20];
   for (int lf = 0; lf <= D; ++lf) {
     int f = elem_facet[e * (D + 1) + lf];
     for (int m = 0; m < b; ++m) L[lf * b + m] = trace_at(free_rank, lam, lamD, f, m, b, false);
@@ -42,12 +42,7 @@ __global__ void k_reconstruct(int64_t ne, int D, int nu, int b, const int32_t* _
   for (int i = 0; i < nu; ++i) {
     double s = 0.0;
     for (int k = 0; k < nu; ++k) s += Ainv[(e * nu + i) * nu + k] * r[k];
-    u[i] = s;
-  }
-  for (int k = 0; k < nu; ++k) {
-    double s = 0.0;
-    for (int i = 0; i < nu; ++i) s += lat_phi[k * nu + i] * u[i];
-    U[e * nu + k] = s;
+    U[e * nu + i] = s;
   }
 }
 
@@ -324,7 +319,7 @@ extern "C" ah_status hdg_reconstruct(const ah_system* s, const double* lam, doub
   const ah_mesh* m = s->mesh;
   if (m->ne == 0) return AH_OK;
   hipLaunchKernelGGL(k_reconstruct, dim3((unsigned)cdiv(m->ne, 128)), dim3(128), 0, st, m->ne, s->D, s->nu, s->b,
-                     m->d_elem_facet, m->d_free_rank, lam, s->d_lamD, s->d_Ainv, s->d_Bm, s->d_Fv, s->tab.d_lat_phi, U);
+                     m->d_elem_facet, m->d_free_rank, lam, s->d_lamD, s->d_Ainv, s->d_Bm, s->d_Fv, U);
   AH_LAUNCHED();
   return AH_OK;
 }

@@ -278,6 +278,23 @@ static double lagr(int dim, int p, const int* beta, const double* lam) {
   return v;
 }
 
+// Its gradient d/dxi_a = d/dlam_{a+1} - d/dlam_0, a < dim.
+static void lagr_grad(int dim, int p, const int* beta, const double* lam, double* g) {
+  double dl[4];
+  for (int k = 0; k <= dim; ++k) {
+    double v = 1.0, d = 0.0, rest = 1.0;
+    for (int c = 0; c <= dim; ++c)
+      for (int m = 0; m < beta[c]; ++m) {
+        const double f = (p * lam[c] - m) / (m + 1.0);
+        if (c != k) { rest *= f; continue; }
+        d = d * f + v * (p / (m + 1.0));
+        v *= f;
+      }
+    dl[k] = d * rest;
+  }
+  for (int a = 0; a < dim; ++a) g[a] = dl[a + 1] - dl[0];
+}
+
 static bool invert_small(int n, std::vector<double>& A) {
   std::vector<double> I(n * n, 0.0);
   for (int i = 0; i < n; ++i) I[i * n + i] = 1.0;
@@ -314,30 +331,23 @@ ah_status build_ref_tables(int D, int p, RefTables& t) {
   t.nq = (int)w.size();
   t.vol_w = w;
   t.vol_lam.assign((size_t)t.nq * (D + 1), 0.0);
-  // element basis: monomials xi^alpha, |alpha| <= p, ordered like the lattice
-  std::vector<int> mono;
-  lattice(D, p, mono);
-  t.mono = mono;
+  lattice(D, p, t.node);
+  std::vector<int> gam((size_t)t.nu * (D + 1));   // barycentric indices of the nodes
+  for (int i = 0; i < t.nu; ++i) {
+    int s = p;
+    for (int a = 0; a < D; ++a) { gam[i * (D + 1) + a + 1] = t.node[i * D + a]; s -= t.node[i * D + a]; }
+    gam[i * (D + 1)] = s;
+  }
   t.vol_phi.assign((size_t)t.nq * t.nu, 0.0);
   t.vol_dphi.assign((size_t)t.nq * t.nu * D, 0.0);
   for (int q = 0; q < t.nq; ++q) {
     double s = 0;
     for (int a = 0; a < D; ++a) { t.vol_lam[q * (D + 1) + a + 1] = xi[q * D + a]; s += xi[q * D + a]; }
     t.vol_lam[q * (D + 1)] = 1.0 - s;
+    const double* lam = &t.vol_lam[q * (D + 1)];
     for (int i = 0; i < t.nu; ++i) {
-      const int* al = &mono[i * D];
-      double v = 1.0;
-      for (int a = 0; a < D; ++a) v *= std::pow(xi[q * D + a], al[a]);
-      t.vol_phi[q * t.nu + i] = v;
-      for (int a = 0; a < D; ++a) {
-        double d = 0.0;
-        if (al[a] > 0) {
-          d = al[a];
-          for (int c = 0; c < D; ++c)
-            d *= std::pow(xi[q * D + c], c == a ? al[c] - 1 : al[c]);
-        }
-        t.vol_dphi[((size_t)q * t.nu + i) * D + a] = d;
-      }
+      t.vol_phi[q * t.nu + i] = lagr(D, p, &gam[i * (D + 1)], lam);
+      lagr_grad(D, p, &gam[i * (D + 1)], lam, &t.vol_dphi[((size_t)q * t.nu + i) * D]);
     }
   }
   // facet rule and Lagrange facet basis (vertex order = sorted global ids)
@@ -357,11 +367,22 @@ ah_status build_ref_tables(int D, int p, RefTables& t) {
   std::vector<int> flat;
   lattice(D - 1, p, flat);
   t.fac_psi.assign((size_t)t.nqf * t.b, 0.0);
+  t.fnode.assign((size_t)t.b * D, 0);
   for (int m = 0; m < t.b; ++m) {
     int beta[3] = {p, 0, 0};
     for (int a = 0; a < D - 1; ++a) { beta[a + 1] = flat[m * (D - 1) + a]; beta[0] -= beta[a + 1]; }
+    for (int a = 0; a < D; ++a) t.fnode[m * D + a] = beta[a];
     for (int q = 0; q < t.nqf; ++q) t.fac_psi[q * t.b + m] = lagr(D - 1, p, beta, &t.fac_mu[q * D]);
   }
+  const int bs = t.b * (t.b + 1) / 2;
+  t.fac_pp.assign((size_t)t.nqf * bs, 0.0);
+  t.fac_mass.assign(bs, 0.0);
+  for (int q = 0; q < t.nqf; ++q)
+    for (int m = 0, k = 0; m < t.b; ++m)
+      for (int n = 0; n <= m; ++n, ++k) {
+        t.fac_pp[(size_t)q * bs + k] = t.fac_psi[q * t.b + m] * t.fac_psi[q * t.b + n];
+        t.fac_mass[k] += t.fac_w[q] * t.fac_pp[(size_t)q * bs + k];
+      }
   std::vector<double> M((size_t)t.b * t.b, 0.0);
   for (int q = 0; q < t.nqf; ++q)
     for (int m = 0; m < t.b; ++m)
@@ -378,7 +399,7 @@ ah_status build_ref_tables(int D, int p, RefTables& t) {
   {
     const int nu = t.nu, nn = nu * nu;
     t.ten_adv.assign((size_t)(D + 1) * D * nn, 0.0);
-    t.ten_dif.assign((size_t)D * D * nn, 0.0);
+    t.ten_dif.assign((size_t)D * (D + 1) / 2 * nn, 0.0);
     for (int q = 0; q < t.nq; ++q) {
       const double wq = t.vol_w[q];
       const double* ph = &t.vol_phi[(size_t)q * nu];
@@ -389,21 +410,32 @@ ah_status build_ref_tables(int D, int p, RefTables& t) {
             const double gi = wq * dp[i * D + r] * ph[j];
             for (int k = 0; k <= D; ++k)
               t.ten_adv[((size_t)(k * D + r) * nn) + i * nu + j] += t.vol_lam[q * (D + 1) + k] * gi;
-            for (int s2 = 0; s2 < D; ++s2)
-              t.ten_dif[((size_t)(r * D + s2) * nn) + i * nu + j] += wq * dp[j * D + r] * dp[i * D + s2];
           }
+          for (int r = 0, rs = 0; r < D; ++r)
+            for (int s2 = r; s2 < D; ++s2, ++rs) {
+              double v = dp[j * D + r] * dp[i * D + s2];
+              if (s2 != r) v += dp[j * D + s2] * dp[i * D + r];
+              t.ten_dif[((size_t)rs * nn) + i * nu + j] += wq * v;
+            }
         }
     }
   }
-  // monomial basis at the element lattice nodes
-  std::vector<int> elat;
-  lattice(D, p, elat);
-  t.lat_phi.assign((size_t)t.nu * t.nu, 0.0);
-  for (int k = 0; k < t.nu; ++k)
-    for (int i = 0; i < t.nu; ++i) {
-      double v = 1.0;
-      for (int a = 0; a < D; ++a) v *= std::pow((double)elat[k * D + a] / p, mono[i * D + a]);
-      t.lat_phi[k * t.nu + i] = v;
+  // normal-derivative tensors of the facets
+  t.ten_dn.assign((size_t)(D + 1) * D * t.nu * t.nu, 0.0);
+  for (int f = 0; f <= D; ++f)
+    for (int q = 0; q < t.nqf; ++q) {
+      double lam[4] = {0, 0, 0, 0};
+      for (int s = 0, v = 0; v <= D; ++v)
+        if (v != f) lam[v] = t.fac_mu[q * D + s++];
+      for (int i = 0; i < t.nu; ++i) {
+        double g[3];
+        lagr_grad(D, p, &gam[i * (D + 1)], lam, g);
+        for (int j = 0; j < t.nu; ++j) {
+          if (gam[j * (D + 1) + f]) continue;   // not a node of this facet: zero trace
+          const double v = t.fac_w[q] * lagr(D, p, &gam[j * (D + 1)], lam);
+          for (int r = 0; r < D; ++r) t.ten_dn[(((size_t)f * D + r) * t.nu + j) * t.nu + i] += v * g[r];
+        }
+      }
     }
   return AH_OK;
 }
@@ -423,9 +455,11 @@ ah_status upload_ref_tables(RefTables& t, Arena& ar) {
   AH_TRY(upload(ar, t.fac_mu, &t.d_fac_mu));
   AH_TRY(upload(ar, t.fac_psi, &t.d_fac_psi));
   AH_TRY(upload(ar, t.fac_proj, &t.d_fac_proj));
-  AH_TRY(upload(ar, t.lat_phi, &t.d_lat_phi));
+  AH_TRY(upload(ar, t.fac_pp, &t.d_fac_pp));
+  AH_TRY(upload(ar, t.fac_mass, &t.d_fac_mass));
   AH_TRY(upload(ar, t.ten_adv, &t.d_ten_adv));
   AH_TRY(upload(ar, t.ten_dif, &t.d_ten_dif));
+  AH_TRY(upload(ar, t.ten_dn, &t.d_ten_dn));
   return AH_OK;
 }
 
@@ -550,7 +584,7 @@ extern "C" ah_status ah_mesh_create(int D, int64_t nv, const double* vert, int64
 
 ah_mesh::~ah_mesh() {
   void* ptrs[] = {d_vert, d_cell, d_elem_facet, d_facet_loc, d_kind, d_bf_index, d_bfacets,
-                  d_facet_vert, d_free_rank, d_elem_slot, d_bsr_ptr, d_bsr_col, d_odb_ptr, d_odb_col,
+                  d_facet_vert, d_free_rank, d_elem_slot, d_facet_slot, d_bsr_ptr, d_bsr_col, d_odb_ptr, d_odb_col,
                   d_pair, d_pair_perm};
   for (void* p : ptrs)
     if (p) (void)hipFree(p);
@@ -583,6 +617,7 @@ ah_status mesh_upload(ah_mesh* m, hipStream_t st) {
   AH_TRY(up(&m->d_facet_vert, m->facet_vert, st));
   AH_TRY(up(&m->d_free_rank, m->free_rank, st));
   AH_TRY(up(&m->d_elem_slot, m->elem_slot, st));
+  AH_TRY(up(&m->d_facet_slot, m->facet_slot, st));
   AH_TRY(up(&m->d_bsr_ptr, m->bsr_ptr, st));
   AH_TRY(up(&m->d_bsr_col, m->bsr_col, st));
   AH_TRY(up(&m->d_odb_ptr, m->odb_ptr, st));
@@ -720,17 +755,24 @@ extern "C" ah_status ah_mesh_set_bc(ah_mesh* m, const int8_t* kind) {
   }
   const int nb = (D + 1) * (D + 1);
   m->elem_slot.assign(m->ne * nb, -1);
+  m->facet_slot.assign(2 * nfree, -1);
+  m->shared_pairs = false;
+  std::vector<uint8_t> written(m->bsr_col.size(), 0);
   for (int64_t e = 0; e < m->ne; ++e)
     for (int i = 0; i <= D; ++i) {
       int32_t ri = m->free_rank[m->elem_facet[e * (D + 1) + i]];
       if (ri < 0) continue;
+      int32_t* fs = &m->facet_slot[2 * (size_t)ri];
+      fs[fs[0] < 0 ? 0 : 1] = (int32_t)(e * (D + 1) + i);
       for (int j = 0; j <= D; ++j) {
         int32_t rj = m->free_rank[m->elem_facet[e * (D + 1) + j]];
         if (rj < 0) continue;
         const int32_t* b0 = &m->bsr_col[m->bsr_ptr[ri]];
         const int32_t* b1 = &m->bsr_col[m->bsr_ptr[ri + 1]];
         const int32_t* it = std::lower_bound(b0, b1, rj);
-        m->elem_slot[e * nb + i * (D + 1) + j] = (int32_t)(m->bsr_ptr[ri] + (it - b0));
+        const int64_t sl = m->bsr_ptr[ri] + (it - b0);
+        m->elem_slot[e * nb + i * (D + 1) + j] = (int32_t)sl;
+        if (i != j && written[sl]++) m->shared_pairs = true;
       }
     }
   m->bc_set = true;
