@@ -726,55 +726,74 @@ __global__ void k_scaled_rowptr(int64_t nfree, const int64_t* __restrict__ bptr,
   }
 }
 
-// One wave per block row R: lane c takes column c of the block row (block
-// c/B, node c%B), reads that column of S's block once and writes its B
-// scaled entries into the B scalar rows, and into the off-diagonal
-// facet-block copy (oval, scaled systems).
-template <int B>
+// A thread per (block row, column of it): a free facet couples to at most the
+// 2 D + 1 facets of its two cells, so thread t of a workgroup takes column
+// t % NC of the workgroup's block row t / NC, reads that column of S's block
+// once and writes its B scaled entries into the B scalar rows, and into the
+// off-diagonal facet-block copy (oval, scaled systems); the rows' D_b^-1 are
+// staged in LDS.  Bound by HBM: 8 bytes in and 20 out per entry (p = 1, 96^3
+// mesh: 764M entries in 4.35 ms; a wave per block row, two thirds of its lanes
+// idle at three columns a block, took 8.94 ms = 2.4 TB/s; p = 2 slab: 123 us,
+// now 80).
+template <int D, int B>
+struct CsrSz {
+  static constexpr int NB = 2 * D + 1;        // blocks of a block row, the diagonal one included
+  static constexpr int NC = NB * B;
+  static constexpr int ROWS = 256 / NC;       // block rows per workgroup
+};
+
+template <int D, int B>
 __global__ __launch_bounds__(256) void k_csr_scaled(int64_t nfree, const int64_t* __restrict__ bptr,
                                                     const int32_t* __restrict__ bcol, const double* __restrict__ bval,
                                                     const double* __restrict__ dinv, int32_t* __restrict__ col,
                                                     double* __restrict__ val, int unscaled,
                                                     const int64_t* __restrict__ optr, double* __restrict__ oval) {
-  const int64_t R = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) >> 6;
-  const int lane = threadIdx.x & 63;
-  if (R >= nfree) return;
+  using S = CsrSz<D, B>;
+  __shared__ double sd[S::ROWS * B * B];
+  const int64_t R0 = (int64_t)blockIdx.x * S::ROWS;
+  if (!unscaled) {
+    const int nd = (int)min((int64_t)S::ROWS, nfree - R0) * B * B;
+    for (int k = threadIdx.x; k < nd; k += 256) sd[k] = dinv[R0 * B * B + k];
+  }
+  __syncthreads();
+  const int rr = threadIdx.x / S::NC, c = threadIdx.x % S::NC;
+  const int64_t R = R0 + rr;
+  if (rr >= S::ROWS || R >= nfree) return;
   const int64_t s0 = bptr[R];
   const int nb = (int)(bptr[R + 1] - s0);
+  if (c >= nb * B) return;
   const int64_t o0 = unscaled ? 0 : optr[R];
-  const int nob = unscaled ? 0 : (int)(optr[R + 1] - o0);
+  const int nob = nb - 1;
   // first entry of the block row and the length of each of its rows
   const int64_t base = unscaled ? (int64_t)B * B * s0 : (int64_t)B * R + (int64_t)B * B * o0;
   const int rlen = unscaled ? B * nb : 1 + B * nob;
-  for (int c = lane; c < nb * B; c += 64) {
-    const int j = c / B, n = c % B;
-    const int64_t s = s0 + j;
-    const int32_t C = bcol[s];
-    double bc[B];
+  const int j = c / B, n = c % B;
+  const int64_t s = s0 + j;
+  const int32_t C = bcol[s];
+  if (!unscaled && C == R) {
+    // the identity block: one diagonal entry per row
+    col[base + (int64_t)n * rlen + j * B] = (int32_t)(R * B + n);
+    val[base + (int64_t)n * rlen + j * B] = 1.0;
+    return;
+  }
+  double bc[B];
 #pragma unroll
-    for (int k = 0; k < B; ++k) bc[k] = bval[s * B * B + k * B + n];
+  for (int k = 0; k < B; ++k) bc[k] = bval[s * B * B + k * B + n];
+  // one diagonal entry precedes the blocks after the diagonal block
+  const int pos = unscaled || C < R ? c : c - B + 1;
+  const int64_t ob = o0 * B * B + (C < R ? j : j - 1) * B + n;
 #pragma unroll
-    for (int m = 0; m < B; ++m) {
-      const int64_t rs = base + (int64_t)m * rlen;
-      if (unscaled) {
-        col[rs + c] = (int32_t)(C * B + n);
-        val[rs + c] = bc[m];
-      } else if (C == R) {
-        if (n == m) {
-          col[rs + j * B] = (int32_t)(R * B + m);
-          val[rs + j * B] = 1.0;
-        }
-      } else {
-        double v = 0.0;
+  for (int m = 0; m < B; ++m) {
+    const int64_t rs = base + (int64_t)m * rlen + pos;
+    col[rs] = (int32_t)(C * B + n);
+    if (unscaled) {
+      val[rs] = bc[m];
+    } else {
+      double v = 0.0;
 #pragma unroll
-        for (int k = 0; k < B; ++k) v += dinv[R * B * B + m * B + k] * bc[k];
-        // one diagonal entry precedes the blocks after the diagonal block
-        const int pos = C < R ? c : c - B + 1;
-        col[rs + pos] = (int32_t)(C * B + n);
-        val[rs + pos] = v;
-        const int jo = C < R ? j : j - 1;
-        oval[o0 * B * B + (int64_t)m * nob * B + jo * B + n] = v;
-      }
+      for (int k = 0; k < B; ++k) v += sd[(rr * B + m) * B + k] * bc[k];
+      val[rs] = v;
+      oval[ob + (int64_t)m * nob * B] = v;
     }
   }
 }
@@ -835,6 +854,7 @@ __global__ void k_neumann(int64_t nbf, int D, int nqf, const int32_t* __restrict
     area = 0.5 * sqrt(fmax(g00 * g11 - g01 * g01, 0.0));
   }
   double acc = 0.0;
+#pragma unroll 5
   for (int q = 0; q < nqf; ++q) acc += fac_w[q] * g_q[bf * nqf + q] * fac_psi[q * B + m];
   H[(int64_t)fr * B + m] += area * acc;
 }
@@ -975,7 +995,7 @@ static ah_status element_dispatch(int D, int p, const ElemArgs& a, hipStream_t s
   return AH_EUNSUPPORTED;
 }
 
-template <int B>
+template <int D, int B>
 static ah_status scale_to_csr(ah_system* s, const ah_mesh* m, const double* Dg, hipStream_t st, int* d_err) {
   const int64_t nfree = s->nfree;
   const int64_t n = nfree * B;
@@ -1002,9 +1022,9 @@ static ah_status scale_to_csr(ah_system* s, const ah_mesh* m, const double* Dg, 
   hipLaunchKernelGGL(k_scaled_rowptr<B>, dim3((unsigned)cdiv(n + 1, 256)), dim3(256), 0, st, nfree, m->d_bsr_ptr,
                      (const int64_t*)m->d_odb_ptr, (int)s->unscaled, s->d_rowptr);
   AH_LAUNCHED();
-  const dim3 gw((unsigned)cdiv(std::max<int64_t>(nfree, 1) * 64, 256));
-  hipLaunchKernelGGL(k_csr_scaled<B>, gw, dim3(256), 0, st, nfree, m->d_bsr_ptr, m->d_bsr_col, s->d_bval, s->d_Dinv,
-                     s->d_col, s->d_val, (int)s->unscaled, (const int64_t*)m->d_odb_ptr, s->d_odv);
+  const dim3 gw((unsigned)cdiv(std::max<int64_t>(nfree, 1), CsrSz<D, B>::ROWS));
+  hipLaunchKernelGGL((k_csr_scaled<D, B>), gw, dim3(256), 0, st, nfree, m->d_bsr_ptr, m->d_bsr_col, s->d_bval,
+                     s->d_Dinv, s->d_col, s->d_val, (int)s->unscaled, (const int64_t*)m->d_odb_ptr, s->d_odv);
   AH_LAUNCHED();
   return AH_OK;
 }
@@ -1019,8 +1039,8 @@ static ah_status rhs_from_neumann(ah_system* s, const double* g_q, hipStream_t s
   const int64_t nbf = (int64_t)m->bfacets.size();
   if (g_q && nbf > 0) {
     hipLaunchKernelGGL(k_neumann<B>, dim3((unsigned)cdiv(nbf * B, 128)), dim3(128), 0, st, nbf, m->D, s->nqf,
-                       m->d_bfacets, m->d_kind, m->d_free_rank, m->d_facet_vert, m->d_vert, s->tab.d_fac_w,
-                       s->tab.d_fac_psi, g_q, s->d_H);
+                       m->d_bfacets, m->d_kind, m->d_free_rank, m->d_facet_vert, m->d_vert, s->tab->d_fac_w,
+                       s->tab->d_fac_psi, g_q, s->d_H);
     AH_LAUNCHED();
   }
   hipLaunchKernelGGL(k_hhat<B>, dim3((unsigned)cdiv(n, 128)), dim3(128), 0, st, s->nfree, s->d_Dinv, s->d_H,
@@ -1043,13 +1063,13 @@ static ah_status rhs_dispatch(int b, ah_system* s, const double* g_q, hipStream_
 
 static ah_status scale_dispatch(int b, ah_system* s, const ah_mesh* m, const double* Dg, hipStream_t st,
                                 int* d_err) {
-  switch (b) {
-    case 2: return scale_to_csr<2>(s, m, Dg, st, d_err);
-    case 3: return scale_to_csr<3>(s, m, Dg, st, d_err);
-    case 4: return scale_to_csr<4>(s, m, Dg, st, d_err);
-    case 6: return scale_to_csr<6>(s, m, Dg, st, d_err);
-    case 10: return scale_to_csr<10>(s, m, Dg, st, d_err);
-  }
+  const int D = m->D;
+  if (D == 2 && b == 2) return scale_to_csr<2, 2>(s, m, Dg, st, d_err);
+  if (D == 2 && b == 3) return scale_to_csr<2, 3>(s, m, Dg, st, d_err);
+  if (D == 2 && b == 4) return scale_to_csr<2, 4>(s, m, Dg, st, d_err);
+  if (D == 3 && b == 3) return scale_to_csr<3, 3>(s, m, Dg, st, d_err);
+  if (D == 3 && b == 6) return scale_to_csr<3, 6>(s, m, Dg, st, d_err);
+  if (D == 3 && b == 10) return scale_to_csr<3, 10>(s, m, Dg, st, d_err);
   set_error("unsupported facet block size %d", b);
   return AH_EUNSUPPORTED;
 }
@@ -1097,7 +1117,7 @@ static ah_status launch_grad(const ElemArgs& a, hipStream_t st) {
 ah_status grad_dispatch(const ah_system* s, const double* a_vert, const double* lam_fwd, const double* lam_adj,
                         double* dJdf_q, double* dnu_elem, hipStream_t st) {
   ElemArgs a{};
-  fill_common(a, s->mesh, s->tab);
+  fill_common(a, s->mesh, *s->tab);
   a.a_vert = a_vert;
   a.nu = 1.0;
   a.alpha = s->alpha;
@@ -1136,11 +1156,11 @@ extern "C" ah_status ah_quad_points(const ah_mesh* mc, int p, double* xq_elem, d
   if (!mc) { set_error("null mesh"); return AH_EINVAL; }
   ah_mesh* m = const_cast<ah_mesh*>(mc);
   hipStream_t st = as_stream(stream);
-  RefTables t;
-  AH_TRY(build_ref_tables(m->D, p, t));
+  std::shared_ptr<const RefTables> tab;
+  AH_TRY(ref_tables(m->D, p, tab));
+  const RefTables& t = *tab;
   Arena tmp;
   tmp.stream = st;
-  AH_TRY(upload_ref_tables(t, tmp));
   double* d_vert = nullptr;
   int32_t *d_cell = nullptr, *d_bf = nullptr, *d_fv = nullptr;
   AH_TRY(tmp.get(&d_vert, m->vert.size()));
@@ -1185,10 +1205,9 @@ static ah_status assemble_impl(const ah_mesh* mc, const ah_hdg_params* prm, doub
   s->keep = prm->keep_element_data != 0;
   s->unscaled = prm->no_block_scale != 0;
   auto fail = [&](ah_status code) { delete s; return code; };
-  ah_status rc = build_ref_tables(m->D, prm->p, s->tab);
+  ah_status rc = ref_tables(m->D, prm->p, s->tab);
   if (rc) return fail(rc);
-  if ((rc = upload_ref_tables(s->tab, s->arena))) return fail(rc);
-  const RefTables& t = s->tab;
+  const RefTables& t = *s->tab;
   s->nu = t.nu; s->b = t.b; s->nl = (m->D + 1) * t.b; s->nq = t.nq; s->nqf = t.nqf;
   s->nfree = m->nfree;
   s->n = m->nfree * t.b;
@@ -1264,11 +1283,11 @@ extern "C" ah_status ah_quad_points_facets(const ah_mesh* mc, int p, double* xq_
   ah_mesh* m = const_cast<ah_mesh*>(mc);
   if (m->nf == 0) return AH_OK;
   hipStream_t st = as_stream(stream);
-  RefTables t;
-  AH_TRY(build_ref_tables(m->D, p, t));
+  std::shared_ptr<const RefTables> tab;
+  AH_TRY(ref_tables(m->D, p, tab));
+  const RefTables& t = *tab;
   Arena tmp;
   tmp.stream = st;
-  AH_TRY(upload_ref_tables(t, tmp));
   std::vector<int32_t> ids((size_t)m->nf);
   for (int64_t f = 0; f < m->nf; ++f) ids[(size_t)f] = (int32_t)f;
   double* d_vert = nullptr;

@@ -5,6 +5,7 @@
 
 #include <cstdint>
 #include <cstdio>
+#include <memory>
 #include <mutex>
 #include <string>
 #include <vector>
@@ -82,7 +83,7 @@ inline int dim_p(int D, int p) {  // dim P_p on a D-simplex
   return D == 0 ? 1 : r;
 }
 
-// Host reference data of (D, p): quadrature and basis tables uploaded once.
+// Reference data of (D, p): quadrature and basis tables.
 // Element basis: Lagrange on the equispaced lattice (lattice order).
 struct RefTables {
   int D = 0, p = 0, nq = 0, nqf = 0, nu = 0, b = 0;
@@ -105,7 +106,8 @@ struct RefTables {
   // normal-derivative tensor of facet f (the one opposite local vertex f):
   //   ten_dn[f][r][j][i] = (1/|F|) int_F d_r phi_i phi_j
   std::vector<double> ten_dn;
-  // device copies
+  // device copies, in one allocation
+  double* d_all = nullptr;
   double* d_vol_w = nullptr;
   double* d_vol_lam = nullptr;
   double* d_vol_phi = nullptr;
@@ -119,10 +121,16 @@ struct RefTables {
   double* d_ten_adv = nullptr;
   double* d_ten_dif = nullptr;
   double* d_ten_dn = nullptr;
+  ~RefTables() { if (d_all) (void)hipFree(d_all); }
 };
 
 ah_status build_ref_tables(int D, int p, RefTables& t);
-ah_status upload_ref_tables(RefTables& t, Arena& arena);
+// The tables of (D, p) on the current device, built and uploaded on first use
+// and shared by every later caller (any thread, any stream: the upload is
+// complete on return, the tables never change).  Up to six entries of at most
+// 0.2 MB per device stay until ah_pool_trim; a system keeps its own alive.
+ah_status ref_tables(int D, int p, std::shared_ptr<const RefTables>& out);
+void ref_tables_release(int dev);
 void gauss_jacobi01(int n, double alpha, double* s, double* w);
 void simplex_rule(int dim, int n, std::vector<double>& xi, std::vector<double>& w);
 void lattice(int dim, int p, std::vector<int>& idx);   // [nn][dim], i_1 fastest

@@ -340,7 +340,7 @@ extern "C" ah_status hdg_inflow_from_trace(const ah_system* prev, const double* 
     lat.beta[k][0] = (int8_t)s0;
   }
   hipLaunchKernelGGL(k_inflow, dim3((unsigned)cdiv(m->npair * prev->nqf, 256)), dim3(256), 0, st, m->npair, prev->D,
-                     prev->p, prev->b, prev->nqf, m->d_pair, m->d_pair_perm, prev->tab.d_fac_mu,
+                     prev->p, prev->b, prev->nqf, m->d_pair, m->d_pair_perm, prev->tab->d_fac_mu,
                      prev->mesh->d_free_rank, lam_prev, prev->d_lamD, lat, g_q_next);
   AH_LAUNCHED();
   return AH_OK;

@@ -440,27 +440,51 @@ ah_status build_ref_tables(int D, int p, RefTables& t) {
   return AH_OK;
 }
 
-static ah_status upload(Arena& ar, const std::vector<double>& h, double** d) {
-  AH_TRY(ar.get(d, h.size()));
-  AH_HIP(hipMemcpyAsync(*d, h.data(), h.size() * sizeof(double), hipMemcpyHostToDevice, ar.stream));
+static std::mutex g_ref_mu;
+static std::map<int, std::shared_ptr<const RefTables>>& ref_cache() {   // by device * 16 + D * 4 + p
+  static auto* c = new std::map<int, std::shared_ptr<const RefTables>>;
+  return *c;
+}
+
+ah_status ref_tables(int D, int p, std::shared_ptr<const RefTables>& out) {
+  if (D < 2 || D > 3 || p < 1 || p > 3) {
+    set_error("unsupported dim_st=%d p=%d (dim_st in 2..3, p in 1..3)", D, p);
+    return AH_EUNSUPPORTED;
+  }
+  int dev = 0;
+  AH_HIP(hipGetDevice(&dev));
+  std::lock_guard<std::mutex> lock(g_ref_mu);
+  auto& slot = ref_cache()[dev * 16 + D * 4 + p];
+  if (!slot) {
+    auto t = std::make_shared<RefTables>();
+    AH_TRY(build_ref_tables(D, p, *t));
+    const std::pair<const std::vector<double>*, double**> parts[] = {
+        {&t->vol_w, &t->d_vol_w}, {&t->vol_lam, &t->d_vol_lam}, {&t->vol_phi, &t->d_vol_phi},
+        {&t->vol_dphi, &t->d_vol_dphi}, {&t->fac_w, &t->d_fac_w}, {&t->fac_mu, &t->d_fac_mu},
+        {&t->fac_psi, &t->d_fac_psi}, {&t->fac_proj, &t->d_fac_proj}, {&t->fac_pp, &t->d_fac_pp},
+        {&t->fac_mass, &t->d_fac_mass}, {&t->ten_adv, &t->d_ten_adv}, {&t->ten_dif, &t->d_ten_dif},
+        {&t->ten_dn, &t->d_ten_dn}};
+    std::vector<double> all;
+    std::vector<size_t> at;
+    for (auto& x : parts) {
+      at.push_back(all.size());
+      all.insert(all.end(), x.first->begin(), x.first->end());
+      all.resize((all.size() + 31) & ~size_t(31), 0.0);
+    }
+    const hipError_t e = hipMalloc((void**)&t->d_all, all.size() * sizeof(double));
+    if (e != hipSuccess) { t->d_all = nullptr; set_error("hipMalloc: %s", hipGetErrorString(e)); return AH_ENOMEM; }
+    AH_HIP(hipMemcpy(t->d_all, all.data(), all.size() * sizeof(double), hipMemcpyHostToDevice));
+    for (size_t k = 0; k < at.size(); ++k) *parts[k].second = t->d_all + at[k];
+    slot = t;
+  }
+  out = slot;
   return AH_OK;
 }
 
-ah_status upload_ref_tables(RefTables& t, Arena& ar) {
-  AH_TRY(upload(ar, t.vol_w, &t.d_vol_w));
-  AH_TRY(upload(ar, t.vol_lam, &t.d_vol_lam));
-  AH_TRY(upload(ar, t.vol_phi, &t.d_vol_phi));
-  AH_TRY(upload(ar, t.vol_dphi, &t.d_vol_dphi));
-  AH_TRY(upload(ar, t.fac_w, &t.d_fac_w));
-  AH_TRY(upload(ar, t.fac_mu, &t.d_fac_mu));
-  AH_TRY(upload(ar, t.fac_psi, &t.d_fac_psi));
-  AH_TRY(upload(ar, t.fac_proj, &t.d_fac_proj));
-  AH_TRY(upload(ar, t.fac_pp, &t.d_fac_pp));
-  AH_TRY(upload(ar, t.fac_mass, &t.d_fac_mass));
-  AH_TRY(upload(ar, t.ten_adv, &t.d_ten_adv));
-  AH_TRY(upload(ar, t.ten_dif, &t.d_ten_dif));
-  AH_TRY(upload(ar, t.ten_dn, &t.d_ten_dn));
-  return AH_OK;
+void ref_tables_release(int dev) {
+  std::lock_guard<std::mutex> lock(g_ref_mu);
+  auto& c = ref_cache();
+  c.erase(c.lower_bound(dev * 16), c.lower_bound((dev + 1) * 16));
 }
 
 }  // namespace ah
@@ -809,6 +833,7 @@ extern "C" ah_status ah_pool_trim(void) {
     return AH_EHIP;
   }
   cache_release_device(dev);
+  ah::ref_tables_release(dev);
   return AH_OK;
 }
 

@@ -11,7 +11,7 @@ struct ah_system {
   bool keep = false;
   bool unscaled = false;      // no facet-block scaling (S_hat = S, D_b^-1 = I)
   ah::Arena arena;
-  ah::RefTables tab;
+  std::shared_ptr<const ah::RefTables> tab;
   int64_t n = 0;        // free DOFs
   int64_t nfree = 0;    // free facets
   int64_t nnzb = 0;     // blocks of the free-facet pattern

@@ -68,3 +68,27 @@ def test_unscaled_keeps_the_diagonal_blocks(D, p):
     v, c = shuffled(D, 2, 5)
     prob = PolynomialProblem(D - 1, p, 3e-2, seed=p)
     check(gpu_system(v, c, prob, p, block_scale=False), setup_problem(v, c, prob, p, block_scale=False))
+
+
+def test_tables_shared_by_threads():
+    """The reference tables are built once per (dimension, degree): threads on
+    their own streams that all meet them first (after a trim) get the systems
+    that a single thread gets."""
+    import threading
+    from paper_2010_11130_amd import pool_trim
+    work = [(D, p) for D in (2, 3) for p in (1, 2, 3)] * 2
+    data = [(shuffled(D, 2, 3), PolynomialProblem(D - 1, p, 3e-2, seed=p), p) for D, p in work]
+    ref = [gpu_system(*vc, prob, p).export()["val"] for vc, prob, p in data]
+    pool_trim()
+    got = [None] * len(data)
+
+    def run(k):
+        with torch.cuda.stream(torch.cuda.Stream()):
+            got[k] = gpu_system(*data[k][0], data[k][1], data[k][2]).export()["val"]
+
+    ths = [threading.Thread(target=run, args=(k,)) for k in range(len(data))]
+    for t in ths:
+        t.start()
+    for t in ths:
+        t.join()
+    assert all(torch.equal(a, b) for a, b in zip(ref, got))
