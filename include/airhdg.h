@@ -275,9 +275,9 @@ typedef struct {
 } ah_setup_info;
 
 /* Environment (read by air_setup; for tests and tuning): AH_TAIL_MAX (rows,
- * default 4096) bounds the first level of the single-workgroup coarse end of
- * the cycle (0: every level runs with grid-wide kernels); AH_TAIL_LDS=0 runs
- * that coarse end from global memory instead of an LDS image; AH_G0 (2, 4,
+ * default 2048, at most 8192) bounds the first level of the dense coarse end
+ * of the cycle, level 0 counting double (0: only the coarsest level is
+ * dense); AH_G0 (2, 4,
  * 8, 16, 32) fixes the lanes per row of the level-0 kernels.  Alternative
  * code paths (the defaults are the faster forms): AH_SWO=0 sweeps over the
  * natural order from the F and C lists after an interpolation pass instead

@@ -2578,13 +2578,8 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
     L0.oval = s->d_odv;
   }
   h->lev.push_back(L0);
-  // the tail never holds level 0 when it has more rows than this
-  int64_t tail_max = 4096;
-  if (const char* e = std::getenv("AH_TAIL_MAX")) tail_max = std::atoll(e);
-  // adjoint: level 0 of a scaled system gets its transpose in the
-  // facet-block layout, and no CSR transpose unless the ordered sweeps or the
-  // tail need it
-  bool at0_csr = true;
+  int64_t end_max = 2048;   // rows up to which a level starts the dense coarse end
+  if (const char* e = std::getenv("AH_TAIL_MAX")) end_max = std::min<int64_t>(std::atoll(e), 8192);
   for (int l = 0;; ++l) {
     AhLevel& L = h->lev[l];
     const int64_t n = L.n;
@@ -2849,55 +2844,6 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
       hipLaunchKernelGGL(k_cast32, g1(L.nnzR), dim3(256), 0, st, L.nnzR, L.Rval, L.Rval32);
       CKH(hipGetLastError());
     }
-    if (prm.adjoint && l == 0 && L.ob && prm.relax < 2 && n > tail_max) {
-      const int64_t nbr = n / L.ob;
-      CK(ar.get(&L.otval, L.nov));
-      CKH(hipMemsetAsync(d_int + 2, 0, sizeof(int), st));
-      hipLaunchKernelGGL(k_fb_transpose, g1(nbr), dim3(256), 0, st, nbr, L.ob, L.optr, L.ocol, L.oval, L.otval,
-                         d_int + 2);
-      CKH(hipGetLastError());
-      int bad = 0;
-      CK(read_bytes(d_int + 2, &bad, sizeof(int), st));
-      if (bad) {
-        L.otval = nullptr;
-      } else {
-        at0_csr = false;
-        if (prm.fp32_cycle) {
-          CK(ar.get(&L.otval32, L.nov));
-          hipLaunchKernelGGL(k_cast32, g1(L.nov), dim3(256), 0, st, L.nov, L.otval, L.otval32);
-          CKH(hipGetLastError());
-        }
-      }
-    }
-    if (prm.adjoint) {
-      if (l > 0 || at0_csr)
-        CK(transpose(n, n, L.rowptr, L.col, L.val, L.nnz, ar, tmp, st, &L.ATptr, &L.ATcol, &L.ATval));
-      CK(transpose(nc, n, L.Rptr, L.Rcol, L.Rval, L.nnzR, ar, tmp, st, &L.RTptr, &L.RTcol, &L.RTval));
-      int32_t* pc = nullptr;
-      int64_t* pp = nullptr;
-      int32_t* pcc = nullptr;
-      CK(tmp.get(&pc, n + 1));
-      CK(tmp.get(&pp, n + 1));
-      hipLaunchKernelGGL(k_p_rowcnt, g1(n), dim3(256), 0, st, n, L.pcol, pc);
-      CKH(hipGetLastError());
-      CK(scan_i32_to_i64(pc, pp, n, st, tmp));
-      int64_t nnzp = 0;
-      CK(read_i64(pp + n, &nnzp, st));
-      CK(tmp.get(&pcc, nnzp));
-      hipLaunchKernelGGL(k_p_fill, g1(n), dim3(256), 0, st, n, L.pcol, pp, pcc);
-      CKH(hipGetLastError());
-      CK(transpose(n, nc, pp, pcc, nullptr, nnzp, ar, tmp, st, &L.PTptr, &L.PTcol, nullptr));
-      L.nnzP = nnzp;
-      if (prm.fp32_cycle) {
-        if (L.ATval) {
-          CK(ar.get(&L.ATval32, L.nnz));
-          hipLaunchKernelGGL(k_cast32, g1(L.nnz), dim3(256), 0, st, L.nnz, L.ATval, L.ATval32);
-        }
-        CK(ar.get(&L.RTval32, L.nnzR));
-        hipLaunchKernelGGL(k_cast32, g1(L.nnzR), dim3(256), 0, st, L.nnzR, L.RTval, L.RTval32);
-        CKH(hipGetLastError());
-      }
-    }
     // (the temporary buffers go back to the pool in stream order)
     tmp.release();
     h->lev.push_back(C);
@@ -2933,10 +2879,69 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
     }
     CKH(hipGetLastError());
   }
-  if (prm.adjoint && !h->lev[0].ATptr && !h->lev[0].otval) {
-    // level 0 is the coarsest: the adjoint FGMRES still needs S_hat^T
+  coarse_end_pick(h, end_max);
+  // adjoint: the transposed operators of the levels above the coarse end.
+  // Level 0 of a scaled system gets A^T in the facet-block layout, and no CSR
+  // transpose unless the ordered sweeps need it; the Krylov operator needs
+  // A_0^T in either form wherever the coarse end starts.
+  if (prm.adjoint) {
+    bool at0_csr = true;
     AhLevel& A0 = h->lev[0];
-    CK(transpose(A0.n, A0.n, A0.rowptr, A0.col, A0.val, A0.nnz, ar, tmp, st, &A0.ATptr, &A0.ATcol, &A0.ATval));
+    if (A0.ob && prm.relax < 2) {
+      const int64_t nbr = A0.n / A0.ob;
+      CK(ar.get(&A0.otval, A0.nov));
+      CKH(hipMemsetAsync(d_int + 1, 0, sizeof(int), st));
+      hipLaunchKernelGGL(k_fb_transpose, g1(nbr), dim3(256), 0, st, nbr, A0.ob, A0.optr, A0.ocol, A0.oval, A0.otval,
+                         d_int + 1);
+      CKH(hipGetLastError());
+      int bad = 0;
+      CK(read_bytes(d_int + 1, &bad, sizeof(int), st));
+      if (bad) {
+        A0.otval = nullptr;
+      } else {
+        at0_csr = false;
+        if (prm.fp32_cycle) {
+          CK(ar.get(&A0.otval32, A0.nov));
+          hipLaunchKernelGGL(k_cast32, g1(A0.nov), dim3(256), 0, st, A0.nov, A0.otval, A0.otval32);
+          CKH(hipGetLastError());
+        }
+      }
+    }
+    for (int l = 0; l < std::max(h->end0, 1); ++l) {
+      AhLevel& L = h->lev[l];
+      const int64_t n = L.n, nc = L.nc;
+      if (l > 0 || at0_csr) {
+        CK(transpose(n, n, L.rowptr, L.col, L.val, L.nnz, ar, tmp, st, &L.ATptr, &L.ATcol, &L.ATval));
+        if (prm.fp32_cycle) {
+          CK(ar.get(&L.ATval32, L.nnz));
+          hipLaunchKernelGGL(k_cast32, g1(L.nnz), dim3(256), 0, st, L.nnz, L.ATval, L.ATval32);
+          CKH(hipGetLastError());
+        }
+      }
+      if (l >= h->end0) break;
+      CK(transpose(nc, n, L.Rptr, L.Rcol, L.Rval, L.nnzR, ar, tmp, st, &L.RTptr, &L.RTcol, &L.RTval));
+      int32_t* pc = nullptr;
+      int64_t* pp = nullptr;
+      int32_t* pcc = nullptr;
+      CK(tmp.get(&pc, n + 1));
+      CK(tmp.get(&pp, n + 1));
+      hipLaunchKernelGGL(k_p_rowcnt, g1(n), dim3(256), 0, st, n, L.pcol, pc);
+      CKH(hipGetLastError());
+      CK(scan_i32_to_i64(pc, pp, n, st, tmp));
+      int64_t nnzp = 0;
+      CK(read_i64(pp + n, &nnzp, st));
+      CK(tmp.get(&pcc, nnzp));
+      hipLaunchKernelGGL(k_p_fill, g1(n), dim3(256), 0, st, n, L.pcol, pp, pcc);
+      CKH(hipGetLastError());
+      CK(transpose(n, nc, pp, pcc, nullptr, nnzp, ar, tmp, st, &L.PTptr, &L.PTcol, nullptr));
+      L.nnzP = nnzp;
+      if (prm.fp32_cycle) {
+        CK(ar.get(&L.RTval32, L.nnzR));
+        hipLaunchKernelGGL(k_cast32, g1(L.nnzR), dim3(256), 0, st, L.nnzR, L.RTval, L.RTval32);
+        CKH(hipGetLastError());
+      }
+      tmp.release();
+    }
   }
   if (prm.relax >= 2) {
     rc = flow_order_build(h, st);
@@ -2977,8 +2982,6 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
     return AH_ESINGULAR;
   }
   h->nfallback = (int64_t)fb;
-  // tail: the levels from the first one with at most tail_max rows are run
-  // by one workgroup inside a single launch per cycle
   {
     if (const char* e = std::getenv("AH_G0")) h->g0 = std::atoi(e);
     if (const char* e = std::getenv("AH_FBB")) h->fbb = std::atoi(e) != 0;
@@ -3025,81 +3028,19 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
       prof_end(ps);
     }
     // coarse levels swept from their lists without a full-block view: the
-    // sweep-ordered CSR copy (not the coarsest level, nor the tail's)
+    // sweep-ordered CSR copy (above the coarse end)
     if (swo)
-      for (int l = 1; l + 1 < nl; ++l) {
-        if (h->lev[l].n < h->list_min || h->lev[l].bb || h->lev[l].n <= tail_max) continue;
+      for (int l = 1; l < h->end0; ++l) {
+        if (h->lev[l].n < h->list_min || h->lev[l].bb) continue;
         ProfScope ps;
         prof_begin(ps, "order_csr", st, 0.0);
         CK(csr_order_build(h, l, st));
         prof_end(ps);
       }
-    std::vector<TailLevel> tl(nl);
-    for (int l = 0; l < nl; ++l) {
-      const AhLevel& L = h->lev[l];
-      TailLevel& T = tl[l];
-      T = TailLevel{};
-      T.n = L.n; T.nc = L.nc; T.nnz = L.nnz; T.nnzR = L.nnzR; T.nnzP = L.nnzP;
-      T.rp = L.rowptr; T.ci = L.col; T.v = L.val; T.v32 = L.val32; T.d = L.diag; T.d32 = L.diag32;
-      T.cf = L.cf; T.pcol = L.pcol;
-      T.Rp = L.Rptr; T.Rc = L.Rcol; T.Rv = L.Rval; T.Rv32 = L.Rval32;
-      T.ATp = L.ATptr; T.ATc = L.ATcol; T.ATv = L.ATval; T.ATv32 = L.ATval32;
-      T.RTp = L.RTptr; T.RTc = L.RTcol; T.RTv = L.RTval; T.RTv32 = L.RTval32;
-      T.PTp = L.PTptr; T.PTc = L.PTcol;
-      T.b = L.b; T.x = L.x; T.y = L.y; T.b32 = L.b32; T.x32 = L.x32; T.y32 = L.y32;
-    }
-    // the tail starts at the first level with at most tail_max rows whose
-    // levels, down to the coarsest, fit in LDS as an FP64 image
-    // (with an ordered relaxation, level 0 is swept outside the tail)
-    const int lt = prm.relax >= 2 ? 1 : 0;
-    h->tail0 = -1;
-    h->tail_lds = false;
-    // AH_TAIL_LDS=0 keeps the tail in global memory (both directions)
-    bool lds_ok = true;
-    if (const char* e = std::getenv("AH_TAIL_LDS")) lds_ok = std::atoi(e) != 0;
-    if (lds_ok && nl <= TAIL_MAX_LEVELS) {
-      for (int l = lt; l < nl; ++l) {
-        if (h->lev[l].n > tail_max) continue;
-        TailLds lo[TAIL_MAX_LEVELS];
-        int64_t oc = 0;
-        const int64_t b64 = tail_lds_layout<8>(tl.data(), l, nl, lo, &oc);
-        if (b64 <= TAIL_LDS_MAX) {
-          h->tail0 = l;
-          h->tail_lds = true;
-          h->tail_bytes[0] = b64;
-          h->tail_bytes[1] = tail_lds_layout<4>(tl.data(), l, nl, lo, &oc);
-          break;
-        }
-      }
-    }
-    // the adjoint's transposed tail from an LDS image of the same levels
-    if (prm.adjoint && h->tail_lds && nl <= TAIL_MAX_LEVELS) {
-      TailLdsT lt_[TAIL_MAX_LEVELS];
-      int64_t oc = 0;
-      const int64_t b64 = tail_lds_layout_t<8>(tl.data(), h->tail0, nl, lt_, &oc);
-      if (b64 <= TAIL_LDS_MAX) {
-        h->tail_lds_t = true;
-        h->tail_bytes_t[0] = b64;
-        h->tail_bytes_t[1] = tail_lds_layout_t<4>(tl.data(), h->tail0, nl, lt_, &oc);
-      }
-    }
-    if (h->tail0 < 0)   // no LDS image fits: small levels run from global memory
-      for (int l = lt; l < nl; ++l)
-        if (h->lev[l].n <= std::min<int64_t>(tail_max, 500)) { h->tail0 = l; break; }
-    rc = ar.get(&h->d_tail, nl);
-    if (rc < 0) { delete h; return rc; }
-    double* pin = pinned_scratch((nl * sizeof(TailLevel) + 7) / 8);
-    if (!pin) { set_error("pinned host allocation failed"); delete h; return AH_ENOMEM; }
-    std::memcpy(pin, tl.data(), nl * sizeof(TailLevel));
-    if (hipMemcpyAsync(h->d_tail, pin, nl * sizeof(TailLevel), hipMemcpyHostToDevice, st) != hipSuccess) {
-      set_error("air_setup: upload of the level table failed");
-      delete h;
-      return AH_EHIP;
-    }
-    rc = tail_image_build(h, st);
+    rc = coarse_end_build(h, st);
     if (rc < 0) { delete h; return rc; }
     if (hipStreamSynchronize(st) != hipSuccess) {
-      set_error("air_setup: upload of the level table failed");
+      set_error("air_setup: building the coarse end failed");
       delete h;
       return AH_EHIP;
     }

@@ -462,533 +462,184 @@ __global__ __launch_bounds__(256) void k_gs_csr(int64_t n, const int32_t* __rest
   if (lane == 0) yn[i] = yo[i] + (g[i] - acc) / d[i];
 }
 
-// Coarse end of the cycle in one workgroup: every level from l0 down,
-// one row per thread, phases separated by workgroup barriers.
-template <class T>
-struct TLv;
-template <>
-struct TLv<double> {
-  __device__ static const double* A(const TailLevel& L) { return L.v; }
-  __device__ static const double* AT(const TailLevel& L) { return L.ATv; }
-  __device__ static const double* R(const TailLevel& L) { return L.Rv; }
-  __device__ static const double* RT(const TailLevel& L) { return L.RTv; }
-  __device__ static const double* d(const TailLevel& L) { return L.d; }
-  __device__ static double* b(const TailLevel& L) { return L.b; }
-  __device__ static double* x(const TailLevel& L) { return L.x; }
-  __device__ static double* y(const TailLevel& L) { return L.y; }
+// One level of the coarse end: what the cycle reads, and the lanes per row of
+// its sweeps and of the restriction into the next level.
+struct EndLevel {
+  const int64_t *rp, *Rp;
+  const int32_t *ci, *pcol, *Rc;
+  const double *v, *d, *Rv;
+  const int8_t* cf;
+  int n, gA, gR;
 };
-template <>
-struct TLv<float> {
-  __device__ static const float* A(const TailLevel& L) { return L.v32; }
-  __device__ static const float* AT(const TailLevel& L) { return L.ATv32; }
-  __device__ static const float* R(const TailLevel& L) { return L.Rv32; }
-  __device__ static const float* RT(const TailLevel& L) { return L.RTv32; }
-  __device__ static const float* d(const TailLevel& L) { return L.d32; }
-  __device__ static float* b(const TailLevel& L) { return L.b32; }
-  __device__ static float* x(const TailLevel& L) { return L.x32; }
-  __device__ static float* y(const TailLevel& L) { return L.y32; }
+constexpr int END_LEVELS = 32;
+struct EndLevels {
+  EndLevel lv[END_LEVELS];
 };
-
-template <class T>
-__device__ inline T row_dot(const int64_t* rp, const int32_t* ci, const T* av, const T* x, int64_t i) {
-  T s = 0;
-  for (int64_t k = rp[i]; k < rp[i + 1]; ++k) s += (av ? av[k] : (T)1) * x[ci[k]];
-  return s;
-}
-
-// Global -> LDS staging for the tail kernel: n elements, eight independent
-// loads in flight per thread (the image is re-staged on every cycle, so the
-// copy must not be one dependent load per iteration).
-template <class D, class S>
-__device__ inline void tail_stage(D* __restrict__ dst, const S* __restrict__ src, int n, int t, int NT) {
-  int k = t;
-  for (; k + 7 * NT < n; k += 8 * NT) {
-    S a[8];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) a[q] = src[k + q * NT];
-#pragma unroll
-    for (int q = 0; q < 8; ++q) dst[k + q * NT] = (D)a[q];
-  }
-  for (; k < n; k += NT) dst[k] = (D)src[k];
-}
-
-// Lanes per row for a tail phase over n rows of mean length avg: as many as
-// the workgroup allows (power of two, at most 32), not more than the row has.
-__device__ inline int tail_lanes(int n, int avg, int NT) {
-  int g = 1;
-  while (g < 32 && 2 * g * n <= NT && g < avg) g *= 2;
-  return g;
-}
+constexpr int END_T = 512;
 
 // Run f(G) with G the compile-time lane count for the runtime value g.
 template <class F>
-__device__ inline void tail_with_lanes(int g, F&& f) {
+__device__ inline void end_with_lanes(int g, F&& f) {
   switch (g) {
     case 1: f(std::integral_constant<int, 1>{}); break;
     case 2: f(std::integral_constant<int, 2>{}); break;
     case 4: f(std::integral_constant<int, 4>{}); break;
     case 8: f(std::integral_constant<int, 8>{}); break;
-    case 16: f(std::integral_constant<int, 16>{}); break;
-    default: f(std::integral_constant<int, 32>{}); break;
+    default: f(std::integral_constant<int, 16>{}); break;
   }
 }
 
-// Row i of an LDS CSR matrix times x, split over the G lanes of a group
-// (lane g takes entries g, g+G, ...); the sum is returned in every lane.
-template <int G, class T, class TS>
-__device__ inline TS tail_row(const int32_t* rp, const int32_t* ci, const T* av, const T* x, int i, int g) {
-  TS s = 0;
-  const int k1 = rp[i + 1];
+// Row i of a CSR matrix times the NC vectors x (interleaved), the sums in
+// every lane of the group.
+template <int G, int NC>
+__device__ inline void end_row(const int64_t* __restrict__ rp, const int32_t* __restrict__ ci,
+                               const double* __restrict__ av, const double* x, int i, int g, double* s) {
+#pragma unroll
+  for (int q = 0; q < NC; ++q) s[q] = 0.0;
+  const int k1 = (int)rp[i + 1];
 #pragma unroll 4
-  for (int k = rp[i] + g; k < k1; k += G) s += (TS)av[k] * (TS)x[ci[k]];
+  for (int k = (int)rp[i] + g; k < k1; k += G) {
+    const double v = av[k];
+    const double* xc = x + ci[k] * NC;
 #pragma unroll
-  for (int o = G / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, G);
-  return s;
+    for (int q = 0; q < NC; ++q) s[q] += v * xc[q];
+  }
+#pragma unroll
+  for (int o = G / 2; o > 0; o >>= 1)
+#pragma unroll
+    for (int q = 0; q < NC; ++q) s[q] += __shfl_xor(s[q], o, G);
 }
 
-// The tail's LDS image written to global memory (layout of
-// tail_lds_layout): int32 row offsets, operator values, diagonals, C/F flags,
-// one-point columns, R, and the coarsest inverse; the work vectors are left
-// unset.
-template <class T>
-__global__ __launch_bounds__(1024) void k_tail_image(const TailLevel* __restrict__ lv, int l0, int nlev,
-                                                     const double* __restrict__ cinv, char* __restrict__ img) {
-  __shared__ TailLds lo[TAIL_MAX_LEVELS];
-  __shared__ int64_t s_cinv;
+// The matrix of the cycle from level 0 of E down: a workgroup applies the
+// cycle (restrictions, coarsest inverse, one-point interpolation and Jacobi
+// sweeps) to NC columns of the identity, with the vectors in LDS and the
+// levels' matrices from L2, and writes its columns of B (and rows of B^T).
+// Runs once per hierarchy; it replaces the same walk in every cycle.
+template <int NC>
+__global__ __launch_bounds__(END_T) void k_end_cols(EndLevels E, int nlev, const double* __restrict__ cinv, int nsw,
+                                                    double omega, double* __restrict__ B, double* __restrict__ Bt) {
+  extern __shared__ double sm[];
   const int t = threadIdx.x;
-  const int NT = blockDim.x;
   const int last = nlev - 1;
-  if (t == 0) {
-    int64_t oc = 0;
-    tail_lds_layout<(int)sizeof(T)>(lv, l0, nlev, lo, &oc);
-    s_cinv = oc;
-  }
+  const int N = E.lv[0].n;
+  const int j0 = blockIdx.x * NC;
+  int tot = 0;
+  for (int l = 0; l < nlev; ++l) tot += E.lv[l].n;
+  double* const bs = sm;                 // right-hand sides, level after level
+  double* const ys = sm + tot * NC;      // results, likewise
+  double* const xs = ys + tot * NC;      // the other sweep buffer
+  for (int k = t; k < N * NC; k += END_T) bs[k] = k / NC == j0 + k % NC ? 1.0 : 0.0;
   __syncthreads();
-#define TI_PTR(type, l, f) reinterpret_cast<type*>(img + lo[(l) - l0].f)
-  for (int l = l0; l < last; ++l) {
-    const TailLevel& L = lv[l];
-    const int n = (int)L.n, nc = (int)L.nc, nnz = (int)L.nnz, nnzR = (int)L.nnzR;
-    tail_stage(TI_PTR(int32_t, l, rp), L.rp, n + 1, t, NT);
-    tail_stage(TI_PTR(int32_t, l, ci), L.ci, nnz, t, NT);
-    tail_stage(TI_PTR(T, l, v), TLv<T>::A(L), nnz, t, NT);
-    tail_stage(TI_PTR(T, l, d), TLv<T>::d(L), n, t, NT);
-    tail_stage(TI_PTR(int8_t, l, cf), L.cf, n, t, NT);
-    tail_stage(TI_PTR(int32_t, l, pc), L.pcol, n, t, NT);
-    tail_stage(TI_PTR(int32_t, l, Rp), L.Rp, nc + 1, t, NT);
-    tail_stage(TI_PTR(int32_t, l, Rc), L.Rc, nnzR, t, NT);
-    tail_stage(TI_PTR(T, l, Rv), TLv<T>::R(L), nnzR, t, NT);
+  int at = 0;
+  for (int l = 0; l < last; ++l) {
+    const EndLevel& L = E.lv[l];
+    const int nc = E.lv[l + 1].n;
+    const double* b = bs + at * NC;
+    double* cb = bs + (at + L.n) * NC;
+    end_with_lanes(L.gR, [&](auto GC) {
+      constexpr int G = decltype(GC)::value;
+      const int g = t % G;
+      for (int i = t / G; i < nc; i += END_T / G) {
+        double s[NC];
+        end_row<G, NC>(L.Rp, L.Rc, L.Rv, b, i, g, s);
+        if (g == 0)
+#pragma unroll
+          for (int q = 0; q < NC; ++q) cb[i * NC + q] = s[q];
+      }
+    });
+    __syncthreads();
+    at += L.n;
   }
-#undef TI_PTR
-  const int nL = (int)lv[last].n;
-  tail_stage(reinterpret_cast<double*>(img + s_cinv), cinv, nL * nL, t, NT);
-}
-
-// Forward coarse end of the cycle from an LDS image: every array of levels
-// l0 .. nlev-1 and the coarsest inverse are copied into LDS, then the
-// restriction, coarsest solve, interpolation and F, F, C sweeps of all these
-// levels run out of LDS with workgroup barriers between the phases; each
-// phase gives a row to a group of lanes sized to the level.  The result of
-// level l0 is written to out.
-template <class T>
-__global__ __launch_bounds__(1024) void k_tail_lds(const TailLevel* __restrict__ lv, int l0, int nlev,
-                                                   const char* __restrict__ img, const T* __restrict__ b_in,
-                                                   T* __restrict__ out, int nsw, T omega) {
-  extern __shared__ __align__(16) char sm[];
-  __shared__ TailLds lo[TAIL_MAX_LEVELS];
-  __shared__ int64_t s_cinv, s_bytes;
-  const int t = threadIdx.x;
-  const int NT = blockDim.x;
-  const int last = nlev - 1;
-  if (t == 0) {
-    int64_t oc = 0;
-    s_bytes = tail_lds_layout<(int)sizeof(T)>(lv, l0, nlev, lo, &oc);
-    s_cinv = oc;
-  }
-  __syncthreads();
-#define TL_PTR(type, l, f) reinterpret_cast<type*>(sm + lo[(l) - l0].f)
-  // stage the image past level l0's input vector in 16-byte chunks, all of a
-  // thread's loads issued before its stores; the input goes into that vector
   {
-    const uint4* __restrict__ src = reinterpret_cast<const uint4*>(img);
-    uint4* dst = reinterpret_cast<uint4*>(sm);
-    const int c1 = (int)(s_bytes >> 4);
-    int c = (int)(lo[0].x >> 4) + t;
-    for (; c + 7 * NT < c1; c += 8 * NT) {
-      uint4 a[8];
+    const int nL = E.lv[last].n;
+    const double* b = bs + at * NC;
+    double* y = ys + at * NC;
+    for (int i = t / 8; i < nL; i += END_T / 8) {
+      double s[NC];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) a[q] = src[c + q * NT];
+      for (int q = 0; q < NC; ++q) s[q] = 0.0;
+      for (int j = t % 8; j < nL; j += 8) {
+        const double c = cinv[(int64_t)i * nL + j];
 #pragma unroll
-      for (int q = 0; q < 8; ++q) dst[c + q * NT] = a[q];
+        for (int q = 0; q < NC; ++q) s[q] += c * b[j * NC + q];
+      }
+#pragma unroll
+      for (int o = 4; o > 0; o >>= 1)
+#pragma unroll
+        for (int q = 0; q < NC; ++q) s[q] += __shfl_xor(s[q], o, 8);
+      if (t % 8 == 0)
+#pragma unroll
+        for (int q = 0; q < NC; ++q) y[i * NC + q] = s[q];
     }
-    for (; c < c1; c += NT) dst[c] = src[c];
-    tail_stage(TL_PTR(T, l0, b), b_in, (int)lv[l0].n, t, NT);
-  }
-  const int nL = (int)lv[last].n;
-  const double* ci_s = reinterpret_cast<const double*>(sm + s_cinv);
-  __syncthreads();
-  // restriction down to the coarsest level
-  for (int l = l0; l < last; ++l) {
-    const int nc = (int)lv[l].nc;
-    const int32_t* Rp = TL_PTR(int32_t, l, Rp);
-    const int32_t* Rc = TL_PTR(int32_t, l, Rc);
-    const T* Rv = TL_PTR(T, l, Rv);
-    const T* b = TL_PTR(T, l, b);
-    T* cb = TL_PTR(T, l + 1, b);
-    const int gR = tail_lanes(nc, nc ? (int)(lv[l].nnzR / nc) : 1, NT);
-    tail_with_lanes(gR, [&](auto GC) {
-      constexpr int G = decltype(GC)::value;
-      const int g = t % G;
-      for (int i = t / G; i < nc; i += NT / G) {
-        const T r = tail_row<G, T, T>(Rp, Rc, Rv, b, i, g);
-        if (g == 0) cb[i] = r;
-      }
-    });
     __syncthreads();
   }
-  // coarsest: y = C^-1 b (FP64 accumulation)
-  {
-    const T* b = TL_PTR(T, last, b);
-    T* z = TL_PTR(T, last, y);
-    tail_with_lanes(tail_lanes(nL, nL, NT), [&](auto GC) {
-      constexpr int G = decltype(GC)::value;
-      const int g = t % G;
-      for (int i = t / G; i < nL; i += NT / G) {
-        double s = 0.0;
-        for (int j = g; j < nL; j += G) s += ci_s[i * nL + j] * (double)b[j];
+  // up: x = P e_c, then the sweeps x -> y (-> x -> y)
+  for (int l = last - 1; l >= 0; --l) {
+    const EndLevel& L = E.lv[l];
+    const double* ec = ys + at * NC;
+    at -= L.n;
+    const double* b = bs + at * NC;
+    double* cur = xs;
+    double* dst = ys + at * NC;
+    for (int i = t; i < L.n; i += END_T) {
+      const int c = L.pcol[i];
 #pragma unroll
-        for (int o = G / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, G);
-        if (g == 0) z[i] = (T)s;
-      }
-    });
+      for (int q = 0; q < NC; ++q) cur[i * NC + q] = c >= 0 ? ec[c * NC + q] : 0.0;
+    }
     __syncthreads();
-  }
-  // up: x = P e_c, then the sweeps ping-pong x -> y -> x -> y
-  for (int l = last - 1; l >= l0; --l) {
-    const int n = (int)lv[l].n;
-    const int32_t* rp = TL_PTR(int32_t, l, rp);
-    const int32_t* ci = TL_PTR(int32_t, l, ci);
-    const T* v = TL_PTR(T, l, v);
-    const T* d = TL_PTR(T, l, d);
-    const int8_t* cf = TL_PTR(int8_t, l, cf);
-    const int32_t* pc = TL_PTR(int32_t, l, pc);
-    const T* bl = TL_PTR(T, l, b);
-    const T* ec = TL_PTR(T, l + 1, y);
-    T* cur = TL_PTR(T, l, x);
-    for (int i = t; i < n; i += NT) cur[i] = pc[i] >= 0 ? ec[pc[i]] : (T)0;
-    __syncthreads();
-    const int gA = tail_lanes(n, n ? (int)(lv[l].nnz / n) : 1, NT);
-    for (int s = 0; s < nsw; ++s) {
-      const int X = (nsw == 1 || s < 2) ? 0 : 1;
-      T* dst = (s % 2 == 0) ? TL_PTR(T, l, y) : TL_PTR(T, l, x);
-      tail_with_lanes(gA, [&](auto GC) {
+    for (int w = 0; w < nsw; ++w) {
+      const int X = (nsw == 1 || w < 2) ? 0 : 1;
+      end_with_lanes(L.gA, [&](auto GC) {
         constexpr int G = decltype(GC)::value;
         const int g = t % G;
-        for (int i = t / G; i < n; i += NT / G) {
-          T xi = cur[i];
-          if (cf[i] == X) {
-            const T di = d[i];
-            const T r = tail_row<G, T, T>(rp, ci, v, cur, i, g);
-            if (fabs((double)di) >= 1e-30) xi += omega * (bl[i] - r) / di;
+        for (int i = t / G; i < L.n; i += END_T / G) {
+          double x[NC];
+#pragma unroll
+          for (int q = 0; q < NC; ++q) x[q] = cur[i * NC + q];
+          if (L.cf[i] == X) {
+            const double d = L.d[i];
+            double s[NC];
+            end_row<G, NC>(L.rp, L.ci, L.v, cur, i, g, s);
+            if (fabs(d) >= 1e-30)
+#pragma unroll
+              for (int q = 0; q < NC; ++q) x[q] += omega * (b[i * NC + q] - s[q]) / d;
           }
-          if (g == 0) dst[i] = xi;
+          if (g == 0)
+#pragma unroll
+            for (int q = 0; q < NC; ++q) dst[i * NC + q] = x[q];
         }
       });
       __syncthreads();
+      double* const o = cur;
       cur = dst;
+      dst = o;
     }
   }
-  // the level-l0 result is in y (odd number of sweeps) or in y (coarsest only)
-  {
-    const T* r = (l0 == last) ? TL_PTR(T, last, y) : TL_PTR(T, l0, y);
-    for (int i = t; i < (int)lv[l0].n; i += NT) out[i] = r[i];
+  for (int k = t; k < N * NC; k += END_T) {
+    const int i = k / NC, q = k % NC;
+    if (j0 + q < N) {
+      B[(int64_t)i * N + j0 + q] = ys[k];
+      if (Bt) Bt[(int64_t)(j0 + q) * N + i] = ys[k];
+    }
   }
-#undef TL_PTR
 }
 
-// The transposed tail's LDS image in global memory (layout of
-// tail_lds_layout_t): A^T, the diagonal, C/F flags, P^T and R^T of every
-// tail level but the coarsest, then the coarsest inverse.
+// z = B r, a wave per row, FP64 matrix and sums: the coarse end of the cycle
+// (or of the transposed one) in one launch.  Latency bound (1209 rows, the
+// fifth level of the 64^2 slab at p = 2: 6 us); the walk over those levels
+// that it replaces took 35 us per cycle, 20 of them in one workgroup.
 template <class T>
-__global__ __launch_bounds__(1024) void k_tail_image_t(const TailLevel* __restrict__ lv, int l0, int nlev,
-                                                       const double* __restrict__ cinv, char* __restrict__ img) {
-  __shared__ TailLdsT lo[TAIL_MAX_LEVELS];
-  __shared__ int64_t s_cinv;
-  const int t = threadIdx.x;
-  const int NT = blockDim.x;
-  const int last = nlev - 1;
-  if (t == 0) {
-    int64_t oc = 0;
-    tail_lds_layout_t<(int)sizeof(T)>(lv, l0, nlev, lo, &oc);
-    s_cinv = oc;
-  }
-  __syncthreads();
-#define TI_PTR(type, l, f) reinterpret_cast<type*>(img + lo[(l) - l0].f)
-  for (int l = l0; l < last; ++l) {
-    const TailLevel& L = lv[l];
-    const int n = (int)L.n, nc = (int)L.nc, nnz = (int)L.nnz, nnzR = (int)L.nnzR, nnzP = (int)L.nnzP;
-    tail_stage(TI_PTR(int32_t, l, ATp), L.ATp, n + 1, t, NT);
-    tail_stage(TI_PTR(int32_t, l, ATc), L.ATc, nnz, t, NT);
-    tail_stage(TI_PTR(T, l, ATv), TLv<T>::AT(L), nnz, t, NT);
-    tail_stage(TI_PTR(T, l, d), TLv<T>::d(L), n, t, NT);
-    tail_stage(TI_PTR(int8_t, l, cf), L.cf, n, t, NT);
-    tail_stage(TI_PTR(int32_t, l, PTp), L.PTp, nc + 1, t, NT);
-    tail_stage(TI_PTR(int32_t, l, PTc), L.PTc, nnzP, t, NT);
-    tail_stage(TI_PTR(int32_t, l, RTp), L.RTp, n + 1, t, NT);
-    tail_stage(TI_PTR(int32_t, l, RTc), L.RTc, nnzR, t, NT);
-    tail_stage(TI_PTR(T, l, RTv), TLv<T>::RT(L), nnzR, t, NT);
-  }
-#undef TI_PTR
-  const int nL = (int)lv[last].n;
-  tail_stage(reinterpret_cast<double*>(img + s_cinv), cinv, nL * nL, t, NT);
-}
-
-// Transposed coarse end of the cycle (adjoint) from an LDS image: on each
-// level the first sweep from zero (C points; F points with one sweep), the
-// F sweeps with A^T, the residual restricted by P^T; the transposed
-// coarsest solve; then on the way up y + R^T e_c.  The result of level l0
-// is written to out.
-template <class T>
-__global__ __launch_bounds__(1024) void k_tail_lds_t(const TailLevel* __restrict__ lv, int l0, int nlev,
-                                                     const char* __restrict__ img, const T* __restrict__ g_in,
-                                                     T* __restrict__ out, int nsw, T omega) {
-  extern __shared__ __align__(16) char sm[];
-  __shared__ TailLdsT lo[TAIL_MAX_LEVELS];
-  __shared__ int64_t s_cinv, s_bytes;
-  const int t = threadIdx.x;
-  const int NT = blockDim.x;
-  const int last = nlev - 1;
-  if (t == 0) {
-    int64_t oc = 0;
-    s_bytes = tail_lds_layout_t<(int)sizeof(T)>(lv, l0, nlev, lo, &oc);
-    s_cinv = oc;
-  }
-  __syncthreads();
-#define TL_PTR(type, l, f) reinterpret_cast<type*>(sm + lo[(l) - l0].f)
-  {
-    const uint4* __restrict__ src = reinterpret_cast<const uint4*>(img);
-    uint4* dst = reinterpret_cast<uint4*>(sm);
-    const int c1 = (int)(s_bytes >> 4);
-    int c = (int)(lo[0].x >> 4) + t;
-    for (; c + 7 * NT < c1; c += 8 * NT) {
-      uint4 a[8];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) a[q] = src[c + q * NT];
-#pragma unroll
-      for (int q = 0; q < 8; ++q) dst[c + q * NT] = a[q];
-    }
-    for (; c < c1; c += NT) dst[c] = src[c];
-    tail_stage(TL_PTR(T, l0, g), g_in, (int)lv[l0].n, t, NT);
-  }
-  const int nL = (int)lv[last].n;
-  const double* ci_s = reinterpret_cast<const double*>(sm + s_cinv);
-  __syncthreads();
-  for (int l = l0; l < last; ++l) {
-    const int n = (int)lv[l].n, nc = (int)lv[l].nc;
-    const int32_t* rp = TL_PTR(int32_t, l, ATp);
-    const int32_t* ci = TL_PTR(int32_t, l, ATc);
-    const T* v = TL_PTR(T, l, ATv);
-    const T* d = TL_PTR(T, l, d);
-    const int8_t* cf = TL_PTR(int8_t, l, cf);
-    const T* g = TL_PTR(T, l, g);
-    T* x = TL_PTR(T, l, x);
-    T* y = TL_PTR(T, l, y);
-    const int X0 = nsw == 1 ? 0 : 1;
-    for (int i = t; i < n; i += NT) {
-      const T di = d[i];
-      x[i] = (cf[i] == X0 && fabs((double)di) >= 1e-30) ? omega * g[i] / di : (T)0;
-    }
-    __syncthreads();
-    const int gA = tail_lanes(n, n ? (int)(lv[l].nnz / n) : 1, NT);
-    // F sweeps x -> y -> x
-    for (int s = 1; s < nsw; ++s) {
-      const T* cur = (s == 1) ? x : y;
-      T* dst = (s == 1) ? y : x;
-      tail_with_lanes(gA, [&](auto GC) {
-        constexpr int G = decltype(GC)::value;
-        const int gl = t % G;
-        for (int i = t / G; i < n; i += NT / G) {
-          T yi = cur[i];
-          if (cf[i] == 0) {
-            const T di = d[i];
-            const T r = tail_row<G, T, T>(rp, ci, v, cur, i, gl);
-            if (fabs((double)di) >= 1e-30) yi += omega * (g[i] - r) / di;
-          }
-          if (gl == 0) dst[i] = yi;
-        }
-      });
-      __syncthreads();
-    }
-    // residual into y, restricted by P^T into the next level's g
-    tail_with_lanes(gA, [&](auto GC) {
-      constexpr int G = decltype(GC)::value;
-      const int gl = t % G;
-      for (int i = t / G; i < n; i += NT / G) {
-        const T r = tail_row<G, T, T>(rp, ci, v, x, i, gl);
-        if (gl == 0) y[i] = g[i] - r;
-      }
-    });
-    __syncthreads();
-    const int32_t* pp = TL_PTR(int32_t, l, PTp);
-    const int32_t* pc = TL_PTR(int32_t, l, PTc);
-    T* cg = TL_PTR(T, l + 1, g);
-    const int gP = tail_lanes(nc, nc ? (int)(lv[l].nnzP / nc) : 1, NT);
-    tail_with_lanes(gP, [&](auto GC) {
-      constexpr int G = decltype(GC)::value;
-      const int gl = t % G;
-      for (int c = t / G; c < nc; c += NT / G) {
-        T s = 0;
-        for (int k = pp[c] + gl; k < pp[c + 1]; k += G) s += y[pc[k]];
-#pragma unroll
-        for (int o = G / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, G);
-        if (gl == 0) cg[c] = s;
-      }
-    });
-    __syncthreads();
-  }
-  // coarsest: e = C^-T g (FP64 accumulation), into the coarsest x (or out)
-  {
-    const T* g = TL_PTR(T, last, g);
-    T* e = TL_PTR(T, last, x);
-    tail_with_lanes(tail_lanes(nL, nL, NT), [&](auto GC) {
-      constexpr int G = decltype(GC)::value;
-      const int gl = t % G;
-      for (int i = t / G; i < nL; i += NT / G) {
-        double s = 0.0;
-        for (int j = gl; j < nL; j += G) s += ci_s[j * nL + i] * (double)g[j];
-#pragma unroll
-        for (int o = G / 2; o > 0; o >>= 1) s += __shfl_xor(s, o, G);
-        if (gl == 0) {
-          if (l0 == last) out[i] = (T)s;
-          else e[i] = (T)s;
-        }
-      }
-    });
-    __syncthreads();
-  }
-  // up: out_l = y_l + R^T e_c (y_l is in x), into the level's g (out at l0)
-  for (int l = last - 1; l >= l0; --l) {
-    const int n = (int)lv[l].n;
-    const T* ec = (l + 1 == last) ? TL_PTR(T, last, x) : TL_PTR(T, l + 1, g);
-    const int32_t* rp = TL_PTR(int32_t, l, RTp);
-    const int32_t* ci = TL_PTR(int32_t, l, RTc);
-    const T* v = TL_PTR(T, l, RTv);
-    const T* yl = TL_PTR(T, l, x);
-    T* gl_out = TL_PTR(T, l, g);
-    const int gR = tail_lanes(n, n ? (int)(lv[l].nnzR / n) : 1, NT);
-    tail_with_lanes(gR, [&](auto GC) {
-      constexpr int G = decltype(GC)::value;
-      const int gl = t % G;
-      for (int i = t / G; i < n; i += NT / G) {
-        const T r = tail_row<G, T, T>(rp, ci, v, ec, i, gl);
-        if (gl == 0) {
-          if (l == l0) out[i] = yl[i] + r;
-          else gl_out[i] = yl[i] + r;
-        }
-      }
-    });
-    __syncthreads();
-  }
-#undef TL_PTR
-}
-
-template <class T, bool TR>
-__global__ __launch_bounds__(1024) void k_tail(const TailLevel* __restrict__ lv, int l0, int nlev,
-                                               const double* __restrict__ cinv, const T* b_in, T* out, int nsw,
-                                               T omega) {
-  const int t = threadIdx.x;
-  const int NT = blockDim.x;
-  const int last = nlev - 1;
-  if (!TR) {
-    const T* b = b_in;
-    for (int l = l0; l < last; ++l) {
-      const TailLevel& L = lv[l];
-      T* cb = TLv<T>::b(lv[l + 1]);
-      for (int64_t i = t; i < L.nc; i += NT) cb[i] = row_dot<T>(L.Rp, L.Rc, TLv<T>::R(L), b, i);
-      __syncthreads();
-      b = cb;
-    }
-    {
-      const TailLevel& LL = lv[last];
-      T* z = last == l0 ? out : TLv<T>::y(LL);
-      for (int64_t i = t; i < LL.n; i += NT) {
-        double s = 0.0;
-        for (int64_t j = 0; j < LL.n; ++j) s += cinv[i * LL.n + j] * (double)b[j];
-        z[i] = (T)s;
-      }
-      __syncthreads();
-    }
-    for (int l = last - 1; l >= l0; --l) {
-      const TailLevel& L = lv[l];
-      const T* bl = l == l0 ? b_in : TLv<T>::b(L);
-      T* outl = l == l0 ? out : TLv<T>::y(L);
-      const T* ec = TLv<T>::y(lv[l + 1]);
-      T* cur = TLv<T>::x(L);
-      T* alt = TLv<T>::y(L);
-      for (int64_t i = t; i < L.n; i += NT) cur[i] = L.pcol[i] >= 0 ? ec[L.pcol[i]] : (T)0;
-      __syncthreads();
-      for (int s = 0; s < nsw; ++s) {
-        const int X = (nsw == 1 || s < 2) ? 0 : 1;
-        T* dst = s == nsw - 1 ? outl : alt;
-        for (int64_t i = t; i < L.n; i += NT) {
-          T xi = cur[i];
-          if (L.cf[i] == X) {
-            T di = TLv<T>::d(L)[i];
-            if (fabs((double)di) >= 1e-30) xi += omega * (bl[i] - row_dot<T>(L.rp, L.ci, TLv<T>::A(L), cur, i)) / di;
-          }
-          dst[i] = xi;
-        }
-        __syncthreads();
-        alt = cur;
-        cur = dst;
-      }
-    }
-  } else {
-    const T* g = b_in;
-    for (int l = l0; l < last; ++l) {
-      const TailLevel& L = lv[l];
-      T* cur = TLv<T>::x(L);
-      T* alt = TLv<T>::y(L);
-      for (int64_t i = t; i < L.n; i += NT) cur[i] = 0;
-      __syncthreads();
-      for (int s = 3 - nsw; s < 3; ++s) {
-        const int X = s == 0 ? 1 : 0;   // C, F, F
-        for (int64_t i = t; i < L.n; i += NT) {
-          T yi = cur[i];
-          if (L.cf[i] == X) {
-            T di = TLv<T>::d(L)[i];
-            if (fabs((double)di) >= 1e-30) yi += omega * (g[i] - row_dot<T>(L.ATp, L.ATc, TLv<T>::AT(L), cur, i)) / di;
-          }
-          alt[i] = yi;
-        }
-        __syncthreads();
-        T* tmp = cur; cur = alt; alt = tmp;
-      }
-      for (int64_t i = t; i < L.n; i += NT) alt[i] = g[i] - row_dot<T>(L.ATp, L.ATc, TLv<T>::AT(L), cur, i);
-      __syncthreads();
-      T* cb = TLv<T>::b(lv[l + 1]);
-      for (int64_t c = t; c < L.nc; c += NT) cb[c] = row_dot<T>(L.PTp, L.PTc, (const T*)nullptr, alt, c);
-      __syncthreads();
-      g = cb;
-    }
-    {
-      const TailLevel& LL = lv[last];
-      T* e = last == l0 ? out : TLv<T>::x(LL);
-      for (int64_t i = t; i < LL.n; i += NT) {
-        double s = 0.0;
-        for (int64_t j = 0; j < LL.n; ++j) s += cinv[j * LL.n + i] * (double)g[j];
-        e[i] = (T)s;
-      }
-      __syncthreads();
-    }
-    for (int l = last - 1; l >= l0; --l) {
-      const TailLevel& L = lv[l];
-      const T* ec = (l + 1 == last) ? TLv<T>::x(lv[l + 1]) : TLv<T>::b(lv[l + 1]);
-      const T* yl = TLv<T>::y(L);   // sweeps start in x and end in y for 1 or 3 sweeps
-      T* outl = l == l0 ? out : TLv<T>::b(L);
-      for (int64_t i = t; i < L.n; i += NT) outl[i] = yl[i] + row_dot<T>(L.RTp, L.RTc, TLv<T>::RT(L), ec, i);
-      __syncthreads();
-    }
-  }
+__global__ __launch_bounds__(256) void k_end_mv(int n, const double* __restrict__ B, const T* __restrict__ r,
+                                                T* __restrict__ z) {
+  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
+  const int lane = threadIdx.x & 63;
+  if (row >= n) return;
+  const double* __restrict__ b = B + (int64_t)row * n;
+  double acc = 0.0;
+#pragma unroll 16
+  for (int j = lane; j < n; j += 64) acc += b[j] * (double)r[j];
+  for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
+  if (lane == 0) z[row] = (T)acc;
 }
 
 template <class T>
@@ -1024,21 +675,6 @@ __global__ void k_sweep_from_zero(int64_t n, const int8_t* __restrict__ cf, int 
 }
 
 static inline int64_t nF0(const AhLevel& L) { return L.n - L.nc; }
-
-// z = C^-1 r (trans = 0) or C^-T r, FP64 coarsest solve; one wave per row.
-template <class T>
-__global__ __launch_bounds__(64) void k_coarse(int n, const double* __restrict__ Ci, const T* __restrict__ r,
-                                               T* __restrict__ z, int trans) {
-  const int row = blockIdx.x;
-  const int lane = threadIdx.x;
-  double acc = 0.0;
-  for (int j = lane; j < n; j += 64) {
-    double c = trans ? Ci[(int64_t)j * n + row] : Ci[(int64_t)row * n + j];
-    acc += c * (double)r[j];
-  }
-  for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
-  if (lane == 0) z[row] = (T)acc;
-}
 
 template <class TA, class TB>
 __global__ void k_cast(int64_t n, const TA* __restrict__ a, TB* __restrict__ b) {
@@ -1509,41 +1145,88 @@ static double rz_bytes(const AhLevel& L) {
          (double)L.n * w + (double)L.nc * w;
 }
 
-ah_status tail_image_build(ah_hier* h, hipStream_t st) {
-  if (!h->tail_lds || h->tail0 < 0) return AH_OK;
-  const int nlev = (int)h->lev.size();
-  for (int w = 0; w < 2; ++w) {
-    if (w == 1 && !h->prm.fp32_cycle) break;
-    double* img = nullptr;
-    AH_TRY(h->arena.get(&img, (h->tail_bytes[w] + 15) / 8 + 2));
-    if (w == 0)
-      hipLaunchKernelGGL(k_tail_image<double>, dim3(1), dim3(1024), 0, st, h->d_tail, h->tail0, nlev, h->cinv,
-                         reinterpret_cast<char*>(img));
-    else
-      hipLaunchKernelGGL(k_tail_image<float>, dim3(1), dim3(1024), 0, st, h->d_tail, h->tail0, nlev, h->cinv,
-                         reinterpret_cast<char*>(img));
-    AH_LAUNCHED();
-    h->tail_img[w] = reinterpret_cast<const char*>(img);
-  }
-  if (h->tail_lds_t) {
-    for (int w = 0; w < 2; ++w) {
-      if (w == 1 && !h->prm.fp32_cycle) break;
-      double* img = nullptr;
-      AH_TRY(h->arena.get(&img, (h->tail_bytes_t[w] + 15) / 8 + 2));
-      if (w == 0)
-        hipLaunchKernelGGL(k_tail_image_t<double>, dim3(1), dim3(1024), 0, st, h->d_tail, h->tail0, nlev, h->cinv,
-                           reinterpret_cast<char*>(img));
-      else
-        hipLaunchKernelGGL(k_tail_image_t<float>, dim3(1), dim3(1024), 0, st, h->d_tail, h->tail0, nlev, h->cinv,
-                           reinterpret_cast<char*>(img));
+// LDS of k_end_cols for the levels from l0 down, per column.
+static int64_t end_lds(const ah_hier* h, int l0) {
+  int64_t tot = 0;
+  for (size_t l = l0; l < h->lev.size(); ++l) tot += h->lev[l].n;
+  return (2 * tot + h->lev[l0].n) * (int64_t)sizeof(double);
+}
+
+constexpr int64_t END_LDS_MAX = 160 * 1024;
+
+// The coarse end starts at the first level of at most end_max rows whose
+// levels' vectors fit in LDS (an ordered relaxation keeps level 0 out), at the
+// latest on the coarsest level.  A dense cycle costs its n^2 values once per
+// application, a walk over the levels about 3 us per launch, four or five
+// launches each (64^2 slab at p = 2, 17 cycles: 4.47 ms per solve with the end
+// at 512 rows, 4.33 at 1535, 4.26 at 2048 (34 MB); 25^3 cube at p = 1 14.6, 14.0
+// and 13.6 ms).  Level 0 is taken only up to half as many rows: its matrix has
+// to pay for itself within one solve of a few cycles.
+void coarse_end_pick(ah_hier* h, int64_t end_max) {
+  const int nl = (int)h->lev.size();
+  int l = nl > 1 && h->prm.relax >= 2 ? 1 : 0;
+  while (l < nl - 1 && (h->lev[l].n > (l == 0 ? end_max / 2 : end_max) || end_lds(h, l) > END_LDS_MAX)) ++l;
+  h->end0 = l;
+}
+
+__global__ void k_dense_transpose(int n, const double* __restrict__ A, double* __restrict__ At) {
+  const int64_t k = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (k < (int64_t)n * n) At[(k % n) * n + k / n] = A[k];
+}
+
+// Lanes per row for n rows of mean length avg in a workgroup of END_T.
+static int end_lanes(int64_t n, int64_t nnz) {
+  const int64_t avg = n ? nnz / n : 1;
+  int g = 1;
+  while (g < 16 && 4 * g < avg) g *= 2;
+  while (g < 16 && 2 * g * n <= END_T && g < avg) g *= 2;
+  return g;
+}
+
+ah_status coarse_end_build(ah_hier* h, hipStream_t st) {
+  const int nl = (int)h->lev.size(), l0 = h->end0;
+  const int64_t n = h->lev[l0].n;
+  if (n == 0) return AH_OK;
+  double *B = nullptr, *Bt = nullptr;
+  if (h->prm.adjoint) AH_TRY(h->arena.get(&Bt, n * n));
+  if (l0 == nl - 1) {
+    h->end_mat = h->cinv;
+    if (Bt) {
+      hipLaunchKernelGGL(k_dense_transpose, g1(n * n), dim3(256), 0, st, (int)n, h->cinv, Bt);
       AH_LAUNCHED();
-      h->tail_img_t[w] = reinterpret_cast<const char*>(img);
     }
+  } else {
+    AH_TRY(h->arena.get(&B, n * n));
+    EndLevels E{};
+    for (int l = l0; l < nl; ++l) {
+      const AhLevel& L = h->lev[l];
+      EndLevel& e = E.lv[l - l0];
+      e.rp = L.rowptr; e.ci = L.col; e.v = L.val; e.d = L.diag; e.cf = L.cf; e.pcol = L.pcol;
+      e.Rp = L.Rptr; e.Rc = L.Rcol; e.Rv = L.Rval;
+      e.n = (int)L.n;
+      e.gA = end_lanes(L.n, L.nnz);
+      e.gR = l + 1 < nl ? end_lanes(L.nc, L.nnzR) : 1;
+    }
+    const int nsw = h->prm.relax == 1 ? 1 : 3;
+    static std::once_flag once;
+    std::call_once(once, [] {
+      (void)hipFuncSetAttribute((const void*)k_end_cols<1>, hipFuncAttributeMaxDynamicSharedMemorySize, END_LDS_MAX);
+      (void)hipFuncSetAttribute((const void*)k_end_cols<2>, hipFuncAttributeMaxDynamicSharedMemorySize, END_LDS_MAX);
+    });
+    const int64_t lds = end_lds(h, l0);
+    if (2 * lds <= END_LDS_MAX)
+      hipLaunchKernelGGL(k_end_cols<2>, dim3((unsigned)cdiv(n, 2)), dim3(END_T), (unsigned)(2 * lds), st, E, nl - l0,
+                         h->cinv, nsw, h->prm.omega, B, Bt);
+    else
+      hipLaunchKernelGGL(k_end_cols<1>, dim3((unsigned)n), dim3(END_T), (unsigned)lds, st, E, nl - l0, h->cinv, nsw,
+                         h->prm.omega, B, Bt);
+    AH_LAUNCHED();
+    h->end_mat = B;
   }
+  h->end_mat_t = Bt;
   return AH_OK;
 }
 
-// ------------------------------------------------------------ V-cycles
 template <class T>
 struct Ops;
 template <>
@@ -1682,30 +1365,10 @@ static ah_status gs_csr_sweep_t(const ah_hier* h, bool fonly, const T* atv, cons
 template <class T>
 static ah_status vcycle(ah_hier* h, int l, const T* b, T* out, hipStream_t st) {
   AhLevel& L = h->lev[l];
-  const int nlev = (int)h->lev.size();
   const int nsw = h->prm.relax == 1 ? 1 : 3;
-  if (h->tail0 >= 0 && l >= h->tail0) {
-    if (h->tail_lds) {
-      static std::once_flag once;
-      std::call_once(once, [] {
-        (void)hipFuncSetAttribute((const void*)k_tail_lds<double>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)TAIL_LDS_MAX);
-        (void)hipFuncSetAttribute((const void*)k_tail_lds<float>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)TAIL_LDS_MAX);
-      });
-      const int64_t bytes = h->tail_bytes[sizeof(T) == 8 ? 0 : 1];
-      hipLaunchKernelGGL((k_tail_lds<T>), dim3(1), dim3(1024), (unsigned)bytes, st, h->d_tail, l, nlev,
-                         h->tail_img[sizeof(T) == 8 ? 0 : 1], b, out, nsw, (T)h->prm.omega);
-    } else {
-      hipLaunchKernelGGL((k_tail<T, false>), dim3(1), dim3(1024), 0, st, h->d_tail, l, nlev, h->cinv, b, out, nsw,
-                         (T)h->prm.omega);
-    }
-    AH_LAUNCHED();
-    return AH_OK;
-  }
-  if (l == nlev - 1) {
+  if (l == h->end0) {
     if (L.n == 0) return AH_OK;
-    hipLaunchKernelGGL(k_coarse<T>, dim3((unsigned)L.n), dim3(64), 0, st, (int)L.n, h->cinv, b, out, 0);
+    hipLaunchKernelGGL(k_end_mv<T>, dim3((unsigned)cdiv(L.n, 4)), dim3(256), 0, st, (int)L.n, h->end_mat, b, out);
     AH_LAUNCHED();
     return AH_OK;
   }
@@ -1874,36 +1537,15 @@ static ah_status vcycle(ah_hier* h, int l, const T* b, T* out, hipStream_t st) {
   return AH_OK;
 }
 
-// Transposed cycle on level l: g -> out (out may alias g, not the level's
-// x or y).  The recursion writes its result over the coarse level's input
-// (or into the coarsest level's x).
+// Transposed cycle on level l: g -> out (out may alias g above the coarse end,
+// not the level's x or y).  The recursion writes its result over the coarse
+// level's input (or into x on the first level of the coarse end).
 template <class T>
 static ah_status vcycle_t(ah_hier* h, int l, const T* g, T* out, hipStream_t st) {
   AhLevel& L = h->lev[l];
-  const int nlev = (int)h->lev.size();
-  if (h->tail0 >= 0 && l >= h->tail0) {
-    if (h->tail_lds_t && l == h->tail0) {
-      static std::once_flag once;
-      std::call_once(once, [] {
-        (void)hipFuncSetAttribute((const void*)k_tail_lds_t<double>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)TAIL_LDS_MAX);
-        (void)hipFuncSetAttribute((const void*)k_tail_lds_t<float>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                  (int)TAIL_LDS_MAX);
-      });
-      const int64_t bytes = h->tail_bytes_t[sizeof(T) == 8 ? 0 : 1];
-      hipLaunchKernelGGL((k_tail_lds_t<T>), dim3(1), dim3(1024), (unsigned)bytes, st, h->d_tail, l, nlev,
-                         h->tail_img_t[sizeof(T) == 8 ? 0 : 1], g, out, h->prm.relax == 1 ? 1 : 3,
-                         (T)h->prm.omega);
-    } else {
-      hipLaunchKernelGGL((k_tail<T, true>), dim3(1), dim3(1024), 0, st, h->d_tail, l, nlev, h->cinv, g, out,
-                         h->prm.relax == 1 ? 1 : 3, (T)h->prm.omega);
-    }
-    AH_LAUNCHED();
-    return AH_OK;
-  }
-  if (l == nlev - 1) {
+  if (l == h->end0) {
     if (L.n == 0) return AH_OK;
-    hipLaunchKernelGGL(k_coarse<T>, dim3((unsigned)L.n), dim3(64), 0, st, (int)L.n, h->cinv, g, out, 1);
+    hipLaunchKernelGGL(k_end_mv<T>, dim3((unsigned)cdiv(L.n, 4)), dim3(256), 0, st, (int)L.n, h->end_mat_t, g, out);
     AH_LAUNCHED();
     return AH_OK;
   }
@@ -1942,7 +1584,7 @@ static ah_status vcycle_t(ah_hier* h, int l, const T* g, T* out, hipStream_t st)
     AH_TRY((fb_any<T, SP_RES>(h, L, true, L.n, Ops<T>::OT(L), cur, g, (T)0, alt, st)));
     AH_TRY((csr_g<T, T, T, SP_MV>(4, L.nc, L.PTptr, L.PTcol, (const T*)nullptr, alt, (const T*)nullptr,
                                   (const T*)nullptr, (const int8_t*)nullptr, 0, (T)0, Ops<T>::b(C), st)));
-    T* ec = (l + 1 == nlev - 1) ? Ops<T>::x(C) : Ops<T>::b(C);
+    T* ec = l + 1 == h->end0 ? Ops<T>::x(C) : Ops<T>::b(C);
     AH_TRY(vcycle_t<T>(h, l + 1, Ops<T>::b(C), ec, st));
     const int GR = pick_g(L.nnzR, L.n);
     AH_TRY((csr_g<T, T, T, SP_ADDMV>(GR, L.n, L.RTptr, L.RTcol, Ops<T>::RT(L), ec, cur, (const T*)nullptr,
@@ -1968,7 +1610,7 @@ static ah_status vcycle_t(ah_hier* h, int l, const T* g, T* out, hipStream_t st)
                                  (const int8_t*)nullptr, 0, (T)0, alt, st)));
   AH_TRY((csr_g<T, T, T, SP_MV>(4, L.nc, L.PTptr, L.PTcol, (const T*)nullptr, alt, (const T*)nullptr,
                                 (const T*)nullptr, (const int8_t*)nullptr, 0, (T)0, Ops<T>::b(C), st)));
-  T* ec = (l + 1 == nlev - 1) ? Ops<T>::x(C) : Ops<T>::b(C);
+  T* ec = l + 1 == h->end0 ? Ops<T>::x(C) : Ops<T>::b(C);
   AH_TRY(vcycle_t<T>(h, l + 1, Ops<T>::b(C), ec, st));
   // out = y + R^T e_c
   const int GR = pick_g(L.nnzR, L.n);

@@ -40,9 +40,10 @@ struct ah_system {
 
 namespace ah {
 
-// Build the LDS image of the forward tail in global memory (once per
-// hierarchy; the cycle then stages it with one contiguous copy).
-ah_status tail_image_build(ah_hier* h, hipStream_t st);
+// Choose the first level of the dense coarse end (at most end_max rows) and
+// form the matrices that apply the cycle from there down (once per hierarchy).
+void coarse_end_pick(ah_hier* h, int64_t end_max);
+ah_status coarse_end_build(ah_hier* h, hipStream_t st);
 // Flow order of the level-0 facet blocks for the ordered relaxations
 // (Lemma 3.1): block levels, blocks and F rows grouped by level.
 ah_status flow_order_build(ah_hier* h, hipStream_t st);
@@ -185,125 +186,20 @@ struct AhLevel {
   float* e32 = nullptr;
 };
 
-// Flat copy of a level's device pointers for the single-workgroup kernel
-// that runs the coarse end of a V-cycle.
-struct TailLevel {
-  int64_t n, nc, nnz, nnzR, nnzP;
-  const int64_t* rp; const int32_t* ci; const double* v; const float* v32;
-  const double* d; const float* d32;
-  const int8_t* cf; const int32_t* pcol;
-  const int64_t* Rp; const int32_t* Rc; const double* Rv; const float* Rv32;
-  const int64_t* ATp; const int32_t* ATc; const double* ATv; const float* ATv32;
-  const int64_t* RTp; const int32_t* RTc; const double* RTv; const float* RTv32;
-  const int64_t* PTp; const int32_t* PTc;
-  double *b, *x, *y;
-  float *b32, *x32, *y32;
-};
-
-// Byte offsets of one level's arrays in the LDS image of the forward tail
-// cycle (row offsets and indices as int32, values and vectors of width W).
-struct TailLds {
-  int32_t rp, ci, v, d, cf, pc, Rp, Rc, Rv, b, x, y;
-};
-
-// Layout of levels l0 .. nlev-1 (the last one is the coarsest: vectors
-// only) followed by the coarsest inverse (FP64).  Every array starts on a
-// 16-byte boundary.  Returns the total size in bytes.
-template <int W>
-__host__ __device__ inline int64_t tail_lds_layout(const TailLevel* lv, int l0, int nlev, TailLds* o,
-                                                   int64_t* o_cinv) {
-  int64_t off = 0;
-  auto take = [&off](int64_t bytes) {
-    const int64_t r = off;
-    off += (bytes + 15) & ~int64_t(15);
-    return (int32_t)r;
-  };
-  for (int l = l0; l < nlev; ++l) {
-    const TailLevel& L = lv[l];
-    TailLds& q = o[l - l0];
-    q = TailLds{};
-    q.b = take(L.n * W);
-    q.x = take(L.n * W);
-    q.y = take(L.n * W);
-    if (l < nlev - 1) {
-      q.rp = take((L.n + 1) * 4);
-      q.ci = take(L.nnz * 4);
-      q.v = take(L.nnz * W);
-      q.d = take(L.n * W);
-      q.cf = take(L.n);
-      q.pc = take(L.n * 4);
-      q.Rp = take((L.nc + 1) * 4);
-      q.Rc = take(L.nnzR * 4);
-      q.Rv = take(L.nnzR * W);
-    }
-  }
-  const int64_t nL = lv[nlev - 1].n;
-  *o_cinv = take(nL * nL * 8);
-  return off;
-}
-
-// The same for the transposed tail cycle of the adjoint: A^T, the diagonal,
-// C/F flags, P^T (coarse rows) and R^T (fine rows) per level; vectors g
-// (input), x and y.
-struct TailLdsT {
-  int32_t ATp, ATc, ATv, d, cf, PTp, PTc, RTp, RTc, RTv, g, x, y;
-};
-
-template <int W>
-__host__ __device__ inline int64_t tail_lds_layout_t(const TailLevel* lv, int l0, int nlev, TailLdsT* o,
-                                                     int64_t* o_cinv) {
-  int64_t off = 0;
-  auto take = [&off](int64_t bytes) {
-    const int64_t r = off;
-    off += (bytes + 15) & ~int64_t(15);
-    return (int32_t)r;
-  };
-  for (int l = l0; l < nlev; ++l) {
-    const TailLevel& L = lv[l];
-    TailLdsT& q = o[l - l0];
-    q = TailLdsT{};
-    q.g = take(L.n * W);
-    q.x = take(L.n * W);
-    q.y = take(L.n * W);
-    if (l < nlev - 1) {
-      q.ATp = take((L.n + 1) * 4);
-      q.ATc = take(L.nnz * 4);
-      q.ATv = take(L.nnz * W);
-      q.d = take(L.n * W);
-      q.cf = take(L.n);
-      q.PTp = take((L.nc + 1) * 4);
-      q.PTc = take(L.nnzP * 4);
-      q.RTp = take((L.n + 1) * 4);
-      q.RTc = take(L.nnzR * 4);
-      q.RTv = take(L.nnzR * W);
-    }
-  }
-  const int64_t nL = lv[nlev - 1].n;
-  *o_cinv = take(nL * nL * 8);
-  return off;
-}
-
-// Largest LDS image the staged tail kernel may use (160 KiB per workgroup on
-// gfx950, less the kernel's static layout table).
-constexpr int64_t TAIL_LDS_MAX = 160 * 1024 - 4096;
-constexpr int TAIL_MAX_LEVELS = 32;
-
 struct ah_hier {
   const ah_system* sys = nullptr;
-  int tail0 = -1;              // first level handled by the single-workgroup tail kernel
-  bool tail_lds = false;       // the forward tail runs from an LDS image of its levels
-  int64_t tail_bytes[2] = {0, 0};   // size of that image with FP64 / FP32 values
-  bool tail_lds_t = false;     // the transposed tail runs from an LDS image too
-  int64_t tail_bytes_t[2] = {0, 0};
-  const char* tail_img_t[2] = {nullptr, nullptr};
+  // the coarse end: from level end0 down the cycle is one dense matrix, row i
+  // of it at end_mat + i n (end_mat_t: of its transpose, adjoint hierarchies);
+  // on the coarsest level that is the inverse
+  int end0 = 0;
+  const double* end_mat = nullptr;
+  const double* end_mat_t = nullptr;
   int g0 = 0;                  // lanes per row of the level-0 kernels (0: from the mean row length)
   int fbb = 1;                 // level-0 kernels by facet block rows where the rows are whole blocks
   int lpb = 0;                 // lanes per block row of those (0: from the mean blocks per row)
   int64_t dcgs_min = (int64_t)1 << 21;   // FGMRES uses delayed CGS2 from this many unknowns on
   int gc = 0;                  // lanes per row of the coarse-level kernels (0: from the mean row length)
   int64_t list_min = (int64_t)1 << 16;   // coarse levels from this many rows on sweep their F and C lists
-  TailLevel* d_tail = nullptr; // device copy of every level's pointers
-  const char* tail_img[2] = {nullptr, nullptr};   // the tail's LDS image (FP64 / FP32), built at setup
   ah::Arena arena;
   ah_air_params prm{};
   std::vector<AhLevel> lev;
