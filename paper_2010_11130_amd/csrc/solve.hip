@@ -25,7 +25,7 @@
 namespace ah {
 
 enum { SP_MV = 0, SP_RES = 1, SP_SWEEP = 2, SP_ADDMV = 3, SP_SWEEP_P = 4, SP_SWEEP_LIST = 5, SP_SWEEP_ORD = 6,
-       SP_RESTRICT = 7, SP_SO_P = 8, SP_SO_E = 9, SP_SO_C = 10 };
+       SP_RESTRICT = 7, SP_SO_P = 8, SP_SO_E = 9, SP_SO_C = 10, SP_SO = 11 };
 
 // MODE SP_MV:      y = A x
 // MODE SP_RES:     y = b - A x
@@ -135,39 +135,112 @@ __global__ __launch_bounds__(256) void k_csr(int64_t n, const int64_t* __restric
 // block row, so the row stream is the values alone.  Modes SP_MV, SP_RES and
 // SP_SWEEP_LIST as in k_csr, with d_i = 1; SP_SWEEP_ORD: SP_SWEEP_LIST with
 // item ii's values at soff[ii] of a copy of the listed rows in list order.
+// SP_SO and SP_SO_P, SP_SO_E, SP_SO_C (block AIR, even B): the sweeps of
+// k_fbb's SP_SWEEP_ORD and of its modes of the same names, by rows: row ii is
+// row ii % B of block item ii / B of the copy (list, optr and ocol per item).
+// For even B a lane takes two values and two entries of x per load (a row, a
+// block and a facet's unknowns all start on an even offset), so the lanes of
+// a row read whole lines and half the load instructions are issued: 64^2
+// slab, p = 2 (84 MB of values, in the Infinity Cache), all rows: 20.0 us with
+// a value per load, 18.7 with two.  At B = 3 a lane takes a whole block.
 template <class TA, class TX, class TY, int B, int G, int MODE>
 __global__ __launch_bounds__(256) void k_fb(int64_t n, const int64_t* __restrict__ optr,
                                             const int32_t* __restrict__ ocol, const TA* __restrict__ ov,
                                             const TX* __restrict__ x, const TY* __restrict__ b, TY omega,
                                             TY* __restrict__ y, const int32_t* __restrict__ list,
-                                            TY* __restrict__ y2, const int64_t* __restrict__ soff) {
+                                            TY* __restrict__ y2, const int64_t* __restrict__ soff,
+                                            const TX* __restrict__ xc, const int32_t* __restrict__ own) {
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t ii = gid / G;
   const int g = (int)(gid % G);
   if (ii >= n) return;
-  const int64_t i = MODE == SP_SWEEP_LIST || MODE == SP_SWEEP_ORD ? (int64_t)list[ii] : ii;
+  constexpr bool SO = MODE == SP_SO || MODE == SP_SO_P || MODE == SP_SO_E || MODE == SP_SO_C;
+  static_assert(!SO || B % 2 == 0, "block items by rows: even B");
+  const int64_t kk = SO ? ii / B : 0;
+  const int64_t i = SO ? (int64_t)list[kk] * B + (ii - kk * B)
+                       : MODE == SP_SWEEP_LIST || MODE == SP_SWEEP_ORD ? (int64_t)list[ii] : ii;
   // the row's own x and b, loaded by every lane ahead of the gather
-  const TY xi = (TY)x[i];
+  TY xi;
+  if (MODE == SP_SO_P) {
+    const int64_t po = own[kk];
+    const TY t = (TY)xc[(po >= 0 ? po : 0) * B + (ii - kk * B)];
+    xi = po >= 0 ? t : (TY)0;
+  } else {
+    xi = (TY)(MODE == SP_SO_E ? x[ii] : MODE == SP_SO_C ? xc[ii] : x[i]);
+  }
   const TY bi = MODE == SP_MV ? (TY)0 : b[i];
-  const int64_t R = i / B;
-  const int m = (int)(i - R * B);
+  const int64_t R = SO ? kk : i / B;
+  const int m = SO ? (int)(ii - kk * B) : (int)(i - R * B);
   const int64_t o0 = optr[R];
   const int len = (int)(optr[R + 1] - o0) * B;
   const TA* __restrict__ v = MODE == SP_SWEEP_ORD ? ov + soff[ii] : ov + o0 * (B * B) + (int64_t)m * len;
   const int32_t* __restrict__ cb = ocol + o0;
   TY acc = 0, acc1 = 0, acc2 = 0, acc3 = 0;
   int e = g;
-  for (; e + 3 * G < len; e += 4 * G) {
-    const int e1 = e + G, e2 = e + 2 * G, e3 = e + 3 * G;
-    const int64_t c0 = (int64_t)cb[e / B] * B + e % B, c1 = (int64_t)cb[e1 / B] * B + e1 % B;
-    const int64_t c2 = (int64_t)cb[e2 / B] * B + e2 % B, c3 = (int64_t)cb[e3 / B] * B + e3 % B;
-    const TY a0 = (TY)v[e], a1 = (TY)v[e1], a2 = (TY)v[e2], a3 = (TY)v[e3];
-    acc += a0 * (TY)x[c0];
-    acc1 += a1 * (TY)x[c1];
-    acc2 += a2 * (TY)x[c2];
-    acc3 += a3 * (TY)x[c3];
+  if constexpr (B % 2 == 0) {
+    constexpr int H = B / 2;
+    typedef TA TA2 __attribute__((ext_vector_type(2)));
+    typedef TX TX2 __attribute__((ext_vector_type(2)));
+    const TA2* __restrict__ v2 = reinterpret_cast<const TA2*>(v);
+    const TX2* __restrict__ x2 = reinterpret_cast<const TX2*>(x);
+    const TX2* __restrict__ xc2 = reinterpret_cast<const TX2*>(xc);
+    // pair q of the row: entries 2 (q % H) and the next of column block cb[q / H]
+    const auto pair = [&](int q) -> TX2 {
+      const int64_t J = cb[q / H];
+      const int c = q % H;
+      if constexpr (MODE == SP_SO_P) {
+        const TX2 t = xc2[(J >= 0 ? J : 0) * H + c];   // loaded in every case: no branch before the wait
+        return J >= 0 ? t : TX2{0, 0};
+      } else if constexpr (MODE == SP_SO_E || MODE == SP_SO_C) {
+        const TX2* __restrict__ xs = J >= 0 ? x2 + J * H : xc2 + (~J) * H;
+        return xs[c];
+      } else {
+        return x2[J * H + c];
+      }
+    };
+    const int np = len / 2;
+    for (; e + 3 * G < np; e += 4 * G) {
+      const TA2 a0 = v2[e], a1 = v2[e + G], a2 = v2[e + 2 * G], a3 = v2[e + 3 * G];
+      const TX2 x0 = pair(e), x1 = pair(e + G), y0 = pair(e + 2 * G), y1 = pair(e + 3 * G);
+      acc += (TY)a0.x * (TY)x0.x + (TY)a0.y * (TY)x0.y;
+      acc1 += (TY)a1.x * (TY)x1.x + (TY)a1.y * (TY)x1.y;
+      acc2 += (TY)a2.x * (TY)y0.x + (TY)a2.y * (TY)y0.y;
+      acc3 += (TY)a3.x * (TY)y1.x + (TY)a3.y * (TY)y1.y;
+    }
+    for (; e < np; e += G) {
+      const TA2 a0 = v2[e];
+      const TX2 x0 = pair(e);
+      acc += (TY)a0.x * (TY)x0.x + (TY)a0.y * (TY)x0.y;
+    }
+  } else {
+    const int nb = len / B;
+    for (; e + G < nb; e += 2 * G) {
+      const int64_t J0 = cb[e], J1 = cb[e + G];
+      const TA* __restrict__ v0 = v + e * B;
+      const TA* __restrict__ v1 = v0 + G * B;
+      TA a0[B], a1[B];
+      TX x0[B], x1[B];
+#pragma unroll
+      for (int c = 0; c < B; ++c) {
+        a0[c] = v0[c];
+        a1[c] = v1[c];
+      }
+#pragma unroll
+      for (int c = 0; c < B; ++c) {
+        x0[c] = x[J0 * B + c];
+        x1[c] = x[J1 * B + c];
+      }
+#pragma unroll
+      for (int c = 0; c < B; ++c) acc += (TY)a0[c] * (TY)x0[c];
+#pragma unroll
+      for (int c = 0; c < B; ++c) acc1 += (TY)a1[c] * (TY)x1[c];
+    }
+    if (e < nb) {
+      const int64_t J = cb[e];
+#pragma unroll
+      for (int c = 0; c < B; ++c) acc += (TY)v[e * B + c] * (TY)x[J * B + c];
+    }
   }
-  for (; e < len; e += G) acc += (TY)v[e] * (TY)x[(int64_t)cb[e / B] * B + e % B];
   acc += (acc1 + acc2) + acc3;
 #pragma unroll
   for (int o = G / 2; o > 0; o >>= 1) acc += __shfl_xor(acc, o, G);
@@ -179,7 +252,7 @@ __global__ __launch_bounds__(256) void k_fb(int64_t n, const int64_t* __restrict
     y[i] = bi - acc;
   } else {
     const TY xn = xi + omega * (bi - acc);
-    y[i] = xn;
+    y[MODE == SP_SO_P || MODE == SP_SO_E ? ii : i] = xn;
     if (y2) y2[i] = xn;
   }
 }
@@ -948,9 +1021,12 @@ static ah_status csr_g(int G, int64_t n, const int64_t* rp, const int32_t* ci, c
 // Lanes per row of the facet-block kernels: about eight values per lane
 // (the row is one chain of dependent loads per lane, so short rows per lane
 // and more rows per wave keep more loads in flight).
-static int fb_lanes(int64_t nvals, int64_t n) {
+// Lanes per row of k_fb.  B = 3 takes a block per lane and step, so two lanes
+// serve a row of six blocks (scalar AIR, 48^3 cube at p = 1: 65.8 ms with two,
+// 66.9 with four, 68.4 with eight lanes).
+static int fb_lanes(int64_t nvals, int64_t n, int B) {
   const double avg = n ? (double)nvals / (double)n : 0.0;
-  if (avg < 12) return 2;
+  if (avg < 12 || (B % 2 && avg < 8 * B)) return 2;
   if (avg < 48) return 4;
   if (avg < 96) return 8;
   return 16;
@@ -959,34 +1035,43 @@ static int fb_lanes(int64_t nvals, int64_t n) {
 template <class TA, class TX, class TY, int MODE, int B>
 static void fb_launch(int G, dim3 grid, hipStream_t st, int64_t n, const int64_t* optr, const int32_t* ocol,
                       const TA* ov, const TX* x, const TY* b, TY omega, TY* y, const int32_t* list, TY* y2,
-                      const int64_t* soff) {
+                      const int64_t* soff, const TX* xc, const int32_t* own) {
+#define FB(GG) hipLaunchKernelGGL((k_fb<TA, TX, TY, B, GG, MODE>), grid, dim3(256), 0, st, n, optr, ocol, ov, x, b, \
+                                  omega, y, list, y2, soff, xc, own)
   switch (G) {
-    case 2: hipLaunchKernelGGL((k_fb<TA, TX, TY, B, 2, MODE>), grid, dim3(256), 0, st, n, optr, ocol, ov, x, b, omega, y, list, y2, soff); break;
-    case 4: hipLaunchKernelGGL((k_fb<TA, TX, TY, B, 4, MODE>), grid, dim3(256), 0, st, n, optr, ocol, ov, x, b, omega, y, list, y2, soff); break;
-    case 8: hipLaunchKernelGGL((k_fb<TA, TX, TY, B, 8, MODE>), grid, dim3(256), 0, st, n, optr, ocol, ov, x, b, omega, y, list, y2, soff); break;
-    default: hipLaunchKernelGGL((k_fb<TA, TX, TY, B, 16, MODE>), grid, dim3(256), 0, st, n, optr, ocol, ov, x, b, omega, y, list, y2, soff); break;
+    case 2: FB(2); break;
+    case 4: FB(4); break;
+    case 8: FB(8); break;
+    default: FB(16); break;
   }
+#undef FB
 }
 
-// Level-0 rows in the off-diagonal facet-block layout (k_fb): n rows (the
-// listed ones for SP_SWEEP_LIST), block size B, G in {2, 4, 8, 16}.
+// Level-0 rows in the facet-block layout (k_fb): n rows (the listed ones for
+// SP_SWEEP_LIST), block size B, G in {2, 4, 8, 16}.
 template <class TA, class TX, class TY, int MODE>
 static ah_status fb_g(int B, int G, int64_t n, const int64_t* optr, const int32_t* ocol, const TA* ov, const TX* x,
                       const TY* b, TY omega, TY* y, hipStream_t st, const char* tag = nullptr, double bytes = 0.0,
-                      const int32_t* list = nullptr, TY* y2 = nullptr, const int64_t* soff = nullptr) {
+                      const int32_t* list = nullptr, TY* y2 = nullptr, const int64_t* soff = nullptr,
+                      const TX* xc = nullptr, const int32_t* own = nullptr) {
   if (n == 0) return AH_OK;
   if (G != 2 && G != 4 && G != 8) G = 16;
   ProfScope ps;
   prof_begin(ps, tag, st, bytes);
   const dim3 grid((unsigned)cdiv(n * G, 256));
-  switch (B) {
-    case 2: fb_launch<TA, TX, TY, MODE, 2>(G, grid, st, n, optr, ocol, ov, x, b, omega, y, list, y2, soff); break;
-    case 3: fb_launch<TA, TX, TY, MODE, 3>(G, grid, st, n, optr, ocol, ov, x, b, omega, y, list, y2, soff); break;
-    case 4: fb_launch<TA, TX, TY, MODE, 4>(G, grid, st, n, optr, ocol, ov, x, b, omega, y, list, y2, soff); break;
-    case 6: fb_launch<TA, TX, TY, MODE, 6>(G, grid, st, n, optr, ocol, ov, x, b, omega, y, list, y2, soff); break;
-    case 10: fb_launch<TA, TX, TY, MODE, 10>(G, grid, st, n, optr, ocol, ov, x, b, omega, y, list, y2, soff); break;
-    default: set_error("unsupported facet block size %d", B); return AH_EUNSUPPORTED;
-  }
+  bool done = false;
+  const auto go = [&](auto BC) {
+    fb_launch<TA, TX, TY, MODE, decltype(BC)::value>(G, grid, st, n, optr, ocol, ov, x, b, omega, y, list, y2, soff,
+                                                     xc, own);
+    done = true;
+  };
+  if (B == 2) go(std::integral_constant<int, 2>{});
+  if (B == 4) go(std::integral_constant<int, 4>{});
+  if (B == 6) go(std::integral_constant<int, 6>{});
+  if (B == 10) go(std::integral_constant<int, 10>{});
+  if constexpr (MODE != SP_SO && MODE != SP_SO_P && MODE != SP_SO_E && MODE != SP_SO_C)
+    if (B == 3) go(std::integral_constant<int, 3>{});
+  if (!done) { set_error("unsupported facet block size %d", B); return AH_EUNSUPPORTED; }
   prof_end(ps);
   AH_LAUNCHED();
   return AH_OK;
@@ -1031,6 +1116,13 @@ static ah_status fbr_g(const AhLevel& L, const T* av, const T* ax, int64_t n, co
 
 // Lanes per block row of k_fbb from the mean number of off-diagonal blocks
 // per block row (C3: 6 -> 8 lanes).
+// Whether the level-0 kernels run by facet block rows (k_fbb): for odd B.  For
+// even B the rows' paired loads are faster on every size measured (p = 2: 64^2
+// slab SpMV 38.9 -> 18.7 us; mapped 36^3, forward and adjoint, 292 -> 253 ms;
+// block AIR on a 32^3 cube 64 -> 50 ms); at B = 3 a row's values cannot be
+// paired, and one gather of x for the whole block wins (96^3 SpMV 1.36 -> 1.0 ms).
+static bool by_blocks(const ah_hier* h, int B) { return h->fbb && B % 2; }
+
 static int fbb_lanes(int64_t nvals, int64_t n, int B) {
   const double nb = n ? (double)nvals / ((double)n * B) : 0.0;
   if (nb <= 2.0) return 2;
@@ -1064,14 +1156,19 @@ static ah_status fbb_g(int B, int L, int64_t n, const int64_t* optr, const int32
   const int64_t nbr = n / B;
   ProfScope ps;
   prof_begin(ps, tag, st, bytes);
-  switch (B) {
-    case 2: fbb_launch<TA, TX, TY, MODE, 2>(L, nbr, st, optr, ocol, ov, x, b, omega, y, list, y2, xc, own); break;
-    case 3: fbb_launch<TA, TX, TY, MODE, 3>(L, nbr, st, optr, ocol, ov, x, b, omega, y, list, y2, xc, own); break;
-    case 4: fbb_launch<TA, TX, TY, MODE, 4>(L, nbr, st, optr, ocol, ov, x, b, omega, y, list, y2, xc, own); break;
-    case 6: fbb_launch<TA, TX, TY, MODE, 6>(L, nbr, st, optr, ocol, ov, x, b, omega, y, list, y2, xc, own); break;
-    case 10: fbb_launch<TA, TX, TY, MODE, 10>(L, nbr, st, optr, ocol, ov, x, b, omega, y, list, y2, xc, own); break;
-    default: set_error("unsupported facet block size %d", B); return AH_EUNSUPPORTED;
+  bool done = false;
+  const auto go = [&](auto BC) {
+    fbb_launch<TA, TX, TY, MODE, decltype(BC)::value>(L, nbr, st, optr, ocol, ov, x, b, omega, y, list, y2, xc, own);
+    done = true;
+  };
+  if (B == 3) go(std::integral_constant<int, 3>{});
+  if constexpr (MODE == SP_RESTRICT) {   // the other modes run by rows for even B
+    if (B == 2) go(std::integral_constant<int, 2>{});
+    if (B == 4) go(std::integral_constant<int, 4>{});
+    if (B == 6) go(std::integral_constant<int, 6>{});
+    if (B == 10) go(std::integral_constant<int, 10>{});
   }
+  if (!done) { set_error("unsupported facet block size %d", B); return AH_EUNSUPPORTED; }
   prof_end(ps);
   AH_LAUNCHED();
   return AH_OK;
@@ -1084,11 +1181,11 @@ template <class T, int MODE>
 static ah_status fb_any(const ah_hier* h, const AhLevel& L, bool blocks, int64_t n, const T* ov, const T* x,
                         const T* b, T om, T* y, hipStream_t st, const char* tag = nullptr, double bytes = 0.0,
                         const int32_t* list = nullptr, T* y2 = nullptr) {
-  if (blocks && h->fbb) {
+  if (blocks && by_blocks(h, L.ob)) {
     const int lp = h->lpb ? h->lpb : fbb_lanes(L.nov, L.n, L.ob);
     return fbb_g<T, T, T, MODE>(L.ob, lp, n, L.optr, L.ocol, ov, x, b, om, y, st, tag, bytes, list, y2);
   }
-  const int Gb = h->g0 ? h->g0 : fb_lanes(L.nov, L.n);
+  const int Gb = h->g0 ? h->g0 : fb_lanes(L.nov, L.n, L.ob);
   return fb_g<T, T, T, MODE>(L.ob, Gb, n, L.optr, L.ocol, ov, x, b, om, y, st, tag, bytes, list, y2);
 }
 
@@ -1283,7 +1380,7 @@ template <class T, int B>
 static ah_status gs_fb_sweep_b(const ah_hier* h, bool fonly, const T* ov, const T* b, const T* xo, T* xn,
                                hipStream_t st) {
   const AhLevel& L = h->lev[0];
-  const int G = fb_lanes(L.nov, L.n) <= 4 ? 4 : 8;
+  const int G = fb_lanes(L.nov, L.n, L.ob) <= 4 ? 4 : 8;
   const std::vector<int64_t>& lp = fonly ? h->ord_lptrF : h->ord_lptr;
   const int64_t scale = fonly ? 1 : B;
   const int4* rec = fonly ? h->ord_finfo : h->ord_info;
@@ -1446,31 +1543,53 @@ static ah_status vcycle(ah_hier* h, int l, const T* b, T* out, hipStream_t st) {
     // block AIR with the sweep-ordered copy: the F blocks, then the C
     // blocks, each set one contiguous range of block rows
     const T* so = Ops<T>::SO(L);
-    const int lp = h->lpb ? h->lpb : fbb_lanes(L.nov, L.n, L.ob);
     const int64_t nbF = nF / L.ob;
-    if (pfree) {
-      // F1: P e_c -> y; F2: y on F, e_c on C -> x and out; C: x on F, e_c on C -> out
-      AH_TRY((fbb_g<T, T, T, SP_SO_P>(L.ob, lp, nF, L.soptr, L.socp, so, ec, b, om, y, st, tf,
-                                      fb_sweep_bytes<T>(L, 0, false, 1), L.sperm, nullptr, ec, L.soown)));
-      AH_TRY((fbb_g<T, T, T, SP_SO_E>(L.ob, lp, nF, L.soptr, L.soce, so, y, b, om, x, st, tf,
-                                      fb_sweep_bytes<T>(L, 0, true, 2), L.sperm, out, ec, nullptr)));
-      AH_TRY((fbb_g<T, T, T, SP_SO_C>(L.ob, lp, L.nc, L.soptr + nbF, L.soce, so, x, b, om, out, st, tc,
-                                      fb_sweep_bytes<T>(L, 1, false, 2), L.sperm + nbF, nullptr, ec)));
+    const double bf1 = fb_sweep_bytes<T>(L, 0, false, 1), bf2 = fb_sweep_bytes<T>(L, 0, true, 2);
+    const double bc2 = fb_sweep_bytes<T>(L, 1, false, 2);
+    if (by_blocks(h, L.ob)) {
+      const int lp = h->lpb ? h->lpb : fbb_lanes(L.nov, L.n, L.ob);
+      if (pfree) {
+        // F1: P e_c -> y; F2: y on F, e_c on C -> x and out; C: x on F, e_c on C -> out
+        AH_TRY((fbb_g<T, T, T, SP_SO_P>(L.ob, lp, nF, L.soptr, L.socp, so, ec, b, om, y, st, tf, bf1, L.sperm,
+                                        nullptr, ec, L.soown)));
+        AH_TRY((fbb_g<T, T, T, SP_SO_E>(L.ob, lp, nF, L.soptr, L.soce, so, y, b, om, x, st, tf, bf2, L.sperm, out, ec,
+                                        nullptr)));
+        AH_TRY((fbb_g<T, T, T, SP_SO_C>(L.ob, lp, L.nc, L.soptr + nbF, L.soce, so, x, b, om, out, st, tc, bc2,
+                                        L.sperm + nbF, nullptr, ec)));
+        return AH_OK;
+      }
+      AH_TRY((fbb_g<T, T, T, SP_SWEEP_ORD>(L.ob, lp, nF, L.soptr, L.socol, so, x, b, om, y, st, tf,
+                                           fb_sweep_bytes<T>(L, 0, false), L.sperm)));
+      if (nsw == 1) return AH_OK;
+      AH_TRY((fbb_g<T, T, T, SP_SWEEP_ORD>(L.ob, lp, nF, L.soptr, L.socol, so, y, b, om, x, st, tf,
+                                           fb_sweep_bytes<T>(L, 0, true), L.sperm, out)));
+      AH_TRY((fbb_g<T, T, T, SP_SWEEP_ORD>(L.ob, lp, L.nc, L.soptr + nbF, L.socol, so, x, b, om, out, st, tc,
+                                           fb_sweep_bytes<T>(L, 1, false), L.sperm + nbF)));
       return AH_OK;
     }
-    AH_TRY((fbb_g<T, T, T, SP_SWEEP_ORD>(L.ob, lp, nF, L.soptr, L.socol, so, x, b, om, y, st, tf,
-                                         fb_sweep_bytes<T>(L, 0, false), L.sperm)));
+    const int Gb = h->g0 ? h->g0 : fb_lanes(L.nov, L.n, L.ob);
+    if (pfree) {
+      AH_TRY((fb_g<T, T, T, SP_SO_P>(L.ob, Gb, nF, L.soptr, L.socp, so, ec, b, om, y, st, tf, bf1, L.sperm, nullptr,
+                                     nullptr, ec, L.soown)));
+      AH_TRY((fb_g<T, T, T, SP_SO_E>(L.ob, Gb, nF, L.soptr, L.soce, so, y, b, om, x, st, tf, bf2, L.sperm, out,
+                                     nullptr, ec)));
+      AH_TRY((fb_g<T, T, T, SP_SO_C>(L.ob, Gb, L.nc, L.soptr + nbF, L.soce, so, x, b, om, out, st, tc, bc2,
+                                     L.sperm + nbF, nullptr, nullptr, ec)));
+      return AH_OK;
+    }
+    AH_TRY((fb_g<T, T, T, SP_SO>(L.ob, Gb, nF, L.soptr, L.socol, so, x, b, om, y, st, tf,
+                                 fb_sweep_bytes<T>(L, 0, false), L.sperm)));
     if (nsw == 1) return AH_OK;
-    AH_TRY((fbb_g<T, T, T, SP_SWEEP_ORD>(L.ob, lp, nF, L.soptr, L.socol, so, y, b, om, x, st, tf,
-                                         fb_sweep_bytes<T>(L, 0, true), L.sperm, out)));
-    AH_TRY((fbb_g<T, T, T, SP_SWEEP_ORD>(L.ob, lp, L.nc, L.soptr + nbF, L.socol, so, x, b, om, out, st, tc,
-                                         fb_sweep_bytes<T>(L, 1, false), L.sperm + nbF)));
+    AH_TRY((fb_g<T, T, T, SP_SO>(L.ob, Gb, nF, L.soptr, L.socol, so, y, b, om, x, st, tf,
+                                 fb_sweep_bytes<T>(L, 0, true), L.sperm, out)));
+    AH_TRY((fb_g<T, T, T, SP_SO>(L.ob, Gb, L.nc, L.soptr + nbF, L.socol, so, x, b, om, out, st, tc,
+                                 fb_sweep_bytes<T>(L, 1, false), L.sperm + nbF)));
     return AH_OK;
   }
   if (l == 0 && !L.fblk && L.rsoff && Ops<T>::SO(L)) {
     // scalar AIR: the rows' values in sweep order (the F rows, then the C rows)
     const T* so = Ops<T>::SO(L);
-    const int Gb = h->g0 ? h->g0 : fb_lanes(L.nov, L.n);
+    const int Gb = h->g0 ? h->g0 : fb_lanes(L.nov, L.n, L.ob);
     AH_TRY((fb_g<T, T, T, SP_SWEEP_ORD>(L.ob, Gb, nF, L.optr, L.ocol, so, x, b, om, y, st, tf,
                                         fb_sweep_bytes<T>(L, 0, false), L.flist, nullptr, L.rsoff)));
     if (nsw == 1) return AH_OK;
@@ -1792,7 +1911,7 @@ struct Op {
 
 static int op_lanes(const ah_hier* h, const Op& A, int64_t n) {
   if (h->g0) return h->g0;
-  return A.ob ? fb_lanes(A.nov, n) : pick_g(h->lev[0].nnz, n);
+  return A.ob ? fb_lanes(A.nov, n, A.ob) : pick_g(h->lev[0].nnz, n);
 }
 
 // Algorithmic bytes of y = A x (x of width wx): the operator once, x once,
@@ -2368,7 +2487,7 @@ static ah_status solve_forward(ah_hier* h, const KWork& W, const double* rhs, do
     A.ocol = L0.ocol;
     A.ov = L0.oval;
     A.nov = L0.nov;
-    A.lpb = h->fbb ? (h->lpb ? h->lpb : fbb_lanes(L0.nov, n, L0.ob)) : 0;
+    A.lpb = by_blocks(h, L0.ob) ? (h->lpb ? h->lpb : fbb_lanes(L0.nov, n, L0.ob)) : 0;
   }
   if (prm.method == 1) return bicgstab(h, A, b, x, prm, 0, st, info);
   return fgmres(h, W, A, b, x, prm, 0, st, info);
@@ -2452,7 +2571,7 @@ extern "C" ah_status air_solve_adjoint(const ah_hier* hc, const double* g, doubl
     AT.ocol = L0.ocol;
     AT.ov = L0.otval;
     AT.nov = L0.nov;
-    AT.lpb = h->fbb ? (h->lpb ? h->lpb : fbb_lanes(L0.nov, n, L0.ob)) : 0;
+    AT.lpb = by_blocks(h, L0.ob) ? (h->lpb ? h->lpb : fbb_lanes(L0.nov, n, L0.ob)) : 0;
   }
   ah_status rc = prm->method == 1 ? bicgstab(h, AT, g, mu, *prm, 1, st, info)
                                    : fgmres(h, W, AT, g, mu, *prm, 1, st, info);
