@@ -366,7 +366,8 @@ ah_status air_solve(const ah_hier* h, const double* rhs, double* x, const ah_sol
  * semantics and results as air_solve with method 0 (FGMRES); the FGMRES
  * workspace comes from a static device array of AH_NOALLOC_SCRATCH_BYTES
  * that the library holds on every GPU it runs on until the process ends,
- * and the host staging is a static per-thread array.  It needs
+ * and the host staging is the thread's pinned buffer where an earlier call on
+ * this thread made one, else a static per-thread array.  It needs
  * 8 ((2 m + 4) n + 1024 (2 m + 4) + 4 (m + 3)) bytes (FP32 cycle: the m Z
  * vectors take 4 bytes per value), rounded up to 256-byte pieces, with
  * m = restart <= AH_NOALLOC_MAX_RESTART.  Returns AH_EUNSUPPORTED for a

@@ -73,6 +73,8 @@ struct Arena {
 // Process-wide pinned host staging buffer (grown on demand, never freed)
 // for small device-to-host reads.
 double* pinned_scratch(size_t doubles);
+// The same buffer if it holds that many already, else null (allocates nothing).
+double* pinned_existing(size_t doubles);
 
 inline int64_t cdiv(int64_t a, int64_t b) { return (a + b - 1) / b; }
 

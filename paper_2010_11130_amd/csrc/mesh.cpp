@@ -157,13 +157,18 @@ void Arena::release() {
   left = 0;
 }
 
+static thread_local double* pin_buf = nullptr;
+static thread_local size_t pin_cap = 0;
+
+double* pinned_existing(size_t doubles) { return doubles <= pin_cap ? pin_buf : nullptr; }
+
 double* pinned_scratch(size_t doubles) {
-  static thread_local double* buf = nullptr;
-  static thread_local size_t cap = 0;
+  double*& buf = pin_buf;
+  size_t& cap = pin_cap;
   if (doubles > cap) {
     size_t want = std::max<size_t>(doubles, 8192);
     double* nb = nullptr;
-    if (hipHostMalloc((void**)&nb, want * sizeof(double), hipHostMallocDefault) != hipSuccess) return nullptr;
+    if (hipHostMalloc((void**)&nb, want * sizeof(double), hipHostMallocCoherent) != hipSuccess) return nullptr;
     // the previous buffer is kept: a caller may still hold it
     buf = nb;
     cap = want;

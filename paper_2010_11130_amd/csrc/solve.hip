@@ -808,64 +808,183 @@ __global__ __launch_bounds__(256) void k_reduce_partial(int nblk, const double* 
   if (threadIdx.x == 0) out[v] = accumulate ? out[v] + red[0] : red[0];
 }
 
-// hs[v] = sum over b of partial[v][b] for v < nv, into LDS: wave v % 4
-// sums a lane-strided slice and reduces it across the wave.  The order is
-// fixed, so every block of a launch obtains the same values.
-__device__ inline void partials_to_lds(const double* __restrict__ partial, int nblk, int nv, double* hs) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6, nw = blockDim.x >> 6;
-  for (int v = wv; v < nv; v += nw) {
-    double s = 0.0;
-    for (int b = lane; b < nblk; b += 64) s += partial[(int64_t)v * nblk + b];
-    for (int o = 32; o > 0; o >>= 1) s += __shfl_xor(s, o, 64);
-    if (lane == 0) hs[v] = s;
+// ---- CGS2 below 2^21 unknowns, five launches per iteration: dots, update,
+// dots, update with the norm, and k_cgs_finish, which normalises w into the
+// next basis vector and hands the scalars to the host.  The basis (2.7 MB per
+// vector on the 64^2 slab at p = 2) stays in the Infinity Cache, so the passes
+// are bound by how many loads are in flight, not by HBM: each thread of the dot
+// pass has two rows of eight vectors and w under way, each of the update pass
+// two rows of eight vectors.  At 16 vectors there: dots 15.0 us with one row of
+// four vectors in flight and 335 partials per dot, 12.0 now; update 19 to
+// 21 us, 13.0 now.
+constexpr int CGS_T = 512;      // threads per block of the dot pass
+constexpr int CGS_B = 128;      // most row blocks of the dot pass: partials per dot
+constexpr int CGS_V = 8;        // vectors per block of the dot pass
+constexpr int CGS_UB = 512;     // most blocks of the update pass: partials of the norm
+
+// partial[v][blk] = V_v . w over the block's rows (v < k), w . w at v = k.
+__global__ __launch_bounds__(CGS_T) void k_cgs_dot(int64_t n, int k, const double* __restrict__ V, int64_t ldv,
+                                                  const double* __restrict__ w, double* __restrict__ partial) {
+  __shared__ double red[CGS_T / 64][CGS_V];
+  const int v0 = blockIdx.y * CGS_V;
+  const double* p[CGS_V];
+#pragma unroll
+  for (int q = 0; q < CGS_V; ++q) p[q] = v0 + q < k ? V + (int64_t)(v0 + q) * ldv : w;
+  double acc[CGS_V];
+#pragma unroll
+  for (int q = 0; q < CGS_V; ++q) acc[q] = 0.0;
+  const int64_t st = (int64_t)gridDim.x * CGS_T;
+  for (int64_t i = (int64_t)blockIdx.x * CGS_T + threadIdx.x; i < n; i += 2 * st) {
+    const int64_t i2 = i + st < n ? i + st : i;
+    const double w0 = w[i], w1 = i + st < n ? w[i2] : 0.0;
+    double a0[CGS_V], a1[CGS_V];
+#pragma unroll
+    for (int q = 0; q < CGS_V; ++q) {
+      a0[q] = p[q][i];
+      a1[q] = p[q][i2];
+    }
+#pragma unroll
+    for (int q = 0; q < CGS_V; ++q) acc[q] += a0[q] * w0 + a1[q] * w1;
   }
+  // the eight sums of a wave together: each exchange halves what a lane carries
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+#pragma unroll
+  for (int h = CGS_V / 2; h >= 1; h >>= 1) {
+    const bool up = lane & (8 * h);
+#pragma unroll
+    for (int q = 0; q < h; ++q) {
+      const double keep = up ? acc[q + h] : acc[q], send = up ? acc[q] : acc[q + h];
+      acc[q] = keep + __shfl_xor(send, 8 * h, 64);
+    }
+  }
+  for (int o = 4; o > 0; o >>= 1) acc[0] += __shfl_xor(acc[0], o, 64);
+  if ((lane & 7) == 0) red[wv][lane >> 3] = acc[0];
   __syncthreads();
+  const int t = threadIdx.x;
+  if (t < CGS_V && v0 + t <= k) {
+    double x = 0.0;
+#pragma unroll
+    for (int q = 0; q < CGS_T / 64; ++q) x += red[q][t];
+    partial[(int64_t)(v0 + t) * gridDim.x + blockIdx.x] = x;
+  }
 }
 
-// Classical Gram-Schmidt step from the block partials of k_multidot
-// (V_v.w for v < k, w.w at k): h = their sums, w -= sum_{v<k} V_v h_v; block
-// 0 also stores h[0..k] in hout.  Dynamic LDS: (k+1) doubles.
-__global__ __launch_bounds__(DOT_T) void k_maxpy_p(int64_t n, int k, const double* __restrict__ V, int64_t ldv,
-                                                   const double* __restrict__ partial, int nblk,
-                                                   double* __restrict__ w, double* __restrict__ hout) {
+// h = the dots' sums over their nb <= CGS_B partials (every block, fixed
+// order), w -= sum_{v<k} V_v h_v; block 0 stores h[0..k] in hout.  pout (or
+// null): partials of the updated w . w per block.  Dynamic LDS: k + 1 doubles.
+__global__ __launch_bounds__(256) void k_cgs_update(int64_t n, int k, const double* __restrict__ V, int64_t ldv,
+                                                    const double* __restrict__ partial, int nb,
+                                                    double* __restrict__ w, double* __restrict__ hout,
+                                                    double* __restrict__ pout) {
   extern __shared__ double hs[];
-  partials_to_lds(partial, nblk, k + 1, hs);
-  if (blockIdx.x == 0)
-    for (int v = threadIdx.x; v <= k; v += DOT_T) hout[v] = hs[v];
-  for (int64_t i = (int64_t)blockIdx.x * DOT_T + threadIdx.x; i < n; i += (int64_t)gridDim.x * DOT_T) {
-    double s = 0.0;
-    for (int v = 0; v < k; ++v) s += V[(int64_t)v * ldv + i] * hs[v];
-    w[i] -= s;
+  __shared__ double red[4];
+  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+  for (int v0 = wv * 4; v0 <= k; v0 += 16) {   // a wave sums four dots at a time
+    double x[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const double* pv = partial + (int64_t)min(v0 + q, k) * nb;
+      x[q] = 0.0;
+#pragma unroll
+      for (int u = 0; u < CGS_B; u += 64) x[q] += lane + u < nb ? pv[lane + u] : 0.0;
+    }
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      for (int o = 32; o > 0; o >>= 1) x[q] += __shfl_xor(x[q], o, 64);
+    if (lane == 0)
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (v0 + q <= k) hs[v0 + q] = x[q];
   }
+  __syncthreads();
+  if (blockIdx.x == 0)
+    for (int v = threadIdx.x; v <= k; v += 256) hout[v] = hs[v];
+  double nrm = 0.0;
+  const int64_t st = (int64_t)gridDim.x * 256;
+  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += 2 * st) {
+    const bool two = i + st < n;
+    const int64_t i2 = two ? i + st : i;
+    const double w0 = w[i], w1 = w[i2];
+    double s0 = 0.0, s1 = 0.0;
+    int v = 0;
+    for (; v + 8 <= k; v += 8) {
+      double a0[8], a1[8];
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        const double* pv = V + (int64_t)(v + q) * ldv;
+        a0[q] = pv[i];
+        a1[q] = pv[i2];
+      }
+#pragma unroll
+      for (int q = 0; q < 8; ++q) {
+        s0 += a0[q] * hs[v + q];
+        s1 += a1[q] * hs[v + q];
+      }
+    }
+    if (v < k) {   // the last one to seven in one step: clamped loads of weight zero
+      double a0[7], a1[7];
+#pragma unroll
+      for (int q = 0; q < 7; ++q) {
+        const double* pv = V + (int64_t)min(v + q, k - 1) * ldv;
+        a0[q] = pv[i];
+        a1[q] = pv[i2];
+      }
+#pragma unroll
+      for (int q = 0; q < 7; ++q) {
+        const double hq = v + q < k ? hs[v + q] : 0.0;
+        s0 += a0[q] * hq;
+        s1 += a1[q] * hq;
+      }
+    }
+    const double x0 = w0 - s0, x1 = w1 - s1;
+    w[i] = x0;
+    nrm += x0 * x0;
+    if (two) {
+      w[i2] = x1;
+      nrm += x1 * x1;
+    }
+  }
+  if (!pout) return;
+  for (int o = 32; o > 0; o >>= 1) nrm += __shfl_xor(nrm, o, 64);
+  if (lane == 0) red[wv] = nrm;
+  __syncthreads();
+  if (threadIdx.x == 0) pout[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
 }
 
-// The same step with the block partial sums of the updated w.w written to
-// pout[blockIdx.x] (nblk blocks; pout must not overlap partial).
-__global__ __launch_bounds__(DOT_T) void k_maxpy_norm(int64_t n, int k, const double* __restrict__ V, int64_t ldv,
-                                                      const double* __restrict__ partial, int nblk,
-                                                      double* __restrict__ w, double* __restrict__ hout,
-                                                      double* __restrict__ pout) {
-  extern __shared__ double hs[];
-  __shared__ double red[DOT_T / 64];
-  partials_to_lds(partial, nblk, k + 1, hs);
-  if (blockIdx.x == 0)
-    for (int v = threadIdx.x; v <= k; v += DOT_T) hout[v] = hs[v];
-  double acc = 0.0;
-  for (int64_t i = (int64_t)blockIdx.x * DOT_T + threadIdx.x; i < n; i += (int64_t)nblk * DOT_T) {
-    double s = 0.0;
-    for (int v = 0; v < k; ++v) s += V[(int64_t)v * ldv + i] * hs[v];
-    double wi = w[i] - s;
-    w[i] = wi;
-    acc += wi * wi;
-  }
-  for (int o = 32; o > 0; o >>= 1) acc += __shfl_xor(acc, o, 64);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = acc;
+// out = w / |w| with |w|^2 the sum of the np <= CGS_UB partials (out null: the
+// sum alone), and the scalars for the host: |w|^2 to hn, and where the host
+// can see device stores (host not null) h1[0..k], h2[0..k] and |w|^2 into its
+// buffer at 0, off and 2 off, then seq into flag, which the host polls.
+__global__ __launch_bounds__(256) void k_cgs_finish(int64_t n, const double* __restrict__ w,
+                                                    const double* __restrict__ part, int np, double* __restrict__ out,
+                                                    double* __restrict__ hn, int k, int off,
+                                                    const double* __restrict__ h1, const double* __restrict__ h2,
+                                                    double* host, unsigned long long* flag, unsigned long long seq) {
+  __shared__ double red[4];
+  const int t = threadIdx.x;
+  double x = 0.0;
+#pragma unroll
+  for (int u = 0; u < CGS_UB; u += 256) x += t + u < np ? part[t + u] : 0.0;
+  for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+  if ((t & 63) == 0) red[t >> 6] = x;
   __syncthreads();
-  if (threadIdx.x == 0) {
-    double s = 0.0;
-    for (int q = 0; q < DOT_T / 64; ++q) s += red[q];
-    pout[blockIdx.x] = s;
+  const double nn = (red[0] + red[1]) + (red[2] + red[3]);
+  if (blockIdx.x == 0) {
+    if (host) {
+      for (int v = t; v <= k; v += 256) {
+        host[v] = h1[v];
+        host[off + v] = h2[v];
+      }
+      if (t == 0) host[2 * off] = nn;
+      __threadfence_system();
+      __syncthreads();
+      if (t == 0) __hip_atomic_store(flag, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
+    }
+    if (t == 0) *hn = nn;
   }
+  if (!out) return;
+  const double s = 1.0 / sqrt(nn);
+  for (int64_t i = (int64_t)blockIdx.x * 256 + t; i < n; i += (int64_t)gridDim.x * 256) out[i] = w[i] * s;
 }
 
 // Delayed CGS2 (the second projection of each basis vector is done one
@@ -969,9 +1088,20 @@ __global__ void k_maxpy(int64_t n, int k, const TV* __restrict__ V, int64_t ldv,
   w[i] += sign * s;
 }
 
-__global__ void k_scale(int64_t n, const double* __restrict__ a, double s, double* __restrict__ b) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i < n) b[i] = a[i] * s;
+// x += sum_v Z_v c_v, the coefficients with the launch.
+constexpr int COMB_MAX = 128;
+struct CombCoef {
+  double c[COMB_MAX];
+};
+template <class TV>
+__global__ __launch_bounds__(256) void k_combine(int64_t n, int k, const TV* __restrict__ Z, int64_t ldz, CombCoef cf,
+                                                 double* __restrict__ x) {
+  const int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i >= n) return;
+  double s = 0.0;
+#pragma unroll 8
+  for (int v = 0; v < k; ++v) s += (double)Z[(int64_t)v * ldz + i] * cf.c[v];
+  x[i] += s;
 }
 
 // Block scaling of a right-hand side by D_b^-1 (trans = 0) or D_b^-T.
@@ -1454,23 +1584,25 @@ static ah_status gs_csr_sweep_t(const ah_hier* h, bool fonly, const T* atv, cons
   return AH_OK;
 }
 
-// Forward cycle on level l: b -> out.  out must differ from b and from the
-// level's sweep buffers x and y (the second F sweep writes its rows into out
-// while other rows still read y): callers pass the level's e buffer or an
-// external vector.  The recursion writes the coarse correction into the
-// coarse level's e.
+// The forward cycle b -> out, in two parts.  The way down restricts b to the
+// coarse end and applies it; the way up interpolates and sweeps level after
+// level.  A level's correction is its e buffer, level 0's is out, which must
+// differ from b and from level 0's sweep buffers x and y (the second F sweep
+// writes its rows into out while other rows still read y).
 template <class T>
-static ah_status vcycle(ah_hier* h, int l, const T* b, T* out, hipStream_t st) {
+static ah_status end_apply(ah_hier* h, const T* b, T* out, hipStream_t st) {
+  const AhLevel& L = h->lev[h->end0];
+  if (L.n == 0) return AH_OK;
+  hipLaunchKernelGGL(k_end_mv<T>, dim3((unsigned)cdiv(L.n, 4)), dim3(256), 0, st, (int)L.n, h->end_mat, b, out);
+  AH_LAUNCHED();
+  return AH_OK;
+}
+
+// b_{l+1} = R_l b
+template <class T>
+static ah_status restrict_level(ah_hier* h, int l, const T* b, hipStream_t st) {
   AhLevel& L = h->lev[l];
-  const int nsw = h->prm.relax == 1 ? 1 : 3;
-  if (l == h->end0) {
-    if (L.n == 0) return AH_OK;
-    hipLaunchKernelGGL(k_end_mv<T>, dim3((unsigned)cdiv(L.n, 4)), dim3(256), 0, st, (int)L.n, h->end_mat, b, out);
-    AH_LAUNCHED();
-    return AH_OK;
-  }
   AhLevel& C = h->lev[l + 1];
-  const int G = (l == 0 && h->g0) ? h->g0 : (l > 0 && h->gc) ? h->gc : pick_g(L.nnz, L.n);
   const int GR = pick_g(L.nnzR, L.nc);
   if (l == 0 && L.rzptr && Ops<T>::RZ(L)) {
     // block AIR: R = [Z I] by coarse blocks
@@ -1482,8 +1614,15 @@ static ah_status vcycle(ah_hier* h, int l, const T* b, T* out, hipStream_t st) {
     AH_TRY((csr_g<T, T, T, SP_MV>(GR, L.nc, L.Rptr, L.Rcol, Ops<T>::R(L), b, (const T*)nullptr, (const T*)nullptr,
                                   (const int8_t*)nullptr, 0, (T)0, Ops<T>::b(C), st)));
   }
-  T* ec = Ops<T>::e(C);
-  AH_TRY(vcycle<T>(h, l + 1, Ops<T>::b(C), ec, st));
+  return AH_OK;
+}
+
+// out = P e_c, then the level's sweeps
+template <class T>
+static ah_status relax_level(ah_hier* h, int l, const T* b, const T* ec, T* out, hipStream_t st) {
+  AhLevel& L = h->lev[l];
+  const int nsw = h->prm.relax == 1 ? 1 : 3;
+  const int G = (l == 0 && h->g0) ? h->g0 : (l > 0 && h->gc) ? h->gc : pick_g(L.nnz, L.n);
   const T om = (T)h->prm.omega;
   const int64_t nF = L.n - L.nc;
   if (l > 0 && L.n < h->list_min) {
@@ -1656,6 +1795,22 @@ static ah_status vcycle(ah_hier* h, int l, const T* b, T* out, hipStream_t st) {
   return AH_OK;
 }
 
+template <class T>
+static ah_status vcycle_down(ah_hier* h, const T* b, hipStream_t st) {
+  for (int l = 0; l < h->end0; ++l) AH_TRY(restrict_level<T>(h, l, l ? Ops<T>::b(h->lev[l]) : b, st));
+  AhLevel& E = h->lev[h->end0];
+  return h->end0 ? end_apply<T>(h, Ops<T>::b(E), Ops<T>::e(E), st) : AH_OK;
+}
+
+template <class T>
+static ah_status vcycle_up(ah_hier* h, const T* b, T* out, hipStream_t st) {
+  if (h->end0 == 0) return end_apply<T>(h, b, out, st);
+  for (int l = h->end0 - 1; l >= 0; --l)
+    AH_TRY(relax_level<T>(h, l, l ? Ops<T>::b(h->lev[l]) : b, Ops<T>::e(h->lev[l + 1]),
+                          l ? Ops<T>::e(h->lev[l]) : out, st));
+  return AH_OK;
+}
+
 // Transposed cycle on level l: g -> out (out may alias g above the coarse end,
 // not the level's x or y).  The recursion writes its result over the coarse
 // level's input (or into x on the first level of the coarse end).
@@ -1739,16 +1894,32 @@ static ah_status vcycle_t(ah_hier* h, int l, const T* g, T* out, hipStream_t st)
 }
 
 // Preconditioner application on level 0 for the requested precision:
-// r (FP64, level-0 scaled space) -> z (FP64) or z32 (FP32).
-static ah_status precond(ah_hier* h, const double* r, double* z, float* z32, int precision, int transpose,
-                         hipStream_t st) {
+// r (FP64, level-0 scaled space) -> z (FP64) or z32 (FP32).  A caller may
+// enqueue the forward cycle's way down ahead of the rest.
+static ah_status precond_down(ah_hier* h, const double* r, int precision, hipStream_t st) {
   AhLevel& L = h->lev[0];
-  if (precision == 0) {
-    return transpose ? vcycle_t<double>(h, 0, r, z, st) : vcycle<double>(h, 0, r, z, st);
-  }
+  if (precision == 0) return vcycle_down<double>(h, r, st);
   hipLaunchKernelGGL((k_cast<double, float>), g1(L.n), dim3(256), 0, st, L.n, r, L.b32);
   AH_LAUNCHED();
-  return transpose ? vcycle_t<float>(h, 0, L.b32, z32, st) : vcycle<float>(h, 0, L.b32, z32, st);
+  return vcycle_down<float>(h, L.b32, st);
+}
+
+static ah_status precond_up(ah_hier* h, const double* r, double* z, float* z32, int precision, hipStream_t st) {
+  if (precision == 0) return vcycle_up<double>(h, r, z, st);
+  return vcycle_up<float>(h, h->lev[0].b32, z32, st);
+}
+
+static ah_status precond(ah_hier* h, const double* r, double* z, float* z32, int precision, int transpose,
+                         hipStream_t st) {
+  if (!transpose) {
+    AH_TRY(precond_down(h, r, precision, st));
+    return precond_up(h, r, z, z32, precision, st);
+  }
+  if (precision == 0) return vcycle_t<double>(h, 0, r, z, st);
+  AhLevel& L = h->lev[0];
+  hipLaunchKernelGGL((k_cast<double, float>), g1(L.n), dim3(256), 0, st, L.n, r, L.b32);
+  AH_LAUNCHED();
+  return vcycle_t<float>(h, 0, L.b32, z32, st);
 }
 
 // ------------------------------------------------------------ FGMRES
@@ -1768,6 +1939,7 @@ struct KWork {
   double* partial = nullptr;
   double* hdev = nullptr;
   double* host = nullptr;
+  bool polled = false;         // host is pinned: kernels store the scalars and a flag there
 };
 
 static ah_status ensure_workspace(ah_hier* h, int m, int precision, hipStream_t st, KWork* W) {
@@ -1799,8 +1971,9 @@ static ah_status ensure_workspace(ah_hier* h, int m, int precision, hipStream_t 
   W->bhat = h->bhat;
   W->partial = h->partial;
   W->hdev = h->hdev;
-  W->host = pinned_scratch(4 * (m + 3));
+  W->host = pinned_scratch(4 * (m + 3) + 1);
   if (!W->host) { set_error("pinned host allocation failed"); return AH_ENOMEM; }
+  W->polled = true;
   return AH_OK;
 }
 
@@ -1937,20 +2110,77 @@ static ah_status op_apply(const Op& A, int G, int64_t n, const TX* x, const doub
 static ah_status fgmres_dcgs2(ah_hier* h, const KWork& W, Op A, const double* bvec, double* x,
                               const ah_solve_params& prm, int transpose, hipStream_t st, ah_solve_info* info);
 
+static ah_status fgmres_cgs2(ah_hier* h, const KWork& W, Op A, const double* bvec, double* x,
+                             const ah_solve_params& prm, int transpose, hipStream_t st, ah_solve_info* info);
+
 static ah_status fgmres(ah_hier* h, const KWork& W, Op A, const double* bvec, double* x, const ah_solve_params& prm,
                         int transpose, hipStream_t st, ah_solve_info* info) {
+  const ah_status rc = (h->lev[0].n >= h->dcgs_min ? fgmres_dcgs2 : fgmres_cgs2)(h, W, A, bvec, x, prm, transpose, st,
+                                                                                 info);
+  // launches of a solve that stopped early may still store into its buffers
+  if (rc < 0) (void)hipStreamSynchronize(st);
+  return rc;
+}
+
+static ah_status fgmres_cgs2(ah_hier* h, const KWork& W, Op A, const double* bvec, double* x,
+                             const ah_solve_params& prm, int transpose, hipStream_t st, ah_solve_info* info) {
   const int64_t n = h->lev[0].n;
-  if (n >= h->dcgs_min) return fgmres_dcgs2(h, W, A, bvec, x, prm, transpose, st, info);
   const int m = std::max(1, prm.restart);
   const int G0 = op_lanes(h, A, n);
   double* hd = W.hdev;
   double* hh = W.host;
   auto t0 = std::chrono::steady_clock::now();
-  // ||b||
-  AH_TRY(multidot(n, 0, W.V, bvec, W.partial, hd, st));
-  AH_HIP(hipMemcpyAsync(hh, hd, sizeof(double), hipMemcpyDeviceToHost, st));
-  AH_HIP(hipStreamSynchronize(st));
-  const double bnorm = std::sqrt(hh[0]);
+  double* h1 = hd;               // [k+1]: dots, then ||w0||^2 at [k]
+  double* h2 = hd + (m + 2);     // [k+1]
+  double* hn = hd + 2 * (m + 2); // [1]
+  double* pn = W.partial + (int64_t)(m + 2) * CGS_B;   // norm partials, clear of the (k+1) nb dot partials
+  const int nb = (int)std::min<int64_t>(CGS_B, std::max<int64_t>(1, cdiv(n, CGS_T)));
+  const int nu = (int)std::min<int64_t>(CGS_UB, std::max<int64_t>(1, cdiv(n, 512)));
+  // The scalars of a step reach the host through its pinned buffer: the last
+  // kernel stores them and then the step's number into a flag, which the host
+  // polls.  Without one (polled false) they are copied.
+  unsigned long long* flag = reinterpret_cast<unsigned long long*>(hh + 4 * (m + 3));
+  unsigned long long seq = 0;
+  if (W.polled) __atomic_store_n(flag, 0ull, __ATOMIC_RELEASE);
+  auto dots = [&](int k, const double* w) {
+    hipLaunchKernelGGL(k_cgs_dot, dim3(nb, (unsigned)cdiv(k + 1, CGS_V)), dim3(CGS_T), 0, st, n, k, W.V, n, w,
+                       W.partial);
+  };
+  auto update = [&](int k, double* hout, double* pout) {
+    hipLaunchKernelGGL(k_cgs_update, dim3(nu), dim3(256), (unsigned)((k + 1) * sizeof(double)), st, n, k, W.V, n,
+                       W.partial, nb, W.w, hout, pout);
+  };
+  auto finish = [&](const double* w, const double* part, int np, double* out, int k) -> ah_status {
+    ++seq;
+    hipLaunchKernelGGL(k_cgs_finish, dim3(out ? nu : 1), dim3(256), 0, st, n, w, part, np, out, hn, k, m + 2, h1, h2,
+                       W.polled ? hh : nullptr, flag, seq);
+    AH_LAUNCHED();
+    return AH_OK;
+  };
+  auto wait = [&]() -> ah_status {
+    if (!W.polled) {
+      AH_HIP(hipMemcpyAsync(hh, hd, (2 * (m + 2) + 1) * sizeof(double), hipMemcpyDeviceToHost, st));
+      AH_HIP(hipStreamSynchronize(st));
+      return AH_OK;
+    }
+    for (unsigned spin = 1; __atomic_load_n(flag, __ATOMIC_ACQUIRE) != seq; ++spin) {
+      __builtin_ia32_pause();
+      if (spin % 65536) continue;
+      // a stream that has stopped will not set the flag any more
+      const hipError_t e = hipStreamQuery(st);
+      (void)hipGetLastError();   // "not ready" is no error of a later launch
+      if (e == hipErrorNotReady || __atomic_load_n(flag, __ATOMIC_ACQUIRE) == seq) continue;
+      set_error("air_solve: %s", e == hipSuccess ? "step result missing" : hipGetErrorString(e));
+      return AH_EHIP;
+    }
+    return AH_OK;
+  };
+  // ||b||; with x = 0 b is also the first residual
+  const bool zero = !prm.x0_given;
+  dots(0, bvec);
+  AH_TRY(finish(bvec, W.partial, nb, zero ? W.V : nullptr, -1));
+  AH_TRY(wait());
+  const double bnorm = std::sqrt(hh[2 * (m + 2)]);
   std::vector<double> H((size_t)(m + 1) * m, 0.0), cs(m), sn(m), g(m + 1), y(m);
   int its = 0;
   bool converged = false;
@@ -1962,29 +2192,33 @@ static ah_status fgmres(ah_hier* h, const KWork& W, Op A, const double* bvec, do
     return AH_OK;
   }
   if (!std::isfinite(bnorm)) { set_error("air_solve: non-finite right-hand side"); return AH_EBREAKDOWN; }
-  while (true) {
-    // r = b - A x
-    AH_TRY((op_apply<double, SP_RES>(A, G0, n, x, bvec, W.r, st)));
-    AH_TRY(multidot(n, 0, W.V, W.r, W.partial, hd, st));
-    AH_HIP(hipMemcpyAsync(hh, hd, sizeof(double), hipMemcpyDeviceToHost, st));
-    AH_HIP(hipStreamSynchronize(st));
-    const double beta = std::sqrt(hh[0]);
+  for (bool first = true;; first = false) {
+    double beta = bnorm;
+    if (!first || !zero) {
+      // r = b - A x
+      AH_TRY((op_apply<double, SP_RES>(A, G0, n, x, bvec, W.r, st)));
+      dots(0, W.r);
+      AH_TRY(finish(W.r, W.partial, nb, W.V, -1));
+      AH_TRY(wait());
+      beta = std::sqrt(hh[2 * (m + 2)]);
+    }
     true_rel = beta / bnorm;
     relres = true_rel;
     if (!std::isfinite(beta)) { set_error("air_solve: breakdown (NaN residual)"); status = AH_EBREAKDOWN; break; }
     if (beta <= prm.tol * bnorm) { converged = true; break; }
     if (its >= prm.maxit) break;
-    hipLaunchKernelGGL(k_scale, g1(n), dim3(256), 0, st, n, W.r, 1.0 / beta, W.V);
-    AH_LAUNCHED();
     std::fill(g.begin(), g.end(), 0.0);
     g[0] = beta;
     int kdone = 0;
+    bool down = false;   // the cycle's way down for V[j] is enqueued already
     for (int j = 0; j < m; ++j) {
       double* vj = W.V + (int64_t)j * n;
       double* zj = W.Z ? W.Z + (int64_t)j * n : nullptr;
       float* zj32 = W.Z32 ? W.Z32 + (int64_t)j * n : nullptr;
-      AH_TRY(precond(h, vj, prm.precision == 0 ? zj : nullptr, prm.precision == 1 ? zj32 : nullptr, prm.precision,
-                     transpose, st));
+      if (down)
+        AH_TRY(precond_up(h, vj, zj, zj32, prm.precision, st));
+      else
+        AH_TRY(precond(h, vj, zj, zj32, prm.precision, transpose, st));
       const double by = op_mv_bytes(h, A, n, prm.precision ? 4.0 : 8.0);
       if (prm.precision == 0)
         AH_TRY((op_apply<double, SP_MV>(A, G0, n, zj, (const double*)nullptr, W.w, st,
@@ -1994,28 +2228,17 @@ static ah_status fgmres(ah_hier* h, const KWork& W, Op A, const double* bvec, do
                                        transpose ? nullptr : "spmv0", by)));
       ++its;
       const int k = j + 1;
-      // CGS2
-      double* h1 = hd;               // [k+1]: dots, then ||w0||^2 at [k]
-      double* h2 = hd + (m + 2);     // [k+1]
-      double* hn = hd + 2 * (m + 2); // [1]
-      // each pass: block partials of the dots, then one kernel that sums
-      // them (every block, fixed order) and updates w
-      {
-        const int nblk = dot_blocks(n);
-        const unsigned hb = (unsigned)((k + 1) * sizeof(double));
-        double* p3 = W.partial + (int64_t)(m + 2) * 1024;   // clear of the (k+1) nblk dot partials
-        hipLaunchKernelGGL(k_multidot, dim3(nblk, (unsigned)cdiv(k + 1, DOT_V)), dim3(DOT_T), 0, st, n, k, W.V, n,
-                           W.w, W.partial, nblk);
-        hipLaunchKernelGGL(k_maxpy_p, dim3(nblk), dim3(DOT_T), hb, st, n, k, W.V, n, W.partial, nblk, W.w, h1);
-        hipLaunchKernelGGL(k_multidot, dim3(nblk, (unsigned)cdiv(k + 1, DOT_V)), dim3(DOT_T), 0, st, n, k, W.V, n,
-                           W.w, W.partial, nblk);
-        hipLaunchKernelGGL(k_maxpy_norm, dim3(nblk), dim3(DOT_T), hb, st, n, k, W.V, n, W.partial, nblk, W.w, h2,
-                           p3);
-        hipLaunchKernelGGL(k_reduce_partial, dim3(1), dim3(256), 0, st, nblk, p3, hn, 0);
-        AH_LAUNCHED();
-      }
-      AH_HIP(hipMemcpyAsync(hh, hd, (3 * (m + 2)) * sizeof(double), hipMemcpyDeviceToHost, st));
-      AH_HIP(hipStreamSynchronize(st));
+      dots(k, W.w);
+      update(k, h1, nullptr);
+      dots(k, W.w);
+      update(k, h2, pn);
+      double* vk = W.V + (int64_t)k * n;
+      AH_TRY(finish(W.w, pn, nu, vk, k));
+      // the next cycle's way down runs while the host takes this step's
+      // scalars (wasted after the last step of a solve: a few small launches)
+      down = W.polled && !transpose && k < m && its < prm.maxit;
+      if (down) AH_TRY(precond_down(h, vk, prm.precision, st));
+      AH_TRY(wait());
       const double w0 = std::sqrt(hh[k]);
       const double hnorm = std::sqrt(hh[2 * (m + 2)]);
       if (!std::isfinite(hnorm) || !std::isfinite(w0)) {
@@ -2042,8 +2265,6 @@ static ah_status fgmres(ah_hier* h, const KWork& W, Op A, const double* bvec, do
       relres = std::fabs(g[k]) / bnorm;
       const bool happy = hnorm <= 1e-14 * w0;
       if (std::fabs(g[k]) <= prm.tol * bnorm || happy || its >= prm.maxit) break;
-      hipLaunchKernelGGL(k_scale, g1(n), dim3(256), 0, st, n, W.w, 1.0 / hnorm, W.V + (int64_t)k * n);
-      AH_LAUNCHED();
     }
     if (status != AH_OK && kdone == 0) break;
     for (int i = kdone - 1; i >= 0; --i) {
@@ -2051,12 +2272,16 @@ static ah_status fgmres(ah_hier* h, const KWork& W, Op A, const double* bvec, do
       for (int c = i + 1; c < kdone; ++c) s -= H[(size_t)i * m + c] * y[c];
       y[i] = s / H[(size_t)i * m + i];
     }
-    AH_HIP(hipMemcpyAsync(hd, y.data(), kdone * sizeof(double), hipMemcpyHostToDevice, st));
-    if (prm.precision == 0)
-      hipLaunchKernelGGL(k_maxpy<double>, g1(n), dim3(256), 0, st, n, kdone, W.Z, n, hd, x, 1.0);
-    else
-      hipLaunchKernelGGL(k_maxpy<float>, g1(n), dim3(256), 0, st, n, kdone, W.Z32, n, hd, x, 1.0);
-    AH_LAUNCHED();
+    for (int v0 = 0; v0 < kdone; v0 += COMB_MAX) {
+      CombCoef cf;
+      const int kc = std::min(COMB_MAX, kdone - v0);
+      std::copy(y.begin() + v0, y.begin() + v0 + kc, cf.c);
+      if (prm.precision == 0)
+        hipLaunchKernelGGL(k_combine<double>, g1(n), dim3(256), 0, st, n, kc, W.Z + (int64_t)v0 * n, n, cf, x);
+      else
+        hipLaunchKernelGGL(k_combine<float>, g1(n), dim3(256), 0, st, n, kc, W.Z32 + (int64_t)v0 * n, n, cf, x);
+      AH_LAUNCHED();
+    }
     if (status != AH_OK) break;
   }
   AH_HIP(hipStreamSynchronize(st));
@@ -2538,8 +2763,12 @@ extern "C" ah_status air_solve_noalloc(const ah_hier* hc, const double* rhs, dou
   char* base = nullptr;
   AH_TRY(scratch_address(&base));
   carve_workspace(base, n, m, prm->precision, &W);
-  static thread_local double stage[4 * (AH_NOALLOC_MAX_RESTART + 3)];   // pageable host staging
-  W.host = stage;
+  // the thread's pinned staging where it exists (a setup on this thread leaves
+  // it), else a pageable array and copies
+  static thread_local double stage[4 * (AH_NOALLOC_MAX_RESTART + 3)];
+  W.host = pinned_existing(4 * (m + 3) + 1);
+  W.polled = W.host != nullptr;
+  if (!W.host) W.host = stage;
   return solve_forward(h, W, rhs, x, *prm, st, info);
 }
 
