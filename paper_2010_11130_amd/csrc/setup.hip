@@ -61,11 +61,12 @@ __global__ __launch_bounds__(256) void k_strength(int64_t n, const int64_t* __re
 
 // state: 0 undecided, 1 C, 2 F
 __global__ void k_pmis_init(int64_t n, const int32_t* __restrict__ infl, int level, uint64_t* __restrict__ key,
-                            int8_t* __restrict__ state) {
+                            int8_t* __restrict__ state, unsigned long long* __restrict__ nbmax) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   key[i] = ((uint64_t)infl[i] << 44) | hash44((uint64_t)i, level);
   state[i] = infl[i] == 0 ? 2 : 0;
+  nbmax[i] = 0;
 }
 
 // 8 lanes per row for the PMIS phases and the one-point kernel.
@@ -212,10 +213,15 @@ __global__ __launch_bounds__(1024) void k_pmis_wg(int n, const int64_t* __restri
   for (int i = t; i < n; i += NT) state_g[i] = st[i];
 }
 
+// C/F marks and flags; also clears the row counts rcnt[0..n] (where given) and
+// the level's four maxima.
 __global__ void k_cf_flags(int64_t n, const int8_t* __restrict__ state, int8_t* __restrict__ cf,
-                           int32_t* __restrict__ isc) {
+                           int32_t* __restrict__ isc, int32_t* __restrict__ rcnt, int* __restrict__ imax) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
+  if (i < 4) imax[i] = 0;
+  if (i > n) return;
+  if (rcnt) rcnt[i] = 0;
+  if (i == n) return;
   int8_t c = state[i] == 1;
   cf[i] = c;
   isc[i] = c;
@@ -1662,9 +1668,8 @@ static int64_t pmis_list_min() {
 static ah_status pmis_split(int64_t n, const int64_t* rp, const int32_t* ci, const uint8_t* strong,
                             const int32_t* infl, int level, uint64_t* key, unsigned long long* nbmax, int8_t* state,
                             unsigned long long* flags, hipStream_t st) {
-  hipLaunchKernelGGL(k_pmis_init, g1(n), dim3(256), 0, st, n, infl, level, key, state);
+  hipLaunchKernelGGL(k_pmis_init, g1(n), dim3(256), 0, st, n, infl, level, key, state, nbmax);
   AH_HIP(hipGetLastError());
-  AH_HIP(hipMemsetAsync(nbmax, 0, n * sizeof(unsigned long long), st));
   const char* wg_env = std::getenv("AH_PMIS_WG_MAX");   // at most PMIS_WG_MAX (its LDS size)
   const int64_t wg_max = wg_env ? std::min<int64_t>(std::atoll(wg_env), PMIS_WG_MAX) : (int64_t)PMIS_WG_MAX;
   if (n <= wg_max) {
@@ -2673,13 +2678,15 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
     // coarse numbering
     int32_t* isc = nullptr;
     int64_t* cidx = nullptr;
+    int32_t* rcnt = nullptr;
+    const bool d2 = prm.lair_distance == 2;
     CK(ar.get(&L.cf, n));
     CK(tmp.get(&isc, n));
     CK(tmp.get(&cidx, n + 1));
-    hipLaunchKernelGGL(k_cf_flags, g1(n), dim3(256), 0, st, n, state, L.cf, isc);
+    if (!d2) CK(tmp.get(&rcnt, n + 1));
+    hipLaunchKernelGGL(k_cf_flags, g1(n + 4), dim3(256), 0, st, n, state, L.cf, isc, rcnt, d_int);
     CKH(hipGetLastError());
     CK(scan_i32_to_i64(isc, cidx, n, st, tmp));
-    const bool d2 = prm.lair_distance == 2;
     int64_t nc = 0;
     // distance one: the point lists and R's row counts are sized for n, and
     // the C-point count is read back together with R's size (one host sync
@@ -2690,13 +2697,11 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
     }
     const int64_t ncap = d2 ? nc : n;
     // one-point P, lAIR row lengths, R A P candidate bound, F-row statistics
-    int32_t *rcnt = nullptr, *clist = nullptr;
+    int32_t* clist = nullptr;
     CK(ar.get(&L.pcol, n));
-    CK(tmp.get(&rcnt, ncap + 1));
+    if (d2) CK(tmp.get(&rcnt, ncap + 1));
     CK(ar.get(&clist, ncap));
     CK(ar.get(&L.flist, n - (d2 ? nc : 0)));
-    if (!d2) CKH(hipMemsetAsync(rcnt, 0, (n + 1) * sizeof(int32_t), st));
-    CKH(hipMemsetAsync(d_int, 0, 4 * sizeof(int), st));
     // strength of the restriction neighbourhoods (theta_r; the same mask
     // when it equals theta)
     uint8_t* strong_r = strong;
@@ -2734,17 +2739,9 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
     CK(ar.get(&L.Rptr, ncap + 1));
     CK(scan_i32_to_i64(rcnt, L.Rptr, ncap, st, tmp));
     int hmax[4];
-    {
-      double* pin = pinned_scratch(6);
-      if (!pin) { set_error("pinned host allocation failed"); tmp.release(); delete h; return AH_ENOMEM; }
-      CKH(hipMemcpyAsync(pin, L.Rptr + ncap, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-      CKH(hipMemcpyAsync(pin + 1, d_int, sizeof(hmax), hipMemcpyDeviceToHost, st));
-      CKH(hipMemcpyAsync(pin + 3, cidx + n, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-      CKH(hipStreamSynchronize(st));
-      std::memcpy(&L.nnzR, pin, sizeof(int64_t));
-      std::memcpy(hmax, pin + 1, sizeof(hmax));
-      std::memcpy(&nc, pin + 3, sizeof(int64_t));
-    }
+    CK(read_values({{L.Rptr + ncap, &L.nnzR, sizeof(int64_t)},
+                    {d_int, hmax, sizeof(hmax)},
+                    {cidx + n, &nc, sizeof(int64_t)}}, st));
     if (!d2 && (nc == 0 || (double)nc > prm.stall * (double)n)) {
       // coarsening stalled: this level is the coarsest
       L.pcol = nullptr;
@@ -2805,14 +2802,8 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
       hipLaunchKernelGGL(k_max_i32, dim3((unsigned)std::min<int64_t>(cdiv(nc, 256), 256)), dim3(256), 0, st, nc, ccnt,
                          d_int + 3);
       CKH(hipGetLastError());
-      double* pin = pinned_scratch(2);
-      if (!pin) { set_error("pinned host allocation failed"); tmp.release(); delete h; return AH_ENOMEM; }
-      CKH(hipMemcpyAsync(pin, C.rowptr + nc, sizeof(int64_t), hipMemcpyDeviceToHost, st));
-      CKH(hipMemcpyAsync(pin + 1, d_int + 2, 2 * sizeof(int), hipMemcpyDeviceToHost, st));
-      CKH(hipStreamSynchronize(st));
-      std::memcpy(&C.nnz, pin, sizeof(int64_t));
       int e2[2];
-      std::memcpy(e2, pin + 1, sizeof(e2));
+      CK(read_values({{C.rowptr + nc, &C.nnz, sizeof(int64_t)}, {d_int + 2, e2, sizeof(e2)}}, st));
       rmax = e2[1];
       if (blk && e2[0]) {
         set_error("air_setup: rows of a facet block differ in their block AIR neighbourhood");

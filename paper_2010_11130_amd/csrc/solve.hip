@@ -2163,17 +2163,7 @@ static ah_status fgmres_cgs2(ah_hier* h, const KWork& W, Op A, const double* bve
       AH_HIP(hipStreamSynchronize(st));
       return AH_OK;
     }
-    for (unsigned spin = 1; __atomic_load_n(flag, __ATOMIC_ACQUIRE) != seq; ++spin) {
-      __builtin_ia32_pause();
-      if (spin % 65536) continue;
-      // a stream that has stopped will not set the flag any more
-      const hipError_t e = hipStreamQuery(st);
-      (void)hipGetLastError();   // "not ready" is no error of a later launch
-      if (e == hipErrorNotReady || __atomic_load_n(flag, __ATOMIC_ACQUIRE) == seq) continue;
-      set_error("air_solve: %s", e == hipSuccess ? "step result missing" : hipGetErrorString(e));
-      return AH_EHIP;
-    }
-    return AH_OK;
+    return poll_flag(flag, seq, st);
   };
   // ||b||; with x = 0 b is also the first residual
   const bool zero = !prm.x0_given;

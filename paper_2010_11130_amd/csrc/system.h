@@ -2,6 +2,8 @@
 // AIR hierarchy, plus device utilities shared by the kernels.
 #pragma once
 
+#include <initializer_list>
+
 #include "common.h"
 
 struct ah_system {
@@ -52,10 +54,19 @@ ah_status flow_order_build(ah_hier* h, hipStream_t st);
 ah_status scan_i64(const int64_t* in, int64_t* out, int64_t n, hipStream_t st, Arena& tmp);
 // Same for int32 counts producing int64 offsets.
 ah_status scan_i32_to_i64(const int32_t* in, int64_t* out, int64_t n, hipStream_t st, Arena& tmp);
-// Read one int64 / a few bytes from the device through the pinned staging
-// buffer (synchronizes the stream).
+// Read a few small device values (multiples of 4 bytes, at most 64 each) in
+// stream order: one launch stores them into pinned host memory and sets a flag
+// that the host polls, instead of a copy per value and a synchronization.
+struct ReadItem {
+  const void* dev;
+  void* host;
+  size_t bytes;
+};
+ah_status read_values(std::initializer_list<ReadItem> items, hipStream_t st);
 ah_status read_i64(const int64_t* d, int64_t* h, hipStream_t st);
 ah_status read_bytes(const void* d, void* h, size_t bytes, hipStream_t st);
+// Wait until the pinned flag holds seq; AH_EHIP if the stream ends without it.
+ah_status poll_flag(const unsigned long long* flag, unsigned long long seq, hipStream_t st);
 
 constexpr int WAVE = 64;
 
