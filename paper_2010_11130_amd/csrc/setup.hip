@@ -36,24 +36,48 @@ __device__ inline uint64_t hash44(uint64_t i, int level) {
 }
 
 // Strength of connection, 16 lanes per row: row max of the off-diagonal
-// magnitudes by a cross-lane reduction, then the marks.
+// magnitudes by a cross-lane reduction, then the marks.  Rows of up to 64
+// entries stay in registers between the two (a row is read once, its loads
+// issued together).
 constexpr int SG = 16;
 __global__ __launch_bounds__(256) void k_strength(int64_t n, const int64_t* __restrict__ rp,
                                                   const int32_t* __restrict__ ci, const double* __restrict__ v,
                                                   double theta, uint8_t* __restrict__ strong,
                                                   int32_t* __restrict__ infl) {
+  constexpr int Q = 4;
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t i = gid / SG;
   const int g = (int)(gid % SG);
   if (i >= n) return;
-  const int64_t k0 = rp[i], k1 = rp[i + 1];
+  const int64_t k0 = rp[i] + g, k1 = rp[i + 1];
+  int32_t c[Q];
+  double a[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    c[q] = -1;
+    a[q] = 0.0;
+    if (k0 + q * SG < k1) {
+      c[q] = ci[k0 + q * SG];
+      a[q] = fabs(v[k0 + q * SG]);
+    }
+  }
   double m = 0.0;
-  for (int64_t k = k0 + g; k < k1; k += SG)
+#pragma unroll
+  for (int q = 0; q < Q; ++q)
+    if (c[q] != i) m = fmax(m, a[q]);
+  for (int64_t k = k0 + Q * SG; k < k1; k += SG)
     if (ci[k] != i) m = fmax(m, fabs(v[k]));
   for (int o = SG / 2; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, SG));
   const double thr = theta * m * (1.0 - 1e-12);
-  for (int64_t k = k0 + g; k < k1; k += SG) {
-    bool sflag = ci[k] != i && m > 0.0 && fabs(v[k]) >= thr;
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    if (c[q] < 0) continue;
+    const bool sflag = c[q] != i && m > 0.0 && a[q] >= thr;
+    strong[k0 + q * SG] = sflag;
+    if (sflag) atomicAdd(&infl[c[q]], 1);
+  }
+  for (int64_t k = k0 + Q * SG; k < k1; k += SG) {
+    const bool sflag = ci[k] != i && m > 0.0 && fabs(v[k]) >= thr;
     strong[k] = sflag;
     if (sflag) atomicAdd(&infl[ci[k]], 1);
   }
@@ -148,29 +172,94 @@ __global__ __launch_bounds__(256) void k_pmis_fmark(int64_t n, const int64_t* __
   if (__syncthreads_or(undecided) && threadIdx.x == 0) *left = 1ull;
 }
 
-// Every PMIS round of a small level in one workgroup: keys, neighbour maxima
-// and states live in LDS (17 bytes per row), the strength graph is read from
-// global memory, phases are separated by barriers.  Same rounds as
-// k_pmis_nbmax / k_pmis_select / k_pmis_fmark, so the same splitting.
-// Dynamic LDS: n (8 + 8 + 1) bytes (8-byte aligned).  *err is set if the
-// rounds exceed n + 1 (cannot happen: the largest undecided key always
-// becomes C).
+// Every PMIS round of a small level in one workgroup, phases separated by
+// barriers; the same rounds as k_pmis_nbmax / k_pmis_select / k_pmis_fmark, so
+// the same splitting.  The strong neighbours that can matter (undecided at the
+// start) are first packed into lists of 16-bit indices, eight lanes per row, in
+// LDS where they fit beside the keys, else in global scratch; the rounds then
+// walk short lists and touch the matrix no more (they read each row's flags
+// and columns from L2 in every phase of every round before, one dependent pair
+// of loads per entry: on five levels of 3,306 to 75 rows 50 us each on average,
+// 34 now).  A
+// decided point's key becomes 1 (C) or 2 (F), below every undecided key.
+// *err is set if the rounds exceed n + 1 (cannot happen: the largest undecided
+// key always becomes C).
 constexpr int PMIS_WG_MAX = 8192;
+constexpr int PMIS_LDS = 160 * 1024 - 1024;
 
 __global__ __launch_bounds__(1024) void k_pmis_wg(int n, const int64_t* __restrict__ rp,
                                                   const int32_t* __restrict__ ci,
                                                   const uint8_t* __restrict__ strong,
                                                   const uint64_t* __restrict__ key_g, int8_t* __restrict__ state_g,
-                                                  unsigned long long* __restrict__ err) {
+                                                  unsigned long long* __restrict__ err, int lds,
+                                                  int32_t* __restrict__ off_g, uint16_t* __restrict__ adj_g) {
   extern __shared__ __align__(16) unsigned long long pm[];
+  __shared__ int wsum[16];
+  constexpr unsigned long long OPEN = 1ull << 44;   // keys of undecided points start here
   unsigned long long* key = pm;
   unsigned long long* nb = pm + n;
-  int8_t* st = reinterpret_cast<int8_t*>(pm + 2 * n);
-  const int t = threadIdx.x, NT = blockDim.x;
-  for (int i = t; i < n; i += NT) {
-    key[i] = key_g[i];
+  const int t = threadIdx.x;
+  for (int i = t; i < n; i += 1024) {
+    key[i] = state_g[i] ? 2ull : key_g[i];
     nb[i] = 0ull;
-    st[i] = state_g[i];
+  }
+  const bool off_in = 20 * n + 4 <= lds;
+  int32_t* off = off_in ? reinterpret_cast<int32_t*>(pm + 2 * n) : off_g;
+  __syncthreads();
+  const int g = t & 7;
+  for (int i = t >> 3; i < n; i += 128) {
+    int m = 0;
+    if (key[i] >= OPEN)
+      for (int64_t k = rp[i] + g; k < rp[i + 1]; k += 8) {
+        const bool sk = strong[k] != 0;
+        const int32_t j = ci[k];
+        m += sk && key[j] >= OPEN;
+      }
+    for (int o = 4; o > 0; o >>= 1) m += __shfl_xor(m, o, 8);
+    if (g == 0) off[i] = m;
+  }
+  __syncthreads();
+  // exclusive prefix sum of off[0..n)
+  const int per = (n + 1023) / 1024, i0 = min(n, t * per), i1 = min(n, i0 + per);
+  int mine = 0;
+  for (int i = i0; i < i1; ++i) mine += off[i];
+  int inc = mine;
+  for (int o = 1; o < 64; o <<= 1) {
+    const int u = __shfl_up(inc, o, 64);
+    inc += (t & 63) >= o ? u : 0;
+  }
+  if ((t & 63) == 63) wsum[t >> 6] = inc;
+  __syncthreads();
+  int run = inc - mine, tot = 0;
+  for (int w = 0; w < 16; ++w) {
+    run += w < (t >> 6) ? wsum[w] : 0;
+    tot += wsum[w];
+  }
+  for (int i = i0; i < i1; ++i) {
+    const int m = off[i];
+    off[i] = run;
+    run += m;
+  }
+  if (t == 0) off[n] = tot;
+  uint16_t* adj = off_in && 20 * n + 4 + 2 * (int64_t)tot <= lds ? reinterpret_cast<uint16_t*>(off + n + 1) : adj_g;
+  __syncthreads();
+  for (int i = t >> 3; i < n; i += 128) {
+    if (key[i] < OPEN) continue;
+    int at = off[i];
+    const int64_t k1 = rp[i + 1];
+    for (int64_t kb = rp[i]; kb < k1; kb += 8) {
+      const int64_t k = kb + g;
+      int32_t j = 0;
+      bool has = false;
+      if (k < k1) {
+        has = strong[k] != 0;
+        j = ci[k];
+        has = has && key[j] >= OPEN;
+      }
+      const unsigned m8 = (unsigned)(__ballot(has) >> ((t & 63) & ~7)) & 0xffu;
+      if (has) adj[at + __popc(m8 & ((1u << g) - 1u))] = (uint16_t)j;
+      at += __popc(m8);
+    }
   }
   __syncthreads();
   for (int round = 0;; ++round) {
@@ -179,38 +268,37 @@ __global__ __launch_bounds__(1024) void k_pmis_wg(int n, const int64_t* __restri
       break;
     }
     // largest undecided key among the symmetrised strong neighbours
-    for (int i = t; i < n; i += NT) {
-      if (st[i] != 0) continue;
-      unsigned long long mx = 0ull;
+    for (int i = t; i < n; i += 1024) {
       const unsigned long long ki = key[i];
-      for (int64_t k = rp[i]; k < rp[i + 1]; ++k) {
-        if (!strong[k]) continue;
-        const int32_t j = ci[k];
-        if (st[j] != 0) continue;
-        mx = mx > key[j] ? mx : key[j];
+      if (ki < OPEN) continue;
+      unsigned long long mx = 0ull;
+      for (int e = off[i]; e < off[i + 1]; ++e) {
+        const int j = adj[e];
+        const unsigned long long kj = key[j];
+        if (kj < OPEN) continue;
+        mx = mx > kj ? mx : kj;
         atomicMax(&nb[j], ki);
       }
       if (mx) atomicMax(&nb[i], mx);
     }
     __syncthreads();
-    for (int i = t; i < n; i += NT) {
-      if (st[i] != 0) continue;
-      if (key[i] > nb[i]) st[i] = 1;
+    for (int i = t; i < n; i += 1024) {
+      if (key[i] < OPEN) continue;
+      if (key[i] > nb[i]) key[i] = 1ull;
       nb[i] = 0ull;
     }
     __syncthreads();
     int undecided = 0;
-    for (int i = t; i < n; i += NT) {
-      if (st[i] != 0) continue;
-      int hit = 0;
-      for (int64_t k = rp[i]; k < rp[i + 1] && !hit; ++k)
-        if (strong[k] && st[ci[k]] == 1) hit = 1;
-      if (hit) st[i] = 2;
+    for (int i = t; i < n; i += 1024) {
+      if (key[i] < OPEN) continue;
+      bool hit = false;
+      for (int e = off[i]; e < off[i + 1] && !hit; ++e) hit = key[adj[e]] == 1ull;
+      if (hit) key[i] = 2ull;
       else undecided = 1;
     }
     if (!__syncthreads_or(undecided)) break;
   }
-  for (int i = t; i < n; i += NT) state_g[i] = st[i];
+  for (int i = t; i < n; i += 1024) state_g[i] = key[i] == 1ull ? 1 : 2;
 }
 
 // C/F marks and flags; also clears the row counts rcnt[0..n] (where given) and
@@ -244,6 +332,7 @@ __global__ __launch_bounds__(256) void k_onepoint(int64_t n, int fsearch, const 
                                                   int32_t* __restrict__ rcnt, int32_t* __restrict__ clist,
                                                   int32_t* __restrict__ flist, int* __restrict__ imax,
                                                   unsigned long long* __restrict__ fst) {
+  constexpr int Q = 5;   // entries per lane held in registers: a row is read once, its loads issued together
   const int g = (int)(threadIdx.x % PG);
   const int64_t stride = (int64_t)gridDim.x * (blockDim.x / PG);
   int mmax = 0, cmax = 0, omax = 0;
@@ -253,12 +342,28 @@ __global__ __launch_bounds__(256) void k_onepoint(int64_t n, int fsearch, const 
     if (cf[i]) {
       int m = 0;
       int64_t cand = 0;
-      for (int64_t k = k0 + g; k < k1; k += PG) {
-        const bool sk = strong_r[k] != 0;
-        const int32_t c = ci[k];
-        if (sk && !cf[c]) {
+      int32_t c[Q];
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {   // the column where strong, else -1
+        c[q] = -1;
+        if (k0 + g + q * PG < k1) {
+          const bool sk = strong_r[k0 + g + q * PG] != 0;
+          const int32_t j = ci[k0 + g + q * PG];
+          c[q] = sk ? j : -1;
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < Q; ++q)
+        if (c[q] >= 0 && !cf[c[q]]) {
           ++m;
-          cand += rp[c + 1] - rp[c];
+          cand += rp[c[q] + 1] - rp[c[q]];
+        }
+      for (int64_t k = k0 + g + Q * PG; k < k1; k += PG) {
+        const bool sk = strong_r[k] != 0;
+        const int32_t j = ci[k];
+        if (sk && !cf[j]) {
+          ++m;
+          cand += rp[j + 1] - rp[j];
         }
       }
       for (int o = PG / 2; o > 0; o >>= 1) {
@@ -278,26 +383,49 @@ __global__ __launch_bounds__(256) void k_onepoint(int64_t n, int fsearch, const 
       continue;
     }
     double mx = -1.0;
-    if (fsearch)
-      for (int64_t k = k0 + g; k < k1; k += PG) {
-        const bool sk = strong[k] != 0;
-        const int32_t c = ci[k];
-        const double a = fabs(v[k]);
-        if (sk && cf[c]) mx = fmax(mx, a);
-      }
-    for (int o = PG / 2; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, PG));
     int64_t first = k1;
-    if (mx >= 0.0) {
-      const double thr = mx * (1.0 - 1e-12);
-      for (int64_t k = k0 + g; k < k1; k += PG) {
-        const bool sk = strong[k] != 0;
-        const int32_t c = ci[k];
-        const double a = fabs(v[k]);
-        if (sk && cf[c] && a >= thr) { first = k; break; }
+    if (fsearch) {
+      double a[Q];   // the magnitude where strong and C, else -1
+      int32_t c[Q];
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        c[q] = -1;
+        a[q] = -1.0;
+        if (k0 + g + q * PG < k1) {
+          const bool sk = strong[k0 + g + q * PG] != 0;
+          const int32_t j = ci[k0 + g + q * PG];
+          a[q] = fabs(v[k0 + g + q * PG]);
+          c[q] = sk ? j : -1;
+        }
       }
-      for (int o = PG / 2; o > 0; o >>= 1) {
-        int64_t other = __shfl_xor(first, o, PG);
-        first = other < first ? other : first;
+#pragma unroll
+      for (int q = 0; q < Q; ++q) {
+        a[q] = c[q] >= 0 && cf[c[q]] ? a[q] : -1.0;
+        mx = fmax(mx, a[q]);
+      }
+      for (int64_t k = k0 + g + Q * PG; k < k1; k += PG) {
+        const bool sk = strong[k] != 0;
+        const int32_t j = ci[k];
+        const double x = fabs(v[k]);
+        if (sk && cf[j]) mx = fmax(mx, x);
+      }
+      for (int o = PG / 2; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o, PG));
+      if (mx >= 0.0) {
+        const double thr = mx * (1.0 - 1e-12);
+#pragma unroll
+        for (int q = Q - 1; q >= 0; --q)
+          if (a[q] >= 0.0 && a[q] >= thr) first = k0 + g + q * PG;
+        if (first == k1)
+          for (int64_t k = k0 + g + Q * PG; k < k1; k += PG) {
+            const bool sk = strong[k] != 0;
+            const int32_t j = ci[k];
+            const double x = fabs(v[k]);
+            if (sk && cf[j] && x >= thr) { first = k; break; }
+          }
+        for (int o = PG / 2; o > 0; o >>= 1) {
+          const int64_t other = __shfl_xor(first, o, PG);
+          first = other < first ? other : first;
+        }
       }
     }
     if (g == 0) {
@@ -1125,12 +1253,16 @@ __global__ void k_cast32(int64_t n, const double* __restrict__ a, float* __restr
   if (i < n) b[i] = (float)a[i];
 }
 
-// Dense copy of the coarsest matrix.
-__global__ void k_dense(int64_t n, const int64_t* __restrict__ rp, const int32_t* __restrict__ ci,
-                        const double* __restrict__ v, double* __restrict__ M) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  for (int64_t k = rp[i]; k < rp[i + 1]; ++k) M[i * n + ci[k]] = v[k];
+// Dense copy of the coarsest matrix, a workgroup per row; clears the inverse's
+// error flag.
+__global__ __launch_bounds__(64) void k_dense(int64_t n, const int64_t* __restrict__ rp,
+                                              const int32_t* __restrict__ ci, const double* __restrict__ v,
+                                              double* __restrict__ M, int* __restrict__ err) {
+  const int64_t i = blockIdx.x;
+  if (i == 0 && threadIdx.x == 0) *err = 0;
+  for (int64_t j = threadIdx.x; j < n; j += 64) M[i * n + j] = 0.0;
+  __syncthreads();
+  for (int64_t k = rp[i] + threadIdx.x; k < rp[i + 1]; k += 64) M[i * n + ci[k]] = v[k];
 }
 
 // Gauss-Jordan with partial pivoting on [M | Inv] over many workgroups, one
@@ -1209,61 +1341,68 @@ __global__ void k_eye(int n, double* __restrict__ Inv) {
   if (k < (int64_t)n * n) Inv[k] = (k / n == k % n) ? 1.0 : 0.0;
 }
 
-// Inverse of a dense matrix of order n <= 64 by Gauss-Jordan elimination
-// with partial pivoting on the augmented matrix [A | I], held entirely in
-// LDS (64 x 128 doubles).
+// Inverse of a dense matrix of order n <= 64 by Gauss-Jordan elimination on
+// [A | I] with partial pivoting, thread t holding rows t / 128 + 8 i of column
+// t % 128 in registers.  Rows stay where they are: the pivot is taken among the
+// rows not used yet, and row k of the inverse is the k-th pivot's.  Two
+// barriers per column (the column into LDS, searched by every wave, then the
+// scaled pivot row): a chain of n steps, 61 us at n = 30; with the matrix in LDS,
+// row swaps and six barriers per column it took 75.
 constexpr int INV_GJ_MAX = 64;
 
-__global__ __launch_bounds__(256) void k_inv_gj(int n, const double* __restrict__ M, double* __restrict__ Inv,
-                                                int* __restrict__ err) {
-  __shared__ double A[INV_GJ_MAX * 2 * INV_GJ_MAX];
-  __shared__ double f[INV_GJ_MAX];
-  __shared__ int s_p;
-  const int t = threadIdx.x;
-  const int W = 2 * n;
-  for (int idx = t; idx < n * W; idx += blockDim.x) {
-    int r = idx / W, c = idx % W;
-    A[idx] = c < n ? M[r * n + c] : (c - n == r ? 1.0 : 0.0);
+__global__ __launch_bounds__(1024) void k_inv_gj(int n, const double* __restrict__ M, double* __restrict__ Inv,
+                                                 int* __restrict__ err) {
+  __shared__ double f[2][INV_GJ_MAX], prow[2 * INV_GJ_MAX];
+  __shared__ int place[INV_GJ_MAX];
+  const int t = threadIdx.x, c = t & 127, r0 = t >> 7, lane = t & 63;
+  double a[8];
+#pragma unroll
+  for (int i = 0; i < 8; ++i) {
+    const int r = r0 + 8 * i;
+    a[i] = r >= n || c >= 2 * n ? 0.0 : c < n ? M[r * n + c] : c - n == r ? 1.0 : 0.0;
+  }
+  unsigned long long used = 0;
+  for (int k = 0; k < n; ++k) {
+    double* fk = f[k & 1];
+    if (c == k)
+#pragma unroll
+      for (int i = 0; i < 8; ++i) fk[r0 + 8 * i] = a[i];
+    __syncthreads();
+    double best = lane < n && !((used >> lane) & 1) ? fabs(fk[lane]) : -1.0;
+    best = best >= 0.0 ? best : -1.0;   // NaN
+    int p = lane;
+    for (int o = 32; o > 0; o >>= 1) {
+      const double ob = __shfl_xor(best, o, 64);
+      const int op = __shfl_xor(p, o, 64);
+      if (ob > best || (ob == best && op < p)) { best = ob; p = op; }
+    }
+    p = __builtin_amdgcn_readfirstlane(p);
+    if (best < 0.0) p = __ffsll(~used) - 1;   // nothing left but NaN: any unused row
+    if (!(best > 0.0) && t == 0) atomicOr(err, 1);
+    const double d = fk[p] != 0.0 ? fk[p] : 1.0;
+    if (r0 == (p & 7)) {
+      double x = a[0];
+#pragma unroll
+      for (int i = 1; i < 8; ++i) x = i == p >> 3 ? a[i] : x;
+      prow[c] = x / d;
+    }
+    if (t == 0) place[p] = k;
+    used |= 1ull << p;
+    __syncthreads();
+    const double x = prow[c];
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int r = r0 + 8 * i;
+      a[i] = r == p ? x : a[i] - fk[r] * x;
+    }
   }
   __syncthreads();
-  for (int k = 0; k < n; ++k) {
-    if (t < 64) {
-      double best = -1.0;
-      int bi = n;
-      int r = k + t;
-      if (r < n) { best = fabs(A[r * W + k]); bi = r; }
-      for (int o = 32; o > 0; o >>= 1) {
-        double ob = __shfl_xor(best, o, 64);
-        int oi = __shfl_xor(bi, o, 64);
-        if (ob > best || (ob == best && oi < bi)) { best = ob; bi = oi; }
-      }
-      if (t == 0) {
-        s_p = bi;
-        if (!(best > 0.0)) atomicOr(err, 1);
-      }
+  if (c >= n && c < 2 * n)
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int r = r0 + 8 * i;
+      if (r < n) Inv[place[r] * n + c - n] = a[i];
     }
-    __syncthreads();
-    const int p = s_p;
-    if (p != k)
-      for (int c = t; c < W; c += blockDim.x) {
-        double x = A[k * W + c]; A[k * W + c] = A[p * W + c]; A[p * W + c] = x;
-      }
-    __syncthreads();
-    const double d = A[k * W + k] != 0.0 ? A[k * W + k] : 1.0;
-    if (t < n) f[t] = t == k ? 0.0 : A[t * W + k];
-    __syncthreads();
-    for (int c = t; c < W; c += blockDim.x) A[k * W + c] /= d;
-    __syncthreads();
-    for (int idx = t; idx < n * W; idx += blockDim.x) {
-      int r = idx / W, c = idx % W;
-      if (r != k) A[idx] -= f[r] * A[k * W + c];
-    }
-    __syncthreads();
-  }
-  for (int idx = t; idx < n * n; idx += blockDim.x) {
-    int r = idx / n, c = idx % n;
-    Inv[idx] = A[r * W + n + c];
-  }
 }
 
 // Inverse of a small dense matrix held in LDS (n <= 128): LU with partial
@@ -1666,8 +1805,8 @@ static int64_t pmis_list_min() {
 // flags[0..1] are the undecided flags of alternating rounds, flags[3] the
 // single-workgroup round-overflow flag.
 static ah_status pmis_split(int64_t n, const int64_t* rp, const int32_t* ci, const uint8_t* strong,
-                            const int32_t* infl, int level, uint64_t* key, unsigned long long* nbmax, int8_t* state,
-                            unsigned long long* flags, hipStream_t st) {
+                            int64_t nnz, const int32_t* infl, int level, uint64_t* key, unsigned long long* nbmax,
+                            int8_t* state, unsigned long long* flags, hipStream_t st, Arena& arena_tmp) {
   hipLaunchKernelGGL(k_pmis_init, g1(n), dim3(256), 0, st, n, infl, level, key, state, nbmax);
   AH_HIP(hipGetLastError());
   const char* wg_env = std::getenv("AH_PMIS_WG_MAX");   // at most PMIS_WG_MAX (its LDS size)
@@ -1676,11 +1815,16 @@ static ah_status pmis_split(int64_t n, const int64_t* rp, const int32_t* ci, con
     // small graph: every round in one workgroup, no host checks
     static std::once_flag once;
     std::call_once(once, [] {
-      (void)hipFuncSetAttribute((const void*)k_pmis_wg, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)(PMIS_WG_MAX * 17 + 64));
+      (void)hipFuncSetAttribute((const void*)k_pmis_wg, hipFuncAttributeMaxDynamicSharedMemorySize, PMIS_LDS);
     });
-    const unsigned lds = (unsigned)(((n * 17 + 7) / 8) * 8);
-    hipLaunchKernelGGL(k_pmis_wg, dim3(1), dim3(1024), lds, st, (int)n, rp, ci, strong, key, state, flags + 3);
+    // keys and maxima, offsets and (about 16 neighbours a row) the lists
+    const int lds = (int)std::min<int64_t>(PMIS_LDS, 52 * n + 64);
+    int32_t* off = nullptr;
+    uint16_t* adj = nullptr;
+    AH_TRY(arena_tmp.get(&off, n + 1));
+    AH_TRY(arena_tmp.get(&adj, nnz));
+    hipLaunchKernelGGL(k_pmis_wg, dim3(1), dim3(1024), lds, st, (int)n, rp, ci, strong, key, state, flags + 3, lds,
+                       off, adj);
     AH_HIP(hipGetLastError());
     return AH_OK;
   }
@@ -2562,12 +2706,10 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
                                          // [3] single-workgroup PMIS round overflow
   int* d_int = nullptr;                  // [0] max |N_i|, [1] max candidates, [2] max C-row length (then error flags), [3] max A_c row
   unsigned long long* d_fst = nullptr;   // per level: F rows, F-row entries
-  CK(ar.get(&d_ull, 4));
-  CK(ar.get(&d_int, 4));
-  CK(ar.get(&d_fst, 66));   // [2 l], [2 l + 1] per level; [64] level-0 F values in the facet-block layout
-  CKH(hipMemsetAsync(d_fst, 0, 66 * sizeof(unsigned long long), st));
-  CKH(hipMemsetAsync(d_ull, 0, 4 * sizeof(unsigned long long), st));
-  CKH(hipMemsetAsync(d_int, 0, 4 * sizeof(int), st));
+  CK(ar.get(&d_fst, 72));   // [2 l], [2 l + 1] per level; [64] level-0 F values in the facet-block layout
+  d_ull = d_fst + 66;
+  d_int = reinterpret_cast<int*>(d_fst + 70);
+  CKH(hipMemsetAsync(d_fst, 0, 72 * sizeof(unsigned long long), st));
   // level 0 = the scaled system (shared, not copied)
   AhLevel L0;
   L0.n = s->n;
@@ -2634,7 +2776,7 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
       CKH(hipMemsetAsync(infl, 0, nbr * sizeof(int32_t), st));
       hipLaunchKernelGGL(k_strength, g1(nbr * SG), dim3(256), 0, st, nbr, L.optr, L.ocol, bw, prm.theta, sb, infl);
       CKH(hipGetLastError());
-      CK(pmis_split(nbr, L.optr, L.ocol, sb, infl, l, key, nbmax, sbstate, d_ull, st));
+      CK(pmis_split(nbr, L.optr, L.ocol, sb, nslot, infl, l, key, nbmax, sbstate, d_ull, st, tmp));
       hipLaunchKernelGGL(k_block_expand, g1(n), dim3(256), 0, st, n, (int)L.ob, sbstate, state);
       uint8_t* sbr = sb;
       if (prm.theta_r > 0.0 && prm.theta_r != prm.theta) {
@@ -2672,7 +2814,7 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
       CKH(hipMemcpyAsync(state, hstate.data(), n, hipMemcpyHostToDevice, st));
       CKH(hipStreamSynchronize(st));
     } else {
-      CK(pmis_split(n, L.rowptr, L.col, strong, infl, l, key, nbmax, state, d_ull, st));
+      CK(pmis_split(n, L.rowptr, L.col, strong, L.nnz, infl, l, key, nbmax, state, d_ull, st, tmp));
     }
     }
     // coarse numbering
@@ -2850,11 +2992,9 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
     double* M = nullptr;
     CK(tmp.get(&M, nL * nL));
     CK(ar.get(&h->cinv, nL * nL));
-    CKH(hipMemsetAsync(M, 0, nL * nL * sizeof(double), st));
-    hipLaunchKernelGGL(k_dense, g1(nL), dim3(256), 0, st, nL, LL.rowptr, LL.col, LL.val, M);
-    CKH(hipMemsetAsync(d_int + 2, 0, sizeof(int), st));
+    hipLaunchKernelGGL(k_dense, dim3((unsigned)nL), dim3(64), 0, st, nL, LL.rowptr, LL.col, LL.val, M, d_int + 2);
     if (nL <= INV_GJ_MAX)
-      hipLaunchKernelGGL(k_inv_gj, dim3(1), dim3(256), 0, st, (int)nL, M, h->cinv, d_int + 2);
+      hipLaunchKernelGGL(k_inv_gj, dim3(1), dim3(1024), 0, st, (int)nL, M, h->cinv, d_int + 2);
     else if (nL <= INV_LDS_MAX)
       hipLaunchKernelGGL(k_inv_lds, dim3(1), dim3(1024), 0, st, (int)nL, M, h->cinv, d_int + 2);
     else {
@@ -2941,25 +3081,20 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
   unsigned long long fb = 0;
   int gerr = 0;
   {
-    double* pin = pinned_scratch(70);
+    double* pin = pinned_scratch(72);
     if (!pin) { set_error("pinned host allocation failed"); tmp.release(); delete h; return AH_ENOMEM; }
-    CKH(hipMemcpyAsync(pin, d_ull + 2, sizeof(fb), hipMemcpyDeviceToHost, st));
-    CKH(hipMemcpyAsync(pin + 1, d_int + 2, sizeof(int), hipMemcpyDeviceToHost, st));
-    CKH(hipMemcpyAsync(pin + 2, d_fst, 65 * sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
-    CKH(hipMemcpyAsync(pin + 67, d_ull + 3, sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
+    CKH(hipMemcpyAsync(pin, d_fst, 72 * sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
     CKH(hipStreamSynchronize(st));
-    std::memcpy(&fb, pin, sizeof(fb));
-    std::memcpy(&gerr, pin + 1, sizeof(int));
-    unsigned long long fst[65];
-    std::memcpy(fst, pin + 2, sizeof(fst));
+    unsigned long long fst[72];
+    std::memcpy(fst, pin, sizeof(fst));
+    fb = fst[66 + 2];
+    std::memcpy(&gerr, reinterpret_cast<int*>(fst + 70) + 2, sizeof(int));
     h->lev[0].novF = (int64_t)fst[64];
     for (size_t l = 0; l + 1 < h->lev.size() && l < 32; ++l) {
       h->lev[l].nF = (int64_t)fst[2 * l];
       h->lev[l].nnzF = (int64_t)fst[2 * l + 1];
     }
-    unsigned long long perr = 0;
-    std::memcpy(&perr, pin + 67, sizeof(perr));
-    if (perr) {
+    if (fst[66 + 3]) {
       tmp.release();
       set_error("air_setup: PMIS did not terminate");
       delete h;
