@@ -38,18 +38,21 @@ __device__ inline uint64_t hash44(uint64_t i, int level) {
 // Strength of connection, 16 lanes per row: row max of the off-diagonal
 // magnitudes by a cross-lane reduction, then the marks.  Rows of up to 64
 // entries stay in registers between the two (a row is read once, its loads
-// issued together).
+// issued together).  Where infl is given (for the coarsening), also counts the
+// rows that depend on each point and packs the row's strong columns at
+// adj[rp[i]], na[i] of them: the coarsening then reads those only.
 constexpr int SG = 16;
 __global__ __launch_bounds__(256) void k_strength(int64_t n, const int64_t* __restrict__ rp,
                                                   const int32_t* __restrict__ ci, const double* __restrict__ v,
                                                   double theta, uint8_t* __restrict__ strong,
-                                                  int32_t* __restrict__ infl) {
+                                                  int32_t* __restrict__ infl, int32_t* __restrict__ adj,
+                                                  int32_t* __restrict__ na) {
   constexpr int Q = 4;
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t i = gid / SG;
   const int g = (int)(gid % SG);
   if (i >= n) return;
-  const int64_t k0 = rp[i] + g, k1 = rp[i + 1];
+  const int64_t kr = rp[i], k1 = rp[i + 1], k0 = kr + g;
   int32_t c[Q];
   double a[Q];
 #pragma unroll
@@ -69,154 +72,169 @@ __global__ __launch_bounds__(256) void k_strength(int64_t n, const int64_t* __re
     if (ci[k] != i) m = fmax(m, fabs(v[k]));
   for (int o = SG / 2; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, SG));
   const double thr = theta * m * (1.0 - 1e-12);
+  const int sh = (threadIdx.x & 63) & ~(SG - 1);
+  int at = 0;
+  const auto mark = [&](int64_t k, int32_t col, bool here, bool sflag) {
+    if (here) strong[k] = sflag;
+    if (!infl) return;
+    const unsigned mk = (unsigned)(__ballot(sflag) >> sh) & ((1u << SG) - 1u);
+    if (sflag) {
+      atomicAdd(&infl[col], 1);
+      adj[kr + at + __popc(mk & ((1u << g) - 1u))] = col;
+    }
+    at += __popc(mk);
+  };
 #pragma unroll
-  for (int q = 0; q < Q; ++q) {
-    if (c[q] < 0) continue;
-    const bool sflag = c[q] != i && m > 0.0 && a[q] >= thr;
-    strong[k0 + q * SG] = sflag;
-    if (sflag) atomicAdd(&infl[c[q]], 1);
+  for (int q = 0; q < Q; ++q)
+    if (kr + q * SG < k1) mark(k0 + q * SG, c[q], c[q] >= 0, c[q] >= 0 && c[q] != i && m > 0.0 && a[q] >= thr);
+  for (int64_t kb = kr + Q * SG; kb < k1; kb += SG) {
+    const int64_t k = kb + g;
+    int32_t col = -1;
+    double x = 0.0;
+    if (k < k1) {
+      col = ci[k];
+      x = fabs(v[k]);
+    }
+    mark(k, col, col >= 0, col >= 0 && col != i && m > 0.0 && x >= thr);
   }
-  for (int64_t k = k0 + Q * SG; k < k1; k += SG) {
-    const bool sflag = ci[k] != i && m > 0.0 && fabs(v[k]) >= thr;
-    strong[k] = sflag;
-    if (sflag) atomicAdd(&infl[ci[k]], 1);
-  }
+  if (infl && g == 0) na[i] = at;
 }
 
-// state: 0 undecided, 1 C, 2 F
+// state: 0 undecided, 1 C, 2 F; clears both rounds' beaten marks.
 __global__ void k_pmis_init(int64_t n, const int32_t* __restrict__ infl, int level, uint64_t* __restrict__ key,
-                            int8_t* __restrict__ state, unsigned long long* __restrict__ nbmax) {
+                            int8_t* __restrict__ state, uint8_t* __restrict__ beaten) {
   int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i >= n) return;
   key[i] = ((uint64_t)infl[i] << 44) | hash44((uint64_t)i, level);
   state[i] = infl[i] == 0 ? 2 : 0;
-  nbmax[i] = 0;
+  beaten[i] = 0;
+  beaten[n + i] = 0;
 }
 
 // 8 lanes per row for the PMIS phases and the one-point kernel.
 constexpr int PG = 8;
 
+// A PMIS round is two kernels.  The first marks the undecided points that an
+// undecided strong neighbour (of the symmetrised graph) equals or beats; the
+// second turns the others into C points and the marked points with a new strong
+// C neighbour into F points.  The second reads states that it also writes, which
+// is safe: an unmarked undecided point counts as C whether its state has changed
+// yet or not, and a marked one does not in either case.  Marks are plain stores
+// of one (two sets, a round's second kernel clears the points of the next set),
+// so no point needs its neighbours' largest key: with a maximum by atomics, the
+// selection in a kernel of its own and the flags of the whole rows read each
+// time, the rounds of 342,528 rows (24 on three levels) took 460 us, 254 now.
+//
 // The round kernels visit rows 0 .. n-1, or the rows list[0 .. n-1] (the
 // points still undecided when the list was made; points only leave that
 // state, so the rows outside the list are no-ops of the round); with nd,
 // the list's length is *nd (at most n, the bound the grid was sized for).
-__global__ __launch_bounds__(256) void k_pmis_nbmax(int64_t n, const int64_t* __restrict__ rp,
-                                                    const int32_t* __restrict__ ci,
-                                                    const uint8_t* __restrict__ strong,
-                                                    const uint64_t* __restrict__ key, const int8_t* __restrict__ state,
-                                                    unsigned long long* __restrict__ nbmax,
-                                                    const int32_t* __restrict__ list, const int64_t* __restrict__ nd) {
+__global__ __launch_bounds__(256) void k_pmis_beat(int64_t n, const int64_t* __restrict__ rp,
+                                                   const int32_t* __restrict__ adj, const int32_t* __restrict__ na,
+                                                   const uint64_t* __restrict__ key, const int8_t* __restrict__ state,
+                                                   uint8_t* __restrict__ beaten, unsigned long long* __restrict__ left,
+                                                   const int32_t* __restrict__ list, const int64_t* __restrict__ nd) {
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t ii = gid / PG;
   const int g = (int)(gid % PG);
+  if (gid == 0) *left = 0;
   if (nd) n = *nd;
   if (ii >= n) return;
   const int64_t i = list ? (int64_t)list[ii] : ii;
+  const int m = na[i];
+  const int64_t k0 = rp[i];
+  const uint64_t ki = key[i];
   if (state[i] != 0) return;
-  unsigned long long mx = 0, ki = key[i];
-  for (int64_t k = rp[i] + g; k < rp[i + 1]; k += PG) {
-    // the flag and the column together (no branch between the two loads)
-    const bool sk = strong[k] != 0;
-    const int32_t j = ci[k];
-    if (!sk) continue;
+  int lost = 0;
+  for (int k = g; k < m; k += PG) {
+    const int32_t j = adj[k0 + k];
+    const uint64_t kj = key[j];
     if (state[j] != 0) continue;
-    mx = mx > key[j] ? mx : key[j];
-    atomicMax(&nbmax[j], ki);      // i depends on j: i is a neighbour of j as well
+    if (kj >= ki) lost = 1;
+    if (ki >= kj) beaten[j] = 1;      // i depends on j: i is a neighbour of j as well
   }
-  for (int o = PG / 2; o > 0; o >>= 1) {
-    unsigned long long other = __shfl_xor(mx, o, PG);
-    mx = mx > other ? mx : other;
-  }
-  if (g == 0 && mx) atomicMax(&nbmax[i], mx);
+  if (lost) beaten[i] = 1;
 }
 
-// New C points: undecided points whose key beats every undecided neighbour.
-// nbmax is reset for the next round (only undecided points carry a value),
-// and the round's undecided flag is cleared.
-__global__ void k_pmis_select(int64_t n, const uint64_t* __restrict__ key, unsigned long long* __restrict__ nbmax,
-                              int8_t* __restrict__ state, unsigned long long* __restrict__ left,
-                              const int32_t* __restrict__ list, const int64_t* __restrict__ nd) {
-  const int64_t ii = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (ii == 0) *left = 0;
-  if (nd) n = *nd;
-  if (ii >= n) return;
-  const int64_t i = list ? (int64_t)list[ii] : ii;
-  if (state[i] != 0) return;
-  if (key[i] > nbmax[i]) state[i] = 1;
-  nbmax[i] = 0;
-}
-
-// Undecided points with a strong C neighbour become F. The kernels with a
-// per-launch result use a capped grid (grid-stride over rows) and one
-// global write per block: a write per wave to one address serializes.
-__global__ __launch_bounds__(256) void k_pmis_fmark(int64_t n, const int64_t* __restrict__ rp,
-                                                    const int32_t* __restrict__ ci,
-                                                    const uint8_t* __restrict__ strong, int8_t* __restrict__ state,
-                                                    unsigned long long* __restrict__ left,
-                                                    const int32_t* __restrict__ list,
-                                                    const int64_t* __restrict__ nd) {
+// The kernels with a per-launch result use a capped grid (grid-stride over
+// rows) and one global write per block: a write per wave to one address
+// serializes.
+__global__ __launch_bounds__(256) void k_pmis_mark(int64_t n, const int64_t* __restrict__ rp,
+                                                   const int32_t* __restrict__ adj, const int32_t* __restrict__ na,
+                                                   int8_t* __restrict__ state, const uint8_t* __restrict__ beaten,
+                                                   uint8_t* __restrict__ beaten_next,
+                                                   unsigned long long* __restrict__ left,
+                                                   const int32_t* __restrict__ list, const int64_t* __restrict__ nd) {
   const int g = (int)(threadIdx.x % PG);
   const int64_t stride = (int64_t)gridDim.x * (blockDim.x / PG);
   int undecided = 0;
   if (nd) n = *nd;
   for (int64_t ii = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / PG; ii < n; ii += stride) {
     const int64_t i = list ? (int64_t)list[ii] : ii;
+    const int m = na[i];
+    const int64_t k0 = rp[i];
+    const uint8_t bi = beaten[i];
     if (state[i] != 0) continue;
     int hit = 0;
-    for (int64_t k = rp[i] + g; k < rp[i + 1]; k += PG)
-      if (strong[k] && state[ci[k]] == 1) hit = 1;
+    if (bi)
+      for (int k = g; k < m; k += PG) {
+        const int32_t j = adj[k0 + k];
+        const uint8_t bj = beaten[j];
+        const int8_t sj = state[j];
+        if (sj == 1 || (sj == 0 && !bj)) hit = 1;
+      }
     for (int o = PG / 2; o > 0; o >>= 1) hit |= __shfl_xor(hit, o, PG);
-    if (!hit) undecided = 1;
-    else if (g == 0) state[i] = 2;
+    if (g == 0) {
+      beaten_next[i] = 0;
+      if (!bi) state[i] = 1;
+      else if (hit) state[i] = 2;
+    }
+    if (bi && !hit) undecided = 1;
   }
   if (__syncthreads_or(undecided) && threadIdx.x == 0) *left = 1ull;
 }
 
 // Every PMIS round of a small level in one workgroup, phases separated by
-// barriers; the same rounds as k_pmis_nbmax / k_pmis_select / k_pmis_fmark, so
-// the same splitting.  The strong neighbours that can matter (undecided at the
-// start) are first packed into lists of 16-bit indices, eight lanes per row, in
-// LDS where they fit beside the keys, else in global scratch; the rounds then
-// walk short lists and touch the matrix no more (they read each row's flags
-// and columns from L2 in every phase of every round before, one dependent pair
-// of loads per entry: on five levels of 3,306 to 75 rows 50 us each on average,
-// 34 now).  A
-// decided point's key becomes 1 (C) or 2 (F), below every undecided key.
+// barriers; the same rounds as k_pmis_beat / k_pmis_mark, so the same splitting.
+// Keys, marks and the lists of strong columns (16 bits each) are copied to LDS
+// first, lists too long for it stay in global memory.  A thread owns the rows
+// threadIdx.x + 1024 q.  A decided point's key becomes 1 (C) or 2 (F), below
+// every undecided key.  The
+// rounds wait on LDS and barriers: 64 us at 5,253 rows, 82 at 3,914 (128 and 176
+// with maxima by atomics and the lists packed here from the rows' flags).
 // *err is set if the rounds exceed n + 1 (cannot happen: the largest undecided
 // key always becomes C).
 constexpr int PMIS_WG_MAX = 8192;
 constexpr int PMIS_LDS = 160 * 1024 - 1024;
 
 __global__ __launch_bounds__(1024) void k_pmis_wg(int n, const int64_t* __restrict__ rp,
-                                                  const int32_t* __restrict__ ci,
-                                                  const uint8_t* __restrict__ strong,
+                                                  const int32_t* __restrict__ adj_g, const int32_t* __restrict__ na,
                                                   const uint64_t* __restrict__ key_g, int8_t* __restrict__ state_g,
-                                                  unsigned long long* __restrict__ err, int lds,
-                                                  int32_t* __restrict__ off_g, uint16_t* __restrict__ adj_g) {
+                                                  unsigned long long* __restrict__ err, int lds) {
   extern __shared__ __align__(16) unsigned long long pm[];
   __shared__ int wsum[16];
   constexpr unsigned long long OPEN = 1ull << 44;   // keys of undecided points start here
+  constexpr int Q = PMIS_WG_MAX / 1024;
   unsigned long long* key = pm;
-  unsigned long long* nb = pm + n;
+  int32_t* off = reinterpret_cast<int32_t*>(pm + n);            // [n + 1]
+  uint16_t* adj = reinterpret_cast<uint16_t*>(off + n + 1);
   const int t = threadIdx.x;
-  for (int i = t; i < n; i += 1024) {
-    key[i] = state_g[i] ? 2ull : key_g[i];
-    nb[i] = 0ull;
-  }
-  const bool off_in = 20 * n + 4 <= lds;
-  int32_t* off = off_in ? reinterpret_cast<int32_t*>(pm + 2 * n) : off_g;
-  __syncthreads();
-  const int g = t & 7;
-  for (int i = t >> 3; i < n; i += 128) {
-    int m = 0;
-    if (key[i] >= OPEN)
-      for (int64_t k = rp[i] + g; k < rp[i + 1]; k += 8) {
-        const bool sk = strong[k] != 0;
-        const int32_t j = ci[k];
-        m += sk && key[j] >= OPEN;
-      }
-    for (int o = 4; o > 0; o >>= 1) m += __shfl_xor(m, o, 8);
-    if (g == 0) off[i] = m;
+  int64_t at[Q];
+  int m[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int i = t + 1024 * q;
+    at[q] = 0;
+    m[q] = 0;
+    if (i < n) {
+      const bool open = state_g[i] == 0;
+      const uint64_t k = key_g[i];
+      const int32_t c = na[i];
+      at[q] = rp[i];
+      m[q] = open ? c : 0;
+      key[i] = open ? k : 2ull;
+      off[i] = m[q];
+    }
   }
   __syncthreads();
   // exclusive prefix sum of off[0..n)
@@ -236,29 +254,26 @@ __global__ __launch_bounds__(1024) void k_pmis_wg(int n, const int64_t* __restri
     tot += wsum[w];
   }
   for (int i = i0; i < i1; ++i) {
-    const int m = off[i];
+    const int c = off[i];
     off[i] = run;
-    run += m;
+    run += c;
   }
-  if (t == 0) off[n] = tot;
-  uint16_t* adj = off_in && 20 * n + 4 + 2 * (int64_t)tot <= lds ? reinterpret_cast<uint16_t*>(off + n + 1) : adj_g;
+  const bool in = 14 * (int64_t)n + 8 + 2 * (int64_t)tot <= lds;
+  uint8_t* beaten = reinterpret_cast<uint8_t*>(in ? adj + tot : adj);   // two sets of n
+  for (int i = t; i < 2 * n; i += 1024) beaten[i] = 0;
   __syncthreads();
-  for (int i = t >> 3; i < n; i += 128) {
-    if (key[i] < OPEN) continue;
-    int at = off[i];
-    const int64_t k1 = rp[i + 1];
-    for (int64_t kb = rp[i]; kb < k1; kb += 8) {
-      const int64_t k = kb + g;
-      int32_t j = 0;
-      bool has = false;
-      if (k < k1) {
-        has = strong[k] != 0;
-        j = ci[k];
-        has = has && key[j] >= OPEN;
-      }
-      const unsigned m8 = (unsigned)(__ballot(has) >> ((t & 63) & ~7)) & 0xffu;
-      if (has) adj[at + __popc(m8 & ((1u << g) - 1u))] = (uint16_t)j;
-      at += __popc(m8);
+  int o[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    o[q] = t + 1024 * q < n ? off[t + 1024 * q] : 0;
+    if (!in) continue;
+    for (int e = 0; e < m[q]; e += 8) {
+      int32_t j[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) j[u] = e + u < m[q] ? adj_g[at[q] + e + u] : 0;
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (e + u < m[q]) adj[o[q] + e + u] = (uint16_t)j[u];
     }
   }
   __syncthreads();
@@ -267,32 +282,43 @@ __global__ __launch_bounds__(1024) void k_pmis_wg(int n, const int64_t* __restri
       if (t == 0) atomicOr(err, 1ull);
       break;
     }
-    // largest undecided key among the symmetrised strong neighbours
-    for (int i = t; i < n; i += 1024) {
+    uint8_t* now = beaten + (round & 1) * n;
+    uint8_t* next = beaten + (~round & 1) * n;
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int i = t + 1024 * q;
+      if (i >= n) break;
       const unsigned long long ki = key[i];
       if (ki < OPEN) continue;
-      unsigned long long mx = 0ull;
-      for (int e = off[i]; e < off[i + 1]; ++e) {
-        const int j = adj[e];
+      bool lost = false;
+      for (int e = 0; e < m[q]; ++e) {
+        const int j = in ? (int)adj[o[q] + e] : adj_g[at[q] + e];
         const unsigned long long kj = key[j];
         if (kj < OPEN) continue;
-        mx = mx > kj ? mx : kj;
-        atomicMax(&nb[j], ki);
+        if (kj >= ki) lost = true;
+        if (ki >= kj) now[j] = 1;
       }
-      if (mx) atomicMax(&nb[i], mx);
+      if (lost) now[i] = 1;
     }
     __syncthreads();
-    for (int i = t; i < n; i += 1024) {
-      if (key[i] < OPEN) continue;
-      if (key[i] > nb[i]) key[i] = 1ull;
-      nb[i] = 0ull;
-    }
-    __syncthreads();
+    // an open key with no mark counts as C, as does a key that has become 1
     int undecided = 0;
-    for (int i = t; i < n; i += 1024) {
+#pragma unroll
+    for (int q = 0; q < Q; ++q) {
+      const int i = t + 1024 * q;
+      if (i >= n) break;
       if (key[i] < OPEN) continue;
+      next[i] = 0;
+      if (!now[i]) {
+        key[i] = 1ull;
+        continue;
+      }
       bool hit = false;
-      for (int e = off[i]; e < off[i + 1] && !hit; ++e) hit = key[adj[e]] == 1ull;
+      for (int e = 0; e < m[q] && !hit; ++e) {
+        const int j = in ? (int)adj[o[q] + e] : adj_g[at[q] + e];
+        const unsigned long long kj = key[j];
+        hit = kj == 1ull || (kj >= OPEN && !now[j]);
+      }
       if (hit) key[i] = 2ull;
       else undecided = 1;
     }
@@ -319,12 +345,16 @@ __global__ void k_cf_flags(int64_t n, const int8_t* __restrict__ state, int8_t* 
 // the number of R A P candidates of its coarse row (row lengths of A over
 // {i} and N_i); for F points their list and the F-row statistics (count,
 // entries).
-// imax[0] = max |N_i|, imax[1] = max candidates, imax[2] = max length of a
-// C row; fst[0..1] = F rows, entries.
+// imax[1] = max candidates, imax[2] = max length of a C row (block AIR only);
+// fst[8 s], fst[8 s + 1] = F rows and their entries, in FST_SLOTS parts.
+// Large workgroups, the maxima only where they grow and the counts spread over
+// lines: five atomics per 256 threads on one line took most of this kernel (72,585
+// rows of 22 entries: 79 us, 20 now).
 // PG lanes per row; the strongest C neighbour is the first in row order
 // (smallest column) within relative 1e-12 of the maximum.  fsearch = 0
 // (block AIR, whose P comes from the block graph): F rows only listed.
-__global__ __launch_bounds__(256) void k_onepoint(int64_t n, int fsearch, const int64_t* __restrict__ rp,
+constexpr int FST_SLOTS = 16;
+__global__ __launch_bounds__(1024) void k_onepoint(int64_t n, int fsearch, const int64_t* __restrict__ rp,
                                                   const int32_t* __restrict__ ci, const double* __restrict__ v,
                                                   const uint8_t* __restrict__ strong,
                                                   const uint8_t* __restrict__ strong_r, const int8_t* __restrict__ cf,
@@ -335,7 +365,7 @@ __global__ __launch_bounds__(256) void k_onepoint(int64_t n, int fsearch, const 
   constexpr int Q = 5;   // entries per lane held in registers: a row is read once, its loads issued together
   const int g = (int)(threadIdx.x % PG);
   const int64_t stride = (int64_t)gridDim.x * (blockDim.x / PG);
-  int mmax = 0, cmax = 0, omax = 0;
+  int cmax = 0, omax = 0;
   unsigned long long fcnt = 0, fent = 0;
   for (int64_t i = ((int64_t)blockIdx.x * blockDim.x + threadIdx.x) / PG; i < n; i += stride) {
     const int64_t k0 = rp[i], k1 = rp[i + 1];
@@ -375,7 +405,6 @@ __global__ __launch_bounds__(256) void k_onepoint(int64_t n, int fsearch, const 
         pcol[i] = (int32_t)cidx[i];
         rcnt[cidx[i]] = 1 + m;
         clist[cidx[i]] = (int32_t)i;
-        mmax = m > mmax ? m : mmax;
         omax = (int)(k1 - k0) > omax ? (int)(k1 - k0) : omax;
         const int c = cand > 0x3fffffff ? 0x3fffffff : (int)cand;
         cmax = c > cmax ? c : cmax;
@@ -437,35 +466,44 @@ __global__ __launch_bounds__(256) void k_onepoint(int64_t n, int fsearch, const 
   }
   // block totals, one atomic each
   for (int o = 32; o > 0; o >>= 1) {
-    int a = __shfl_xor(mmax, o, 64), c = __shfl_xor(cmax, o, 64), ow = __shfl_xor(omax, o, 64);
-    mmax = a > mmax ? a : mmax;
+    const int c = __shfl_xor(cmax, o, 64), ow = __shfl_xor(omax, o, 64);
     cmax = c > cmax ? c : cmax;
     omax = ow > omax ? ow : omax;
     fcnt += __shfl_xor(fcnt, o, 64);
     fent += __shfl_xor(fent, o, 64);
   }
-  __shared__ int sm[3][4];
-  __shared__ unsigned long long su[2][4];
+  __shared__ int sm[2][16];
+  __shared__ unsigned long long su[2][16];
   const int w = threadIdx.x / 64;
   if ((threadIdx.x & 63) == 0) {
-    sm[0][w] = mmax; sm[1][w] = cmax; sm[2][w] = omax;
+    sm[0][w] = cmax; sm[1][w] = omax;
     su[0][w] = fcnt; su[1][w] = fent;
   }
   __syncthreads();
   if (threadIdx.x == 0) {
     for (int k = 1; k < (int)(blockDim.x / 64); ++k) {
-      mmax = sm[0][k] > mmax ? sm[0][k] : mmax;
-      cmax = sm[1][k] > cmax ? sm[1][k] : cmax;
-      omax = sm[2][k] > omax ? sm[2][k] : omax;
+      cmax = sm[0][k] > cmax ? sm[0][k] : cmax;
+      omax = sm[1][k] > omax ? sm[1][k] : omax;
       fcnt += su[0][k];
       fent += su[1][k];
     }
-    if (mmax) atomicMax(&imax[0], mmax);
-    if (cmax) atomicMax(&imax[1], cmax);
-    if (omax) atomicMax(&imax[2], omax);
-    if (fcnt) atomicAdd(&fst[0], fcnt);
-    if (fent) atomicAdd(&fst[1], fent);
+    unsigned long long* f = fst + 8 * (blockIdx.x % FST_SLOTS);
+    if (cmax > *(volatile int*)&imax[1]) atomicMax(&imax[1], cmax);
+    if (!fsearch && omax > *(volatile int*)&imax[2]) atomicMax(&imax[2], omax);
+    if (fcnt) {
+      atomicAdd(&f[0], fcnt);
+      atomicAdd(&f[1], fent);
+    }
   }
+}
+
+// Sums of the parts, a workgroup per level: fst[2 l], fst[2 l + 1].
+__global__ void k_fst_sum(const unsigned long long* __restrict__ parts, unsigned long long* __restrict__ fst) {
+  const int l = blockIdx.x, k = threadIdx.x;
+  if (k > 1) return;
+  unsigned long long x = 0;
+  for (int q = 0; q < FST_SLOTS; ++q) x += parts[(l * FST_SLOTS + q) * 8 + k];
+  fst[2 * l + k] = x;
 }
 
 __device__ inline double wave_sum(double v) {
@@ -1207,7 +1245,8 @@ __global__ __launch_bounds__(64) void k_rap_blk(int64_t ncb, const int64_t* __re
 // per row.
 __global__ __launch_bounds__(256) void k_diag(int64_t n, const int64_t* __restrict__ rp,
                                               const int32_t* __restrict__ ci, const double* __restrict__ v,
-                                              double* __restrict__ d, float* __restrict__ d32) {
+                                              double* __restrict__ d, float* __restrict__ d32, int64_t nz,
+                                              int32_t* __restrict__ zero) {
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t i = gid / PG;
   const int g = (int)(gid % PG);
@@ -1224,6 +1263,7 @@ __global__ __launch_bounds__(256) void k_diag(int64_t n, const int64_t* __restri
   }
   if (g != 0) return;
   d[i] = x;
+  if (zero && i < nz) zero[i] = 0;
   if (d32) d32[i] = (float)x;
 }
 
@@ -1341,49 +1381,75 @@ __global__ void k_eye(int n, double* __restrict__ Inv) {
   if (k < (int64_t)n * n) Inv[k] = (k / n == k % n) ? 1.0 : 0.0;
 }
 
-// Inverse of a dense matrix of order n <= 64 by Gauss-Jordan elimination on
-// [A | I] with partial pivoting, thread t holding rows t / 128 + 8 i of column
-// t % 128 in registers.  Rows stay where they are: the pivot is taken among the
-// rows not used yet, and row k of the inverse is the k-th pivot's.  Two
-// barriers per column (the column into LDS, searched by every wave, then the
-// scaled pivot row): a chain of n steps, 61 us at n = 30; with the matrix in LDS,
-// row swaps and six barriers per column it took 75.
+// Inverse of a dense matrix of order n <= N (32 or 64) by Gauss-Jordan
+// elimination on [A | I] with partial pivoting, thread t holding R rows of column
+// t % 2N in registers.  Rows stay where they are: the pivot is taken among the
+// rows not used yet, and row k of the inverse is the k-th pivot's.  Two barriers
+// per column (the column into LDS, searched by every wave, then the scaled pivot
+// row): a chain of n steps, which the instructions of the search and the division
+// bound, so four waves and no more: at n = 31, 44 us with 16 waves, 33 with four
+// (75 with the matrix in LDS, row swaps and six barriers per column).
 constexpr int INV_GJ_MAX = 64;
 
-__global__ __launch_bounds__(1024) void k_inv_gj(int n, const double* __restrict__ M, double* __restrict__ Inv,
-                                                 int* __restrict__ err) {
-  __shared__ double f[2][INV_GJ_MAX], prow[2 * INV_GJ_MAX];
-  __shared__ int place[INV_GJ_MAX];
-  const int t = threadIdx.x, c = t & 127, r0 = t >> 7, lane = t & 63;
-  double a[8];
+// Largest of 64 values >= 0, one per lane, in every lane: shifts and broadcasts
+// within the vector registers (six exchanges through LDS hardware cost as much
+// as the rest of a step).  As whole numbers such values keep their order, and a
+// lane without a source reads 0.
+__device__ inline double wave_max_dpp(double x) {
+  unsigned long long v = (unsigned long long)__double_as_longlong(x);
+#define AH_STEP(ctrl, rows)                                                                        \
+  {                                                                                                \
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)v, ctrl, rows, 0xf, false);       \
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(v >> 32), ctrl, rows, 0xf, false); \
+    const unsigned long long y = ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo;          \
+    v = y > v ? y : v;                                                                             \
+  }
+  AH_STEP(0x111, 0xf)   // row_shr:1, 2, 4, 8: the last lane of each 16 holds their maximum
+  AH_STEP(0x112, 0xf)
+  AH_STEP(0x114, 0xf)
+  AH_STEP(0x118, 0xf)
+  AH_STEP(0x142, 0xa)   // row_bcast:15 into rows 1 and 3
+  AH_STEP(0x143, 0xc)   // row_bcast:31 into rows 2 and 3
+#undef AH_STEP
+  const unsigned lo = __builtin_amdgcn_readlane((int)(unsigned)v, 63);
+  const unsigned hi = __builtin_amdgcn_readlane((int)(unsigned)(v >> 32), 63);
+  return __longlong_as_double((long long)(((unsigned long long)hi << 32) | lo));
+}
+
+template <int N>
+__global__ __launch_bounds__(256) void k_inv_gj(int n, const double* __restrict__ M, double* __restrict__ Inv,
+                                                int* __restrict__ err) {
+  constexpr int W = 2 * N, R = N * W / 256;
+  __shared__ double f[2][64], prow[W];
+  __shared__ int place[N];
+  const int t = threadIdx.x, c = t % W, r0 = t / W * R, lane = t & 63;
+  double a[R];
 #pragma unroll
-  for (int i = 0; i < 8; ++i) {
-    const int r = r0 + 8 * i;
+  for (int i = 0; i < R; ++i) {
+    const int r = r0 + i;
     a[i] = r >= n || c >= 2 * n ? 0.0 : c < n ? M[r * n + c] : c - n == r ? 1.0 : 0.0;
   }
+  if (t < 128) f[t / 64][t % 64] = 0.0;
+  __syncthreads();
   unsigned long long used = 0;
   for (int k = 0; k < n; ++k) {
     double* fk = f[k & 1];
     if (c == k)
 #pragma unroll
-      for (int i = 0; i < 8; ++i) fk[r0 + 8 * i] = a[i];
+      for (int i = 0; i < R; ++i) fk[r0 + i] = a[i];
     __syncthreads();
-    double best = lane < n && !((used >> lane) & 1) ? fabs(fk[lane]) : -1.0;
-    best = best >= 0.0 ? best : -1.0;   // NaN
-    int p = lane;
-    for (int o = 32; o > 0; o >>= 1) {
-      const double ob = __shfl_xor(best, o, 64);
-      const int op = __shfl_xor(p, o, 64);
-      if (ob > best || (ob == best && op < p)) { best = ob; p = op; }
-    }
-    p = __builtin_amdgcn_readfirstlane(p);
-    if (best < 0.0) p = __ffsll(~used) - 1;   // nothing left but NaN: any unused row
-    if (!(best > 0.0) && t == 0) atomicOr(err, 1);
+    const double mag = fabs(fk[lane]);
+    const bool open = lane < n && !((used >> lane) & 1) && mag > 0.0;   // false for NaN
+    const double best = wave_max_dpp(open ? mag : 0.0);
+    const unsigned long long at = __ballot(open && mag == best);
+    // nothing left but zeros and NaN: any unused row
+    const int p = at ? __ffsll((long long)at) - 1 : __ffsll((long long)~used) - 1;
+    if (!at && t == 0) atomicOr(err, 1);
     const double d = fk[p] != 0.0 ? fk[p] : 1.0;
-    if (r0 == (p & 7)) {
+    if (p >= r0 && p < r0 + R) {
       double x = a[0];
 #pragma unroll
-      for (int i = 1; i < 8; ++i) x = i == p >> 3 ? a[i] : x;
+      for (int i = 1; i < R; ++i) x = i == p - r0 ? a[i] : x;
       prow[c] = x / d;
     }
     if (t == 0) place[p] = k;
@@ -1391,16 +1457,13 @@ __global__ __launch_bounds__(1024) void k_inv_gj(int n, const double* __restrict
     __syncthreads();
     const double x = prow[c];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int r = r0 + 8 * i;
-      a[i] = r == p ? x : a[i] - fk[r] * x;
-    }
+    for (int i = 0; i < R; ++i) a[i] = r0 + i == p ? x : a[i] - fk[r0 + i] * x;
   }
   __syncthreads();
   if (c >= n && c < 2 * n)
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int r = r0 + 8 * i;
+    for (int i = 0; i < R; ++i) {
+      const int r = r0 + i;
       if (r < n) Inv[place[r] * n + c - n] = a[i];
     }
 }
@@ -1800,14 +1863,13 @@ static int64_t pmis_list_min() {
   return e ? (int64_t)std::atoll(e) : (int64_t)1 << 20;
 }
 
-// PMIS C/F splitting of the graph (n, rp, ci) over its strong entries:
-// state[i] = 1 (C) or 2 (F).  key and nbmax hold n entries of scratch;
-// flags[0..1] are the undecided flags of alternating rounds, flags[3] the
-// single-workgroup round-overflow flag.
-static ah_status pmis_split(int64_t n, const int64_t* rp, const int32_t* ci, const uint8_t* strong,
-                            int64_t nnz, const int32_t* infl, int level, uint64_t* key, unsigned long long* nbmax,
-                            int8_t* state, unsigned long long* flags, hipStream_t st, Arena& arena_tmp) {
-  hipLaunchKernelGGL(k_pmis_init, g1(n), dim3(256), 0, st, n, infl, level, key, state, nbmax);
+// PMIS C/F splitting of the graph of the strong entries (row i's columns at
+// adj[rp[i]], na[i] of them): state[i] = 1 (C) or 2 (F).  key holds n entries of
+// scratch, beaten 2 n; flags are the two round flags, flags[3] the error flag.
+static ah_status pmis_split(int64_t n, const int64_t* rp, const int32_t* adj, const int32_t* na,
+                            const int32_t* infl, int level, uint64_t* key, uint8_t* beaten, int8_t* state,
+                            unsigned long long* flags, hipStream_t st) {
+  hipLaunchKernelGGL(k_pmis_init, g1(n), dim3(256), 0, st, n, infl, level, key, state, beaten);
   AH_HIP(hipGetLastError());
   const char* wg_env = std::getenv("AH_PMIS_WG_MAX");   // at most PMIS_WG_MAX (its LDS size)
   const int64_t wg_max = wg_env ? std::min<int64_t>(std::atoll(wg_env), PMIS_WG_MAX) : (int64_t)PMIS_WG_MAX;
@@ -1817,32 +1879,30 @@ static ah_status pmis_split(int64_t n, const int64_t* rp, const int32_t* ci, con
     std::call_once(once, [] {
       (void)hipFuncSetAttribute((const void*)k_pmis_wg, hipFuncAttributeMaxDynamicSharedMemorySize, PMIS_LDS);
     });
-    // keys and maxima, offsets and (about 16 neighbours a row) the lists
-    const int lds = (int)std::min<int64_t>(PMIS_LDS, 52 * n + 64);
-    int32_t* off = nullptr;
-    uint16_t* adj = nullptr;
-    AH_TRY(arena_tmp.get(&off, n + 1));
-    AH_TRY(arena_tmp.get(&adj, nnz));
-    hipLaunchKernelGGL(k_pmis_wg, dim3(1), dim3(1024), lds, st, (int)n, rp, ci, strong, key, state, flags + 3, lds,
-                       off, adj);
+    // 14 bytes per row, and lists of 16 columns on average
+    const int lds = (int)std::min<int64_t>(PMIS_LDS, 46 * n + 64);
+    hipLaunchKernelGGL(k_pmis_wg, dim3(1), dim3(1024), lds, st, (int)n, rp, adj, na, key, state, flags + 3, lds);
     AH_HIP(hipGetLastError());
     return AH_OK;
   }
+  const auto mark = [&](int round, int64_t nl, const int32_t* list, const int64_t* nd) {
+    unsigned long long* left_d = flags + (round & 1);
+    uint8_t* now = beaten + (round & 1) * n;
+    uint8_t* next = beaten + (~round & 1) * n;
+    hipLaunchKernelGGL(k_pmis_beat, g1(nl * PG), dim3(256), 0, st, nl, rp, adj, na, key, state, now, left_d, list, nd);
+    hipLaunchKernelGGL(k_pmis_mark, grows(nl), dim3(256), 0, st, nl, rp, adj, na, state, now, next, left_d, list, nd);
+  };
   if (n < pmis_list_min()) {
     // rounds over all points (launch-latency bound: listing costs more)
     for (int round = 0;; ++round) {
       if (round > 10000) { set_error("air_setup: PMIS did not terminate"); return AH_EINVAL; }
-      unsigned long long* left_d = flags + (round & 1);
-      hipLaunchKernelGGL(k_pmis_nbmax, g1(n * PG), dim3(256), 0, st, n, rp, ci, strong, key, state, nbmax, nullptr,
-                         nullptr);
-      hipLaunchKernelGGL(k_pmis_select, g1(n), dim3(256), 0, st, n, key, nbmax, state, left_d, nullptr, nullptr);
-      hipLaunchKernelGGL(k_pmis_fmark, grows(n), dim3(256), 0, st, n, rp, ci, strong, state, left_d, nullptr, nullptr);
+      mark(round, n, nullptr, nullptr);
       AH_HIP(hipGetLastError());
       // rounds run in pairs between host checks: a round after the last
       // undecided point is gone changes nothing and leaves its flag at 0
       if ((round & 1) == 0) continue;
       unsigned long long left = 0;
-      AH_TRY(read_bytes(left_d, &left, sizeof(left), st));
+      AH_TRY(read_bytes(flags + 1, &left, sizeof(left), st));
       if (left == 0) return AH_OK;
     }
   }
@@ -1866,10 +1926,7 @@ static ah_status pmis_split(int64_t n, const int64_t* rp, const int32_t* ci, con
   int64_t nl = n;   // host bound of the list length
   for (int round = 0;; ++round) {
     if (round > 10000) { tmp.release(); set_error("air_setup: PMIS did not terminate"); return AH_EINVAL; }
-    unsigned long long* left_d = flags + (round & 1);
-    hipLaunchKernelGGL(k_pmis_nbmax, g1(nl * PG), dim3(256), 0, st, nl, rp, ci, strong, key, state, nbmax, list, nd);
-    hipLaunchKernelGGL(k_pmis_select, g1(nl), dim3(256), 0, st, nl, key, nbmax, state, left_d, list, nd);
-    hipLaunchKernelGGL(k_pmis_fmark, grows(nl), dim3(256), 0, st, nl, rp, ci, strong, state, left_d, list, nd);
+    mark(round, nl, list, nd);
     int32_t* out = lists[round & 1];
     int64_t* p = pos[round & 1];
     hipLaunchKernelGGL(k_pmis_uflag, g1(nl), dim3(256), 0, st, nl, state, list, nd, flag);
@@ -2706,10 +2763,14 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
                                          // [3] single-workgroup PMIS round overflow
   int* d_int = nullptr;                  // [0] max |N_i|, [1] max candidates, [2] max C-row length (then error flags), [3] max A_c row
   unsigned long long* d_fst = nullptr;   // per level: F rows, F-row entries
-  CK(ar.get(&d_fst, 72));   // [2 l], [2 l + 1] per level; [64] level-0 F values in the facet-block layout
+  // [2 l], [2 l + 1] per level; [64] level-0 F values in the facet-block layout;
+  // flags; the parts of the per-level counts
+  constexpr int FST_HEAD = 72;
+  const int64_t nfst = FST_HEAD + 32 * FST_SLOTS * 8;
+  CK(ar.get(&d_fst, nfst));
   d_ull = d_fst + 66;
   d_int = reinterpret_cast<int*>(d_fst + 70);
-  CKH(hipMemsetAsync(d_fst, 0, 72 * sizeof(unsigned long long), st));
+  CKH(hipMemsetAsync(d_fst, 0, nfst * sizeof(unsigned long long), st));
   // level 0 = the scaled system (shared, not copied)
   AhLevel L0;
   L0.n = s->n;
@@ -2742,18 +2803,31 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
         CKH(hipGetLastError());
       }
     }
-    hipLaunchKernelGGL(k_diag, g1(n * PG), dim3(256), 0, st, n, L.rowptr, L.col, L.val, L.diag, L.diag32);
-    CKH(hipGetLastError());
-    CK(ar.get(&L.b, n)); CK(ar.get(&L.x, n)); CK(ar.get(&L.y, n)); CK(ar.get(&L.e, n));
-    if (prm.fp32_cycle) {
-      CK(ar.get(&L.b32, n)); CK(ar.get(&L.x32, n)); CK(ar.get(&L.y32, n)); CK(ar.get(&L.e32, n));
-    }
-    if (n <= prm.max_coarse || l == prm.max_levels - 1) break;
     // block AIR on level 0: strength and PMIS on the facet-block graph, the
     // scalar strong mask (restriction threshold) and the states expanded
     // to the rows of each block; P follows after the scalar pass below
     const bool blk = prm.block_air && l == 0;
     const int64_t nbr = blk ? n / L.ob : 0;
+    // graph of the coarsening (none on the coarsest level)
+    const bool coarsest = n <= prm.max_coarse || l == prm.max_levels - 1;
+    const int64_t ng = coarsest ? 0 : blk ? nbr : n;
+    int32_t *infl = nullptr, *adj = nullptr, *na = nullptr;
+    uint64_t* key = nullptr;
+    uint8_t* beaten = nullptr;
+    if (!coarsest && (blk || prm.coarsening != 1)) {
+      CK(tmp.get(&infl, ng));
+      CK(tmp.get(&adj, blk ? (int64_t)s->mesh->odb_col.size() : L.nnz));
+      CK(tmp.get(&na, ng));
+      CK(tmp.get(&key, ng));
+      CK(tmp.get(&beaten, 2 * ng));
+    }
+    hipLaunchKernelGGL(k_diag, g1(n * PG), dim3(256), 0, st, n, L.rowptr, L.col, L.val, L.diag, L.diag32, ng, infl);
+    CKH(hipGetLastError());
+    CK(ar.get(&L.b, n)); CK(ar.get(&L.x, n)); CK(ar.get(&L.y, n)); CK(ar.get(&L.e, n));
+    if (prm.fp32_cycle) {
+      CK(ar.get(&L.b32, n)); CK(ar.get(&L.x32, n)); CK(ar.get(&L.y32, n)); CK(ar.get(&L.e32, n));
+    }
+    if (coarsest) break;
     double* bw = nullptr;
     uint8_t* sb = nullptr;
     uint8_t* strong = nullptr;
@@ -2762,44 +2836,31 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
     CK(tmp.get(&state, n));
     if (blk) {
       const int64_t nslot = (int64_t)s->mesh->odb_col.size();
-      int32_t* infl = nullptr;
-      uint64_t* key = nullptr;
-      unsigned long long* nbmax = nullptr;
       int8_t* sbstate = nullptr;
       CK(tmp.get(&bw, nslot));
       CK(tmp.get(&sb, nslot));
-      CK(tmp.get(&infl, nbr));
-      CK(tmp.get(&key, nbr));
-      CK(tmp.get(&nbmax, nbr));
       CK(tmp.get(&sbstate, nbr));
       hipLaunchKernelGGL(k_block_weights, g1(nbr * SG), dim3(256), 0, st, nbr, (int)L.ob, L.optr, L.oval, bw);
-      CKH(hipMemsetAsync(infl, 0, nbr * sizeof(int32_t), st));
-      hipLaunchKernelGGL(k_strength, g1(nbr * SG), dim3(256), 0, st, nbr, L.optr, L.ocol, bw, prm.theta, sb, infl);
+      hipLaunchKernelGGL(k_strength, g1(nbr * SG), dim3(256), 0, st, nbr, L.optr, L.ocol, bw, prm.theta, sb, infl,
+                         adj, na);
       CKH(hipGetLastError());
-      CK(pmis_split(nbr, L.optr, L.ocol, sb, nslot, infl, l, key, nbmax, sbstate, d_ull, st, tmp));
+      CK(pmis_split(nbr, L.optr, adj, na, infl, l, key, beaten, sbstate, d_ull, st));
       hipLaunchKernelGGL(k_block_expand, g1(n), dim3(256), 0, st, n, (int)L.ob, sbstate, state);
       uint8_t* sbr = sb;
       if (prm.theta_r > 0.0 && prm.theta_r != prm.theta) {
         CK(tmp.get(&sbr, nslot));
-        CKH(hipMemsetAsync(infl, 0, nbr * sizeof(int32_t), st));
         hipLaunchKernelGGL(k_strength, g1(nbr * SG), dim3(256), 0, st, nbr, L.optr, L.ocol, bw, prm.theta_r, sbr,
-                           infl);
+                           (int32_t*)nullptr, (int32_t*)nullptr, (int32_t*)nullptr);
       }
       hipLaunchKernelGGL(k_block_mask, g1(n * PG), dim3(256), 0, st, n, (int)L.ob, L.rowptr, L.col, L.optr, L.ocol,
                          sbr, strong);
       CKH(hipGetLastError());
     } else {
     // strength
-    int32_t* infl = nullptr;
-    CK(tmp.get(&infl, n));
-    CKH(hipMemsetAsync(infl, 0, n * sizeof(int32_t), st));
-    hipLaunchKernelGGL(k_strength, g1(n * SG), dim3(256), 0, st, n, L.rowptr, L.col, L.val, prm.theta, strong, infl);
+    hipLaunchKernelGGL(k_strength, g1(n * SG), dim3(256), 0, st, n, L.rowptr, L.col, L.val, prm.theta, strong, infl,
+                       adj, na);
     CKH(hipGetLastError());
     // PMIS
-    uint64_t* key = nullptr;
-    unsigned long long* nbmax = nullptr;
-    CK(tmp.get(&key, n));
-    CK(tmp.get(&nbmax, n));
     if (prm.coarsening == 1) {
       // Ruge-Stueben first pass on the host from the strong pattern
       std::vector<int64_t> hrp(n + 1);
@@ -2814,7 +2875,7 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
       CKH(hipMemcpyAsync(state, hstate.data(), n, hipMemcpyHostToDevice, st));
       CKH(hipStreamSynchronize(st));
     } else {
-      CK(pmis_split(n, L.rowptr, L.col, strong, L.nnz, infl, l, key, nbmax, state, d_ull, st, tmp));
+      CK(pmis_split(n, L.rowptr, adj, na, infl, l, key, beaten, state, d_ull, st));
     }
     }
     // coarse numbering
@@ -2848,16 +2909,14 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
     // when it equals theta)
     uint8_t* strong_r = strong;
     if (!blk && prm.theta_r > 0.0 && prm.theta_r != prm.theta) {
-      int32_t* infl_r = nullptr;
       CK(tmp.get(&strong_r, L.nnz));
-      CK(tmp.get(&infl_r, n));
-      CKH(hipMemsetAsync(infl_r, 0, n * sizeof(int32_t), st));
       hipLaunchKernelGGL(k_strength, g1(n * SG), dim3(256), 0, st, n, L.rowptr, L.col, L.val, prm.theta_r, strong_r,
-                         infl_r);
+                         (int32_t*)nullptr, (int32_t*)nullptr, (int32_t*)nullptr);
       CKH(hipGetLastError());
     }
-    hipLaunchKernelGGL(k_onepoint, grows(n), dim3(256), 0, st, n, blk ? 0 : 1, L.rowptr, L.col, L.val, strong, strong_r, L.cf,
-                       cidx, L.pcol, rcnt, clist, L.flist, d_int, d_fst + 2 * l);
+    hipLaunchKernelGGL(k_onepoint, dim3((unsigned)std::min<int64_t>(cdiv(n, 1024 / PG), 512)), dim3(1024), 0, st, n,
+                       blk ? 0 : 1, L.rowptr, L.col, L.val, strong, strong_r, L.cf, cidx, L.pcol, rcnt, clist, L.flist,
+                       d_int, d_fst + FST_HEAD + (int64_t)l * FST_SLOTS * 8);
     CKH(hipGetLastError());
     if (blk) {
       hipLaunchKernelGGL(k_block_pcol, g1(nbr), dim3(256), 0, st, nbr, (int)L.ob, L.optr, L.ocol, bw, sb, L.cf, cidx,
@@ -2874,12 +2933,11 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
       CKH(hipGetLastError());
       CKH(hipMemsetAsync(d_int, 0, 2 * sizeof(int), st));
       const dim3 gm((unsigned)std::min<int64_t>(cdiv(nc, 256), 256));
-      hipLaunchKernelGGL(k_max_i32, gm, dim3(256), 0, st, nc, mcnt, d_int);
       hipLaunchKernelGGL(k_max_i32, gm, dim3(256), 0, st, nc, c2, d_int + 1);
       CKH(hipGetLastError());
     }
     CK(ar.get(&L.Rptr, ncap + 1));
-    CK(scan_i32_to_i64(rcnt, L.Rptr, ncap, st, tmp));
+    CK(scan_i32_to_i64(rcnt, L.Rptr, ncap, st, tmp, d_int));   // and the longest row of R
     int hmax[4];
     CK(read_values({{L.Rptr + ncap, &L.nnzR, sizeof(int64_t)},
                     {d_int, hmax, sizeof(hmax)},
@@ -2901,7 +2959,7 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
     }
     CK(ar.get(&L.Rcol, L.nnzR));
     CK(ar.get(&L.Rval, L.nnzR));
-    const int maxm = hmax[0];
+    const int maxm = hmax[0] - 1;
     // the smallest local-system capacity that holds every neighbourhood
     // (LDS per workgroup, hence occupancy, grows with its square)
     if (maxm > 64) {
@@ -2936,14 +2994,11 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
     if (rblk) CK(rap_blk_dispatch(hsb, (int)L.ob, false, nc / L.ob, L, clist, ccnt, nullptr, nullptr, nullptr, st));
     else CK(rap_dispatch(hs, nc, L, ccnt, nullptr, nullptr, nullptr, false, st));
     CK(ar.get(&C.rowptr, nc + 1));
-    CK(scan_i32_to_i64(ccnt, C.rowptr, nc, st, tmp));
+    CK(scan_i32_to_i64(ccnt, C.rowptr, nc, st, tmp, d_int + 3));
     // the numeric pass hashes a row's distinct coarse columns only: size its
     // table from the largest row of A_c
     int rmax = 0;
     {
-      hipLaunchKernelGGL(k_max_i32, dim3((unsigned)std::min<int64_t>(cdiv(nc, 256), 256)), dim3(256), 0, st, nc, ccnt,
-                         d_int + 3);
-      CKH(hipGetLastError());
       int e2[2];
       CK(read_values({{C.rowptr + nc, &C.nnz, sizeof(int64_t)}, {d_int + 2, e2, sizeof(e2)}}, st));
       rmax = e2[1];
@@ -2994,7 +3049,8 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
     CK(ar.get(&h->cinv, nL * nL));
     hipLaunchKernelGGL(k_dense, dim3((unsigned)nL), dim3(64), 0, st, nL, LL.rowptr, LL.col, LL.val, M, d_int + 2);
     if (nL <= INV_GJ_MAX)
-      hipLaunchKernelGGL(k_inv_gj, dim3(1), dim3(1024), 0, st, (int)nL, M, h->cinv, d_int + 2);
+      hipLaunchKernelGGL(nL <= 32 ? k_inv_gj<32> : k_inv_gj<64>, dim3(1), dim3(256), 0, st, (int)nL, M, h->cinv,
+                         d_int + 2);
     else if (nL <= INV_LDS_MAX)
       hipLaunchKernelGGL(k_inv_lds, dim3(1), dim3(1024), 0, st, (int)nL, M, h->cinv, d_int + 2);
     else {
@@ -3083,6 +3139,8 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
   {
     double* pin = pinned_scratch(72);
     if (!pin) { set_error("pinned host allocation failed"); tmp.release(); delete h; return AH_ENOMEM; }
+    hipLaunchKernelGGL(k_fst_sum, dim3((unsigned)h->lev.size()), dim3(64), 0, st, d_fst + FST_HEAD, d_fst);
+    CKH(hipGetLastError());
     CKH(hipMemcpyAsync(pin, d_fst, 72 * sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
     CKH(hipStreamSynchronize(st));
     unsigned long long fst[72];

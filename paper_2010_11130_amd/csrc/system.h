@@ -53,7 +53,8 @@ ah_status flow_order_build(ah_hier* h, hipStream_t st);
 // Exclusive prefix sum of n int64 values into out[0..n] (out[n] = total).
 ah_status scan_i64(const int64_t* in, int64_t* out, int64_t n, hipStream_t st, Arena& tmp);
 // Same for int32 counts producing int64 offsets.
-ah_status scan_i32_to_i64(const int32_t* in, int64_t* out, int64_t n, hipStream_t st, Arena& tmp);
+// (vmax, where given: the largest value on the device, at least 0)
+ah_status scan_i32_to_i64(const int32_t* in, int64_t* out, int64_t n, hipStream_t st, Arena& tmp, int* vmax = nullptr);
 // Read a few small device values (multiples of 4 bytes, at most 64 each) in
 // stream order: one launch stores them into pinned host memory and sets a flag
 // that the host polls, instead of a copy per value and a synchronization.

@@ -15,113 +15,201 @@ namespace ah {
 // addition and a total took two to five launches each (setup of 342,528 rows,
 // nine levels: 2790 us with those and a copy per value read back, 2536 with these
 // and polled reads).
-constexpr int SCAN_PER = 16;
+// A tile is CH chunks of four neighbouring values per thread, so a wave
+// reads 1 KiB and writes 2 KiB in one piece each time; 16 values in a row per
+// thread made every store touch 64 lines (14,912 values in one workgroup: 16 us,
+// 8 now)
+// (one chunk up to 4096 values in one workgroup: a shorter chain).
+constexpr int SCAN_CH = 4;
+constexpr int SCAN_PER = 4 * SCAN_CH;
 constexpr int SCAN_ONE = 1024 * SCAN_PER;
 constexpr int SCAN_TILE = 256 * SCAN_PER;
 
-// Sum over the workgroup's values before thread t's x, and of all of them.
-template <int T>
-__device__ inline int64_t block_prefix(int64_t x, int64_t* red, int64_t* total) {
-  const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-  int64_t inc = x;
-#pragma unroll
-  for (int o = 1; o < 64; o <<= 1) {
-    const int64_t u = __shfl_up(inc, o, 64);
-    inc += lane >= o ? u : 0;
+// in[base .. base + 3], zero from n on; vec: 16-byte aligned arrays.
+template <class T>
+__device__ inline void scan_load(const T* __restrict__ in, int64_t base, int64_t n, int vec, T (&v)[4]) {
+  typedef int I4 __attribute__((ext_vector_type(4)));
+  typedef long L2 __attribute__((ext_vector_type(2)));
+  if (vec && base + 4 <= n) {
+    if constexpr (sizeof(T) == 4) {
+      const I4 x = *reinterpret_cast<const I4*>(in + base);
+      v[0] = x.x; v[1] = x.y; v[2] = x.z; v[3] = x.w;
+    } else {
+      const L2 x = *reinterpret_cast<const L2*>(in + base), y = *reinterpret_cast<const L2*>(in + base + 2);
+      v[0] = x.x; v[1] = x.y; v[2] = y.x; v[3] = y.y;
+    }
+    return;
   }
-  if (lane == 63) red[wv] = inc;
-  __syncthreads();
-  int64_t before = inc - x, all = 0;
 #pragma unroll
-  for (int w = 0; w < T / 64; ++w) {
-    const int64_t r = red[w];
-    before += w < wv ? r : 0;
-    all += r;
-  }
-  *total = all;
-  return before;
+  for (int q = 0; q < 4; ++q) v[q] = base + q < n ? in[base + q] : 0;
 }
 
-template <class T, int NT>
-__global__ __launch_bounds__(NT) void k_scan_sums(const T* __restrict__ in, int64_t n, int64_t* __restrict__ sums) {
-  __shared__ int64_t red[NT / 64];
-  const int64_t base = (int64_t)blockIdx.x * (NT * SCAN_PER) + threadIdx.x;
-  int64_t x = 0;
-#pragma unroll
-  for (int q = 0; q < SCAN_PER; ++q) {
-    const int64_t i = base + (int64_t)q * NT;
-    x += i < n ? (int64_t)in[i] : 0;
-  }
+__device__ inline int64_t wave_sum(int64_t x) {
   for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-  if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = x;
+  return x;
+}
+__device__ inline int64_t wave_max(int64_t x) {
+  for (int o = 32; o > 0; o >>= 1) {
+    const int64_t y = __shfl_xor(x, o, 64);
+    x = y > x ? y : x;
+  }
+  return x;
+}
+
+// Sums of the tiles, then (from sums + gridDim.x) their largest values.
+template <class T, int NT>
+__global__ __launch_bounds__(NT) void k_scan_sums(const T* __restrict__ in, int64_t n, int vec,
+                                                  int64_t* __restrict__ sums) {
+  __shared__ int64_t red[2][NT / 64];
+  const int64_t base = (int64_t)blockIdx.x * (NT * SCAN_PER) + threadIdx.x * 4;
+  T v[SCAN_CH][4];
+#pragma unroll
+  for (int c = 0; c < SCAN_CH; ++c) scan_load(in, base + c * (NT * 4), n, vec, v[c]);
+  int64_t x = 0, m = 0;
+#pragma unroll
+  for (int c = 0; c < SCAN_CH; ++c)
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      x += v[c][q];
+      m = v[c][q] > m ? v[c][q] : m;
+    }
+  x = wave_sum(x);
+  m = wave_max(m);
+  if ((threadIdx.x & 63) == 0) {
+    red[0][threadIdx.x >> 6] = x;
+    red[1][threadIdx.x >> 6] = m;
+  }
   __syncthreads();
   if (threadIdx.x == 0) {
-    int64_t t = 0;
-    for (int w = 0; w < NT / 64; ++w) t += red[w];
-    sums[blockIdx.x] = t;
+    for (int w = 1; w < NT / 64; ++w) {
+      x += red[0][w];
+      m = red[1][w] > m ? red[1][w] : m;
+    }
+    sums[blockIdx.x] = x;
+    sums[gridDim.x + blockIdx.x] = m;
   }
 }
 
-// The tile's prefix sums; sums null: a single tile.
-template <class T, int NT>
-__global__ __launch_bounds__(NT) void k_scan_out(const T* __restrict__ in, int64_t n,
-                                                 const int64_t* __restrict__ sums, int64_t* __restrict__ out) {
-  __shared__ int64_t red[2][NT / 64];
-  int64_t carry = 0;
+// The tile's prefix sums; sums null: a single tile.  The last tile also writes
+// the total to out[n] and, where vmax is given, the largest value (at least 0).
+template <class T, int NT, int CH>
+__global__ __launch_bounds__(NT) void k_scan_out(const T* __restrict__ in, int64_t n, int vec,
+                                                 const int64_t* __restrict__ sums, int64_t* __restrict__ out,
+                                                 int* __restrict__ vmax) {
+  constexpr int W = NT / 64;
+  __shared__ int64_t red[2][W], part[CH * W];
+  typedef long L2 __attribute__((ext_vector_type(2)));
+  const int t = threadIdx.x, lane = t & 63, w = t >> 6;
+  const bool last = blockIdx.x == gridDim.x - 1;
+  const int64_t base = (int64_t)blockIdx.x * (NT * 4 * CH) + t * 4;
+  T v[CH][4];
+#pragma unroll
+  for (int c = 0; c < CH; ++c) scan_load(in, base + c * (NT * 4), n, vec, v[c]);
+  int64_t before = 0, m = 0;
   if (sums) {
-    int64_t x = 0;
-    for (int b = threadIdx.x; b < (int)blockIdx.x; b += NT) x += sums[b];
-    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
-    if ((threadIdx.x & 63) == 0) red[0][threadIdx.x >> 6] = x;
-    __syncthreads();
+    for (int b = t; b < (int)blockIdx.x; b += NT) before += sums[b];
+    if (last && vmax)
+      for (int b = t; b < (int)gridDim.x; b += NT) m = sums[gridDim.x + b] > m ? sums[gridDim.x + b] : m;
+  } else if (vmax) {
 #pragma unroll
-    for (int w = 0; w < NT / 64; ++w) carry += red[0][w];
-  }
-  const int64_t base = ((int64_t)blockIdx.x * NT + threadIdx.x) * SCAN_PER;
-  int64_t v[SCAN_PER], tot = 0;
+    for (int c = 0; c < CH; ++c)
 #pragma unroll
-  for (int q = 0; q < SCAN_PER; ++q) {
-    v[q] = base + q < n ? (int64_t)in[base + q] : 0;
-    tot += v[q];
+      for (int q = 0; q < 4; ++q) m = v[c][q] > m ? v[c][q] : m;
   }
-  int64_t all = 0;
-  int64_t run = carry + block_prefix<NT>(tot, red[1], &all);
+  if (sums) before = wave_sum(before);
+  if (vmax) m = wave_max(m);
+  if (lane == 0) {
+    red[0][w] = before;
+    red[1][w] = m;
+  }
+  // inclusive sums over the lanes of each chunk
+  int64_t own[CH], inc[CH];
 #pragma unroll
-  for (int q = 0; q < SCAN_PER; ++q) {
-    if (base + q < n) out[base + q] = run;
-    run += v[q];
+  for (int c = 0; c < CH; ++c) own[c] = inc[c] = (int64_t)v[c][0] + v[c][1] + v[c][2] + v[c][3];
+#pragma unroll
+  for (int o = 1; o < 64; o <<= 1)
+#pragma unroll
+    for (int c = 0; c < CH; ++c) {
+      const int64_t u = __shfl_up(inc[c], o, 64);
+      inc[c] += lane >= o ? u : 0;
+    }
+  if (lane == 63)
+#pragma unroll
+    for (int c = 0; c < CH; ++c) part[c * W + w] = inc[c];
+  __syncthreads();
+  if (t < 64) {   // the first wave scans the waves' sums, chunk by chunk
+    int64_t carry = 0;
+    for (int k = 0; k < W; ++k) carry += red[0][k];
+    const int64_t x = t < CH * W ? part[t] : 0;
+    int64_t y = x;
+#pragma unroll
+    for (int o = 1; o < 64; o <<= 1) {
+      const int64_t u = __shfl_up(y, o, 64);
+      y += t >= o ? u : 0;
+    }
+    if (t < CH * W) part[t] = carry + y - x;
+    if (last && t == 63) {
+      out[n] = carry + y;
+      if (vmax) {
+        for (int k = 0; k < W; ++k) m = red[1][k] > m ? red[1][k] : m;
+        *vmax = (int)m;
+      }
+    }
   }
-  if (blockIdx.x == gridDim.x - 1 && threadIdx.x == 0) out[n] = carry + all;
+  __syncthreads();
+#pragma unroll
+  for (int c = 0; c < CH; ++c) {
+    const int64_t i = base + c * (NT * 4);
+    const int64_t r0 = part[c * W + w] + inc[c] - own[c];
+    const int64_t r1 = r0 + v[c][0], r2 = r1 + v[c][1], r3 = r2 + v[c][2];
+    if (vec && i + 4 <= n) {
+      *reinterpret_cast<L2*>(out + i) = L2{r0, r1};
+      *reinterpret_cast<L2*>(out + i + 2) = L2{r2, r3};
+    } else {
+      if (i < n) out[i] = r0;
+      if (i + 1 < n) out[i + 1] = r1;
+      if (i + 2 < n) out[i + 2] = r2;
+      if (i + 3 < n) out[i + 3] = r3;
+    }
+  }
 }
 
 template <class T>
-static ah_status scan_impl(const T* in, int64_t* out, int64_t n, hipStream_t st, Arena& tmp) {
+static ah_status scan_impl(const T* in, int64_t* out, int64_t n, hipStream_t st, Arena& tmp, int* vmax) {
+  const int vec = (reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) % 16 == 0;
+  if (n <= 4096) {
+    hipLaunchKernelGGL((k_scan_out<T, 1024, 1>), dim3(1), dim3(1024), 0, st, in, n, vec, (const int64_t*)nullptr, out,
+                       vmax);
+    AH_LAUNCHED();
+    return AH_OK;
+  }
   if (n <= SCAN_ONE) {
-    hipLaunchKernelGGL((k_scan_out<T, 1024>), dim3(1), dim3(1024), 0, st, in, n, (const int64_t*)nullptr, out);
+    hipLaunchKernelGGL((k_scan_out<T, 1024, SCAN_CH>), dim3(1), dim3(1024), 0, st, in, n, vec, (const int64_t*)nullptr, out,
+                       vmax);
     AH_LAUNCHED();
     return AH_OK;
   }
   const bool large = n > 1024 * (int64_t)SCAN_TILE;
   const int64_t nb = cdiv(n, large ? SCAN_ONE : SCAN_TILE);
   int64_t* sums = nullptr;
-  AH_TRY(tmp.get(&sums, nb));
+  AH_TRY(tmp.get(&sums, 2 * nb));
   if (large) {
-    hipLaunchKernelGGL((k_scan_sums<T, 1024>), dim3((unsigned)nb), dim3(1024), 0, st, in, n, sums);
-    hipLaunchKernelGGL((k_scan_out<T, 1024>), dim3((unsigned)nb), dim3(1024), 0, st, in, n, sums, out);
+    hipLaunchKernelGGL((k_scan_sums<T, 1024>), dim3((unsigned)nb), dim3(1024), 0, st, in, n, vec, sums);
+    hipLaunchKernelGGL((k_scan_out<T, 1024, SCAN_CH>), dim3((unsigned)nb), dim3(1024), 0, st, in, n, vec, sums, out, vmax);
   } else {
-    hipLaunchKernelGGL((k_scan_sums<T, 256>), dim3((unsigned)nb), dim3(256), 0, st, in, n, sums);
-    hipLaunchKernelGGL((k_scan_out<T, 256>), dim3((unsigned)nb), dim3(256), 0, st, in, n, sums, out);
+    hipLaunchKernelGGL((k_scan_sums<T, 256>), dim3((unsigned)nb), dim3(256), 0, st, in, n, vec, sums);
+    hipLaunchKernelGGL((k_scan_out<T, 256, SCAN_CH>), dim3((unsigned)nb), dim3(256), 0, st, in, n, vec, sums, out, vmax);
   }
   AH_LAUNCHED();
   return AH_OK;
 }
 
 ah_status scan_i64(const int64_t* in, int64_t* out, int64_t n, hipStream_t st, Arena& tmp) {
-  return scan_impl<int64_t>(in, out, n, st, tmp);
+  return scan_impl<int64_t>(in, out, n, st, tmp, nullptr);
 }
 
-ah_status scan_i32_to_i64(const int32_t* in, int64_t* out, int64_t n, hipStream_t st, Arena& tmp) {
-  return scan_impl<int32_t>(in, out, n, st, tmp);
+ah_status scan_i32_to_i64(const int32_t* in, int64_t* out, int64_t n, hipStream_t st, Arena& tmp, int* vmax) {
+  return scan_impl<int32_t>(in, out, n, st, tmp, vmax);
 }
 
 // Copies the words of up to READ_MAX device values into pinned host memory,
