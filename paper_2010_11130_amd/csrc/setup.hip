@@ -354,6 +354,7 @@ __global__ void k_cf_flags(int64_t n, const int8_t* __restrict__ state, int8_t* 
 // (smallest column) within relative 1e-12 of the maximum.  fsearch = 0
 // (block AIR, whose P comes from the block graph): F rows only listed.
 constexpr int FST_SLOTS = 16;
+constexpr int FALL_SLOTS = 64;   // a lane each in k_fst_sum
 __global__ __launch_bounds__(1024) void k_onepoint(int64_t n, int fsearch, const int64_t* __restrict__ rp,
                                                   const int32_t* __restrict__ ci, const double* __restrict__ v,
                                                   const uint8_t* __restrict__ strong,
@@ -497,9 +498,19 @@ __global__ __launch_bounds__(1024) void k_onepoint(int64_t n, int fsearch, const
   }
 }
 
-// Sums of the parts, a workgroup per level: fst[2 l], fst[2 l + 1].
-__global__ void k_fst_sum(const unsigned long long* __restrict__ parts, unsigned long long* __restrict__ fst) {
+// Sums of the parts: fst[2 l], fst[2 l + 1] by workgroup l, and by the last one
+// the rows without a local system.
+__global__ __launch_bounds__(64) void k_fst_sum(int nlev, const unsigned long long* __restrict__ parts,
+                                                unsigned long long* __restrict__ fst,
+                                                const unsigned long long* __restrict__ falls,
+                                                unsigned long long* __restrict__ nfall) {
   const int l = blockIdx.x, k = threadIdx.x;
+  if (l == nlev) {
+    unsigned long long x = falls[8 * k];
+    for (int o = 32; o > 0; o >>= 1) x += __shfl_xor(x, o, 64);
+    if (k == 0) *nfall = x;
+    return;
+  }
   if (k > 1) return;
   unsigned long long x = 0;
   for (int q = 0; q < FST_SLOTS; ++q) x += parts[(l * FST_SLOTS + q) * 8 + k];
@@ -716,6 +727,229 @@ __device__ bool lu_solve_wave(int m, double* T, double* z, int zs, int nrhs, dou
   return bad;
 }
 
+// Rows without a local system are counted in FALL_SLOTS parts on lines of their
+// own (one counter took 7 ns per such row: most of the time on meshes with many).
+__device__ inline void count_fall(unsigned long long* nfall, unsigned long long k) {
+  atomicAdd(&nfall[8 * (blockIdx.x % FALL_SLOTS)], k);
+}
+
+// Maximum over the G = 8 or 16 lanes of a group of a double >= 0, within the
+// vector registers; as whole numbers such values keep their order.
+template <int G>
+__device__ inline double group_max(double x) {
+  unsigned long long v = (unsigned long long)__double_as_longlong(x);
+#define AH_STEP(ctrl)                                                                             \
+  {                                                                                               \
+    const int lo = __builtin_amdgcn_update_dpp(0, (int)(unsigned)v, ctrl, 0xf, 0xf, false);       \
+    const int hi = __builtin_amdgcn_update_dpp(0, (int)(unsigned)(v >> 32), ctrl, 0xf, 0xf, false); \
+    const unsigned long long y = ((unsigned long long)(unsigned)hi << 32) | (unsigned)lo;         \
+    v = y > v ? y : v;                                                                            \
+  }
+  AH_STEP(0xb1)    // quad_perm [1,0,3,2]
+  AH_STEP(0x4e)    // quad_perm [2,3,0,1]
+  AH_STEP(0x141)   // row_half_mirror
+  if constexpr (G == 16) AH_STEP(0x140)   // row_mirror
+#undef AH_STEP
+  return __longlong_as_double((long long)v);
+}
+
+// lAIR rows with neighbourhoods of at most M = 8 or 16 points (distance one), M
+// lanes per C point: eight or four rows share a wave.  Lane r of a group holds
+// row r of the local system in registers; LU with partial pivoting without row
+// swaps (the pivot is taken among the rows not used yet), the right-hand side
+// carried along, then back substitution by columns: the operations of
+// lu_solve_wave.  The kernel waits on chains of dependent loads (row, strong F
+// points, their rows), so the number of rows in flight is what counts: with a
+// wave per row, a search per entry and the system in LDS the level of 558,750
+// rows (238,412 C points, M = 8) took 297 us, 78 now; one of 14,486,325 (M = 16)
+// 6.9 ms, 3.5 now.
+template <int M>
+__global__ __launch_bounds__(64) void k_lair_group(int64_t nc, const int64_t* __restrict__ rp,
+                                                   const int32_t* __restrict__ ci, const double* __restrict__ v,
+                                                   const uint8_t* __restrict__ strong, const int8_t* __restrict__ cf,
+                                                   const int32_t* __restrict__ clist, const int64_t* __restrict__ Rptr,
+                                                   int32_t* __restrict__ Rcol, double* __restrict__ Rval,
+                                                   unsigned long long* __restrict__ nfall) {
+  constexpr int NQ = 64 / M;   // groups
+  constexpr int S = M + 1;     // row stride of the system in LDS
+  constexpr int U = 32 / M;    // entries per lane loaded together
+  __shared__ int32_t N[NQ][M];
+  __shared__ double T[NQ][M * S], zl[NQ][M];
+  const int lane = threadIdx.x, g = lane % M, q = lane / M;
+  const int64_t ic = (int64_t)blockIdx.x * NQ + q;
+  const bool live = ic < nc;
+  const int64_t i = live ? clist[ic] : 0;
+  const int64_t k0 = live ? rp[i] : 0, k1 = live ? rp[i + 1] : 0;
+  const int64_t out = live ? Rptr[ic] : 0;
+  N[q][g] = -1;
+#pragma unroll
+  for (int c = 0; c < M; ++c) T[q][g * S + c] = 0.0;
+  __syncthreads();
+  // N_i and the right-hand side in row order (columns are sorted)
+  int m = 0;
+  for (int64_t kb = k0; __any(kb < k1); kb += 32) {
+    int32_t c[U];
+    double a[U];
+    bool f[U];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int64_t k = kb + u * M + g;
+      c[u] = 0;
+      a[u] = 0.0;
+      f[u] = false;
+      if (k < k1) {
+        f[u] = strong[k] != 0;
+        c[u] = ci[k];
+        a[u] = v[k];
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < U; ++u) f[u] = f[u] && !cf[c[u]];
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const unsigned mask = (unsigned)(__ballot(f[u]) >> (q * M)) & ((1u << M) - 1u);
+      const int pos = m + __popc(mask & ((1u << g) - 1u));
+      if (f[u] && pos < M) {
+        N[q][pos] = c[u];
+        zl[q][pos] = -a[u];
+      }
+      m += __popc(mask);
+    }
+  }
+  __syncthreads();
+  // m > M cannot occur: the host picks M >= max |N_i|
+  const bool none = live && (m == 0 || m > M);
+  if (none) {
+    if (g == 0) {
+      Rcol[out] = (int32_t)i;
+      Rval[out] = 1.0;
+    }
+    m = 0;
+  }
+  int mmax = m;
+#pragma unroll
+  for (int o = 32; o >= M; o >>= 1) mmax = max(mmax, __shfl_xor(mmax, o, 64));
+  mmax = __builtin_amdgcn_readfirstlane(mmax);
+  int32_t Nr[M];
+#pragma unroll
+  for (int c = 0; c < M; ++c) Nr[c] = N[q][c];
+  // T[c][r] = A[N_r, N_c]: the rows N_r one after the other, the next one's
+  // first entries loaded ahead
+  int64_t s0 = 0;
+  int len = 0;
+  if (g < m) {
+    const int64_t j = N[q][g];
+    s0 = rp[j];
+    len = (int)(rp[j + 1] - s0);
+  }
+  int32_t pc[U];
+  double pa[U];
+  const auto load = [&](int64_t s, int l, int e0) {
+#pragma unroll
+    for (int u = 0; u < U; ++u) {
+      const int e = e0 + u * M + g;
+      pc[u] = -2;
+      pa[u] = 0.0;
+      if (e < l) {
+        pc[u] = ci[s + e];
+        pa[u] = v[s + e];
+      }
+    }
+  };
+  int64_t s = __shfl(s0, 0, M);
+  int l = __shfl(len, 0, M);
+  load(s, l, 0);
+  for (int r = 0; r < mmax; ++r) {
+    const int64_t sn = __shfl(s0, (r + 1) % M, M);
+    const int ln = r + 1 < M ? __shfl(len, (r + 1) % M, M) : 0;
+    for (int e0 = 0;; e0 += 32) {
+      int32_t c[U];
+      double a[U];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        c[u] = pc[u];
+        a[u] = pa[u];
+      }
+      const bool more = __any(e0 + 32 < l);
+      if (more) load(s, l, e0 + 32);
+      else load(sn, ln, 0);
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        int at = -1;
+#pragma unroll
+        for (int x = 0; x < M; ++x) at = c[u] == Nr[x] ? x : at;
+        if (at >= 0) T[q][at * S + r] = a[u];
+      }
+      if (!more) break;
+    }
+    s = sn;
+    l = ln;
+  }
+  __syncthreads();
+  double a[M];
+  double sc = 0.0;
+#pragma unroll
+  for (int c = 0; c < M; ++c) {
+    a[c] = T[q][g * S + c];
+    sc = fmax(sc, fabs(a[c]));
+  }
+  sc = group_max<M>(sc);
+  double z = g < m ? zl[q][g] : 0.0;
+  bool bad = false;
+  int step = g < m ? M : -1;   // the elimination step whose pivot row this is
+  int piv[M];
+#pragma unroll
+  for (int k = 0; k < M; ++k) {
+    piv[k] = 0;
+    if (k >= mmax) continue;
+    const bool open = step == M;
+    const double best = group_max<M>(open && fabs(a[k]) >= 0.0 ? fabs(a[k]) : 0.0);
+    const unsigned at = (unsigned)(__ballot(open && fabs(a[k]) == best) >> (q * M)) & ((1u << M) - 1u);
+    const unsigned any = (unsigned)(__ballot(open) >> (q * M)) & ((1u << M) - 1u);
+    if (k < m) {
+      const int p = __ffs((int)(at ? at : any)) - 1;   // all NaN: any row
+      piv[k] = p;
+    }
+    const int p = piv[k];
+    const double pk = __shfl(a[k], p, M);
+    if (k < m && fabs(pk) <= 1e-14 * sc) bad = true;
+    if (g == p && k < m) step = k;
+    const double f = step == M && k < m ? a[k] / (bad ? 1.0 : pk) : 0.0;
+    const double zp = __shfl(z, p, M);
+#pragma unroll
+    for (int c = k + 1; c < M; ++c) {
+      if (c >= mmax) continue;
+      const double x = __shfl(a[c], p, M);
+      if (step == M) a[c] -= f * x;
+    }
+    if (step == M) z -= f * zp;
+  }
+  double x = 0.0;
+#pragma unroll
+  for (int c = M - 1; c >= 0; --c) {
+    if (c >= mmax) continue;
+    const double zc = __shfl(z / (bad ? 1.0 : a[c]), piv[c], M);
+    if (c >= m) continue;
+    if (g == c) x = zc;
+    if (step >= 0 && step < c) z -= a[c] * zc;
+  }
+  // row in increasing column order: N is sorted, the C point itself is not in N
+  int ins = 0;
+#pragma unroll
+  for (int c = 0; c < M; ++c) ins += c < m && Nr[c] < i;
+  if (g < m) {
+    const int pos = g < ins ? g : g + 1;
+    Rcol[out + pos] = N[q][g];
+    Rval[out + pos] = bad ? 0.0 : x;
+    if (g == 0) {
+      Rcol[out + ins] = (int32_t)i;
+      Rval[out + ins] = 1.0;
+    }
+  }
+  const unsigned long long fall = __ballot(g == 0 && live && (none || bad));
+  if (lane == 0 && fall) count_fall(nfall, (unsigned long long)__popcll(fall));
+}
+
 template <int MAXM, bool D2>
 __global__ __launch_bounds__(64) void k_lair(int64_t nc, const int64_t* __restrict__ rp, const int32_t* __restrict__ ci,
                                              const double* __restrict__ v, const uint8_t* __restrict__ strong,
@@ -773,7 +1007,7 @@ __global__ __launch_bounds__(64) void k_lair(int64_t nc, const int64_t* __restri
     if (lane == 0) {
       Rcol[out] = (int32_t)i;
       Rval[out] = 1.0;
-      atomicAdd(nfall, 1ull);
+      count_fall(nfall, 1ull);
     }
     return;
   }
@@ -797,7 +1031,7 @@ __global__ __launch_bounds__(64) void k_lair(int64_t nc, const int64_t* __restri
   if (lane == 0) {
     Rcol[out + ins] = (int32_t)i;
     Rval[out + ins] = 1.0;
-    if (bad) atomicAdd(nfall, 1ull);
+    if (bad) count_fall(nfall, 1ull);
   }
 }
 
@@ -853,7 +1087,7 @@ __global__ __launch_bounds__(64) void k_lair_blk(int64_t ncb, int b, const int64
       Rcol[out] = (int32_t)(i0 + lane);
       Rval[out] = 1.0;
     }
-    if (lane == 0) atomicAdd(nfall, (unsigned long long)b);
+    if (lane == 0) count_fall(nfall, (unsigned long long)b);
     return;
   }
   for (int k = lane; k < m * m; k += 64) T[k] = 0.0;
@@ -880,7 +1114,7 @@ __global__ __launch_bounds__(64) void k_lair_blk(int64_t ncb, int b, const int64
       Rval[out + ins] = 1.0;
     }
   }
-  if (bad && lane == 0) atomicAdd(nfall, (unsigned long long)b);
+  if (bad && lane == 0) count_fall(nfall, (unsigned long long)b);
 }
 
 // R A P per coarse row with an LDS open-addressing hash on the coarse
@@ -1776,8 +2010,12 @@ __global__ void k_block_pcol(int64_t nbr, int b, const int64_t* __restrict__ opt
 template <int M, bool D2>
 static void lair_launch(int64_t nc, const AhLevel& L, const uint8_t* strong, const int32_t* clist,
                         unsigned long long* nfall, hipStream_t st) {
-  hipLaunchKernelGGL((k_lair<M, D2>), dim3((unsigned)nc), dim3(64), 0, st, nc, L.rowptr, L.col, L.val, strong, L.cf,
-                     clist, L.Rptr, L.Rcol, L.Rval, nfall);
+  if constexpr (!D2 && M <= 16)
+    hipLaunchKernelGGL((k_lair_group<M>), dim3((unsigned)cdiv(nc, 64 / M)), dim3(64), 0, st, nc, L.rowptr, L.col, L.val,
+                       strong, L.cf, clist, L.Rptr, L.Rcol, L.Rval, nfall);
+  else
+    hipLaunchKernelGGL((k_lair<M, D2>), dim3((unsigned)nc), dim3(64), 0, st, nc, L.rowptr, L.col, L.val, strong, L.cf,
+                       clist, L.Rptr, L.Rcol, L.Rval, nfall);
 }
 
 // lAIR restriction rows with local systems of capacity cap (8, 16, 32, 64)
@@ -2766,9 +3004,10 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
   // [2 l], [2 l + 1] per level; [64] level-0 F values in the facet-block layout;
   // flags; the parts of the per-level counts
   constexpr int FST_HEAD = 72;
-  const int64_t nfst = FST_HEAD + 32 * FST_SLOTS * 8;
+  const int64_t nfst = FST_HEAD + 32 * FST_SLOTS * 8 + FALL_SLOTS * 8;
   CK(ar.get(&d_fst, nfst));
   d_ull = d_fst + 66;
+  unsigned long long* d_fall = d_fst + FST_HEAD + 32 * FST_SLOTS * 8;
   d_int = reinterpret_cast<int*>(d_fst + 70);
   CKH(hipMemsetAsync(d_fst, 0, nfst * sizeof(unsigned long long), st));
   // level 0 = the scaled system (shared, not copied)
@@ -2973,9 +3212,9 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
     }
     if (blk && L.ob <= LB_BMAX) {
       CKH(hipMemsetAsync(d_int + 2, 0, sizeof(int), st));
-      CK(lair_blk_dispatch(cap, nc / L.ob, (int)L.ob, L, strong_r, clist, d_ull + 2, d_int + 2, st));
+      CK(lair_blk_dispatch(cap, nc / L.ob, (int)L.ob, L, strong_r, clist, d_fall, d_int + 2, st));
     } else {
-      CK(lair_dispatch(cap, d2, nc, L, strong_r, clist, d_ull + 2, st));
+      CK(lair_dispatch(cap, d2, nc, L, strong_r, clist, d_fall, st));
     }
     CKH(hipGetLastError());
     // R A P
@@ -3139,7 +3378,8 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
   {
     double* pin = pinned_scratch(72);
     if (!pin) { set_error("pinned host allocation failed"); tmp.release(); delete h; return AH_ENOMEM; }
-    hipLaunchKernelGGL(k_fst_sum, dim3((unsigned)h->lev.size()), dim3(64), 0, st, d_fst + FST_HEAD, d_fst);
+    hipLaunchKernelGGL(k_fst_sum, dim3((unsigned)h->lev.size() + 1), dim3(64), 0, st, (int)h->lev.size(), d_fst + FST_HEAD,
+                       d_fst, d_fall, d_ull + 2);
     CKH(hipGetLastError());
     CKH(hipMemcpyAsync(pin, d_fst, 72 * sizeof(unsigned long long), hipMemcpyDeviceToHost, st));
     CKH(hipStreamSynchronize(st));

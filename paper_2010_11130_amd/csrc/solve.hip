@@ -541,14 +541,13 @@ struct EndLevel {
   const int64_t *rp, *Rp;
   const int32_t *ci, *pcol, *Rc;
   const double *v, *d, *Rv;
-  const int8_t* cf;
-  int n, gA, gR;
+  const int32_t* list[2];   // its F and its C points
+  int n, nc, gA, gR;
 };
 constexpr int END_LEVELS = 32;
 struct EndLevels {
   EndLevel lv[END_LEVELS];
 };
-constexpr int END_T = 512;
 
 // Run f(G) with G the compile-time lane count for the runtime value g.
 template <class F>
@@ -562,33 +561,51 @@ __device__ inline void end_with_lanes(int g, F&& f) {
   }
 }
 
-// Row i of a CSR matrix times the NC vectors x (interleaved), the sums in
-// every lane of the group.
-template <int G, int NC>
-__device__ inline void end_row(const int64_t* __restrict__ rp, const int32_t* __restrict__ ci,
-                               const double* __restrict__ av, const double* x, int i, int g, double* s) {
+// f(i, s) for the rows i = row(0) .. row(n - 1) of a CSR matrix, s the row times
+// the NC vectors x (interleaved), in every lane of the row's G lanes; the next
+// row's extent is loaded ahead.
+template <int END_T, int G, int NC, class Row, class F>
+__device__ inline void end_rows(int n, Row&& row, const int64_t* __restrict__ rp, const int32_t* __restrict__ ci,
+                                const double* __restrict__ av, const double* x, F&& f) {
+  const int g = threadIdx.x % G;
+  int ii = threadIdx.x / G;
+  int i = ii < n ? row(ii) : 0;
+  int k = ii < n ? (int)rp[i] : 0, k1 = ii < n ? (int)rp[i + 1] : 0;
+  while (ii < n) {
+    const int in = ii + END_T / G, j = in < n ? row(in) : 0;
+    const int kn = in < n ? (int)rp[j] : 0, kn1 = in < n ? (int)rp[j + 1] : 0;
+    double s[NC];
 #pragma unroll
-  for (int q = 0; q < NC; ++q) s[q] = 0.0;
-  const int k1 = (int)rp[i + 1];
+    for (int q = 0; q < NC; ++q) s[q] = 0.0;
 #pragma unroll 4
-  for (int k = (int)rp[i] + g; k < k1; k += G) {
-    const double v = av[k];
-    const double* xc = x + ci[k] * NC;
+    for (k += g; k < k1; k += G) {
+      const double v = av[k];
+      const double* xc = x + ci[k] * NC;
 #pragma unroll
-    for (int q = 0; q < NC; ++q) s[q] += v * xc[q];
+      for (int q = 0; q < NC; ++q) s[q] += v * xc[q];
+    }
+#pragma unroll
+    for (int o = G / 2; o > 0; o >>= 1)
+#pragma unroll
+      for (int q = 0; q < NC; ++q) s[q] += __shfl_xor(s[q], o, G);
+    f(i, g, s);
+    ii = in;
+    i = j;
+    k = kn;
+    k1 = kn1;
   }
-#pragma unroll
-  for (int o = G / 2; o > 0; o >>= 1)
-#pragma unroll
-    for (int q = 0; q < NC; ++q) s[q] += __shfl_xor(s[q], o, G);
 }
 
 // The matrix of the cycle from level 0 of E down: a workgroup applies the
 // cycle (restrictions, coarsest inverse, one-point interpolation and Jacobi
-// sweeps) to NC columns of the identity, with the vectors in LDS and the
-// levels' matrices from L2, and writes its columns of B (and rows of B^T).
-// Runs once per hierarchy; it replaces the same walk in every cycle.
-template <int NC>
+// sweeps over the F or C points) to NC columns of the identity, with the vectors
+// in LDS and the levels' matrices from L2, and writes its columns of B (and rows
+// of B^T).  Runs once per hierarchy; it replaces the same walk in every cycle.
+// Bound by the latency of the row loads in the one workgroup that a CU's LDS
+// holds, so 16 waves, rows by lists and the next extent ahead: 1956 rows on five
+// levels 322 us with 8 waves over all rows, 228 now.  Where the vectors leave room
+// for two workgroups, 8 waves each (540 rows: 34 us; 47 with 16).
+template <int NC, int END_T>
 __global__ __launch_bounds__(END_T) void k_end_cols(EndLevels E, int nlev, const double* __restrict__ cinv, int nsw,
                                                     double omega, double* __restrict__ B, double* __restrict__ Bt) {
   extern __shared__ double sm[];
@@ -599,8 +616,8 @@ __global__ __launch_bounds__(END_T) void k_end_cols(EndLevels E, int nlev, const
   int tot = 0;
   for (int l = 0; l < nlev; ++l) tot += E.lv[l].n;
   double* const bs = sm;                 // right-hand sides, level after level
-  double* const ys = sm + tot * NC;      // results, likewise
-  double* const xs = ys + tot * NC;      // the other sweep buffer
+  double* const ys = sm + tot * NC;      // the level's result
+  double* const xs = ys + N * NC;        // the other sweep buffer
   for (int k = t; k < N * NC; k += END_T) bs[k] = k / NC == j0 + k % NC ? 1.0 : 0.0;
   __syncthreads();
   int at = 0;
@@ -611,14 +628,11 @@ __global__ __launch_bounds__(END_T) void k_end_cols(EndLevels E, int nlev, const
     double* cb = bs + (at + L.n) * NC;
     end_with_lanes(L.gR, [&](auto GC) {
       constexpr int G = decltype(GC)::value;
-      const int g = t % G;
-      for (int i = t / G; i < nc; i += END_T / G) {
-        double s[NC];
-        end_row<G, NC>(L.Rp, L.Rc, L.Rv, b, i, g, s);
+      end_rows<END_T, G, NC>(nc, [](int i) { return i; }, L.Rp, L.Rc, L.Rv, b, [&](int i, int g, const double* s) {
         if (g == 0)
 #pragma unroll
           for (int q = 0; q < NC; ++q) cb[i * NC + q] = s[q];
-      }
+      });
     });
     __syncthreads();
     at += L.n;
@@ -626,7 +640,6 @@ __global__ __launch_bounds__(END_T) void k_end_cols(EndLevels E, int nlev, const
   {
     const int nL = E.lv[last].n;
     const double* b = bs + at * NC;
-    double* y = ys + at * NC;
     for (int i = t / 8; i < nL; i += END_T / 8) {
       double s[NC];
 #pragma unroll
@@ -642,45 +655,47 @@ __global__ __launch_bounds__(END_T) void k_end_cols(EndLevels E, int nlev, const
         for (int q = 0; q < NC; ++q) s[q] += __shfl_xor(s[q], o, 8);
       if (t % 8 == 0)
 #pragma unroll
-        for (int q = 0; q < NC; ++q) y[i * NC + q] = s[q];
+        for (int q = 0; q < NC; ++q) ys[i * NC + q] = s[q];
     }
     __syncthreads();
   }
-  // up: x = P e_c, then the sweeps x -> y (-> x -> y)
+  // up: x = P e_c, then the sweeps x -> y (-> x -> y); a sweep's other points
+  // are in both buffers already where the sweep before was over the same list
   for (int l = last - 1; l >= 0; --l) {
     const EndLevel& L = E.lv[l];
-    const double* ec = ys + at * NC;
     at -= L.n;
     const double* b = bs + at * NC;
     double* cur = xs;
-    double* dst = ys + at * NC;
+    double* dst = ys;
     for (int i = t; i < L.n; i += END_T) {
       const int c = L.pcol[i];
 #pragma unroll
-      for (int q = 0; q < NC; ++q) cur[i * NC + q] = c >= 0 ? ec[c * NC + q] : 0.0;
+      for (int q = 0; q < NC; ++q) cur[i * NC + q] = c >= 0 ? ys[c * NC + q] : 0.0;
     }
     __syncthreads();
     for (int w = 0; w < nsw; ++w) {
       const int X = (nsw == 1 || w < 2) ? 0 : 1;
+      const int32_t* mine = L.list[X];
+      const int nX = X ? L.nc : L.n - L.nc, nO = L.n - nX;
+      if (w != 1)
+        for (int ii = t; ii < nO; ii += END_T) {
+          const int i = L.list[!X][ii];
+#pragma unroll
+          for (int q = 0; q < NC; ++q) dst[i * NC + q] = cur[i * NC + q];
+        }
       end_with_lanes(L.gA, [&](auto GC) {
         constexpr int G = decltype(GC)::value;
-        const int g = t % G;
-        for (int i = t / G; i < L.n; i += END_T / G) {
-          double x[NC];
+        end_rows<END_T, G, NC>(nX, [&](int ii) { return mine[ii]; }, L.rp, L.ci, L.v, cur,
+                        [&](int i, int g, const double* s) {
+                          if (g != 0) return;
+                          const double d = L.d[i];
 #pragma unroll
-          for (int q = 0; q < NC; ++q) x[q] = cur[i * NC + q];
-          if (L.cf[i] == X) {
-            const double d = L.d[i];
-            double s[NC];
-            end_row<G, NC>(L.rp, L.ci, L.v, cur, i, g, s);
-            if (fabs(d) >= 1e-30)
-#pragma unroll
-              for (int q = 0; q < NC; ++q) x[q] += omega * (b[i * NC + q] - s[q]) / d;
-          }
-          if (g == 0)
-#pragma unroll
-            for (int q = 0; q < NC; ++q) dst[i * NC + q] = x[q];
-        }
+                          for (int q = 0; q < NC; ++q) {
+                            double x = cur[i * NC + q];
+                            if (fabs(d) >= 1e-30) x += omega * (b[i * NC + q] - s[q]) / d;
+                            dst[i * NC + q] = x;
+                          }
+                        });
       });
       __syncthreads();
       double* const o = cur;
@@ -1376,7 +1391,7 @@ static double rz_bytes(const AhLevel& L) {
 static int64_t end_lds(const ah_hier* h, int l0) {
   int64_t tot = 0;
   for (size_t l = l0; l < h->lev.size(); ++l) tot += h->lev[l].n;
-  return (2 * tot + h->lev[l0].n) * (int64_t)sizeof(double);
+  return (tot + 2 * h->lev[l0].n) * (int64_t)sizeof(double);
 }
 
 constexpr int64_t END_LDS_MAX = 160 * 1024;
@@ -1401,12 +1416,12 @@ __global__ void k_dense_transpose(int n, const double* __restrict__ A, double* _
   if (k < (int64_t)n * n) At[(k % n) * n + k / n] = A[k];
 }
 
-// Lanes per row for n rows of mean length avg in a workgroup of END_T.
-static int end_lanes(int64_t n, int64_t nnz) {
+// Lanes per row for n rows of mean length avg in a workgroup of nt threads.
+static int end_lanes(int64_t n, int64_t nnz, int nt) {
   const int64_t avg = n ? nnz / n : 1;
   int g = 1;
   while (g < 16 && 4 * g < avg) g *= 2;
-  while (g < 16 && 2 * g * n <= END_T && g < avg) g *= 2;
+  while (g < 16 && 2 * g * n <= nt && g < avg) g *= 2;
   return g;
 }
 
@@ -1424,29 +1439,32 @@ ah_status coarse_end_build(ah_hier* h, hipStream_t st) {
     }
   } else {
     AH_TRY(h->arena.get(&B, n * n));
+    const int64_t lds = end_lds(h, l0);
+    const int cols = 2 * lds <= END_LDS_MAX ? 2 : 1;
+    const int nt = 2 * cols * lds <= END_LDS_MAX ? 512 : 1024;
     EndLevels E{};
     for (int l = l0; l < nl; ++l) {
       const AhLevel& L = h->lev[l];
       EndLevel& e = E.lv[l - l0];
-      e.rp = L.rowptr; e.ci = L.col; e.v = L.val; e.d = L.diag; e.cf = L.cf; e.pcol = L.pcol;
+      e.rp = L.rowptr; e.ci = L.col; e.v = L.val; e.d = L.diag; e.pcol = L.pcol;
+      e.list[0] = L.flist; e.list[1] = L.clist;
       e.Rp = L.Rptr; e.Rc = L.Rcol; e.Rv = L.Rval;
       e.n = (int)L.n;
-      e.gA = end_lanes(L.n, L.nnz);
-      e.gR = l + 1 < nl ? end_lanes(L.nc, L.nnzR) : 1;
+      e.nc = (int)L.nc;
+      e.gA = end_lanes(L.n, L.nnz, nt);
+      e.gR = l + 1 < nl ? end_lanes(L.nc, L.nnzR, nt) : 1;
     }
     const int nsw = h->prm.relax == 1 ? 1 : 3;
+    const auto k = cols == 2 ? (nt == 512 ? k_end_cols<2, 512> : k_end_cols<2, 1024>)
+                             : (nt == 512 ? k_end_cols<1, 512> : k_end_cols<1, 1024>);
     static std::once_flag once;
     std::call_once(once, [] {
-      (void)hipFuncSetAttribute((const void*)k_end_cols<1>, hipFuncAttributeMaxDynamicSharedMemorySize, END_LDS_MAX);
-      (void)hipFuncSetAttribute((const void*)k_end_cols<2>, hipFuncAttributeMaxDynamicSharedMemorySize, END_LDS_MAX);
+      for (const void* f : {(const void*)k_end_cols<1, 512>, (const void*)k_end_cols<2, 512>,
+                            (const void*)k_end_cols<1, 1024>, (const void*)k_end_cols<2, 1024>})
+        (void)hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, END_LDS_MAX);
     });
-    const int64_t lds = end_lds(h, l0);
-    if (2 * lds <= END_LDS_MAX)
-      hipLaunchKernelGGL(k_end_cols<2>, dim3((unsigned)cdiv(n, 2)), dim3(END_T), (unsigned)(2 * lds), st, E, nl - l0,
-                         h->cinv, nsw, h->prm.omega, B, Bt);
-    else
-      hipLaunchKernelGGL(k_end_cols<1>, dim3((unsigned)n), dim3(END_T), (unsigned)lds, st, E, nl - l0, h->cinv, nsw,
-                         h->prm.omega, B, Bt);
+    hipLaunchKernelGGL(k, dim3((unsigned)cdiv(n, cols)), dim3(nt), (unsigned)(cols * lds), st, E, nl - l0, h->cinv,
+                       nsw, h->prm.omega, B, Bt);
     AH_LAUNCHED();
     h->end_mat = B;
   }
