@@ -40,13 +40,15 @@ __device__ inline uint64_t hash44(uint64_t i, int level) {
 // entries stay in registers between the two (a row is read once, its loads
 // issued together).  Where infl is given (for the coarsening), also counts the
 // rows that depend on each point and packs the row's strong columns at
-// adj[rp[i]], na[i] of them: the coarsening then reads those only.
+// adj[rp[i]], na[i] of them: the coarsening then reads those only.  Where dg is
+// given, also the row's diagonal entry (zero if it has none).
 constexpr int SG = 16;
 __global__ __launch_bounds__(256) void k_strength(int64_t n, const int64_t* __restrict__ rp,
                                                   const int32_t* __restrict__ ci, const double* __restrict__ v,
                                                   double theta, uint8_t* __restrict__ strong,
                                                   int32_t* __restrict__ infl, int32_t* __restrict__ adj,
-                                                  int32_t* __restrict__ na) {
+                                                  int32_t* __restrict__ na, double* __restrict__ dg,
+                                                  float* __restrict__ dg32) {
   constexpr int Q = 4;
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t i = gid / SG;
@@ -61,9 +63,26 @@ __global__ __launch_bounds__(256) void k_strength(int64_t n, const int64_t* __re
     a[q] = 0.0;
     if (k0 + q * SG < k1) {
       c[q] = ci[k0 + q * SG];
-      a[q] = fabs(v[k0 + q * SG]);
+      a[q] = v[k0 + q * SG];
     }
   }
+  const int sh = (threadIdx.x & 63) & ~(SG - 1);
+  if (dg) {
+    bool hit = false;
+    double x = 0.0;
+#pragma unroll
+    for (int q = 0; q < Q; ++q)
+      if (c[q] == i) { x = a[q]; hit = true; }
+    for (int64_t k = k0 + Q * SG; k < k1; k += SG)
+      if (ci[k] == i) { x = v[k]; hit = true; }
+    const unsigned mk = (unsigned)(__ballot(hit) >> sh) & ((1u << SG) - 1u);
+    if (hit || (!mk && g == 0)) {
+      dg[i] = x;
+      if (dg32) dg32[i] = (float)x;
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < Q; ++q) a[q] = fabs(a[q]);
   double m = 0.0;
 #pragma unroll
   for (int q = 0; q < Q; ++q)
@@ -72,7 +91,6 @@ __global__ __launch_bounds__(256) void k_strength(int64_t n, const int64_t* __re
     if (ci[k] != i) m = fmax(m, fabs(v[k]));
   for (int o = SG / 2; o > 0; o >>= 1) m = fmax(m, __shfl_xor(m, o, SG));
   const double thr = theta * m * (1.0 - 1e-12);
-  const int sh = (threadIdx.x & 63) & ~(SG - 1);
   int at = 0;
   const auto mark = [&](int64_t k, int32_t col, bool here, bool sflag) {
     if (here) strong[k] = sflag;
@@ -194,12 +212,14 @@ __global__ __launch_bounds__(256) void k_pmis_mark(int64_t n, const int64_t* __r
   if (__syncthreads_or(undecided) && threadIdx.x == 0) *left = 1ull;
 }
 
-// Every PMIS round of a small level in one workgroup, phases separated by
-// barriers; the same rounds as k_pmis_beat / k_pmis_mark, so the same splitting.
+// The coarsening of a small level in one workgroup, phases separated by barriers:
+// the start of k_pmis_init, the same rounds as k_pmis_beat / k_pmis_mark, so the same splitting.
 // Keys, marks and the lists of strong columns (16 bits each) are copied to LDS
 // first, lists too long for it stay in global memory.  A thread owns the rows
 // threadIdx.x + 1024 q.  A decided point's key becomes 1 (C) or 2 (F), below
-// every undecided key.  The
+// every undecided key.  Where cf is given, the result goes there with what
+// k_cf_flags and the scan of its flags would leave (cidx[0 .. n], cleared rcnt
+// and imax): three launches fewer per level.  The
 // rounds wait on LDS and barriers: 64 us at 5,253 rows, 82 at 3,914 (128 and 176
 // with maxima by atomics and the lists packed here from the rows' flags).
 // *err is set if the rounds exceed n + 1 (cannot happen: the largest undecided
@@ -209,12 +229,15 @@ constexpr int PMIS_LDS = 160 * 1024 - 1024;
 
 __global__ __launch_bounds__(1024) void k_pmis_wg(int n, const int64_t* __restrict__ rp,
                                                   const int32_t* __restrict__ adj_g, const int32_t* __restrict__ na,
-                                                  const uint64_t* __restrict__ key_g, int8_t* __restrict__ state_g,
-                                                  unsigned long long* __restrict__ err, int lds) {
+                                                  const int32_t* __restrict__ infl, int level,
+                                                  int8_t* __restrict__ state_g, unsigned long long* __restrict__ err,
+                                                  int lds, int8_t* __restrict__ cf, int64_t* __restrict__ cidx,
+                                                  int32_t* __restrict__ rcnt, int* __restrict__ imax) {
   extern __shared__ __align__(16) unsigned long long pm[];
   __shared__ int wsum[16];
   constexpr unsigned long long OPEN = 1ull << 44;   // keys of undecided points start here
   constexpr int Q = PMIS_WG_MAX / 1024;
+  __shared__ int cw[Q * 16];   // C points per wave and row of its threads
   unsigned long long* key = pm;
   int32_t* off = reinterpret_cast<int32_t*>(pm + n);            // [n + 1]
   uint16_t* adj = reinterpret_cast<uint16_t*>(off + n + 1);
@@ -227,12 +250,10 @@ __global__ __launch_bounds__(1024) void k_pmis_wg(int n, const int64_t* __restri
     at[q] = 0;
     m[q] = 0;
     if (i < n) {
-      const bool open = state_g[i] == 0;
-      const uint64_t k = key_g[i];
-      const int32_t c = na[i];
+      const int32_t f = infl[i], c = na[i];
       at[q] = rp[i];
-      m[q] = open ? c : 0;
-      key[i] = open ? k : 2ull;
+      m[q] = f ? c : 0;
+      key[i] = f ? ((unsigned long long)f << 44) | hash44((uint64_t)i, level) : 2ull;
       off[i] = m[q];
     }
   }
@@ -324,8 +345,43 @@ __global__ __launch_bounds__(1024) void k_pmis_wg(int n, const int64_t* __restri
     }
     if (!__syncthreads_or(undecided)) break;
   }
-  for (int i = t; i < n; i += 1024) state_g[i] = key[i] == 1ull ? 1 : 2;
+  if (!cf) {
+    for (int i = t; i < n; i += 1024) state_g[i] = key[i] == 1ull ? 1 : 2;
+    return;
+  }
+  int below[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int i = t + 1024 * q;
+    const unsigned long long b = __ballot(i < n && key[i] == 1ull);
+    below[q] = __popcll(b & ((1ull << (t & 63)) - 1ull));
+    if ((t & 63) == 0) cw[q * 16 + (t >> 6)] = __popcll(b);
+  }
+  __syncthreads();
+  if (t < 64) {
+    const int a = cw[2 * t], b = cw[2 * t + 1];
+    int s = a + b;
+    for (int o = 1; o < 64; o <<= 1) {
+      const int u = __shfl_up(s, o, 64);
+      s += t >= o ? u : 0;
+    }
+    cw[2 * t] = s - a - b;
+    cw[2 * t + 1] = s - b;
+    if (t == 63) cidx[n] = s;
+  }
+  __syncthreads();
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int i = t + 1024 * q;
+    if (i >= n) break;
+    cf[i] = key[i] == 1ull;
+    cidx[i] = cw[q * 16 + (t >> 6)] + below[q];
+  }
+  if (rcnt)
+    for (int i = t; i <= n; i += 1024) rcnt[i] = 0;
+  if (t < 4) imax[t] = 0;
 }
+static_assert(PMIS_WG_MAX / 1024 * 16 == 128, "two counts per lane of the first wave");
 
 // C/F marks and flags; also clears the row counts rcnt[0..n] (where given) and
 // the level's four maxima.
@@ -2104,11 +2160,12 @@ static int64_t pmis_list_min() {
 // PMIS C/F splitting of the graph of the strong entries (row i's columns at
 // adj[rp[i]], na[i] of them): state[i] = 1 (C) or 2 (F).  key holds n entries of
 // scratch, beaten 2 n; flags are the two round flags, flags[3] the error flag.
+// Where cf is given and one workgroup does it all, cf, cidx, rcnt and imax are
+// written instead of the states (k_pmis_wg) and *numbered is set.
 static ah_status pmis_split(int64_t n, const int64_t* rp, const int32_t* adj, const int32_t* na,
                             const int32_t* infl, int level, uint64_t* key, uint8_t* beaten, int8_t* state,
-                            unsigned long long* flags, hipStream_t st) {
-  hipLaunchKernelGGL(k_pmis_init, g1(n), dim3(256), 0, st, n, infl, level, key, state, beaten);
-  AH_HIP(hipGetLastError());
+                            unsigned long long* flags, hipStream_t st, int8_t* cf, int64_t* cidx, int32_t* rcnt,
+                            int* imax, bool* numbered) {
   const char* wg_env = std::getenv("AH_PMIS_WG_MAX");   // at most PMIS_WG_MAX (its LDS size)
   const int64_t wg_max = wg_env ? std::min<int64_t>(std::atoll(wg_env), PMIS_WG_MAX) : (int64_t)PMIS_WG_MAX;
   if (n <= wg_max) {
@@ -2119,10 +2176,14 @@ static ah_status pmis_split(int64_t n, const int64_t* rp, const int32_t* adj, co
     });
     // 14 bytes per row, and lists of 16 columns on average
     const int lds = (int)std::min<int64_t>(PMIS_LDS, 46 * n + 64);
-    hipLaunchKernelGGL(k_pmis_wg, dim3(1), dim3(1024), lds, st, (int)n, rp, adj, na, key, state, flags + 3, lds);
+    hipLaunchKernelGGL(k_pmis_wg, dim3(1), dim3(1024), lds, st, (int)n, rp, adj, na, infl, level, state,
+                       flags + 3, lds, cf, cidx, rcnt, imax);
     AH_HIP(hipGetLastError());
+    *numbered = cf != nullptr;
     return AH_OK;
   }
+  hipLaunchKernelGGL(k_pmis_init, g1(n), dim3(256), 0, st, n, infl, level, key, state, beaten);
+  AH_HIP(hipGetLastError());
   const auto mark = [&](int round, int64_t nl, const int32_t* list, const int64_t* nd) {
     unsigned long long* left_d = flags + (round & 1);
     uint8_t* now = beaten + (round & 1) * n;
@@ -3054,15 +3115,21 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
     uint64_t* key = nullptr;
     uint8_t* beaten = nullptr;
     if (!coarsest && (blk || prm.coarsening != 1)) {
-      CK(tmp.get(&infl, ng));
+      // below level 0 the level's x, cleared with its row pointers
+      if (l == 0) CK(tmp.get(&infl, ng));
+      else infl = reinterpret_cast<int32_t*>(L.x);
       CK(tmp.get(&adj, blk ? (int64_t)s->mesh->odb_col.size() : L.nnz));
       CK(tmp.get(&na, ng));
       CK(tmp.get(&key, ng));
       CK(tmp.get(&beaten, 2 * ng));
+      if (l == 0 && !blk) CKH(hipMemsetAsync(infl, 0, ng * sizeof(int32_t), st));
     }
-    hipLaunchKernelGGL(k_diag, g1(n * PG), dim3(256), 0, st, n, L.rowptr, L.col, L.val, L.diag, L.diag32, ng, infl);
-    CKH(hipGetLastError());
-    CK(ar.get(&L.b, n)); CK(ar.get(&L.x, n)); CK(ar.get(&L.y, n)); CK(ar.get(&L.e, n));
+    if (coarsest || blk) {   // elsewhere the strength kernel finds the diagonal
+      hipLaunchKernelGGL(k_diag, g1(n * PG), dim3(256), 0, st, n, L.rowptr, L.col, L.val, L.diag, L.diag32, ng, infl);
+      CKH(hipGetLastError());
+    }
+    CK(ar.get(&L.b, n)); CK(ar.get(&L.y, n)); CK(ar.get(&L.e, n));
+    if (l == 0) CK(ar.get(&L.x, n));
     if (prm.fp32_cycle) {
       CK(ar.get(&L.b32, n)); CK(ar.get(&L.x32, n)); CK(ar.get(&L.y32, n)); CK(ar.get(&L.e32, n));
     }
@@ -3073,6 +3140,13 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
     int8_t* state = nullptr;
     CK(tmp.get(&strong, L.nnz));
     CK(tmp.get(&state, n));
+    int64_t* cidx = nullptr;
+    int32_t* rcnt = nullptr;
+    const bool d2 = prm.lair_distance == 2;
+    bool numbered = false;   // cf, cidx and the cleared counts are there already
+    CK(ar.get(&L.cf, n));
+    CK(tmp.get(&cidx, n + 1));
+    if (!d2) CK(tmp.get(&rcnt, n + 1));
     if (blk) {
       const int64_t nslot = (int64_t)s->mesh->odb_col.size();
       int8_t* sbstate = nullptr;
@@ -3081,15 +3155,16 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
       CK(tmp.get(&sbstate, nbr));
       hipLaunchKernelGGL(k_block_weights, g1(nbr * SG), dim3(256), 0, st, nbr, (int)L.ob, L.optr, L.oval, bw);
       hipLaunchKernelGGL(k_strength, g1(nbr * SG), dim3(256), 0, st, nbr, L.optr, L.ocol, bw, prm.theta, sb, infl,
-                         adj, na);
+                         adj, na, (double*)nullptr, (float*)nullptr);
       CKH(hipGetLastError());
-      CK(pmis_split(nbr, L.optr, adj, na, infl, l, key, beaten, sbstate, d_ull, st));
+      CK(pmis_split(nbr, L.optr, adj, na, infl, l, key, beaten, sbstate, d_ull, st, nullptr, nullptr, nullptr,
+                    nullptr, &numbered));
       hipLaunchKernelGGL(k_block_expand, g1(n), dim3(256), 0, st, n, (int)L.ob, sbstate, state);
       uint8_t* sbr = sb;
       if (prm.theta_r > 0.0 && prm.theta_r != prm.theta) {
         CK(tmp.get(&sbr, nslot));
         hipLaunchKernelGGL(k_strength, g1(nbr * SG), dim3(256), 0, st, nbr, L.optr, L.ocol, bw, prm.theta_r, sbr,
-                           (int32_t*)nullptr, (int32_t*)nullptr, (int32_t*)nullptr);
+                           (int32_t*)nullptr, (int32_t*)nullptr, (int32_t*)nullptr, (double*)nullptr, (float*)nullptr);
       }
       hipLaunchKernelGGL(k_block_mask, g1(n * PG), dim3(256), 0, st, n, (int)L.ob, L.rowptr, L.col, L.optr, L.ocol,
                          sbr, strong);
@@ -3097,7 +3172,7 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
     } else {
     // strength
     hipLaunchKernelGGL(k_strength, g1(n * SG), dim3(256), 0, st, n, L.rowptr, L.col, L.val, prm.theta, strong, infl,
-                       adj, na);
+                       adj, na, L.diag, L.diag32);
     CKH(hipGetLastError());
     // PMIS
     if (prm.coarsening == 1) {
@@ -3114,21 +3189,17 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
       CKH(hipMemcpyAsync(state, hstate.data(), n, hipMemcpyHostToDevice, st));
       CKH(hipStreamSynchronize(st));
     } else {
-      CK(pmis_split(n, L.rowptr, adj, na, infl, l, key, beaten, state, d_ull, st));
+      CK(pmis_split(n, L.rowptr, adj, na, infl, l, key, beaten, state, d_ull, st, L.cf, cidx, rcnt, d_int, &numbered));
     }
     }
     // coarse numbering
-    int32_t* isc = nullptr;
-    int64_t* cidx = nullptr;
-    int32_t* rcnt = nullptr;
-    const bool d2 = prm.lair_distance == 2;
-    CK(ar.get(&L.cf, n));
-    CK(tmp.get(&isc, n));
-    CK(tmp.get(&cidx, n + 1));
-    if (!d2) CK(tmp.get(&rcnt, n + 1));
-    hipLaunchKernelGGL(k_cf_flags, g1(n + 4), dim3(256), 0, st, n, state, L.cf, isc, rcnt, d_int);
-    CKH(hipGetLastError());
-    CK(scan_i32_to_i64(isc, cidx, n, st, tmp));
+    if (!numbered) {
+      int32_t* isc = nullptr;
+      CK(tmp.get(&isc, n));
+      hipLaunchKernelGGL(k_cf_flags, g1(n + 4), dim3(256), 0, st, n, state, L.cf, isc, rcnt, d_int);
+      CKH(hipGetLastError());
+      CK(scan_i32_to_i64(isc, cidx, n, st, tmp));
+    }
     int64_t nc = 0;
     // distance one: the point lists and R's row counts are sized for n, and
     // the C-point count is read back together with R's size (one host sync
@@ -3150,7 +3221,7 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
     if (!blk && prm.theta_r > 0.0 && prm.theta_r != prm.theta) {
       CK(tmp.get(&strong_r, L.nnz));
       hipLaunchKernelGGL(k_strength, g1(n * SG), dim3(256), 0, st, n, L.rowptr, L.col, L.val, prm.theta_r, strong_r,
-                         (int32_t*)nullptr, (int32_t*)nullptr, (int32_t*)nullptr);
+                         (int32_t*)nullptr, (int32_t*)nullptr, (int32_t*)nullptr, (double*)nullptr, (float*)nullptr);
       CKH(hipGetLastError());
     }
     hipLaunchKernelGGL(k_onepoint, dim3((unsigned)std::min<int64_t>(cdiv(n, 1024 / PG), 512)), dim3(1024), 0, st, n,
@@ -3176,11 +3247,11 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
       CKH(hipGetLastError());
     }
     CK(ar.get(&L.Rptr, ncap + 1));
-    CK(scan_i32_to_i64(rcnt, L.Rptr, ncap, st, tmp, d_int));   // and the longest row of R
-    int hmax[4];
-    CK(read_values({{L.Rptr + ncap, &L.nnzR, sizeof(int64_t)},
-                    {d_int, hmax, sizeof(hmax)},
-                    {cidx + n, &nc, sizeof(int64_t)}}, st));
+    int hmax[4];   // [0] from the scan: the longest row of R
+    CK(scan_i32_read(rcnt, L.Rptr, ncap, st, tmp, d_int, nullptr,
+                     {{L.Rptr + ncap, &L.nnzR, sizeof(int64_t)},
+                      {d_int, hmax, sizeof(hmax)},
+                      {cidx + n, &nc, sizeof(int64_t)}}));
     if (!d2 && (nc == 0 || (double)nc > prm.stall * (double)n)) {
       // coarsening stalled: this level is the coarsest
       L.pcol = nullptr;
@@ -3233,13 +3304,14 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
     if (rblk) CK(rap_blk_dispatch(hsb, (int)L.ob, false, nc / L.ob, L, clist, ccnt, nullptr, nullptr, nullptr, st));
     else CK(rap_dispatch(hs, nc, L, ccnt, nullptr, nullptr, nullptr, false, st));
     CK(ar.get(&C.rowptr, nc + 1));
-    CK(scan_i32_to_i64(ccnt, C.rowptr, nc, st, tmp, d_int + 3));
+    CK(ar.get(&C.x, nc));   // cleared: the next level's counts of dependent rows
     // the numeric pass hashes a row's distinct coarse columns only: size its
     // table from the largest row of A_c
     int rmax = 0;
     {
       int e2[2];
-      CK(read_values({{C.rowptr + nc, &C.nnz, sizeof(int64_t)}, {d_int + 2, e2, sizeof(e2)}}, st));
+      CK(scan_i32_read(ccnt, C.rowptr, nc, st, tmp, d_int + 3, reinterpret_cast<int32_t*>(C.x),
+                       {{C.rowptr + nc, &C.nnz, sizeof(int64_t)}, {d_int + 2, e2, sizeof(e2)}}));
       rmax = e2[1];
       if (blk && e2[0]) {
         set_error("air_setup: rows of a facet block differ in their block AIR neighbourhood");

@@ -64,6 +64,10 @@ struct ReadItem {
   size_t bytes;
 };
 ah_status read_values(std::initializer_list<ReadItem> items, hipStream_t st);
+// scan_i32_to_i64 (zero, where given: n values cleared on the way) and then
+// read_values, one launch where one workgroup does the scan.
+ah_status scan_i32_read(const int32_t* in, int64_t* out, int64_t n, hipStream_t st, Arena& tmp, int* vmax,
+                        int32_t* zero, std::initializer_list<ReadItem> items);
 ah_status read_i64(const int64_t* d, int64_t* h, hipStream_t st);
 ah_status read_bytes(const void* d, void* h, size_t bytes, hipStream_t st);
 // Wait until the pinned flag holds seq; AH_EHIP if the stream ends without it.

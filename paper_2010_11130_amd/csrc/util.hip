@@ -6,6 +6,30 @@
 
 namespace ah {
 
+// The words of up to READ_MAX device values for pinned host memory, and then seq
+// for the flag that the host polls; flag null: nothing.
+constexpr int READ_MAX = 6;
+constexpr int READ_WORDS = 16;
+struct ReadArgs {
+  const uint32_t* src[READ_MAX];
+  int words[READ_MAX];
+  uint32_t* host;
+  unsigned long long* flag;
+  unsigned long long seq;
+};
+
+// The copy, by the workgroup's first wave: one wave's stores and one fence (a
+// fence by each of 16 waves took 8 us).
+__device__ inline void read_out(const ReadArgs& a) {
+  if (threadIdx.x >= 64) return;
+  for (int x = threadIdx.x; x < READ_MAX * READ_WORDS; x += 64) {
+    const int v = x / READ_WORDS, w = x % READ_WORDS;
+    if (w < a.words[v]) a.host[x] = a.src[v][w];
+  }
+  __threadfence_system();
+  if (threadIdx.x == 0) __hip_atomic_store(a.flag, a.seq, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_SYSTEM);
+}
+
 // Exclusive prefix sums in at most two launches: SCAN_PER values per thread, a
 // tile per workgroup.  Up to one large tile a single workgroup does it all;
 // beyond, the tiles' sums come first and every workgroup of the second launch
@@ -92,10 +116,13 @@ __global__ __launch_bounds__(NT) void k_scan_sums(const T* __restrict__ in, int6
 
 // The tile's prefix sums; sums null: a single tile.  The last tile also writes
 // the total to out[n] and, where vmax is given, the largest value (at least 0).
+// zero (or null): n values cleared on the way.  A single tile can also hand
+// values to the host when it is done, its own among them.
 template <class T, int NT, int CH>
 __global__ __launch_bounds__(NT) void k_scan_out(const T* __restrict__ in, int64_t n, int vec,
                                                  const int64_t* __restrict__ sums, int64_t* __restrict__ out,
-                                                 int* __restrict__ vmax) {
+                                                 int* __restrict__ vmax, int32_t* __restrict__ zero,
+                                                 ReadArgs rd) {
   constexpr int W = NT / 64;
   __shared__ int64_t red[2][W], part[CH * W];
   typedef long L2 __attribute__((ext_vector_type(2)));
@@ -171,21 +198,31 @@ __global__ __launch_bounds__(NT) void k_scan_out(const T* __restrict__ in, int64
       if (i + 2 < n) out[i + 2] = r2;
       if (i + 3 < n) out[i + 3] = r3;
     }
+    if (zero) {
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+        if (i + q < n) zero[i + q] = 0;
+    }
+  }
+  if (rd.flag) {
+    __syncthreads();   // total and largest value, written by the first wave too
+    read_out(rd);
   }
 }
 
 template <class T>
-static ah_status scan_impl(const T* in, int64_t* out, int64_t n, hipStream_t st, Arena& tmp, int* vmax) {
+static ah_status scan_impl(const T* in, int64_t* out, int64_t n, hipStream_t st, Arena& tmp, int* vmax, int32_t* zero,
+                           const ReadArgs& rd) {
   const int vec = (reinterpret_cast<uintptr_t>(in) | reinterpret_cast<uintptr_t>(out)) % 16 == 0;
   if (n <= 4096) {
     hipLaunchKernelGGL((k_scan_out<T, 1024, 1>), dim3(1), dim3(1024), 0, st, in, n, vec, (const int64_t*)nullptr, out,
-                       vmax);
+                       vmax, zero, rd);
     AH_LAUNCHED();
     return AH_OK;
   }
   if (n <= SCAN_ONE) {
     hipLaunchKernelGGL((k_scan_out<T, 1024, SCAN_CH>), dim3(1), dim3(1024), 0, st, in, n, vec, (const int64_t*)nullptr, out,
-                       vmax);
+                       vmax, zero, rd);
     AH_LAUNCHED();
     return AH_OK;
   }
@@ -195,40 +232,26 @@ static ah_status scan_impl(const T* in, int64_t* out, int64_t n, hipStream_t st,
   AH_TRY(tmp.get(&sums, 2 * nb));
   if (large) {
     hipLaunchKernelGGL((k_scan_sums<T, 1024>), dim3((unsigned)nb), dim3(1024), 0, st, in, n, vec, sums);
-    hipLaunchKernelGGL((k_scan_out<T, 1024, SCAN_CH>), dim3((unsigned)nb), dim3(1024), 0, st, in, n, vec, sums, out, vmax);
+    hipLaunchKernelGGL((k_scan_out<T, 1024, SCAN_CH>), dim3((unsigned)nb), dim3(1024), 0, st, in, n, vec, sums, out, vmax,
+                       zero, rd);
   } else {
     hipLaunchKernelGGL((k_scan_sums<T, 256>), dim3((unsigned)nb), dim3(256), 0, st, in, n, vec, sums);
-    hipLaunchKernelGGL((k_scan_out<T, 256, SCAN_CH>), dim3((unsigned)nb), dim3(256), 0, st, in, n, vec, sums, out, vmax);
+    hipLaunchKernelGGL((k_scan_out<T, 256, SCAN_CH>), dim3((unsigned)nb), dim3(256), 0, st, in, n, vec, sums, out, vmax,
+                       zero, rd);
   }
   AH_LAUNCHED();
   return AH_OK;
 }
 
 ah_status scan_i64(const int64_t* in, int64_t* out, int64_t n, hipStream_t st, Arena& tmp) {
-  return scan_impl<int64_t>(in, out, n, st, tmp, nullptr);
+  return scan_impl<int64_t>(in, out, n, st, tmp, nullptr, nullptr, ReadArgs{});
 }
 
 ah_status scan_i32_to_i64(const int32_t* in, int64_t* out, int64_t n, hipStream_t st, Arena& tmp, int* vmax) {
-  return scan_impl<int32_t>(in, out, n, st, tmp, vmax);
+  return scan_impl<int32_t>(in, out, n, st, tmp, vmax, nullptr, ReadArgs{});
 }
 
-// Copies the words of up to READ_MAX device values into pinned host memory,
-// then seq into the flag that the host polls.
-constexpr int READ_MAX = 6;
-constexpr int READ_WORDS = 16;
-struct ReadArgs {
-  const uint32_t* src[READ_MAX];
-  int words[READ_MAX];
-};
-
-__global__ __launch_bounds__(128) void k_read(ReadArgs a, uint32_t* host, unsigned long long* flag,
-                                              unsigned long long seq) {
-  const int v = threadIdx.x / READ_WORDS, w = threadIdx.x % READ_WORDS;
-  if (v < READ_MAX && w < a.words[v]) host[v * READ_WORDS + w] = a.src[v][w];
-  __threadfence_system();
-  __syncthreads();
-  if (threadIdx.x == 0) __hip_atomic_store(flag, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
-}
+__global__ __launch_bounds__(64) void k_read(ReadArgs a) { read_out(a); }
 
 ah_status poll_flag(const unsigned long long* flag, unsigned long long seq, hipStream_t st) {
   for (unsigned spin = 1; __atomic_load_n(flag, __ATOMIC_ACQUIRE) != seq; ++spin) {
@@ -244,32 +267,57 @@ ah_status poll_flag(const unsigned long long* flag, unsigned long long seq, hipS
   return AH_OK;
 }
 
-ah_status read_values(std::initializer_list<ReadItem> items, hipStream_t st) {
+// The kernel's arguments for the items, the thread's pinned buffer and the next
+// number of its flag.
+static ah_status read_args(std::initializer_list<ReadItem> items, ReadArgs* a) {
   // the last 64 doubles of the smallest pinned buffer: values, then the flag
   constexpr size_t AT = 8192 - 64;
   static_assert(READ_MAX * READ_WORDS * 4 + 8 <= 64 * 8, "values and flag");
   static thread_local unsigned long long seq = 0;
   double* pin = pinned_scratch(AT + 64);
   if (!pin) { set_error("pinned host allocation failed"); return AH_ENOMEM; }
-  uint32_t* host = reinterpret_cast<uint32_t*>(pin + AT);
-  unsigned long long* flag = reinterpret_cast<unsigned long long*>(pin + AT + 63);
-  ReadArgs a{};
+  *a = ReadArgs{};
+  a->host = reinterpret_cast<uint32_t*>(pin + AT);
+  a->flag = reinterpret_cast<unsigned long long*>(pin + AT + 63);
+  a->seq = ++seq;
   int n = 0;
   for (const ReadItem& it : items) {
     if (n == READ_MAX || it.bytes % 4 || it.bytes > READ_WORDS * 4) {
       set_error("read_values: bad item");
       return AH_EINVAL;
     }
-    a.src[n] = static_cast<const uint32_t*>(it.dev);
-    a.words[n++] = (int)(it.bytes / 4);
+    a->src[n] = static_cast<const uint32_t*>(it.dev);
+    a->words[n++] = (int)(it.bytes / 4);
   }
-  __atomic_store_n(flag, 0ull, __ATOMIC_RELEASE);
-  hipLaunchKernelGGL(k_read, dim3(1), dim3(128), 0, st, a, host, flag, ++seq);
-  AH_LAUNCHED();
-  AH_TRY(poll_flag(flag, seq, st));
-  n = 0;
-  for (const ReadItem& it : items) std::memcpy(it.host, host + READ_WORDS * n++, it.bytes);
+  __atomic_store_n(a->flag, 0ull, __ATOMIC_RELEASE);
   return AH_OK;
+}
+
+static ah_status read_wait(std::initializer_list<ReadItem> items, const ReadArgs& a, hipStream_t st) {
+  AH_TRY(poll_flag(a.flag, a.seq, st));
+  int n = 0;
+  for (const ReadItem& it : items) std::memcpy(it.host, a.host + READ_WORDS * n++, it.bytes);
+  return AH_OK;
+}
+
+ah_status read_values(std::initializer_list<ReadItem> items, hipStream_t st) {
+  ReadArgs a;
+  AH_TRY(read_args(items, &a));
+  hipLaunchKernelGGL(k_read, dim3(1), dim3(64), 0, st, a);
+  AH_LAUNCHED();
+  return read_wait(items, a, st);
+}
+
+ah_status scan_i32_read(const int32_t* in, int64_t* out, int64_t n, hipStream_t st, Arena& tmp, int* vmax,
+                        int32_t* zero, std::initializer_list<ReadItem> items) {
+  if (n > SCAN_ONE) {
+    AH_TRY(scan_impl<int32_t>(in, out, n, st, tmp, vmax, zero, ReadArgs{}));
+    return read_values(items, st);
+  }
+  ReadArgs a;
+  AH_TRY(read_args(items, &a));
+  AH_TRY(scan_impl<int32_t>(in, out, n, st, tmp, vmax, zero, a));
+  return read_wait(items, a, st);
 }
 
 ah_status read_i64(const int64_t* d, int64_t* h, hipStream_t st) { return read_values({{d, h, sizeof(int64_t)}}, st); }
