@@ -819,65 +819,78 @@ __device__ inline double group_max(double x) {
 // wave per row, a search per entry and the system in LDS the level of 558,750
 // rows (238,412 C points, M = 8) took 297 us, 78 now; one of 14,486,325 (M = 16)
 // 6.9 ms, 3.5 now.
-template <int M>
+// B > 1: the rows of a block AIR C block (level 0), i0 .. i0 + B - 1.  Every row
+// of a block holds the same off-diagonal blocks in full, so N (the rows of the
+// strong F blocks) and its order come from each row alike; the system is factored
+// once and the B right-hand sides are carried along, so each row gets the values
+// of B = 1.  *err is set if the rows of a block disagree on |N|.
+// 31,795,200 rows in blocks of three: 11.0 ms with a wave per block, 7.0 now.
+template <int M, int B>
 __global__ __launch_bounds__(64) void k_lair_group(int64_t nc, const int64_t* __restrict__ rp,
                                                    const int32_t* __restrict__ ci, const double* __restrict__ v,
                                                    const uint8_t* __restrict__ strong, const int8_t* __restrict__ cf,
                                                    const int32_t* __restrict__ clist, const int64_t* __restrict__ Rptr,
                                                    int32_t* __restrict__ Rcol, double* __restrict__ Rval,
-                                                   unsigned long long* __restrict__ nfall) {
+                                                   unsigned long long* __restrict__ nfall, int* __restrict__ err) {
   constexpr int NQ = 64 / M;   // groups
   constexpr int S = M + 1;     // row stride of the system in LDS
   constexpr int U = 32 / M;    // entries per lane loaded together
+  static_assert(B <= M, "a lane per row of a block without a system");
   __shared__ int32_t N[NQ][M];
-  __shared__ double T[NQ][M * S], zl[NQ][M];
+  __shared__ double T[NQ][M * S], zl[NQ][B][M];
   const int lane = threadIdx.x, g = lane % M, q = lane / M;
   const int64_t ic = (int64_t)blockIdx.x * NQ + q;
   const bool live = ic < nc;
-  const int64_t i = live ? clist[ic] : 0;
-  const int64_t k0 = live ? rp[i] : 0, k1 = live ? rp[i + 1] : 0;
-  const int64_t out = live ? Rptr[ic] : 0;
+  const int64_t i = live ? clist[ic * B] : 0;
   N[q][g] = -1;
 #pragma unroll
   for (int c = 0; c < M; ++c) T[q][g * S + c] = 0.0;
   __syncthreads();
   // N_i and the right-hand side in row order (columns are sorted)
   int m = 0;
-  for (int64_t kb = k0; __any(kb < k1); kb += 32) {
-    int32_t c[U];
-    double a[U];
-    bool f[U];
+#pragma unroll 1
+  for (int y = 0; y < B; ++y) {
+    const int64_t k0 = live ? rp[i + y] : 0, k1 = live ? rp[i + y + 1] : 0;
+    int my = 0;
+    for (int64_t kb = k0; __any(kb < k1); kb += 32) {
+      int32_t c[U];
+      double a[U];
+      bool f[U];
 #pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const int64_t k = kb + u * M + g;
-      c[u] = 0;
-      a[u] = 0.0;
-      f[u] = false;
-      if (k < k1) {
-        f[u] = strong[k] != 0;
-        c[u] = ci[k];
-        a[u] = v[k];
+      for (int u = 0; u < U; ++u) {
+        const int64_t k = kb + u * M + g;
+        c[u] = 0;
+        a[u] = 0.0;
+        f[u] = false;
+        if (k < k1) {
+          f[u] = strong[k] != 0;
+          c[u] = ci[k];
+          a[u] = v[k];
+        }
+      }
+#pragma unroll
+      for (int u = 0; u < U; ++u) f[u] = f[u] && !cf[c[u]];
+#pragma unroll
+      for (int u = 0; u < U; ++u) {
+        const unsigned mask = (unsigned)(__ballot(f[u]) >> (q * M)) & ((1u << M) - 1u);
+        const int pos = my + __popc(mask & ((1u << g) - 1u));
+        if (f[u] && pos < M) {
+          if (y == 0) N[q][pos] = c[u];
+          zl[q][y][pos] = -a[u];
+        }
+        my += __popc(mask);
       }
     }
-#pragma unroll
-    for (int u = 0; u < U; ++u) f[u] = f[u] && !cf[c[u]];
-#pragma unroll
-    for (int u = 0; u < U; ++u) {
-      const unsigned mask = (unsigned)(__ballot(f[u]) >> (q * M)) & ((1u << M) - 1u);
-      const int pos = m + __popc(mask & ((1u << g) - 1u));
-      if (f[u] && pos < M) {
-        N[q][pos] = c[u];
-        zl[q][pos] = -a[u];
-      }
-      m += __popc(mask);
-    }
+    if (y == 0) m = my;
+    else if (my != m && g == 0) atomicOr(err, 1);
   }
   __syncthreads();
   // m > M cannot occur: the host picks M >= max |N_i|
   const bool none = live && (m == 0 || m > M);
   if (none) {
-    if (g == 0) {
-      Rcol[out] = (int32_t)i;
+    if (g < B) {
+      const int64_t out = Rptr[ic * B + g];
+      Rcol[out] = (int32_t)(i + g);
       Rval[out] = 1.0;
     }
     m = 0;
@@ -950,7 +963,9 @@ __global__ __launch_bounds__(64) void k_lair_group(int64_t nc, const int64_t* __
     sc = fmax(sc, fabs(a[c]));
   }
   sc = group_max<M>(sc);
-  double z = g < m ? zl[q][g] : 0.0;
+  double z[B];
+#pragma unroll
+  for (int y = 0; y < B; ++y) z[y] = g < m ? zl[q][y][g] : 0.0;
   bool bad = false;
   int step = g < m ? M : -1;   // the elimination step whose pivot row this is
   int piv[M];
@@ -971,23 +986,32 @@ __global__ __launch_bounds__(64) void k_lair_group(int64_t nc, const int64_t* __
     if (k < m && fabs(pk) <= 1e-14 * sc) bad = true;
     if (g == p && k < m) step = k;
     const double f = step == M && k < m ? a[k] / (bad ? 1.0 : pk) : 0.0;
-    const double zp = __shfl(z, p, M);
+    double zp[B];
+#pragma unroll
+    for (int y = 0; y < B; ++y) zp[y] = __shfl(z[y], p, M);
 #pragma unroll
     for (int c = k + 1; c < M; ++c) {
       if (c >= mmax) continue;
       const double x = __shfl(a[c], p, M);
       if (step == M) a[c] -= f * x;
     }
-    if (step == M) z -= f * zp;
+    if (step == M)
+#pragma unroll
+      for (int y = 0; y < B; ++y) z[y] -= f * zp[y];
   }
-  double x = 0.0;
+  double x[B];
+#pragma unroll
+  for (int y = 0; y < B; ++y) x[y] = 0.0;
 #pragma unroll
   for (int c = M - 1; c >= 0; --c) {
     if (c >= mmax) continue;
-    const double zc = __shfl(z / (bad ? 1.0 : a[c]), piv[c], M);
-    if (c >= m) continue;
-    if (g == c) x = zc;
-    if (step >= 0 && step < c) z -= a[c] * zc;
+#pragma unroll
+    for (int y = 0; y < B; ++y) {
+      const double zc = __shfl(z[y] / (bad ? 1.0 : a[c]), piv[c], M);
+      if (c >= m) continue;
+      if (g == c) x[y] = zc;
+      if (step >= 0 && step < c) z[y] -= a[c] * zc;
+    }
   }
   // row in increasing column order: N is sorted, the C point itself is not in N
   int ins = 0;
@@ -995,15 +1019,19 @@ __global__ __launch_bounds__(64) void k_lair_group(int64_t nc, const int64_t* __
   for (int c = 0; c < M; ++c) ins += c < m && Nr[c] < i;
   if (g < m) {
     const int pos = g < ins ? g : g + 1;
-    Rcol[out + pos] = N[q][g];
-    Rval[out + pos] = bad ? 0.0 : x;
-    if (g == 0) {
-      Rcol[out + ins] = (int32_t)i;
-      Rval[out + ins] = 1.0;
+#pragma unroll
+    for (int y = 0; y < B; ++y) {
+      const int64_t out = Rptr[ic * B + y];
+      Rcol[out + pos] = N[q][g];
+      Rval[out + pos] = bad ? 0.0 : x[y];
+      if (g == 0) {
+        Rcol[out + ins] = (int32_t)(i + y);
+        Rval[out + ins] = 1.0;
+      }
     }
   }
   const unsigned long long fall = __ballot(g == 0 && live && (none || bad));
-  if (lane == 0 && fall) count_fall(nfall, (unsigned long long)__popcll(fall));
+  if (lane == 0 && fall) count_fall(nfall, (unsigned long long)(B * __popcll(fall)));
 }
 
 template <int MAXM, bool D2>
@@ -2067,8 +2095,8 @@ template <int M, bool D2>
 static void lair_launch(int64_t nc, const AhLevel& L, const uint8_t* strong, const int32_t* clist,
                         unsigned long long* nfall, hipStream_t st) {
   if constexpr (!D2 && M <= 16)
-    hipLaunchKernelGGL((k_lair_group<M>), dim3((unsigned)cdiv(nc, 64 / M)), dim3(64), 0, st, nc, L.rowptr, L.col, L.val,
-                       strong, L.cf, clist, L.Rptr, L.Rcol, L.Rval, nfall);
+    hipLaunchKernelGGL((k_lair_group<M, 1>), dim3((unsigned)cdiv(nc, 64 / M)), dim3(64), 0, st, nc, L.rowptr, L.col, L.val,
+                       strong, L.cf, clist, L.Rptr, L.Rcol, L.Rval, nfall, (int*)nullptr);
   else
     hipLaunchKernelGGL((k_lair<M, D2>), dim3((unsigned)nc), dim3(64), 0, st, nc, L.rowptr, L.col, L.val, strong, L.cf,
                        clist, L.Rptr, L.Rcol, L.Rval, nfall);
@@ -2089,18 +2117,29 @@ static ah_status lair_dispatch(int cap, bool d2, int64_t nc, const AhLevel& L, c
   return AH_OK;
 }
 
-// Block AIR lAIR rows, one wave per C block (capacity as lair_dispatch).
+// Block AIR lAIR rows (capacity as lair_dispatch): up to 16 points and the block
+// sizes of degree 1 to 3 by groups of lanes, otherwise a wave per C block.
 static ah_status lair_blk_dispatch(int cap, int64_t ncb, int b, const AhLevel& L, const uint8_t* strong,
                                    const int32_t* clist, unsigned long long* nfall, int* err, hipStream_t st) {
   if (ncb == 0) return AH_OK;
 #define LB(M) hipLaunchKernelGGL((k_lair_blk<M>), dim3((unsigned)ncb), dim3(64), 0, st, ncb, b, L.rowptr, L.col, \
                                  L.val, strong, L.cf, clist, L.Rptr, L.Rcol, L.Rval, nfall, err)
+#define LG(M, B)                                                                                                  \
+  case B:                                                                                                         \
+    hipLaunchKernelGGL((k_lair_group<M, B>), dim3((unsigned)cdiv(ncb, 64 / M)), dim3(64), 0, st, ncb, L.rowptr,   \
+                       L.col, L.val, strong, L.cf, clist, L.Rptr, L.Rcol, L.Rval, nfall, err);                    \
+    break;
   switch (cap) {
-    case 8: LB(8); break;
-    case 16: LB(16); break;
+    case 8:
+      switch (b) { LG(8, 2) LG(8, 3) LG(8, 4) LG(8, 6) default: LB(8); }
+      break;
+    case 16:
+      switch (b) { LG(16, 2) LG(16, 3) LG(16, 4) LG(16, 6) LG(16, 10) default: LB(16); }
+      break;
     case 32: LB(32); break;
     default: LB(64); break;
   }
+#undef LG
 #undef LB
   AH_LAUNCHED();
   return AH_OK;
