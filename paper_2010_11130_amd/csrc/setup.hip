@@ -151,11 +151,15 @@ __global__ __launch_bounds__(256) void k_pmis_beat(int64_t n, const int64_t* __r
                                                    const int32_t* __restrict__ adj, const int32_t* __restrict__ na,
                                                    const uint64_t* __restrict__ key, const int8_t* __restrict__ state,
                                                    uint8_t* __restrict__ beaten, unsigned long long* __restrict__ left,
-                                                   const int32_t* __restrict__ list, const int64_t* __restrict__ nd) {
+                                                   int* __restrict__ cnt, const int32_t* __restrict__ list,
+                                                   const int64_t* __restrict__ nd) {
   const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   const int64_t ii = gid / PG;
   const int g = (int)(gid % PG);
-  if (gid == 0) *left = 0;
+  if (gid == 0) {
+    *left = 0;
+    *cnt = 0;
+  }
   if (nd) n = *nd;
   if (ii >= n) return;
   const int64_t i = list ? (int64_t)list[ii] : ii;
@@ -212,92 +216,22 @@ __global__ __launch_bounds__(256) void k_pmis_mark(int64_t n, const int64_t* __r
   if (__syncthreads_or(undecided) && threadIdx.x == 0) *left = 1ull;
 }
 
-// The coarsening of a small level in one workgroup, phases separated by barriers:
-// the start of k_pmis_init, the same rounds as k_pmis_beat / k_pmis_mark, so the same splitting.
-// Keys, marks and the lists of strong columns (16 bits each) are copied to LDS
-// first, lists too long for it stay in global memory.  A thread owns the rows
-// threadIdx.x + 1024 q.  A decided point's key becomes 1 (C) or 2 (F), below
-// every undecided key.  Where cf is given, the result goes there with what
-// k_cf_flags and the scan of its flags would leave (cidx[0 .. n], cleared rcnt
-// and imax): three launches fewer per level.  The
-// rounds wait on LDS and barriers: 64 us at 5,253 rows, 82 at 3,914 (128 and 176
-// with maxima by atomics and the lists packed here from the rows' flags).
-// *err is set if the rounds exceed n + 1 (cannot happen: the largest undecided
-// key always becomes C).
+// PMIS rounds of n <= PMIS_WG_MAX points in one workgroup of 1024 threads: keys in
+// LDS, thread t owning the points t + 1024 q with m[q] strong columns nbr(q, e).
+// A decided point's key becomes 1 (C) or 2 (F), below every undecided key.  *err
+// is set if the rounds exceed n + 1 (cannot happen: the largest undecided key
+// always becomes C).
 constexpr int PMIS_WG_MAX = 8192;
 constexpr int PMIS_LDS = 160 * 1024 - 1024;
+constexpr int PMIS_Q = PMIS_WG_MAX / 1024;
+constexpr unsigned long long PMIS_OPEN = 1ull << 44;   // keys of undecided points start here
 
-__global__ __launch_bounds__(1024) void k_pmis_wg(int n, const int64_t* __restrict__ rp,
-                                                  const int32_t* __restrict__ adj_g, const int32_t* __restrict__ na,
-                                                  const int32_t* __restrict__ infl, int level,
-                                                  int8_t* __restrict__ state_g, unsigned long long* __restrict__ err,
-                                                  int lds, int8_t* __restrict__ cf, int64_t* __restrict__ cidx,
-                                                  int32_t* __restrict__ rcnt, int* __restrict__ imax) {
-  extern __shared__ __align__(16) unsigned long long pm[];
-  __shared__ int wsum[16];
-  constexpr unsigned long long OPEN = 1ull << 44;   // keys of undecided points start here
-  constexpr int Q = PMIS_WG_MAX / 1024;
-  __shared__ int cw[Q * 16];   // C points per wave and row of its threads
-  unsigned long long* key = pm;
-  int32_t* off = reinterpret_cast<int32_t*>(pm + n);            // [n + 1]
-  uint16_t* adj = reinterpret_cast<uint16_t*>(off + n + 1);
+template <class F>
+__device__ inline void pmis_rounds(int n, unsigned long long* key, uint8_t* beaten, const int (&m)[PMIS_Q], F&& nbr,
+                                   unsigned long long* err) {
+  constexpr unsigned long long OPEN = PMIS_OPEN;
+  constexpr int Q = PMIS_Q;
   const int t = threadIdx.x;
-  int64_t at[Q];
-  int m[Q];
-#pragma unroll
-  for (int q = 0; q < Q; ++q) {
-    const int i = t + 1024 * q;
-    at[q] = 0;
-    m[q] = 0;
-    if (i < n) {
-      const int32_t f = infl[i], c = na[i];
-      at[q] = rp[i];
-      m[q] = f ? c : 0;
-      key[i] = f ? ((unsigned long long)f << 44) | hash44((uint64_t)i, level) : 2ull;
-      off[i] = m[q];
-    }
-  }
-  __syncthreads();
-  // exclusive prefix sum of off[0..n)
-  const int per = (n + 1023) / 1024, i0 = min(n, t * per), i1 = min(n, i0 + per);
-  int mine = 0;
-  for (int i = i0; i < i1; ++i) mine += off[i];
-  int inc = mine;
-  for (int o = 1; o < 64; o <<= 1) {
-    const int u = __shfl_up(inc, o, 64);
-    inc += (t & 63) >= o ? u : 0;
-  }
-  if ((t & 63) == 63) wsum[t >> 6] = inc;
-  __syncthreads();
-  int run = inc - mine, tot = 0;
-  for (int w = 0; w < 16; ++w) {
-    run += w < (t >> 6) ? wsum[w] : 0;
-    tot += wsum[w];
-  }
-  for (int i = i0; i < i1; ++i) {
-    const int c = off[i];
-    off[i] = run;
-    run += c;
-  }
-  const bool in = 14 * (int64_t)n + 8 + 2 * (int64_t)tot <= lds;
-  uint8_t* beaten = reinterpret_cast<uint8_t*>(in ? adj + tot : adj);   // two sets of n
-  for (int i = t; i < 2 * n; i += 1024) beaten[i] = 0;
-  __syncthreads();
-  int o[Q];
-#pragma unroll
-  for (int q = 0; q < Q; ++q) {
-    o[q] = t + 1024 * q < n ? off[t + 1024 * q] : 0;
-    if (!in) continue;
-    for (int e = 0; e < m[q]; e += 8) {
-      int32_t j[8];
-#pragma unroll
-      for (int u = 0; u < 8; ++u) j[u] = e + u < m[q] ? adj_g[at[q] + e + u] : 0;
-#pragma unroll
-      for (int u = 0; u < 8; ++u)
-        if (e + u < m[q]) adj[o[q] + e + u] = (uint16_t)j[u];
-    }
-  }
-  __syncthreads();
   for (int round = 0;; ++round) {
     if (round > n + 1) {
       if (t == 0) atomicOr(err, 1ull);
@@ -313,7 +247,7 @@ __global__ __launch_bounds__(1024) void k_pmis_wg(int n, const int64_t* __restri
       if (ki < OPEN) continue;
       bool lost = false;
       for (int e = 0; e < m[q]; ++e) {
-        const int j = in ? (int)adj[o[q] + e] : adj_g[at[q] + e];
+        const int j = nbr(q, e);
         const unsigned long long kj = key[j];
         if (kj < OPEN) continue;
         if (kj >= ki) lost = true;
@@ -336,7 +270,7 @@ __global__ __launch_bounds__(1024) void k_pmis_wg(int n, const int64_t* __restri
       }
       bool hit = false;
       for (int e = 0; e < m[q] && !hit; ++e) {
-        const int j = in ? (int)adj[o[q] + e] : adj_g[at[q] + e];
+        const int j = nbr(q, e);
         const unsigned long long kj = key[j];
         hit = kj == 1ull || (kj >= OPEN && !now[j]);
       }
@@ -345,6 +279,99 @@ __global__ __launch_bounds__(1024) void k_pmis_wg(int n, const int64_t* __restri
     }
     if (!__syncthreads_or(undecided)) break;
   }
+}
+
+// Exclusive prefix sums of off[0 .. n) in place by 1024 threads; off[n] and the
+// result are the total.  Ends on a barrier's far side for off's writers only.
+__device__ inline int pmis_offsets(int n, int32_t* off, int* wsum) {
+  const int t = threadIdx.x;
+  const int per = (n + 1023) / 1024, i0 = min(n, t * per), i1 = min(n, i0 + per);
+  int mine = 0;
+  for (int i = i0; i < i1; ++i) mine += off[i];
+  int inc = mine;
+  for (int o = 1; o < 64; o <<= 1) {
+    const int u = __shfl_up(inc, o, 64);
+    inc += (t & 63) >= o ? u : 0;
+  }
+  if ((t & 63) == 63) wsum[t >> 6] = inc;
+  __syncthreads();
+  int run = inc - mine, tot = 0;
+  for (int w = 0; w < 16; ++w) {
+    run += w < (t >> 6) ? wsum[w] : 0;
+    tot += wsum[w];
+  }
+  for (int i = i0; i < i1; ++i) {
+    const int c = off[i];
+    off[i] = run;
+    run += c;
+  }
+  if (t == 0) off[n] = tot;
+  return tot;
+}
+
+// The coarsening of a small level in one workgroup, phases separated by barriers:
+// the start of k_pmis_init, the same rounds as k_pmis_beat / k_pmis_mark, so the same splitting.
+// Keys, marks and the lists of strong columns (16 bits each) are copied to LDS
+// first, lists too long for it stay in global memory.  A thread owns the rows
+// threadIdx.x + 1024 q.  Where cf is given, the result goes there with what
+// k_cf_flags and the scan of its flags would leave (cidx[0 .. n], cleared rcnt
+// and imax): three launches fewer per level.  The
+// rounds wait on LDS and barriers: 64 us at 5,253 rows, 82 at 3,914 (128 and 176
+// with maxima by atomics and the lists packed here from the rows' flags).
+__global__ __launch_bounds__(1024) void k_pmis_wg(int n, const int64_t* __restrict__ rp,
+                                                  const int32_t* __restrict__ adj_g, const int32_t* __restrict__ na,
+                                                  const int32_t* __restrict__ infl, int level,
+                                                  int8_t* __restrict__ state_g, unsigned long long* __restrict__ err,
+                                                  int lds, int8_t* __restrict__ cf, int64_t* __restrict__ cidx,
+                                                  int32_t* __restrict__ rcnt, int* __restrict__ imax) {
+  extern __shared__ __align__(16) unsigned long long pm[];
+  __shared__ int wsum[16];
+  constexpr int Q = PMIS_Q;
+  __shared__ int cw[Q * 16];   // C points per wave and row of its threads
+  unsigned long long* key = pm;
+  int32_t* off = reinterpret_cast<int32_t*>(pm + n);            // [n + 1]
+  uint16_t* adj = reinterpret_cast<uint16_t*>(off + n + 1);
+  const int t = threadIdx.x;
+  int64_t at[Q];
+  int m[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int i = t + 1024 * q;
+    at[q] = 0;
+    m[q] = 0;
+    if (i < n) {
+      const int32_t f = infl[i], c = na[i];
+      at[q] = rp[i];
+      m[q] = f ? c : 0;
+      key[i] = f ? ((unsigned long long)f << 44) | hash44((uint64_t)i, level) : 2ull;
+      off[i] = m[q];
+    }
+  }
+  __syncthreads();
+  const int tot = pmis_offsets(n, off, wsum);
+  const bool in = 14 * (int64_t)n + 8 + 2 * (int64_t)tot <= lds;
+  uint8_t* beaten = reinterpret_cast<uint8_t*>(in ? adj + tot : adj);   // two sets of n
+  for (int i = t; i < 2 * n; i += 1024) beaten[i] = 0;
+  __syncthreads();
+  int o[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    o[q] = t + 1024 * q < n ? off[t + 1024 * q] : 0;
+    if (!in) continue;
+    for (int e = 0; e < m[q]; e += 8) {
+      int32_t j[8];
+#pragma unroll
+      for (int u = 0; u < 8; ++u) j[u] = e + u < m[q] ? adj_g[at[q] + e + u] : 0;
+#pragma unroll
+      for (int u = 0; u < 8; ++u)
+        if (e + u < m[q]) adj[o[q] + e + u] = (uint16_t)j[u];
+    }
+  }
+  __syncthreads();
+  if (in)
+    pmis_rounds(n, key, beaten, m, [&](int q, int e) { return (int)adj[o[q] + e]; }, err);
+  else
+    pmis_rounds(n, key, beaten, m, [&](int q, int e) { return adj_g[at[q] + e]; }, err);
   if (!cf) {
     for (int i = t; i < n; i += 1024) state_g[i] = key[i] == 1ull ? 1 : 2;
     return;
@@ -382,6 +409,111 @@ __global__ __launch_bounds__(1024) void k_pmis_wg(int n, const int64_t* __restri
   if (t < 4) imax[t] = 0;
 }
 static_assert(PMIS_WG_MAX / 1024 * 16 == 128, "two counts per lane of the first wave");
+
+// The points still undecided (in any order): the first cap of them in list, with
+// their places in loc; *cnt of them in all.
+__global__ __launch_bounds__(1024) void k_pmis_open(int64_t n, const int8_t* __restrict__ state, int cap,
+                                                    int32_t* __restrict__ list, uint16_t* __restrict__ loc,
+                                                    int* __restrict__ cnt) {
+  __shared__ int ws[17];
+  const int64_t i = (int64_t)blockIdx.x * 1024 + threadIdx.x;
+  const bool open = i < n && state[i] == 0;
+  const unsigned long long b = __ballot(open);
+  const int w = threadIdx.x >> 6, lane = threadIdx.x & 63;
+  if (lane == 0) ws[w] = __popcll(b);
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    int s = 0;
+    for (int k = 0; k < 16; ++k) {
+      const int c = ws[k];
+      ws[k] = s;
+      s += c;
+    }
+    ws[16] = s ? atomicAdd(cnt, s) : 0;
+  }
+  __syncthreads();
+  const int at = ws[16] + ws[w] + __popcll(b & ((1ull << lane) - 1ull));
+  if (open && at < cap) {
+    list[at] = (int32_t)i;
+    loc[i] = (uint16_t)at;
+  }
+}
+
+// The rounds that are left over the *cnt <= cap points of list, in one workgroup
+// (among themselves: a decided strong neighbour is F, as a point with a C one is
+// F itself).  *left is cleared when it is done; more points than cap, or more
+// columns than LDS holds, are left for further rounds.  The rounds at the end
+// have little to do and cost two launches each, and a look from the host every
+// other one: setup of 342,528 rows (three levels of grid-wide rounds) 1658 us with
+// rounds to the end, 1569 so.
+__global__ __launch_bounds__(1024) void k_pmis_finish(const int* __restrict__ cnt, int cap,
+                                                      const int32_t* __restrict__ list,
+                                                      const uint16_t* __restrict__ loc,
+                                                      const int64_t* __restrict__ rp,
+                                                      const int32_t* __restrict__ adj_g,
+                                                      const int32_t* __restrict__ na,
+                                                      const uint64_t* __restrict__ key_g, int8_t* __restrict__ state,
+                                                      unsigned long long* __restrict__ left,
+                                                      unsigned long long* __restrict__ err) {
+  extern __shared__ __align__(16) unsigned long long pm[];
+  __shared__ int wsum[16];
+  constexpr int Q = PMIS_Q;
+  const int t = threadIdx.x, n = *cnt;
+  if (n == 0 || n > cap) return;
+  unsigned long long* key = pm;
+  int32_t* off = reinterpret_cast<int32_t*>(pm + n);            // [n + 1]
+  uint16_t* adj = reinterpret_cast<uint16_t*>(off + n + 1);
+  int64_t at[Q];
+  int m[Q], all[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    const int k = t + 1024 * q;
+    at[q] = 0;
+    all[q] = 0;
+    if (k < n) {
+      const int32_t i = list[k];
+      at[q] = rp[i];
+      all[q] = na[i];
+      key[k] = key_g[i];
+    }
+  }
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    m[q] = 0;
+    for (int e = 0; e < all[q]; e += 4) {
+      int32_t j[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) j[u] = e + u < all[q] ? adj_g[at[q] + e + u] : -1;
+#pragma unroll
+      for (int u = 0; u < 4; ++u) m[q] += j[u] >= 0 && state[j[u]] == 0;
+    }
+    if (t + 1024 * q < n) off[t + 1024 * q] = m[q];
+  }
+  __syncthreads();
+  const int tot = pmis_offsets(n, off, wsum);
+  if (14 * (int64_t)n + 8 + 2 * (int64_t)tot > PMIS_LDS) return;
+  uint8_t* beaten = reinterpret_cast<uint8_t*>(adj + tot);      // two sets of n
+  for (int k = t; k < 2 * n; k += 1024) beaten[k] = 0;
+  __syncthreads();
+  int o[Q];
+#pragma unroll
+  for (int q = 0; q < Q; ++q) {
+    o[q] = t + 1024 * q < n ? off[t + 1024 * q] : 0;
+    int p = o[q];
+    for (int e = 0; e < all[q]; e += 4) {
+      int32_t j[4];
+#pragma unroll
+      for (int u = 0; u < 4; ++u) j[u] = e + u < all[q] ? adj_g[at[q] + e + u] : -1;
+#pragma unroll
+      for (int u = 0; u < 4; ++u)
+        if (j[u] >= 0 && state[j[u]] == 0) adj[p++] = loc[j[u]];
+    }
+  }
+  __syncthreads();
+  pmis_rounds(n, key, beaten, m, [&](int q, int e) { return (int)adj[o[q] + e]; }, err);
+  for (int k = t; k < n; k += 1024) state[list[k]] = key[k] == 1ull ? 1 : 2;
+  if (t == 0) *left = 0;
+}
 
 // C/F marks and flags; also clears the row counts rcnt[0..n] (where given) and
 // the level's four maxima.
@@ -2204,15 +2336,16 @@ static int64_t pmis_list_min() {
 static ah_status pmis_split(int64_t n, const int64_t* rp, const int32_t* adj, const int32_t* na,
                             const int32_t* infl, int level, uint64_t* key, uint8_t* beaten, int8_t* state,
                             unsigned long long* flags, hipStream_t st, int8_t* cf, int64_t* cidx, int32_t* rcnt,
-                            int* imax, bool* numbered) {
+                            int* imax, bool* numbered, Arena& scratch) {
   const char* wg_env = std::getenv("AH_PMIS_WG_MAX");   // at most PMIS_WG_MAX (its LDS size)
   const int64_t wg_max = wg_env ? std::min<int64_t>(std::atoll(wg_env), PMIS_WG_MAX) : (int64_t)PMIS_WG_MAX;
+  static std::once_flag once;
+  std::call_once(once, [] {
+    (void)hipFuncSetAttribute((const void*)k_pmis_wg, hipFuncAttributeMaxDynamicSharedMemorySize, PMIS_LDS);
+    (void)hipFuncSetAttribute((const void*)k_pmis_finish, hipFuncAttributeMaxDynamicSharedMemorySize, PMIS_LDS);
+  });
   if (n <= wg_max) {
     // small graph: every round in one workgroup, no host checks
-    static std::once_flag once;
-    std::call_once(once, [] {
-      (void)hipFuncSetAttribute((const void*)k_pmis_wg, hipFuncAttributeMaxDynamicSharedMemorySize, PMIS_LDS);
-    });
     // 14 bytes per row, and lists of 16 columns on average
     const int lds = (int)std::min<int64_t>(PMIS_LDS, 46 * n + 64);
     hipLaunchKernelGGL(k_pmis_wg, dim3(1), dim3(1024), lds, st, (int)n, rp, adj, na, infl, level, state,
@@ -2223,11 +2356,29 @@ static ah_status pmis_split(int64_t n, const int64_t* rp, const int32_t* adj, co
   }
   hipLaunchKernelGGL(k_pmis_init, g1(n), dim3(256), 0, st, n, infl, level, key, state, beaten);
   AH_HIP(hipGetLastError());
+  // the points left for one workgroup: at most cap (5 to 43 us for them; several
+  // thousand points took it 70 to 160 us, longer than the rounds)
+  const int cap = (int)std::max<int64_t>(std::min<int64_t>(wg_max, 2048), 0);
+  int32_t* open = nullptr;
+  uint16_t* loc = nullptr;
+  int* cnt = nullptr;
+  AH_TRY(scratch.get(&open, std::max(cap, 1)));
+  AH_TRY(scratch.get(&loc, n));
+  AH_TRY(scratch.get(&cnt, 1));
+  const auto finish = [&](int round) -> ah_status {
+    if (cap == 0) return AH_OK;
+    hipLaunchKernelGGL(k_pmis_open, g1(n, 1024), dim3(1024), 0, st, n, state, cap, open, loc, cnt);
+    hipLaunchKernelGGL(k_pmis_finish, dim3(1), dim3(1024), PMIS_LDS, st, cnt, cap, open, loc, rp, adj, na, key, state,
+                       flags + (round & 1), flags + 3);
+    AH_LAUNCHED();
+    return AH_OK;
+  };
   const auto mark = [&](int round, int64_t nl, const int32_t* list, const int64_t* nd) {
     unsigned long long* left_d = flags + (round & 1);
     uint8_t* now = beaten + (round & 1) * n;
     uint8_t* next = beaten + (~round & 1) * n;
-    hipLaunchKernelGGL(k_pmis_beat, g1(nl * PG), dim3(256), 0, st, nl, rp, adj, na, key, state, now, left_d, list, nd);
+    hipLaunchKernelGGL(k_pmis_beat, g1(nl * PG), dim3(256), 0, st, nl, rp, adj, na, key, state, now, left_d, cnt,
+                       list, nd);
     hipLaunchKernelGGL(k_pmis_mark, grows(nl), dim3(256), 0, st, nl, rp, adj, na, state, now, next, left_d, list, nd);
   };
   if (n < pmis_list_min()) {
@@ -2236,9 +2387,12 @@ static ah_status pmis_split(int64_t n, const int64_t* rp, const int32_t* adj, co
       if (round > 10000) { set_error("air_setup: PMIS did not terminate"); return AH_EINVAL; }
       mark(round, n, nullptr, nullptr);
       AH_HIP(hipGetLastError());
-      // rounds run in pairs between host checks: a round after the last
-      // undecided point is gone changes nothing and leaves its flag at 0
-      if ((round & 1) == 0) continue;
+      // rounds run in pairs between host checks (four before the first one of a
+      // larger graph, which has more than one workgroup's points left before
+      // that): a round after the last undecided point is gone changes nothing and
+      // leaves its flag at 0
+      if ((round & 1) == 0 || (round == 1 && n > 8 * PMIS_WG_MAX)) continue;
+      AH_TRY(finish(round));
       unsigned long long left = 0;
       AH_TRY(read_bytes(flags + 1, &left, sizeof(left), st));
       if (left == 0) return AH_OK;
@@ -2276,11 +2430,16 @@ static ah_status pmis_split(int64_t n, const int64_t* rp, const int32_t* adj, co
     list = out;
     nd = p + nl;
     if ((round & 1) == 0) continue;
-    int64_t cnt = 0;
-    rc = read_bytes(nd, &cnt, sizeof(cnt), st);
+    int64_t left = 0;
+    rc = read_bytes(nd, &left, sizeof(left), st);
     if (rc < 0) { tmp.release(); return rc; }
-    if (cnt == 0) { tmp.release(); return AH_OK; }
-    nl = cnt;
+    if (left == 0) { tmp.release(); return AH_OK; }
+    nl = left;
+    if (nl > cap) continue;
+    unsigned long long more = 0;
+    rc = finish(round);
+    if (rc == AH_OK) rc = read_bytes(flags + 1, &more, sizeof(more), st);
+    if (rc < 0 || more == 0) { tmp.release(); return rc < 0 ? rc : AH_OK; }
   }
 }
 
@@ -3197,7 +3356,7 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
                          adj, na, (double*)nullptr, (float*)nullptr);
       CKH(hipGetLastError());
       CK(pmis_split(nbr, L.optr, adj, na, infl, l, key, beaten, sbstate, d_ull, st, nullptr, nullptr, nullptr,
-                    nullptr, &numbered));
+                    nullptr, &numbered, tmp));
       hipLaunchKernelGGL(k_block_expand, g1(n), dim3(256), 0, st, n, (int)L.ob, sbstate, state);
       uint8_t* sbr = sb;
       if (prm.theta_r > 0.0 && prm.theta_r != prm.theta) {
@@ -3228,7 +3387,8 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
       CKH(hipMemcpyAsync(state, hstate.data(), n, hipMemcpyHostToDevice, st));
       CKH(hipStreamSynchronize(st));
     } else {
-      CK(pmis_split(n, L.rowptr, adj, na, infl, l, key, beaten, state, d_ull, st, L.cf, cidx, rcnt, d_int, &numbered));
+      CK(pmis_split(n, L.rowptr, adj, na, infl, l, key, beaten, state, d_ull, st, L.cf, cidx, rcnt, d_int, &numbered,
+                    tmp));
     }
     }
     // coarse numbering

@@ -1,6 +1,6 @@
 """Setup kernels at the edges of their layouts: the one-workgroup PMIS with its
-lists in LDS, with only their offsets there and with both in global memory;
-strength and one-point interpolation of rows longer than the entries a lane
+lists in LDS, with only their offsets there and with both in global memory, and
+as the end of grid-wide rounds; strength and one-point interpolation of rows longer than the entries a lane
 keeps in registers; the register-held inverse of the coarsest matrix.
 
 The splitting and the interpolation are compared exactly, with the grid-wide
@@ -44,6 +44,26 @@ def test_one_workgroup_rounds_give_the_same_split(monkeypatch, kind, n, p, air):
     for l in range(h.info["levels"] - 1):
         a, b = h.level(l), ref.level(l)
         assert torch.equal(a["cf"], b["cf"]) and torch.equal(a["pcol"], b["pcol"]), l
+
+
+@pytest.mark.parametrize("list_min", ["0", "1000000000"])
+@pytest.mark.parametrize("kind,n,p,air", [("stack", (3, 15), 2, {}),              # 8748 rows
+                                          ("square", 64, 3, {}), ("cube", 9, 2, {"theta": 0.02}),
+                                          ("slab", 40, 2, {}), ("cube", 16, 1, {"block_air": 1})])
+def test_last_rounds_in_one_workgroup_give_the_same_split(monkeypatch, kind, n, p, air, list_min):
+    from paper_2010_11130_amd import Hierarchy
+    print("case", kind, n, p, air, list_min, flush=True)
+    monkeypatch.setenv("AH_PMIS_LIST_MIN", list_min)
+    s = gpu_system(*problem(kind, n, p))
+    got = {}
+    for cap in ("8192", "50", "0"):
+        monkeypatch.setenv("AH_PMIS_WG_MAX", cap)
+        h = Hierarchy(s, max_coarse=2, **air)
+        got[cap] = [(h.level(l)["cf"], h.level(l)["pcol"]) for l in range(h.info["levels"] - 1)]
+    for cap in ("8192", "50"):
+        assert len(got[cap]) == len(got["0"])
+        for (a, pa), (b, pb) in zip(got[cap], got["0"]):
+            assert torch.equal(a, b) and torch.equal(pa, pb)
 
 
 @pytest.mark.parametrize("kind,n,p,theta,theta_r,longest", [("square", 9, 1, 0.25, 0.25, 8),
