@@ -762,6 +762,31 @@ __global__ void k_sweep_from_zero(int64_t n, const int8_t* __restrict__ cf, int 
   y[i] = v;
 }
 
+// b = P^T r on the coarse points (four lanes per row; P has a one per fine point
+// at most), and where x is given the coarse level's first sweep on it
+// (k_sweep_from_zero), which saves that launch.
+template <class T>
+__global__ __launch_bounds__(256) void k_restrict_pt(int64_t n, const int64_t* __restrict__ ptr,
+                                                     const int32_t* __restrict__ col, const T* __restrict__ r,
+                                                     T* __restrict__ b, const int8_t* __restrict__ cf, int X,
+                                                     const T* __restrict__ d, T omega, T* __restrict__ x,
+                                                     T* __restrict__ y) {
+  const int64_t gid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  const int64_t i = gid / 4;
+  if (i >= n) return;
+  T acc = 0;
+  const int64_t k1 = ptr[i + 1];
+  for (int64_t k = ptr[i] + (gid & 3); k < k1; k += 4) acc += r[col[k]];
+  acc += __shfl_xor(acc, 2, 4);
+  acc += __shfl_xor(acc, 1, 4);
+  if (gid & 3) return;
+  b[i] = acc;
+  if (!x) return;
+  const T v = cf[i] == X && fabs((double)d[i]) >= 1e-30 ? omega * acc / d[i] : (T)0;
+  x[i] = v;
+  y[i] = v;
+}
+
 static inline int64_t nF0(const AhLevel& L) { return L.n - L.nc; }
 
 template <class TA, class TB>
@@ -1829,9 +1854,41 @@ static ah_status vcycle_up(ah_hier* h, const T* b, T* out, hipStream_t st) {
   return AH_OK;
 }
 
+// One F sweep of the transposed cycle on level l, from -> to.
+template <class T>
+static ah_status vcycle_t_fsweep(ah_hier* h, AhLevel& L, int l, const T* from, const T* g, T* to, hipStream_t st) {
+  const T om = (T)h->prm.omega;
+  if (l == 0 && Ops<T>::OT(L))   // A_0^T by facet blocks
+    return fb_any<T, SP_SWEEP_LIST>(h, L, L.fblk, nF0(L), Ops<T>::OT(L), from, g, om, to, st, nullptr, 0.0, L.flist);
+  return csr_g<T, T, T, SP_SWEEP_LIST>(pick_g(L.nnz, L.n), nF0(L), L.ATptr, L.ATcol, Ops<T>::AT(L), from, g,
+                                       Ops<T>::d(L), L.cf, 0, om, to, st, nullptr, 0.0, L.flist);
+}
+
+// The transposed cycle's sweeps up to the first one over the F points on level 0
+// (false: an ordered relaxation, or level 0 in the coarse end).  Few launches, as
+// they are wasted after the last step of a solve.
+static bool vcycle_t_starts(const ah_hier* h) { return h->end0 > 0 && h->prm.relax < 2; }
+
+template <class T>
+static ah_status vcycle_t_start(ah_hier* h, const T* g, hipStream_t st) {
+  AhLevel& L = h->lev[0];
+  const T om = (T)h->prm.omega;
+  T* cur = Ops<T>::x(L);
+  T* alt = Ops<T>::y(L);
+  // the first sweep (C points, or the F points with one sweep) starts from
+  // zero, y_X = omega g_X / d_X, written to both buffers; the F sweeps then
+  // alternate over the F list
+  const int X = h->prm.relax == 1 ? 0 : 1;
+  hipLaunchKernelGGL((k_sweep_from_zero<T>), g1(L.n), dim3(256), 0, st, L.n, L.cf, X, g, Ops<T>::d(L), om, cur, alt);
+  AH_LAUNCHED();
+  return h->prm.relax == 1 ? AH_OK : vcycle_t_fsweep<T>(h, L, 0, cur, g, alt, st);
+}
+
 // Transposed cycle on level l: g -> out (out may alias g above the coarse end,
-// not the level's x or y).  The recursion writes its result over the coarse
-// level's input (or into x on the first level of the coarse end).
+// not the level's x or y).  On level 0 the start (vcycle_t_start) is done, on the
+// levels below the first sweep came with the restriction.  The recursion writes
+// its result over the coarse level's input (or into x on the first level of the
+// coarse end).
 template <class T>
 static ah_status vcycle_t(ah_hier* h, int l, const T* g, T* out, hipStream_t st) {
   AhLevel& L = h->lev[l];
@@ -1858,51 +1915,24 @@ static ah_status vcycle_t(ah_hier* h, int l, const T* g, T* out, hipStream_t st)
       AH_TRY(gs_csr_sweep_t<T>(h, true, Ops<T>::AT(L), Ops<T>::d(L), g, cur, alt, st));
       std::swap(cur, alt);
     }
-  } else if (fbt) {
-    // A_0^T by facet blocks: the first sweep (C points, or the F points
-    // with one sweep) starts from zero, y_X = omega g_X / d_X, written to
-    // both buffers; the F sweeps then alternate over the F list
-    const int X = h->prm.relax == 1 ? 0 : 1;
-    hipLaunchKernelGGL((k_sweep_from_zero<T>), g1(L.n), dim3(256), 0, st, L.n, L.cf, X, g, Ops<T>::d(L), om, cur,
-                       alt);
-    AH_LAUNCHED();
-    if (h->prm.relax != 1) {
-      AH_TRY((fb_any<T, SP_SWEEP_LIST>(h, L, L.fblk, nF0(L), Ops<T>::OT(L), cur, g, om, alt, st, nullptr, 0.0,
-                                       L.flist)));
-      AH_TRY((fb_any<T, SP_SWEEP_LIST>(h, L, L.fblk, nF0(L), Ops<T>::OT(L), alt, g, om, cur, st, nullptr, 0.0,
-                                       L.flist)));
-    }
-    // residual g - A^T y, restricted by P^T
-    AH_TRY((fb_any<T, SP_RES>(h, L, true, L.n, Ops<T>::OT(L), cur, g, (T)0, alt, st)));
-    AH_TRY((csr_g<T, T, T, SP_MV>(4, L.nc, L.PTptr, L.PTcol, (const T*)nullptr, alt, (const T*)nullptr,
-                                  (const T*)nullptr, (const int8_t*)nullptr, 0, (T)0, Ops<T>::b(C), st)));
-    T* ec = l + 1 == h->end0 ? Ops<T>::x(C) : Ops<T>::b(C);
-    AH_TRY(vcycle_t<T>(h, l + 1, Ops<T>::b(C), ec, st));
-    const int GR = pick_g(L.nnzR, L.n);
-    AH_TRY((csr_g<T, T, T, SP_ADDMV>(GR, L.n, L.RTptr, L.RTcol, Ops<T>::RT(L), ec, cur, (const T*)nullptr,
-                                     (const int8_t*)nullptr, 0, (T)0, out, st)));
-    return AH_OK;
-  } else {
-    // the first sweep (C points, or the F points with one sweep) starts from
-    // zero, y_X = omega g_X / d_X, written to both buffers; the F sweeps then
-    // alternate over the F list
-    const int X = h->prm.relax == 1 ? 0 : 1;
-    hipLaunchKernelGGL((k_sweep_from_zero<T>), g1(L.n), dim3(256), 0, st, L.n, L.cf, X, g, Ops<T>::d(L), om, cur,
-                       alt);
-    AH_LAUNCHED();
-    if (h->prm.relax != 1) {
-      AH_TRY((csr_g<T, T, T, SP_SWEEP_LIST>(G, nF0(L), L.ATptr, L.ATcol, Ops<T>::AT(L), cur, g, Ops<T>::d(L), L.cf, 0,
-                                            om, alt, st, nullptr, 0.0, L.flist)));
-      AH_TRY((csr_g<T, T, T, SP_SWEEP_LIST>(G, nF0(L), L.ATptr, L.ATcol, Ops<T>::AT(L), alt, g, Ops<T>::d(L), L.cf, 0,
-                                            om, cur, st, nullptr, 0.0, L.flist)));
-    }
+  } else if (h->prm.relax != 1) {
+    if (l > 0) AH_TRY(vcycle_t_fsweep<T>(h, L, l, cur, g, alt, st));
+    AH_TRY(vcycle_t_fsweep<T>(h, L, l, alt, g, cur, st));
   }
   // residual g - A^T y, restricted by P^T
-  AH_TRY((csr_g<T, T, T, SP_RES>(G, L.n, L.ATptr, L.ATcol, Ops<T>::AT(L), cur, g, (const T*)nullptr,
-                                 (const int8_t*)nullptr, 0, (T)0, alt, st)));
-  AH_TRY((csr_g<T, T, T, SP_MV>(4, L.nc, L.PTptr, L.PTcol, (const T*)nullptr, alt, (const T*)nullptr,
-                                (const T*)nullptr, (const int8_t*)nullptr, 0, (T)0, Ops<T>::b(C), st)));
-  T* ec = l + 1 == h->end0 ? Ops<T>::x(C) : Ops<T>::b(C);
+  if (fbt)
+    AH_TRY((fb_any<T, SP_RES>(h, L, true, L.n, Ops<T>::OT(L), cur, g, (T)0, alt, st)));
+  else
+    AH_TRY((csr_g<T, T, T, SP_RES>(G, L.n, L.ATptr, L.ATcol, Ops<T>::AT(L), cur, g, (const T*)nullptr,
+                                   (const int8_t*)nullptr, 0, (T)0, alt, st)));
+  const bool sweeps = l + 1 < h->end0;
+  if (L.nc > 0) {
+    hipLaunchKernelGGL(k_restrict_pt<T>, g1(4 * L.nc), dim3(256), 0, st, L.nc, L.PTptr, L.PTcol, alt, Ops<T>::b(C), C.cf,
+                       h->prm.relax == 1 ? 0 : 1, Ops<T>::d(C), om, sweeps ? Ops<T>::x(C) : nullptr,
+                       sweeps ? Ops<T>::y(C) : nullptr);
+    AH_LAUNCHED();
+  }
+  T* ec = sweeps ? Ops<T>::b(C) : Ops<T>::x(C);
   AH_TRY(vcycle_t<T>(h, l + 1, Ops<T>::b(C), ec, st));
   // out = y + R^T e_c
   const int GR = pick_g(L.nnzR, L.n);
@@ -1913,31 +1943,30 @@ static ah_status vcycle_t(ah_hier* h, int l, const T* g, T* out, hipStream_t st)
 
 // Preconditioner application on level 0 for the requested precision:
 // r (FP64, level-0 scaled space) -> z (FP64) or z32 (FP32).  A caller may
-// enqueue the forward cycle's way down ahead of the rest.
-static ah_status precond_down(ah_hier* h, const double* r, int precision, hipStream_t st) {
+// enqueue the first part (the forward cycle's way down, the transposed one's
+// start) ahead of the rest.
+static ah_status precond_down(ah_hier* h, const double* r, int precision, int transpose, hipStream_t st) {
   AhLevel& L = h->lev[0];
-  if (precision == 0) return vcycle_down<double>(h, r, st);
-  hipLaunchKernelGGL((k_cast<double, float>), g1(L.n), dim3(256), 0, st, L.n, r, L.b32);
-  AH_LAUNCHED();
-  return vcycle_down<float>(h, L.b32, st);
+  if (precision) {
+    hipLaunchKernelGGL((k_cast<double, float>), g1(L.n), dim3(256), 0, st, L.n, r, L.b32);
+    AH_LAUNCHED();
+  }
+  if (transpose) {
+    if (!vcycle_t_starts(h)) return AH_OK;
+    return precision ? vcycle_t_start<float>(h, L.b32, st) : vcycle_t_start<double>(h, r, st);
+  }
+  return precision ? vcycle_down<float>(h, L.b32, st) : vcycle_down<double>(h, r, st);
 }
-
-static ah_status precond_up(ah_hier* h, const double* r, double* z, float* z32, int precision, hipStream_t st) {
-  if (precision == 0) return vcycle_up<double>(h, r, z, st);
-  return vcycle_up<float>(h, h->lev[0].b32, z32, st);
+static ah_status precond_up(ah_hier* h, const double* r, double* z, float* z32, int precision, int transpose,
+                            hipStream_t st) {
+  const float* r32 = h->lev[0].b32;
+  if (transpose) return precision ? vcycle_t<float>(h, 0, r32, z32, st) : vcycle_t<double>(h, 0, r, z, st);
+  return precision ? vcycle_up<float>(h, r32, z32, st) : vcycle_up<double>(h, r, z, st);
 }
-
 static ah_status precond(ah_hier* h, const double* r, double* z, float* z32, int precision, int transpose,
                          hipStream_t st) {
-  if (!transpose) {
-    AH_TRY(precond_down(h, r, precision, st));
-    return precond_up(h, r, z, z32, precision, st);
-  }
-  if (precision == 0) return vcycle_t<double>(h, 0, r, z, st);
-  AhLevel& L = h->lev[0];
-  hipLaunchKernelGGL((k_cast<double, float>), g1(L.n), dim3(256), 0, st, L.n, r, L.b32);
-  AH_LAUNCHED();
-  return vcycle_t<float>(h, 0, L.b32, z32, st);
+  AH_TRY(precond_down(h, r, precision, transpose, st));
+  return precond_up(h, r, z, z32, precision, transpose, st);
 }
 
 // ------------------------------------------------------------ FGMRES
@@ -2224,7 +2253,7 @@ static ah_status fgmres_cgs2(ah_hier* h, const KWork& W, Op A, const double* bve
       double* zj = W.Z ? W.Z + (int64_t)j * n : nullptr;
       float* zj32 = W.Z32 ? W.Z32 + (int64_t)j * n : nullptr;
       if (down)
-        AH_TRY(precond_up(h, vj, zj, zj32, prm.precision, st));
+        AH_TRY(precond_up(h, vj, zj, zj32, prm.precision, transpose, st));
       else
         AH_TRY(precond(h, vj, zj, zj32, prm.precision, transpose, st));
       const double by = op_mv_bytes(h, A, n, prm.precision ? 4.0 : 8.0);
@@ -2243,9 +2272,9 @@ static ah_status fgmres_cgs2(ah_hier* h, const KWork& W, Op A, const double* bve
       double* vk = W.V + (int64_t)k * n;
       AH_TRY(finish(W.w, pn, nu, vk, k));
       // the next cycle's way down runs while the host takes this step's
-      // scalars (wasted after the last step of a solve: a few small launches)
-      down = W.polled && !transpose && k < m && its < prm.maxit;
-      if (down) AH_TRY(precond_down(h, vk, prm.precision, st));
+      // scalars (wasted after the last step of a solve: a few launches)
+      down = W.polled && k < m && its < prm.maxit;
+      if (down) AH_TRY(precond_down(h, vk, prm.precision, transpose, st));
       AH_TRY(wait());
       const double w0 = std::sqrt(hh[k]);
       const double hnorm = std::sqrt(hh[2 * (m + 2)]);
