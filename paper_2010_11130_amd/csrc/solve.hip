@@ -861,6 +861,25 @@ constexpr int CGS_T = 512;      // threads per block of the dot pass
 constexpr int CGS_B = 128;      // most row blocks of the dot pass: partials per dot
 constexpr int CGS_V = 8;        // vectors per block of the dot pass
 constexpr int CGS_UB = 512;     // most blocks of the update pass: partials of the norm
+constexpr int CGS_ONE_R = 2;    // most rows per thread of the one-workgroup step
+constexpr int CGS_ONE_K = 15;   // and most vectors
+
+// The eight sums of a wave together (each exchange halves what a lane carries):
+// lanes 8 q .. 8 q + 7 return the wave's sum of acc[q].
+__device__ inline double cgs_wave_sums(double (&acc)[CGS_V]) {
+  const int lane = threadIdx.x & 63;
+#pragma unroll
+  for (int h = CGS_V / 2; h >= 1; h >>= 1) {
+    const bool up = lane & (8 * h);
+#pragma unroll
+    for (int q = 0; q < h; ++q) {
+      const double keep = up ? acc[q + h] : acc[q], send = up ? acc[q] : acc[q + h];
+      acc[q] = keep + __shfl_xor(send, 8 * h, 64);
+    }
+  }
+  for (int o = 4; o > 0; o >>= 1) acc[0] += __shfl_xor(acc[0], o, 64);
+  return acc[0];
+}
 
 // partial[v][blk] = V_v . w over the block's rows (v < k), w . w at v = k.
 __global__ __launch_bounds__(CGS_T) void k_cgs_dot(int64_t n, int k, const double* __restrict__ V, int64_t ldv,
@@ -886,19 +905,9 @@ __global__ __launch_bounds__(CGS_T) void k_cgs_dot(int64_t n, int k, const doubl
 #pragma unroll
     for (int q = 0; q < CGS_V; ++q) acc[q] += a0[q] * w0 + a1[q] * w1;
   }
-  // the eight sums of a wave together: each exchange halves what a lane carries
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-#pragma unroll
-  for (int h = CGS_V / 2; h >= 1; h >>= 1) {
-    const bool up = lane & (8 * h);
-#pragma unroll
-    for (int q = 0; q < h; ++q) {
-      const double keep = up ? acc[q + h] : acc[q], send = up ? acc[q] : acc[q + h];
-      acc[q] = keep + __shfl_xor(send, 8 * h, 64);
-    }
-  }
-  for (int o = 4; o > 0; o >>= 1) acc[0] += __shfl_xor(acc[0], o, 64);
-  if ((lane & 7) == 0) red[wv][lane >> 3] = acc[0];
+  const double sum = cgs_wave_sums(acc);
+  if ((lane & 7) == 0) red[wv][lane >> 3] = sum;
   __syncthreads();
   const int t = threadIdx.x;
   if (t < CGS_V && v0 + t <= k) {
@@ -989,6 +998,105 @@ __global__ __launch_bounds__(256) void k_cgs_update(int64_t n, int k, const doub
   if (lane == 0) red[wv] = nrm;
   __syncthreads();
   if (threadIdx.x == 0) pout[blockIdx.x] = (red[0] + red[1]) + (red[2] + red[3]);
+}
+
+// A whole step of CGS2 in one workgroup: h1 = V^T w, w -= V h1, h2 = V^T w,
+// w -= V h2, out = w / |w|, and the scalars as k_cgs_finish leaves them.  R rows
+// per thread, w in registers throughout.  Four passes over V by one CU against five
+// dependent launches of about 4 us each.  1,536 unknowns, us per iteration with one
+// launch and with five: 32 and 34 to 38 at 4 to 10 vectors, 42 and 37 to 41 at 10 to
+// 20, 52 and 38 to 46 at 20 to 28, so up to two batches of eight (w . w is one of
+// them); 5,184 unknowns at eight rows per thread: 96 and 66.  Dynamic LDS:
+// 17 (k + 1) doubles.
+template <int R>
+__global__ __launch_bounds__(1024) void k_cgs_one(int64_t n, int k, const double* __restrict__ V, int64_t ldv,
+                                                  const double* __restrict__ w, double* __restrict__ out,
+                                                  double* __restrict__ hn, double* __restrict__ h1,
+                                                  double* __restrict__ h2, int off, double* host,
+                                                  unsigned long long* flag, unsigned long long seq) {
+  extern __shared__ double hs[];
+  constexpr int NW = 16;
+  double* red = hs + k + 1;   // [NW][k + 1]
+  const int t = threadIdx.x, lane = t & 63, wv = t >> 6;
+  unsigned i[R];
+  double x[R];
+#pragma unroll
+  for (int r = 0; r < R; ++r) {
+    const bool in = r * 1024 + t < n;
+    i[r] = in ? r * 1024 + t : (unsigned)n - 1;
+    x[r] = in ? w[i[r]] : 0.0;
+  }
+  for (int pass = 0; pass < 2; ++pass) {
+    for (int v = 0; v <= k; v += CGS_V) {
+      double a[CGS_V][R], acc[CGS_V];
+#pragma unroll
+      for (int q = 0; q < CGS_V; ++q)
+        if (v + q < k) {
+          const double* pv = V + (int64_t)(v + q) * ldv;
+#pragma unroll
+          for (int r = 0; r < R; ++r) a[q][r] = pv[i[r]];
+        }
+#pragma unroll
+      for (int q = 0; q < CGS_V; ++q) {
+        acc[q] = 0.0;
+        if (v + q <= k)
+#pragma unroll
+          for (int r = 0; r < R; ++r) acc[q] += (v + q < k ? a[q][r] : x[r]) * x[r];
+      }
+      const double sum = cgs_wave_sums(acc);
+      if ((lane & 7) == 0 && v + (lane >> 3) <= k) red[wv * (k + 1) + v + (lane >> 3)] = sum;
+    }
+    __syncthreads();
+    for (int v = t; v <= k; v += 1024) {
+      double h = 0.0;
+#pragma unroll
+      for (int q = 0; q < NW; ++q) h += red[q * (k + 1) + v];
+      hs[v] = h;
+      (pass ? h2 : h1)[v] = h;
+      if (host) host[pass * off + v] = h;
+    }
+    __syncthreads();
+    double s[R];
+#pragma unroll
+    for (int r = 0; r < R; ++r) s[r] = 0.0;
+    for (int v = 0; v < k; v += CGS_V) {
+      double a[CGS_V][R];
+#pragma unroll
+      for (int q = 0; q < CGS_V; ++q)
+        if (v + q < k) {
+          const double* pv = V + (int64_t)(v + q) * ldv;
+#pragma unroll
+          for (int r = 0; r < R; ++r) a[q][r] = pv[i[r]];
+        }
+#pragma unroll
+      for (int q = 0; q < CGS_V; ++q)
+        if (v + q < k)
+#pragma unroll
+          for (int r = 0; r < R; ++r) s[r] += a[q][r] * hs[v + q];
+    }
+#pragma unroll
+    for (int r = 0; r < R; ++r) x[r] = r * 1024 + t < n ? x[r] - s[r] : 0.0;
+  }
+  double nn = 0.0;
+#pragma unroll
+  for (int r = 0; r < R; ++r) nn += x[r] * x[r];
+  for (int o = 32; o > 0; o >>= 1) nn += __shfl_xor(nn, o, 64);
+  if (lane == 0) red[wv] = nn;
+  __syncthreads();
+  nn = 0.0;
+#pragma unroll
+  for (int q = 0; q < NW; ++q) nn += red[q];
+  const double s = 1.0 / sqrt(nn);
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+    if (r * 1024 + t < n) out[i[r]] = x[r] * s;
+  if (t <= k || t == 0) __threadfence_system();   // the waves that wrote to the host
+  if (t == 0) {
+    *hn = nn;
+    if (host) host[2 * off] = nn;
+  }
+  __syncthreads();
+  if (host && t == 0) __hip_atomic_store(flag, seq, __ATOMIC_RELEASE, __HIP_MEMORY_SCOPE_SYSTEM);
 }
 
 // out = w / |w| with |w|^2 the sum of the np <= CGS_UB partials (out null: the
@@ -2197,6 +2305,11 @@ static ah_status fgmres_cgs2(ah_hier* h, const KWork& W, Op A, const double* bve
     hipLaunchKernelGGL(k_cgs_update, dim3(nu), dim3(256), (unsigned)((k + 1) * sizeof(double)), st, n, k, W.V, n,
                        W.partial, nb, W.w, hout, pout);
   };
+  auto one = [&](int k, double* out) {
+    ++seq;
+    hipLaunchKernelGGL(n <= 1024 ? k_cgs_one<1> : k_cgs_one<2>, dim3(1), dim3(1024), (unsigned)(17 * (k + 1) * sizeof(double)), st, n, k, W.V, n, W.w, out,
+                       hn, h1, h2, m + 2, W.polled ? hh : nullptr, flag, seq);
+  };
   auto finish = [&](const double* w, const double* part, int np, double* out, int k) -> ah_status {
     ++seq;
     hipLaunchKernelGGL(k_cgs_finish, dim3(out ? nu : 1), dim3(256), 0, st, n, w, part, np, out, hn, k, m + 2, h1, h2,
@@ -2265,12 +2378,17 @@ static ah_status fgmres_cgs2(ah_hier* h, const KWork& W, Op A, const double* bve
                                        transpose ? nullptr : "spmv0", by)));
       ++its;
       const int k = j + 1;
-      dots(k, W.w);
-      update(k, h1, nullptr);
-      dots(k, W.w);
-      update(k, h2, pn);
       double* vk = W.V + (int64_t)k * n;
-      AH_TRY(finish(W.w, pn, nu, vk, k));
+      if (n <= 1024 * CGS_ONE_R && k <= CGS_ONE_K) {
+        one(k, vk);
+        AH_LAUNCHED();
+      } else {
+        dots(k, W.w);
+        update(k, h1, nullptr);
+        dots(k, W.w);
+        update(k, h2, pn);
+        AH_TRY(finish(W.w, pn, nu, vk, k));
+      }
       // the next cycle's way down runs while the host takes this step's
       // scalars (wasted after the last step of a solve: a few launches)
       down = W.polled && k < m && its < prm.maxit;

@@ -1,8 +1,9 @@
 """FGMRES below 2^21 unknowns: the step's scalars reach the host through a
 polled flag, or by copies where the thread has no pinned buffer; the solve at
 the edges of its launch shapes (a handful of unknowns, row counts around a
-block, more vectors than a combination's coefficient block holds), with a
-given start, a zero right-hand side, step limits and restarts.
+block, around the step in one workgroup (2048 unknowns, 15 vectors), more
+vectors than a combination's coefficient block holds), with a given start, a
+zero right-hand side, step limits and restarts.
 
 Tolerances: residuals are recomputed in FP64 from the exported system, twice
 the requested tolerance; the two transports run the same kernels, so their
@@ -32,8 +33,8 @@ def residual(s, x):
     return np.linalg.norm(b - A @ x.cpu().numpy()) / np.linalg.norm(b)
 
 
-@pytest.mark.parametrize("kind,n,p", [("square", 1, 1), ("square", 3, 2), ("square", 13, 1), ("square", 40, 1),
-                                      ("cube", 9, 1)])
+@pytest.mark.parametrize("kind,n,p", [("square", 1, 1), ("square", 3, 2), ("square", 13, 1), ("square", 18, 1),
+                                      ("square", 19, 1), ("square", 40, 1), ("cube", 9, 1)])
 @pytest.mark.parametrize("restart,relax", [(100, 0), (4, 0), (300, 1)])
 def test_solution_and_start(kind, n, p, restart, relax):
     from paper_2010_11130_amd import Hierarchy
