@@ -1,4 +1,4 @@
-"""FGMRES below 2^21 unknowns: the step's scalars reach the host through a
+"""FGMRES, with both orthogonalisations: the step's scalars reach the host through a
 polled flag, or by copies where the thread has no pinned buffer; the solve at
 the edges of its launch shapes (a handful of unknowns, row counts around a
 block, around the step in one workgroup (2048 unknowns, 15 vectors), more
@@ -36,9 +36,11 @@ def residual(s, x):
 @pytest.mark.parametrize("kind,n,p", [("square", 1, 1), ("square", 3, 2), ("square", 13, 1), ("square", 18, 1),
                                       ("square", 19, 1), ("square", 40, 1), ("cube", 9, 1)])
 @pytest.mark.parametrize("restart,relax", [(100, 0), (4, 0), (300, 1)])
-def test_solution_and_start(kind, n, p, restart, relax):
+@pytest.mark.parametrize("delayed", [False, True])
+def test_solution_and_start(monkeypatch, kind, n, p, restart, relax, delayed):
     from paper_2010_11130_amd import Hierarchy
-    print("case", kind, n, p, restart, relax, flush=True)
+    print("case", kind, n, p, restart, relax, delayed, flush=True)
+    monkeypatch.setenv("AH_DCGS_MIN", "0" if delayed else "1000000000")
     s = system(kind, n, p)
     # one F sweep per level converges slowly: more than 128 vectors in one combination
     h = Hierarchy(s, relax=relax, max_coarse=4, omega=0.5 if relax else 1.0)
@@ -64,11 +66,13 @@ def test_limits_and_zero_rhs():
     assert info["converged"] and float(x.abs().max()) == 0.0
 
 
+@pytest.mark.parametrize("delayed", [False, True])
 @pytest.mark.parametrize("precision", [0, 1])
-def test_copied_scalars_give_the_polled_result(precision):
+def test_copied_scalars_give_the_polled_result(monkeypatch, precision, delayed):
     """A thread that has never set anything up has no pinned buffer, and the
     allocation-free solve must not make one."""
     from paper_2010_11130_amd import Hierarchy
+    monkeypatch.setenv("AH_DCGS_MIN", "0" if delayed else "1000000000")
     s = system("cube", 4, 1)
     h = Hierarchy(s, fp32_cycle=1)
     kw = dict(noalloc=True, tol=1e-9, restart=30, precision=precision)
