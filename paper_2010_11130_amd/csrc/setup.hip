@@ -2263,10 +2263,10 @@ static ah_status lair_blk_dispatch(int cap, int64_t ncb, int b, const AhLevel& L
     break;
   switch (cap) {
     case 8:
-      switch (b) { LG(8, 2) LG(8, 3) LG(8, 4) LG(8, 6) default: LB(8); }
+      switch (b) { LG(8, 2) LG(8, 3) LG(8, 4) LG(8, 6) LG(16, 10) default: LB(32); }
       break;
     case 16:
-      switch (b) { LG(16, 2) LG(16, 3) LG(16, 4) LG(16, 6) LG(16, 10) default: LB(16); }
+      switch (b) { LG(16, 2) LG(16, 3) LG(16, 4) LG(16, 6) LG(16, 10) default: LB(32); }
       break;
     case 32: LB(32); break;
     default: LB(64); break;
