@@ -2281,6 +2281,16 @@ static ah_status combine_add(int k, const double* y, int64_t n, const KWork& W, 
   return AH_OK;
 }
 
+// b = 0: x = 0.  Waits for the stream as every other end of a solve does: the
+// host has seen the norm, but the kernel that stored it may still be writing
+// the first basis vector, in a workspace that another solve may use next.
+static ah_status zero_solution(int64_t n, double* x, hipStream_t st, ah_solve_info* info) {
+  AH_HIP(hipMemsetAsync(x, 0, n * sizeof(double), st));
+  AH_HIP(hipStreamSynchronize(st));
+  if (info) { info->iters = 0; info->converged = 1; info->relres = 0; info->true_relres = 0; }
+  return AH_OK;
+}
+
 static ah_status fgmres_dcgs2(ah_hier* h, const KWork& W, Op A, const double* bvec, double* x,
                               const ah_solve_params& prm, int transpose, hipStream_t st, ah_solve_info* info);
 
@@ -2355,11 +2365,7 @@ static ah_status fgmres_cgs2(ah_hier* h, const KWork& W, Op A, const double* bve
   bool converged = false;
   double relres = 1.0, true_rel = 1.0;
   ah_status status = AH_OK;
-  if (!(bnorm > 0.0)) {
-    AH_HIP(hipMemsetAsync(x, 0, n * sizeof(double), st));
-    if (info) { info->iters = 0; info->converged = 1; info->relres = 0; info->true_relres = 0; }
-    return AH_OK;
-  }
+  if (!(bnorm > 0.0)) return zero_solution(n, x, st, info);
   if (!std::isfinite(bnorm)) { set_error("air_solve: non-finite right-hand side"); return AH_EBREAKDOWN; }
   for (bool first = true;; first = false) {
     double beta = bnorm;
@@ -2507,11 +2513,7 @@ static ah_status fgmres_dcgs2(ah_hier* h, const KWork& W, Op A, const double* bv
   AH_TRY(multidot(n, 0, W.V, bvec, W.partial, hd, st));
   AH_TRY(fetch(1));
   const double bnorm = std::sqrt(hh[0]);
-  if (!(bnorm > 0.0)) {
-    AH_HIP(hipMemsetAsync(x, 0, n * sizeof(double), st));
-    if (info) { info->iters = 0; info->converged = 1; info->relres = 0; info->true_relres = 0; }
-    return AH_OK;
-  }
+  if (!(bnorm > 0.0)) return zero_solution(n, x, st, info);
   if (!std::isfinite(bnorm)) { set_error("air_solve: non-finite right-hand side"); return AH_EBREAKDOWN; }
   // Hr: Hessenberg columns as formed (rows 0..m); Hg: the same after the
   // Givens rotations; Rt: the triangular factor of Z~ = Z R
@@ -2715,11 +2717,7 @@ static ah_status bicgstab(ah_hier* h, Op A, const double* bvec, double* x, const
   bool converged = false;
   double relres = 1.0, true_rel = 1.0;
   ah_status status = AH_OK;
-  if (!(bnorm > 0.0)) {
-    AH_HIP(hipMemsetAsync(x, 0, n * sizeof(double), st));
-    if (info) { info->iters = 0; info->converged = 1; info->relres = 0; info->true_relres = 0; }
-    return AH_OK;
-  }
+  if (!(bnorm > 0.0)) return zero_solution(n, x, st, info);
   if (!std::isfinite(bnorm)) { set_error("air_solve: non-finite right-hand side"); return AH_EBREAKDOWN; }
   const double ones[3] = {1.0, 1.0, 1.0};
   while (true) {
