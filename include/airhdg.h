@@ -73,6 +73,10 @@ const char* ah_last_error(void);
  *     of the allocation, after the last work using it has been enqueued on
  *     that stream (destroy calls, end of temporaries).
  * Memory keeps the allocator it came from when the registration changes.
+ * The reference tables of a (dimension, degree) pair (at most 0.2 MB) are
+ * uploaded once per device and shared while no allocator is registered (six
+ * pairs, held until ah_pool_trim or their last system's end, whichever is
+ * later); with a registered allocator each system has its own copy from it.
  * Both NULL restores the pool; one NULL is AH_EINVAL.  The registration is
  * process-wide and may be changed from any thread; the callbacks may run on
  * any thread that calls the library. */
@@ -82,8 +86,9 @@ ah_status ah_set_allocator(ah_alloc_fn alloc, ah_free_fn free, void* ctx);
 
 /* Gives the blocks that the library's caching allocator holds for the
  * current device, freed by objects and not reused yet, back to the device
- * (hipFree).  Waits for the device first.  Objects that are alive keep
- * their memory.  AH_EHIP on a runtime error. */
+ * (hipFree), and the shared reference tables that no living system uses.
+ * Waits for the device first.  Objects that are alive keep their memory.
+ * AH_EHIP on a runtime error. */
 ah_status ah_pool_trim(void);
 
 /* ---------------------------------------------------------------- mesh ---

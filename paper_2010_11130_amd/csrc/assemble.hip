@@ -1156,11 +1156,11 @@ extern "C" ah_status ah_quad_points(const ah_mesh* mc, int p, double* xq_elem, d
   if (!mc) { set_error("null mesh"); return AH_EINVAL; }
   ah_mesh* m = const_cast<ah_mesh*>(mc);
   hipStream_t st = as_stream(stream);
-  std::shared_ptr<const RefTables> tab;
-  AH_TRY(ref_tables(m->D, p, tab));
-  const RefTables& t = *tab;
   Arena tmp;
   tmp.stream = st;
+  std::shared_ptr<const RefTables> tab;
+  AH_TRY(ref_tables(m->D, p, tmp, tab));
+  const RefTables& t = *tab;
   double* d_vert = nullptr;
   int32_t *d_cell = nullptr, *d_bf = nullptr, *d_fv = nullptr;
   AH_TRY(tmp.get(&d_vert, m->vert.size()));
@@ -1205,7 +1205,7 @@ static ah_status assemble_impl(const ah_mesh* mc, const ah_hdg_params* prm, doub
   s->keep = prm->keep_element_data != 0;
   s->unscaled = prm->no_block_scale != 0;
   auto fail = [&](ah_status code) { delete s; return code; };
-  ah_status rc = ref_tables(m->D, prm->p, s->tab);
+  ah_status rc = ref_tables(m->D, prm->p, s->arena, s->tab);
   if (rc) return fail(rc);
   const RefTables& t = *s->tab;
   s->nu = t.nu; s->b = t.b; s->nl = (m->D + 1) * t.b; s->nq = t.nq; s->nqf = t.nqf;
@@ -1283,11 +1283,11 @@ extern "C" ah_status ah_quad_points_facets(const ah_mesh* mc, int p, double* xq_
   ah_mesh* m = const_cast<ah_mesh*>(mc);
   if (m->nf == 0) return AH_OK;
   hipStream_t st = as_stream(stream);
-  std::shared_ptr<const RefTables> tab;
-  AH_TRY(ref_tables(m->D, p, tab));
-  const RefTables& t = *tab;
   Arena tmp;
   tmp.stream = st;
+  std::shared_ptr<const RefTables> tab;
+  AH_TRY(ref_tables(m->D, p, tmp, tab));
+  const RefTables& t = *tab;
   std::vector<int32_t> ids((size_t)m->nf);
   for (int64_t f = 0; f < m->nf; ++f) ids[(size_t)f] = (int32_t)f;
   double* d_vert = nullptr;

@@ -108,7 +108,7 @@ struct RefTables {
   // normal-derivative tensor of facet f (the one opposite local vertex f):
   //   ten_dn[f][r][j][i] = (1/|F|) int_F d_r phi_i phi_j
   std::vector<double> ten_dn;
-  // device copies, in one allocation
+  // device copies, in one allocation (d_all where it is the tables' own)
   double* d_all = nullptr;
   double* d_vol_w = nullptr;
   double* d_vol_lam = nullptr;
@@ -127,11 +127,14 @@ struct RefTables {
 };
 
 ah_status build_ref_tables(int D, int p, RefTables& t);
-// The tables of (D, p) on the current device, built and uploaded on first use
-// and shared by every later caller (any thread, any stream: the upload is
-// complete on return, the tables never change).  Up to six entries of at most
-// 0.2 MB per device stay until ah_pool_trim; a system keeps its own alive.
-ah_status ref_tables(int D, int p, std::shared_ptr<const RefTables>& out);
+// The tables of (D, p) on the current device, built on first use; the upload is
+// complete on return and the tables never change.  With the library's own pool
+// the device copy is shared by every later caller (any thread, any stream): up
+// to six entries of at most 0.2 MB per device stay until ah_pool_trim; a system
+// keeps its own alive.  Where the caller's allocator is registered, the copy
+// lies in the arena, as all memory of the object it belongs to: memory from
+// that allocator is tied to a stream and must not outlive the object.
+ah_status ref_tables(int D, int p, Arena& ar, std::shared_ptr<const RefTables>& out);
 void ref_tables_release(int dev);
 void gauss_jacobi01(int n, double alpha, double* s, double* w);
 void simplex_rule(int dim, int n, std::vector<double>& xi, std::vector<double>& w);

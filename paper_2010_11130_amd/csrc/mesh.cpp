@@ -61,6 +61,17 @@ void cache_release_device(int dev) {
 }
 }  // namespace
 
+static hipError_t malloc_or_release(void** p, size_t bytes, int dev) {
+  hipError_t e = hipMalloc(p, bytes);
+  if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) {
+    (void)hipGetLastError();
+    (void)hipDeviceSynchronize();
+    cache_release_device(dev);
+    e = hipMalloc(p, bytes);
+  }
+  return e;
+}
+
 static hipError_t cache_alloc(void** p, size_t* bytes, hipStream_t st, int dev) {
   *bytes = (*bytes + CACHE_ROUND - 1) / CACHE_ROUND * CACHE_ROUND;
   {
@@ -76,14 +87,7 @@ static hipError_t cache_alloc(void** p, size_t* bytes, hipStream_t st, int dev) 
       }
     }
   }
-  hipError_t e = hipMalloc(p, *bytes);
-  if (e == hipErrorOutOfMemory || e == hipErrorMemoryAllocation) {
-    (void)hipGetLastError();
-    (void)hipDeviceSynchronize();
-    cache_release_device(dev);
-    e = hipMalloc(p, *bytes);
-  }
-  return e;
+  return malloc_or_release(p, *bytes, dev);
 }
 
 static void cache_free(void* p, size_t bytes, hipStream_t st, int dev) {
@@ -445,44 +449,83 @@ ah_status build_ref_tables(int D, int p, RefTables& t) {
   return AH_OK;
 }
 
+// Device copies of the tables: in one piece, each table on a 256-byte boundary.
+static std::vector<std::pair<const std::vector<double>*, double**>> ref_parts(RefTables& t) {
+  return {{&t.vol_w, &t.d_vol_w}, {&t.vol_lam, &t.d_vol_lam}, {&t.vol_phi, &t.d_vol_phi},
+          {&t.vol_dphi, &t.d_vol_dphi}, {&t.fac_w, &t.d_fac_w}, {&t.fac_mu, &t.d_fac_mu},
+          {&t.fac_psi, &t.d_fac_psi}, {&t.fac_proj, &t.d_fac_proj}, {&t.fac_pp, &t.d_fac_pp},
+          {&t.fac_mass, &t.d_fac_mass}, {&t.ten_adv, &t.d_ten_adv}, {&t.ten_dif, &t.d_ten_dif},
+          {&t.ten_dn, &t.d_ten_dn}};
+}
+
+static size_t ref_place(RefTables& t, double* base) {
+  size_t at = 0;
+  for (auto& x : ref_parts(t)) {
+    if (base) *x.second = base + at;
+    at += (x.first->size() + 31) & ~size_t(31);
+  }
+  return at;
+}
+
 static std::mutex g_ref_mu;
-static std::map<int, std::shared_ptr<const RefTables>>& ref_cache() {   // by device * 16 + D * 4 + p
-  static auto* c = new std::map<int, std::shared_ptr<const RefTables>>;
+typedef std::map<int, std::shared_ptr<const RefTables>> RefCache;
+static RefCache& ref_host() {    // without device copies, by D * 4 + p
+  static auto* c = new RefCache;
+  return *c;
+}
+static RefCache& ref_cache() {   // by device * 16 + D * 4 + p
+  static auto* c = new RefCache;
   return *c;
 }
 
-ah_status ref_tables(int D, int p, std::shared_ptr<const RefTables>& out) {
+ah_status ref_tables(int D, int p, Arena& ar, std::shared_ptr<const RefTables>& out) {
   if (D < 2 || D > 3 || p < 1 || p > 3) {
     set_error("unsupported dim_st=%d p=%d (dim_st in 2..3, p in 1..3)", D, p);
     return AH_EUNSUPPORTED;
   }
   int dev = 0;
   AH_HIP(hipGetDevice(&dev));
+  bool own;
+  {
+    std::lock_guard<std::mutex> lock(g_alloc_mu);
+    own = !g_alloc;
+  }
   std::lock_guard<std::mutex> lock(g_ref_mu);
-  auto& slot = ref_cache()[dev * 16 + D * 4 + p];
-  if (!slot) {
+  if (own) {
+    auto it = ref_cache().find(dev * 16 + D * 4 + p);
+    if (it != ref_cache().end()) { out = it->second; return AH_OK; }
+  }
+  auto& host = ref_host()[D * 4 + p];
+  if (!host) {
     auto t = std::make_shared<RefTables>();
     AH_TRY(build_ref_tables(D, p, *t));
-    const std::pair<const std::vector<double>*, double**> parts[] = {
-        {&t->vol_w, &t->d_vol_w}, {&t->vol_lam, &t->d_vol_lam}, {&t->vol_phi, &t->d_vol_phi},
-        {&t->vol_dphi, &t->d_vol_dphi}, {&t->fac_w, &t->d_fac_w}, {&t->fac_mu, &t->d_fac_mu},
-        {&t->fac_psi, &t->d_fac_psi}, {&t->fac_proj, &t->d_fac_proj}, {&t->fac_pp, &t->d_fac_pp},
-        {&t->fac_mass, &t->d_fac_mass}, {&t->ten_adv, &t->d_ten_adv}, {&t->ten_dif, &t->d_ten_dif},
-        {&t->ten_dn, &t->d_ten_dn}};
-    std::vector<double> all;
-    std::vector<size_t> at;
-    for (auto& x : parts) {
-      at.push_back(all.size());
-      all.insert(all.end(), x.first->begin(), x.first->end());
-      all.resize((all.size() + 31) & ~size_t(31), 0.0);
-    }
-    const hipError_t e = hipMalloc((void**)&t->d_all, all.size() * sizeof(double));
-    if (e != hipSuccess) { t->d_all = nullptr; set_error("hipMalloc: %s", hipGetErrorString(e)); return AH_ENOMEM; }
-    AH_HIP(hipMemcpy(t->d_all, all.data(), all.size() * sizeof(double), hipMemcpyHostToDevice));
-    for (size_t k = 0; k < at.size(); ++k) *parts[k].second = t->d_all + at[k];
-    slot = t;
+    host = t;
   }
-  out = slot;
+  auto t = std::make_shared<RefTables>(*host);
+  const size_t size = ref_place(*t, nullptr);
+  double* base = nullptr;
+  if (own) {
+    const hipError_t e = malloc_or_release((void**)&base, size * sizeof(double), dev);
+    if (e != hipSuccess) {
+      (void)hipGetLastError();
+      set_error("device allocation of %zu bytes failed: %s", size * sizeof(double), hipGetErrorString(e));
+      return AH_ENOMEM;
+    }
+    t->d_all = base;
+  } else {
+    AH_TRY(ar.get(&base, size));
+  }
+  ref_place(*t, base);
+  std::vector<double> all(size, 0.0);
+  for (auto& x : ref_parts(*t)) std::copy(x.first->begin(), x.first->end(), all.begin() + (*x.second - base));
+  if (own) {
+    AH_HIP(hipMemcpy(base, all.data(), size * sizeof(double), hipMemcpyHostToDevice));
+    ref_cache()[dev * 16 + D * 4 + p] = t;
+  } else {
+    AH_HIP(hipMemcpyAsync(base, all.data(), size * sizeof(double), hipMemcpyHostToDevice, ar.stream));
+    AH_HIP(hipStreamSynchronize(ar.stream));   // all goes away
+  }
+  out = t;
   return AH_OK;
 }
 
