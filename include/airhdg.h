@@ -416,7 +416,9 @@ ah_status hdg_assemble_grad(const ah_system* s, const double* a_vert, const doub
 /* Gaussian sources phi_k(X) = exp(-|X - X_k|^2 / (2 w^2)) at points X dev
  * [npts][dim_st]; centers dev [K][dim_st].
  *   forward:   f dev [npts] = sum_k c_k phi_k(X)          (c dev [K])
- *   transpose: dc dev [K] = sum_pts y(X) phi_k(X)         (y dev [npts]) */
+ *   transpose: dc dev [K] = sum_pts y(X) phi_k(X)         (y dev [npts])
+ * The transpose takes the points in pieces, with at most 32 MB or 2 KB per
+ * centre (the larger) of temporary device memory. */
 ah_status ah_source_gauss(int dim_st, int64_t npts, const double* X, int K, const double* centers,
                           double width, const double* c, double* f, void* stream);
 ah_status ah_source_gauss_T(int dim_st, int64_t npts, const double* X, int K,

@@ -253,9 +253,10 @@ __global__ __launch_bounds__(256) void k_gauss_t(int64_t npts, const double* __r
   if (t < k1 - k0) partial[(int64_t)blockIdx.x * K + k0 + t] = red[0][t] + red[1][t] + red[2][t] + red[3][t];
 }
 
-// out[k] = sum over blocks of partial[blk][k], eight k per workgroup.
+// out[k] = sum over blocks of partial[blk][k] (add: on top of what is there),
+// eight k per workgroup.
 __global__ __launch_bounds__(256) void k_cols_sum(int K, int nblk, const double* __restrict__ partial,
-                                                  double* __restrict__ out) {
+                                                  double* __restrict__ out, int add) {
   __shared__ double red[256];
   const int k = blockIdx.x * 8 + (threadIdx.x & 7);
   double s = 0.0;
@@ -267,7 +268,7 @@ __global__ __launch_bounds__(256) void k_cols_sum(int K, int nblk, const double*
     if ((int)threadIdx.x < o) red[threadIdx.x] += red[threadIdx.x + o];
     __syncthreads();
   }
-  if (threadIdx.x < 8 && k < K) out[k] = red[threadIdx.x];
+  if (threadIdx.x < 8 && k < K) out[k] = add ? out[k] + red[threadIdx.x] : red[threadIdx.x];
 }
 
 // A few points per SIMD make the kernels latency bound: from 2^19 points on
@@ -291,16 +292,25 @@ template <int D>
 static ah_status gauss_t_launch(int64_t npts, const double* X, int K, const double* C, double inv2w2,
                                 const double* y, double* dc, Arena& tmp, hipStream_t st) {
   const bool many = npts >= GAUSS_MANY;
-  const int nblk = (int)std::max<int64_t>(1, cdiv(npts, many ? 2048 : 256));
+  const int per = many ? 2048 : 256;   // points per block
   const int kc = many ? 64 : 8;
+  // the points in pieces whose partial sums take at most 32 MB (or 256 per
+  // centre): one piece up to 8.4M points with 1024 centres or fewer
+  const int64_t most = std::max<int64_t>(256, std::min<int64_t>(4096, ((int64_t)1 << 22) / K));
   double* part = nullptr;
-  AH_TRY(tmp.get(&part, (int64_t)K * nblk));
-  const dim3 grid(nblk, (unsigned)cdiv(K, kc));
-  if (many)
-    hipLaunchKernelGGL((k_gauss_t<D, 8>), grid, dim3(256), 0, st, npts, X, K, C, inv2w2, y, part, kc);
-  else
-    hipLaunchKernelGGL((k_gauss_t<D, 1>), grid, dim3(256), 0, st, npts, X, K, C, inv2w2, y, part, kc);
-  hipLaunchKernelGGL(k_cols_sum, dim3((unsigned)cdiv(K, 8)), dim3(256), 0, st, K, nblk, part, dc);
+  AH_TRY(tmp.get(&part, (int64_t)K * std::min(most, std::max<int64_t>(1, cdiv(npts, per)))));
+  int64_t i0 = 0;
+  do {
+    const int64_t m = std::min(npts - i0, most * per);
+    const int nblk = (int)std::max<int64_t>(1, cdiv(m, per));
+    const dim3 grid(nblk, (unsigned)cdiv(K, kc));
+    if (many)
+      hipLaunchKernelGGL((k_gauss_t<D, 8>), grid, dim3(256), 0, st, m, X + i0 * D, K, C, inv2w2, y + i0, part, kc);
+    else
+      hipLaunchKernelGGL((k_gauss_t<D, 1>), grid, dim3(256), 0, st, m, X + i0 * D, K, C, inv2w2, y + i0, part, kc);
+    hipLaunchKernelGGL(k_cols_sum, dim3((unsigned)cdiv(K, 8)), dim3(256), 0, st, K, nblk, part, dc, (int)(i0 > 0));
+    i0 += m;
+  } while (i0 < npts);
   AH_LAUNCHED();
   return AH_OK;
 }

@@ -1,0 +1,65 @@
+"""Bounds of the memory that a call takes beside its results, counted by a
+registered allocator."""
+import contextlib
+
+import numpy as np
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+CHUNK = 32 << 20       # smallest request of a library object
+
+
+class Meter:
+    """Device memory from torch, with the live and the largest live size."""
+
+    def __init__(self):
+        self.sizes, self.live, self.peak = {}, 0, 0
+
+    def alloc(self, ctx, nbytes, stream):
+        ptr = torch.cuda.caching_allocator_alloc(int(nbytes), stream=int(stream or 0))
+        self.sizes[ptr] = nbytes
+        self.live += nbytes
+        self.peak = max(self.peak, self.live)
+        return ptr
+
+    def free(self, ctx, ptr, nbytes, stream):
+        self.live -= self.sizes.pop(ptr)
+        torch.cuda.caching_allocator_delete(ptr)
+
+
+@contextlib.contextmanager
+def metered():
+    from paper_2010_11130_amd import lib
+    from paper_2010_11130_amd._lib import ALLOC_FN, FREE_FN
+    m = Meter()
+    cbs = (ALLOC_FN(m.alloc), FREE_FN(m.free))
+    assert lib().ah_set_allocator(cbs[0], cbs[1], None) == 0
+    m.callbacks = cbs
+    try:
+        yield m
+    finally:
+        lib().ah_set_allocator(ALLOC_FN(), FREE_FN(), None)
+
+
+@pytest.mark.parametrize("npts,K", [(1100000, 32768), (9 << 20, 300), (70000, 40000)])
+def test_transposed_sources_in_pieces(npts, K):
+    """More points than one piece holds: the partial sums stay within 32 MB or
+    256 per centre, and the sums are those of the definition (tolerance: a few
+    roundings of the argument |x - c|^2 / (2 w^2) per term, summed in absolute
+    value; the sums run in blocks)."""
+    from paper_2010_11130_amd import source_gauss_T
+    print("case", npts, K, flush=True)
+    rng = np.random.default_rng(K)
+    X, cen = (torch.as_tensor(rng.uniform(0, 1, (m, 2)), device="cuda") for m in (npts, K))
+    y = torch.as_tensor(rng.standard_normal(npts), device="cuda")
+    w = 0.1
+    with metered() as m:
+        dc = source_gauss_T(X, cen, w, y)
+    assert m.live == 0 and m.peak <= max(1 << 25, 256 * 8 * K) + CHUNK
+    eps = 2.0 ** -52
+    for k in [0, 1, K // 2, K - 1]:
+        arg = ((X - cen[k]) ** 2).sum(1) / (2 * w * w)
+        phi = torch.exp(-arg)
+        bound = (16 * eps * (1 + arg) * phi + 64 * eps * phi) @ y.abs()
+        assert float((dc[k] - y @ phi).abs()) <= float(bound)
