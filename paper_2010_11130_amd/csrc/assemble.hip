@@ -995,8 +995,10 @@ static ah_status element_dispatch(int D, int p, const ElemArgs& a, hipStream_t s
   return AH_EUNSUPPORTED;
 }
 
+// parts: the arena of Dg, given back before the matrix is allocated.
 template <int D, int B>
-static ah_status scale_to_csr(ah_system* s, const ah_mesh* m, const double* Dg, hipStream_t st, int* d_err) {
+static ah_status scale_to_csr(ah_system* s, const ah_mesh* m, const double* Dg, Arena& parts, hipStream_t st,
+                              int* d_err) {
   const int64_t nfree = s->nfree;
   const int64_t n = nfree * B;
   Arena& ar = s->arena;
@@ -1009,6 +1011,7 @@ static ah_status scale_to_csr(ah_system* s, const ah_mesh* m, const double* Dg, 
     hipLaunchKernelGGL(k_diag_inv<B>, dim3(cdiv(std::max<int64_t>(nfree, 1), 64)), dim3(64), 0, st, nfree,
                        m->d_facet_slot, Dg, s->d_Dinv, d_err);
   AH_LAUNCHED();
+  parts.release();
   const int64_t nob = (int64_t)m->odb_col.size();
   s->nnz = s->unscaled ? (int64_t)B * B * s->nnzb : n + (int64_t)B * B * nob;
   if (s->nnz >= ((int64_t)1 << 31)) {
@@ -1061,15 +1064,15 @@ static ah_status rhs_dispatch(int b, ah_system* s, const double* g_q, hipStream_
   return AH_EUNSUPPORTED;
 }
 
-static ah_status scale_dispatch(int b, ah_system* s, const ah_mesh* m, const double* Dg, hipStream_t st,
-                                int* d_err) {
+static ah_status scale_dispatch(int b, ah_system* s, const ah_mesh* m, const double* Dg, Arena& parts,
+                                hipStream_t st, int* d_err) {
   const int D = m->D;
-  if (D == 2 && b == 2) return scale_to_csr<2, 2>(s, m, Dg, st, d_err);
-  if (D == 2 && b == 3) return scale_to_csr<2, 3>(s, m, Dg, st, d_err);
-  if (D == 2 && b == 4) return scale_to_csr<2, 4>(s, m, Dg, st, d_err);
-  if (D == 3 && b == 3) return scale_to_csr<3, 3>(s, m, Dg, st, d_err);
-  if (D == 3 && b == 6) return scale_to_csr<3, 6>(s, m, Dg, st, d_err);
-  if (D == 3 && b == 10) return scale_to_csr<3, 10>(s, m, Dg, st, d_err);
+  if (D == 2 && b == 2) return scale_to_csr<2, 2>(s, m, Dg, parts, st, d_err);
+  if (D == 2 && b == 3) return scale_to_csr<2, 3>(s, m, Dg, parts, st, d_err);
+  if (D == 2 && b == 4) return scale_to_csr<2, 4>(s, m, Dg, parts, st, d_err);
+  if (D == 3 && b == 3) return scale_to_csr<3, 3>(s, m, Dg, parts, st, d_err);
+  if (D == 3 && b == 6) return scale_to_csr<3, 6>(s, m, Dg, parts, st, d_err);
+  if (D == 3 && b == 10) return scale_to_csr<3, 10>(s, m, Dg, parts, st, d_err);
   set_error("unsupported facet block size %d", b);
   return AH_EUNSUPPORTED;
 }
@@ -1227,7 +1230,8 @@ static ah_status assemble_impl(const ah_mesh* mc, const ah_hdg_params* prm, doub
   }
   int* d_err = nullptr;
   if ((rc = ar.get(&d_err, 1))) return fail(rc);
-  // the elements' parts of the diagonal blocks and of H, summed per facet
+  // the elements' parts of the diagonal blocks and of H, summed per facet and
+  // then given back, before the matrix (which takes more) is allocated
   Arena tmp;
   tmp.stream = st;
   auto fail_tmp = [&](ah_status code) { tmp.release(); return fail(code); };
@@ -1264,8 +1268,7 @@ static ah_status assemble_impl(const ah_mesh* mc, const ah_hdg_params* prm, doub
   if (s->n > 0)
     hipLaunchKernelGGL(k_h_sum, dim3((unsigned)cdiv(s->n, 256)), dim3(256), 0, st, s->n, t.b, m->d_facet_slot, Hk,
                        s->d_H0);
-  if ((rc = scale_dispatch(t.b, s, m, Dg, st, d_err))) return fail_tmp(rc);
-  tmp.release();
+  if ((rc = scale_dispatch(t.b, s, m, Dg, tmp, st, d_err))) return fail_tmp(rc);
   if ((rc = rhs_dispatch(t.b, s, g_q, st))) return fail(rc);
   int herr = 0;
   if ((rc = read_bytes(d_err, &herr, sizeof(int), st))) return fail(rc);

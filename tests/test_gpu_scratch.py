@@ -6,6 +6,10 @@ import numpy as np
 import pytest
 import torch
 
+from workloads import kuhn_cube_mesh
+from workloads.problems import PolynomialProblem
+from gpu_cases import gpu_system
+
 pytestmark = pytest.mark.gpu
 CHUNK = 32 << 20       # smallest request of a library object
 
@@ -63,3 +67,18 @@ def test_transposed_sources_in_pieces(npts, K):
         phi = torch.exp(-arg)
         bound = (16 * eps * (1 + arg) * phi + 64 * eps * phi) @ y.abs()
         assert float((dc[k] - y @ phi).abs()) <= float(bound)
+
+
+@pytest.mark.parametrize("keep", [False, True])
+@pytest.mark.parametrize("block_scale", [False, True])
+def test_assembly_needs_no_more_than_it_keeps(keep, block_scale):
+    """The elements' parts of the diagonal blocks (79 MB here) are gone before
+    the matrix is there."""
+    print("case", keep, block_scale, flush=True)
+    v, c = kuhn_cube_mesh(16)
+    prob = PolynomialProblem(2, 3, 1e-2, seed=3, a_lin=np.zeros((2, 3)))
+    with metered() as m:
+        s = gpu_system(v, c, prob, 3, keep=keep, block_scale=block_scale)
+        assert m.peak <= m.live + CHUNK
+        del s
+    assert m.live == 0
