@@ -3254,8 +3254,12 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
   Arena tmp;
   tmp.stream = st;
   ah_status rc = AH_OK;
-#define CK(x) do { rc = (x); if (rc < 0) { tmp.release(); delete h; return rc; } } while (0)
-#define CKH(x) do { hipError_t e_ = (x); if (e_ != hipSuccess) { set_error("air_setup: %s", hipGetErrorString(e_)); tmp.release(); delete h; return AH_EHIP; } } while (0)
+  // what a large level's coarsening alone needs, given back before its
+  // restriction and the next level's matrix are allocated
+  Arena graph;
+  graph.stream = st;
+#define CK(x) do { rc = (x); if (rc < 0) { graph.release(); tmp.release(); delete h; return rc; } } while (0)
+#define CKH(x) do { hipError_t e_ = (x); if (e_ != hipSuccess) { set_error("air_setup: %s", hipGetErrorString(e_)); graph.release(); tmp.release(); delete h; return AH_EHIP; } } while (0)
   unsigned long long* d_ull = nullptr;   // [0..1] undecided counts (alternating rounds), [2] lAIR fallbacks,
                                          // [3] single-workgroup PMIS round overflow
   int* d_int = nullptr;                  // [0] max |N_i|, [1] max candidates, [2] max C-row length (then error flags), [3] max A_c row
@@ -3309,17 +3313,20 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
     // graph of the coarsening (none on the coarsest level)
     const bool coarsest = n <= prm.max_coarse || l == prm.max_levels - 1;
     const int64_t ng = coarsest ? 0 : blk ? nbr : n;
+    const int64_t nadj = blk ? (int64_t)s->mesh->odb_col.size() : L.nnz;
+    // (what fits in a chunk comes from the one that the level needs anyway)
+    Arena& gr = nadj * 4 > (int64_t)Arena::CHUNK ? graph : tmp;
     int32_t *infl = nullptr, *adj = nullptr, *na = nullptr;
     uint64_t* key = nullptr;
     uint8_t* beaten = nullptr;
     if (!coarsest && (blk || prm.coarsening != 1)) {
       // below level 0 the level's x, cleared with its row pointers
-      if (l == 0) CK(tmp.get(&infl, ng));
+      if (l == 0) CK(gr.get(&infl, ng));
       else infl = reinterpret_cast<int32_t*>(L.x);
-      CK(tmp.get(&adj, blk ? (int64_t)s->mesh->odb_col.size() : L.nnz));
-      CK(tmp.get(&na, ng));
-      CK(tmp.get(&key, ng));
-      CK(tmp.get(&beaten, 2 * ng));
+      CK(gr.get(&adj, nadj));
+      CK(gr.get(&na, ng));
+      CK(gr.get(&key, ng));
+      CK(gr.get(&beaten, 2 * ng));
       if (l == 0 && !blk) CKH(hipMemsetAsync(infl, 0, ng * sizeof(int32_t), st));
     }
     if (coarsest || blk) {   // elsewhere the strength kernel finds the diagonal
@@ -3337,7 +3344,7 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
     uint8_t* strong = nullptr;
     int8_t* state = nullptr;
     CK(tmp.get(&strong, L.nnz));
-    CK(tmp.get(&state, n));
+    CK(gr.get(&state, n));
     int64_t* cidx = nullptr;
     int32_t* rcnt = nullptr;
     const bool d2 = prm.lair_distance == 2;
@@ -3350,13 +3357,13 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
       int8_t* sbstate = nullptr;
       CK(tmp.get(&bw, nslot));
       CK(tmp.get(&sb, nslot));
-      CK(tmp.get(&sbstate, nbr));
+      CK(gr.get(&sbstate, nbr));
       hipLaunchKernelGGL(k_block_weights, g1(nbr * SG), dim3(256), 0, st, nbr, (int)L.ob, L.optr, L.oval, bw);
       hipLaunchKernelGGL(k_strength, g1(nbr * SG), dim3(256), 0, st, nbr, L.optr, L.ocol, bw, prm.theta, sb, infl,
                          adj, na, (double*)nullptr, (float*)nullptr);
       CKH(hipGetLastError());
       CK(pmis_split(nbr, L.optr, adj, na, infl, l, key, beaten, sbstate, d_ull, st, nullptr, nullptr, nullptr,
-                    nullptr, &numbered, tmp));
+                    nullptr, &numbered, gr));
       hipLaunchKernelGGL(k_block_expand, g1(n), dim3(256), 0, st, n, (int)L.ob, sbstate, state);
       uint8_t* sbr = sb;
       if (prm.theta_r > 0.0 && prm.theta_r != prm.theta) {
@@ -3388,17 +3395,18 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
       CKH(hipStreamSynchronize(st));
     } else {
       CK(pmis_split(n, L.rowptr, adj, na, infl, l, key, beaten, state, d_ull, st, L.cf, cidx, rcnt, d_int, &numbered,
-                    tmp));
+                    gr));
     }
     }
     // coarse numbering
     if (!numbered) {
       int32_t* isc = nullptr;
-      CK(tmp.get(&isc, n));
+      CK(gr.get(&isc, n));
       hipLaunchKernelGGL(k_cf_flags, g1(n + 4), dim3(256), 0, st, n, state, L.cf, isc, rcnt, d_int);
       CKH(hipGetLastError());
       CK(scan_i32_to_i64(isc, cidx, n, st, tmp));
     }
+    graph.release();
     int64_t nc = 0;
     // distance one: the point lists and R's row counts are sized for n, and
     // the C-point count is read back together with R's size (one host sync

@@ -82,3 +82,20 @@ def test_assembly_needs_no_more_than_it_keeps(keep, block_scale):
         assert m.peak <= m.live + CHUNK
         del s
     assert m.live == 0
+
+
+def test_setup_gives_the_coarsening_back(monkeypatch):
+    """Scalar setup of 988,416 rows, 36.6M entries: beside what the hierarchy
+    keeps, a level needs its strength mask (a byte per entry), row counters and
+    offsets (24 bytes per row) and the chunk of its small buffers; the
+    coarsening's packed columns (four bytes per entry) are gone by then."""
+    from paper_2010_11130_amd import Hierarchy
+    monkeypatch.setenv("AH_SWO", "0")       # no copies of the operators after the last level
+    v, c = kuhn_cube_mesh(24)
+    s = gpu_system(v, c, PolynomialProblem(2, 2, 1e-2, seed=3, a_lin=np.zeros((2, 3))), 2, keep=False)
+    with metered() as m:
+        h = Hierarchy(s)
+        print("peak", m.peak >> 20, "kept", m.live >> 20, "MB", flush=True)
+        assert m.peak <= m.live + s.nnz + 24 * s.n + 2 * CHUNK
+        del h
+    assert m.live == 0
