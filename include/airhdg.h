@@ -149,7 +149,8 @@ ah_status ah_quad_points_facets(const ah_mesh* m, int p, double* xq_facet, void*
  *           g_D on Dirichlet facets, g_N on Neumann facets; NULL = 0.
  * Returns AH_ESINGULAR if a facet diagonal block or an element block is
  * singular (e.g. a characteristic facet at nu = 0), AH_EINVAL for nu < 0 or
- * p outside 1..3.  Synchronizes the stream. */
+ * p outside 1..3.  Synchronizes the stream.  Temporary device memory: 8 (D+1)
+ * (b^2 + b) bytes per cell, given back before the matrix is allocated. */
 typedef struct {
   int p;
   double alpha;
@@ -227,7 +228,13 @@ ah_status hdg_inflow_from_trace(const ah_system* prev, const double* lam_prev,
  * neighbours (paths through F points only; at most 64 points, else
  * AH_EUNSUPPORTED); theta_r > 0 gives the restriction neighbourhoods their
  * own strength threshold (Section 4 uses 0.3 for R and 0.2 for the
- * coarsening), theta stays that of the coarsening and of P. */
+ * coarsening), theta stays that of the coarsening and of P.
+ * Temporary device memory, beside what the hierarchy keeps: while a level is
+ * coarsened 5 bytes per stored entry and about 35 per row of it (block AIR,
+ * level 0: 13 per facet block and one per entry), 1 byte per entry and about
+ * 20 per row after that; with adjoint a second copy of the entries of one
+ * matrix at a time (12 bytes each; R, P and the operators that are transposed
+ * as CSR).  Chunks of 32 MB are the least taken. */
 typedef struct {
   double theta;        /* strength threshold, default 0.25 */
   int max_coarse;      /* default 64 */

@@ -2090,9 +2090,9 @@ __global__ void k_fb_transpose(int64_t nbr, int B, const int64_t* __restrict__ o
   }
 }
 
-static ah_status transpose(int64_t nrow, int64_t ncol, const int64_t* rp, const int32_t* ci, const double* v,
-                           int64_t nnz, Arena& ar, Arena& tmp, hipStream_t st, int64_t** tp, int32_t** tc,
-                           double** tv) {
+static ah_status transpose_with(int64_t nrow, int64_t ncol, const int64_t* rp, const int32_t* ci, const double* v,
+                                int64_t nnz, Arena& ar, Arena& tmp, hipStream_t st, int64_t** tp, int32_t** tc,
+                                double** tv) {
   int32_t* cnt = nullptr;
   AH_TRY(tmp.get(&cnt, ncol + 1));
   AH_HIP(hipMemsetAsync(cnt, 0, (ncol + 1) * sizeof(int32_t), st));
@@ -2119,6 +2119,19 @@ static ah_status transpose(int64_t nrow, int64_t ncol, const int64_t* rp, const 
                        ncol, *tp, sc, sv, *tc, tv ? *tv : nullptr);
   AH_LAUNCHED();
   return AH_OK;
+}
+
+// The scattered entries of a large matrix (a second copy of them) go back to
+// the pool, in stream order, before anything else is allocated.
+static ah_status transpose(int64_t nrow, int64_t ncol, const int64_t* rp, const int32_t* ci, const double* v,
+                           int64_t nnz, Arena& ar, Arena& tmp, hipStream_t st, int64_t** tp, int32_t** tc,
+                           double** tv) {
+  Arena own;
+  own.stream = st;
+  const bool large = nnz * (tv ? 12 : 4) > (int64_t)Arena::CHUNK;
+  const ah_status rc = transpose_with(nrow, ncol, rp, ci, v, nnz, ar, large ? own : tmp, st, tp, tc, tv);
+  own.release();
+  return rc;
 }
 
 // out[0] = max(out[0], max of a[0..n)): grid-stride, one atomic per block.

@@ -15,21 +15,38 @@ CHUNK = 32 << 20       # smallest request of a library object
 
 
 class Meter:
-    """Device memory from torch, with the live and the largest live size."""
+    """Device memory from torch, with the live and the largest live size, and
+    what was taken and given back in order."""
 
     def __init__(self):
-        self.sizes, self.live, self.peak = {}, 0, 0
+        self.sizes, self.live, self.peak, self.log = {}, 0, 0, []
 
     def alloc(self, ctx, nbytes, stream):
         ptr = torch.cuda.caching_allocator_alloc(int(nbytes), stream=int(stream or 0))
         self.sizes[ptr] = nbytes
         self.live += nbytes
         self.peak = max(self.peak, self.live)
+        self.log.append((ptr, nbytes))
         return ptr
 
     def free(self, ctx, ptr, nbytes, stream):
         self.live -= self.sizes.pop(ptr)
+        self.log.append((ptr, -nbytes))
         torch.cuda.caching_allocator_delete(ptr)
+
+
+    def most_given_back(self):
+        """The largest sum at one time of pieces that have been given back."""
+        open_, pieces, at, most = {}, [], 0, 0
+        for k, (ptr, size) in enumerate(self.log):
+            if size > 0:
+                open_[ptr] = k
+            else:
+                pieces += [(open_.pop(ptr), -size), (k, size)]
+        for _, size in sorted(pieces):
+            at += size
+            most = max(most, at)
+        return most
 
 
 @contextlib.contextmanager
@@ -97,5 +114,20 @@ def test_setup_gives_the_coarsening_back(monkeypatch):
         h = Hierarchy(s)
         print("peak", m.peak >> 20, "kept", m.live >> 20, "MB", flush=True)
         assert m.peak <= m.live + s.nnz + 24 * s.n + 2 * CHUNK
+        del h
+    assert m.live == 0
+
+
+def test_transposes_one_after_the_other():
+    """The adjoint setup of an unscaled system, whose level-0 matrix is
+    transposed entry by entry: one second copy of the entries at a time."""
+    from paper_2010_11130_amd import Hierarchy
+    v, c = kuhn_cube_mesh(32)
+    s = gpu_system(v, c, PolynomialProblem(2, 2, 1e-2, seed=3, a_lin=np.zeros((2, 3))), 2, keep=False,
+                   block_scale=False)
+    with metered() as m:
+        h = Hierarchy(s, adjoint=1)
+        print("rows", s.n, "entries", s.nnz, "most", m.most_given_back() >> 20, "MB", flush=True)
+        assert m.most_given_back() <= 12 * s.nnz + 4 * s.n + 2 * CHUNK
         del h
     assert m.live == 0
