@@ -11,6 +11,7 @@
  *     D = d + 1 is the space-time dimension (2 or 3), p in {1, 2, 3}.
  *   - Pointers marked "host" are host memory, "dev" are device memory
  *     (hipMalloc'd or torch tensors); the caller owns every pointer argument.
+ *     Arrays need the alignment of their values, no more.
  *   - stream: a hipStream_t passed as void* (NULL = default stream).  Device
  *     work is enqueued on it.  Calls that return an info struct or sizes
  *     synchronize the stream before returning.
@@ -230,9 +231,9 @@ ah_status hdg_inflow_from_trace(const ah_system* prev, const double* lam_prev,
  * own strength threshold (Section 4 uses 0.3 for R and 0.2 for the
  * coarsening), theta stays that of the coarsening and of P.
  * Temporary device memory, beside what the hierarchy keeps: while a level is
- * coarsened 5 bytes per stored entry and about 35 per row of it (block AIR,
- * level 0: 13 per facet block and one per entry), 1 byte per entry and about
- * 20 per row after that; with adjoint a second copy of the entries of one
+ * coarsened 5 bytes per stored entry and about 35 per row of it, 65 from 2^20
+ * rows on (block AIR, level 0: 13 per facet block and one per entry), 1 byte
+ * per entry and about 20 per row after that; with adjoint a second copy of the entries of one
  * matrix at a time (12 bytes each; R, P and the operators that are transposed
  * as CSR).  Chunks of 32 MB are the least taken. */
 typedef struct {

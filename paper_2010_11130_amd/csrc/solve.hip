@@ -180,7 +180,8 @@ __global__ __launch_bounds__(256) void k_fb(int64_t n, const int64_t* __restrict
   if constexpr (B % 2 == 0) {
     constexpr int H = B / 2;
     typedef TA TA2 __attribute__((ext_vector_type(2)));
-    typedef TX TX2 __attribute__((ext_vector_type(2)));
+    // x may be the caller's vector, aligned to its values only
+    typedef TX TX2 __attribute__((ext_vector_type(2), aligned(sizeof(TX))));
     const TA2* __restrict__ v2 = reinterpret_cast<const TA2*>(v);
     const TX2* __restrict__ x2 = reinterpret_cast<const TX2*>(x);
     const TX2* __restrict__ xc2 = reinterpret_cast<const TX2*>(xc);
