@@ -296,11 +296,12 @@ typedef struct {
  * natural order from the F and C lists after an interpolation pass instead
  * of from the copies in sweep order (the same sums, bit for bit); AH_L1B=0
  * sweeps level 1 of block AIR by CSR rows, AH_RZB=0 restricts from level 0
- * by CSR rows and AH_FBB=0 runs the level-0 kernels by rows (the same
- * operators, summed in another order).  Size thresholds: AH_DCGS_MIN (delayed CGS2),
- * AH_LIST_MIN (list sweeps on coarse levels), AH_PMIS_WG_MAX,
- * AH_PMIS_LIST_MIN; lanes: AH_GC (coarse levels), AH_LPB (level-0 block
- * rows), AH_L1LP (level 1). */
+ * by CSR rows and AH_FBB=0 runs the level-0 kernels of an odd facet size by
+ * rows, from the lists in the natural order (the same operators, summed in
+ * another order); even facet sizes always run by rows.  Size thresholds:
+ * AH_DCGS_MIN (delayed CGS2), AH_LIST_MIN (list sweeps on coarse levels),
+ * AH_PMIS_WG_MAX, AH_PMIS_LIST_MIN; lanes: AH_GC (coarse levels), AH_LPB
+ * (level-0 block rows, so odd facet sizes only), AH_L1LP (level 1). */
 
 /* Defaults for ah_air_params / ah_solve_params. */
 void ah_air_defaults(ah_air_params* p);

@@ -3716,8 +3716,9 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
     if (const char* e = std::getenv("AH_L1B")) l1b = std::atoi(e) != 0;
     if (const char* e = std::getenv("AH_RZB")) rzb = std::atoi(e) != 0;
     if (const char* e = std::getenv("AH_SWO")) swo = std::atoi(e) != 0;
-    // level 0 under block AIR with Jacobi sweeps: the sweep-ordered copy
-    if (swo && nl > 1 && h->lev[0].fblk && prm.relax < 2 && h->fbb) {
+    // level 0 under block AIR with Jacobi sweeps: the sweep-ordered copy (odd
+    // block sizes read it by block rows only)
+    if (swo && nl > 1 && h->lev[0].fblk && prm.relax < 2 && (h->fbb || h->lev[0].ob % 2 == 0)) {
       ProfScope ps;
       prof_begin(ps, "order0", st, 0.0);
       CK(sweep_order_build(h, st));
