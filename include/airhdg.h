@@ -298,7 +298,10 @@ typedef struct {
  * sweeps level 1 of block AIR by CSR rows, AH_RZB=0 restricts from level 0
  * by CSR rows and AH_FBB=0 runs the level-0 kernels of an odd facet size by
  * rows, from the lists in the natural order (the same operators, summed in
- * another order); even facet sizes always run by rows.  Size thresholds:
+ * another order); even facet sizes always run by rows; AH_POLL=0 copies the
+ * scalars of an FGMRES step to the host and synchronizes, as a thread without
+ * a pinned buffer does, instead of polling a flag (the same results, bit for
+ * bit).  Size thresholds:
  * AH_DCGS_MIN (delayed CGS2), AH_LIST_MIN (list sweeps on coarse levels),
  * AH_PMIS_WG_MAX, AH_PMIS_LIST_MIN; lanes: AH_GC (coarse levels), AH_LPB
  * (level-0 block rows, so odd facet sizes only), AH_L1LP (level 1). */

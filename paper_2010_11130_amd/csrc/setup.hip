@@ -3703,6 +3703,7 @@ extern "C" ah_status air_setup(const ah_system* s, const ah_air_params* prm_in, 
     if (const char* e = std::getenv("AH_FBB")) h->fbb = std::atoi(e) != 0;
     if (const char* e = std::getenv("AH_LPB")) h->lpb = std::atoi(e);
     if (h->lpb != 2 && h->lpb != 4 && h->lpb != 8) h->lpb = 0;
+    if (const char* e = std::getenv("AH_POLL")) h->poll = std::atoi(e) != 0;
     if (const char* e = std::getenv("AH_DCGS_MIN")) h->dcgs_min = std::atoll(e);
     if (const char* e = std::getenv("AH_GC")) h->gc = std::atoi(e);
     if (h->gc != 2 && h->gc != 4 && h->gc != 8 && h->gc != 16 && h->gc != 32) h->gc = 0;

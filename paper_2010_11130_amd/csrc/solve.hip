@@ -2132,7 +2132,7 @@ static ah_status ensure_workspace(ah_hier* h, int m, int precision, hipStream_t 
   W->hdev = h->hdev;
   W->host = pinned_scratch(4 * (m + 3) + 1);
   if (!W->host) { set_error("pinned host allocation failed"); return AH_ENOMEM; }
-  W->polled = true;
+  W->polled = h->poll;
   return AH_OK;
 }
 
@@ -2945,7 +2945,7 @@ extern "C" ah_status air_solve_noalloc(const ah_hier* hc, const double* rhs, dou
   // it), else a pageable array and copies
   static thread_local double stage[4 * (AH_NOALLOC_MAX_RESTART + 3)];
   W.host = pinned_existing(4 * (m + 3) + 1);
-  W.polled = W.host != nullptr;
+  W.polled = W.host && h->poll;
   if (!W.host) W.host = stage;
   return solve_forward(h, W, rhs, x, *prm, st, info);
 }

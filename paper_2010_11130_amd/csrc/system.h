@@ -212,6 +212,7 @@ struct ah_hier {
   const double* end_mat_t = nullptr;
   int g0 = 0;                  // lanes per row of the level-0 kernels (0: from the mean row length)
   int fbb = 1;                 // level-0 kernels by facet block rows where the rows are whole blocks
+  bool poll = true;            // FGMRES scalars by a polled flag (else by copies)
   int lpb = 0;                 // lanes per block row of those (0: from the mean blocks per row)
   int64_t dcgs_min = (int64_t)1 << 21;   // FGMRES uses delayed CGS2 from this many unknowns on
   int gc = 0;                  // lanes per row of the coarse-level kernels (0: from the mean row length)
