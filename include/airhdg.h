@@ -230,6 +230,10 @@ ah_status hdg_inflow_from_trace(const ah_system* prev, const double* lam_prev,
  * AH_EUNSUPPORTED); theta_r > 0 gives the restriction neighbourhoods their
  * own strength threshold (Section 4 uses 0.3 for R and 0.2 for the
  * coarsening), theta stays that of the coarsening and of P.
+ * The coarse end of the cycle (the first level of at most 2048 rows, 1024 for
+ * level 0, or the coarsest one) is kept as one dense FP64 matrix, with adjoint
+ * its transpose too: at most 34 MB each, 537 MB where the coarsening stalls at
+ * the dense limit of 8192 points.
  * Temporary device memory, beside what the hierarchy keeps: while a level is
  * coarsened 5 bytes per stored entry and about 35 per row of it, 65 from 2^20
  * rows on (block AIR, level 0: 13 per facet block and one per entry), 1 byte

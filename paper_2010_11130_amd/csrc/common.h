@@ -70,8 +70,8 @@ struct Arena {
   void release();
 };
 
-// Process-wide pinned host staging buffer (grown on demand, never freed)
-// for small device-to-host reads.
+// The calling thread's pinned host staging buffer (grown on demand, never
+// freed) for small device-to-host reads.
 double* pinned_scratch(size_t doubles);
 // The same buffer if it holds that many already, else null (allocates nothing).
 double* pinned_existing(size_t doubles);

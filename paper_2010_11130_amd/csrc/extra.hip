@@ -156,7 +156,7 @@ __device__ inline double gauss_arg(const double* x, const double* __restrict__ c
 // with every S-th centre, whose coordinates are wave-uniform (scalar) loads.
 // Bound by the FP64 vector units: about 24 operations per (point, centre)
 // pair against 8 (D + 1) bytes per point.  5.3M points x 256 centres: 1997 us
-// with the general exponential and a point per thread, 1278 us now.
+// with the general exponential and a point per thread, 1208 us now.
 template <int D, int P, int S>
 __global__ __launch_bounds__(256) void k_gauss(int64_t npts, const double* __restrict__ X, int K,
                                                const double* __restrict__ C, double inv2w2,
@@ -206,7 +206,7 @@ __global__ __launch_bounds__(256) void k_gauss(int64_t npts, const double* __res
 // halving the number of values a lane still carries (10 exchanges for eight
 // sums, not 48).  Bound like k_gauss.  One centre per block row instead read
 // X and y once per centre: 5567 us at 5.3M points x 256 centres (44 GB of
-// cache reads, 7.9 TB/s), 1431 us now.
+// cache reads, 7.9 TB/s), 1352 us now and 26 for the sums over blocks.
 template <int D, int P>
 __global__ __launch_bounds__(256) void k_gauss_t(int64_t npts, const double* __restrict__ X, int K,
                                                  const double* __restrict__ C, double inv2w2,

@@ -731,14 +731,6 @@ __global__ __launch_bounds__(256) void k_end_mv(int n, const double* __restrict_
   if (lane == 0) z[row] = (T)acc;
 }
 
-template <class T>
-__global__ void k_interp(int64_t n, const int32_t* __restrict__ pcol, const T* __restrict__ ec, T* __restrict__ x) {
-  int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i >= n) return;
-  int32_t c = pcol[i];
-  x[i] = c >= 0 ? ec[c] : (T)0;
-}
-
 // x = y = P e_c (one-point interpolation, both sweep buffers)
 template <class T>
 __global__ void k_interp2(int64_t n, const int32_t* __restrict__ pcol, const T* __restrict__ ec,
@@ -1300,10 +1292,9 @@ static ah_status csr_g(int G, int64_t n, const int64_t* rp, const int32_t* ci, c
   return AH_OK;
 }
 
-// Lanes per row of the facet-block kernels: about eight values per lane
-// (the row is one chain of dependent loads per lane, so short rows per lane
-// and more rows per wave keep more loads in flight).
-// Lanes per row of k_fb.  B = 3 takes a block per lane and step, so two lanes
+// Lanes per row of k_fb: about eight values per lane (the row is one chain of
+// dependent loads per lane, so short rows per lane and more rows per wave keep
+// more loads in flight).  B = 3 takes a block per lane and step, so two lanes
 // serve a row of six blocks (scalar AIR, 48^3 cube at p = 1: 65.8 ms with two,
 // 66.9 with four, 68.4 with eight lanes).
 static int fb_lanes(int64_t nvals, int64_t n, int B) {
@@ -1396,8 +1387,6 @@ static ah_status fbr_g(const AhLevel& L, const T* av, const T* ax, int64_t n, co
   return AH_OK;
 }
 
-// Lanes per block row of k_fbb from the mean number of off-diagonal blocks
-// per block row (C3: 6 -> 8 lanes).
 // Whether the level-0 kernels run by facet block rows (k_fbb): for odd B.  For
 // even B the rows' paired loads are faster on every size measured (p = 2: 64^2
 // slab SpMV 38.9 -> 18.7 us; mapped 36^3, forward and adjoint, 292 -> 253 ms;
@@ -1405,6 +1394,8 @@ static ah_status fbr_g(const AhLevel& L, const T* av, const T* ax, int64_t n, co
 // paired, and one gather of x for the whole block wins (96^3 SpMV 1.36 -> 1.0 ms).
 static bool by_blocks(const ah_hier* h, int B) { return h->fbb && B % 2; }
 
+// Lanes per block row of k_fbb from the mean number of off-diagonal blocks per
+// block row (six in 2-D + time: eight lanes).
 static int fbb_lanes(int64_t nvals, int64_t n, int B) {
   const double nb = n ? (double)nvals / ((double)n * B) : 0.0;
   if (nb <= 2.0) return 2;

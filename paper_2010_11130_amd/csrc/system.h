@@ -214,7 +214,14 @@ struct ah_hier {
   int fbb = 1;                 // level-0 kernels by facet block rows where the rows are whole blocks
   bool poll = true;            // FGMRES scalars by a polled flag (else by copies)
   int lpb = 0;                 // lanes per block row of those (0: from the mean blocks per row)
-  int64_t dcgs_min = (int64_t)1 << 21;   // FGMRES uses delayed CGS2 from this many unknowns on
+  // FGMRES uses delayed CGS2 from this many unknowns on: two passes over the
+  // basis per iteration instead of four, but a host round trip between them.
+  // ms per solve with CGS2 and with the delayed form (same iterations): slabs at
+  // p = 2, 0.34M 2.49 and 2.58, 0.77M 5.00 and 5.08, 1.4M 9.66 and 9.49; cubes at
+  // p = 1, scalar AIR, 0.29M 4.80 and 4.67, 0.63M 9.11 and 8.71, 2.0M 26.2 and
+  // 23.4; block AIR, 0.97M 9.84 and 9.29, 2.0M 19.4 and 17.4, 3.1M 32.4 and 27.8.
+  // So the line stands above the place where the two meet (0.3M to 1M).
+  int64_t dcgs_min = (int64_t)1 << 21;
   int gc = 0;                  // lanes per row of the coarse-level kernels (0: from the mean row length)
   int64_t list_min = (int64_t)1 << 16;   // coarse levels from this many rows on sweep their F and C lists
   ah::Arena arena;
