@@ -172,7 +172,9 @@ double* pinned_scratch(size_t doubles) {
   if (doubles > cap) {
     size_t want = std::max<size_t>(doubles, 8192);
     double* nb = nullptr;
-    if (hipHostMalloc((void**)&nb, want * sizeof(double), hipHostMallocCoherent) != hipSuccess) return nullptr;
+    // kernels store into it, on whichever device the thread uses next
+    if (hipHostMalloc((void**)&nb, want * sizeof(double), hipHostMallocCoherent | hipHostMallocPortable) != hipSuccess)
+      return nullptr;
     // the previous buffer is kept: a caller may still hold it
     buf = nb;
     cap = want;
