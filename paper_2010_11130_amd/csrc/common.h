@@ -127,13 +127,14 @@ struct RefTables {
 };
 
 ah_status build_ref_tables(int D, int p, RefTables& t);
-// The tables of (D, p) on the current device, built on first use; the upload is
-// complete on return and the tables never change.  With the library's own pool
-// the device copy is shared by every later caller (any thread, any stream): up
-// to six entries of at most 0.2 MB per device stay until ah_pool_trim; a system
-// keeps its own alive.  Where the caller's allocator is registered, the copy
-// lies in the arena, as all memory of the object it belongs to: memory from
-// that allocator is tied to a stream and must not outlive the object.
+// The tables of (D, p) on the current device, built on first use; they never
+// change.  With the library's own pool the device copy is shared by every later
+// caller (any thread, any stream: its upload is complete on return): up to six
+// entries of at most 0.2 MB per device stay until ah_pool_trim; a system keeps
+// its own alive.  Where the caller's allocator is registered, the copy lies in
+// the arena, as all memory of the object it belongs to (memory from that
+// allocator is tied to a stream and must not outlive the object), and is
+// uploaded on the arena's stream.
 ah_status ref_tables(int D, int p, Arena& ar, std::shared_ptr<const RefTables>& out);
 void ref_tables_release(int dev);
 void gauss_jacobi01(int n, double alpha, double* s, double* w);

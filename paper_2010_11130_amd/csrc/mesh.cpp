@@ -471,8 +471,12 @@ static size_t ref_place(RefTables& t, double* base) {
 
 static std::mutex g_ref_mu;
 typedef std::map<int, std::shared_ptr<const RefTables>> RefCache;
-static RefCache& ref_host() {    // without device copies, by D * 4 + p
-  static auto* c = new RefCache;
+struct RefHost {
+  RefTables t;                  // without device copies
+  std::vector<double> image;    // what is uploaded; stays, so an upload may read it later
+};
+static std::map<int, RefHost>& ref_host() {   // by D * 4 + p
+  static auto* c = new std::map<int, RefHost>;
   return *c;
 }
 static RefCache& ref_cache() {   // by device * 16 + D * 4 + p
@@ -492,40 +496,40 @@ ah_status ref_tables(int D, int p, Arena& ar, std::shared_ptr<const RefTables>& 
     std::lock_guard<std::mutex> lock(g_alloc_mu);
     own = !g_alloc;
   }
-  std::lock_guard<std::mutex> lock(g_ref_mu);
+  std::unique_lock<std::mutex> lock(g_ref_mu);
   if (own) {
     auto it = ref_cache().find(dev * 16 + D * 4 + p);
     if (it != ref_cache().end()) { out = it->second; return AH_OK; }
   }
-  auto& host = ref_host()[D * 4 + p];
-  if (!host) {
-    auto t = std::make_shared<RefTables>();
-    AH_TRY(build_ref_tables(D, p, *t));
-    host = t;
+  RefHost& host = ref_host()[D * 4 + p];
+  if (host.image.empty()) {
+    AH_TRY(build_ref_tables(D, p, host.t));
+    host.image.assign(ref_place(host.t, nullptr), 0.0);
+    size_t at = 0;
+    for (auto& x : ref_parts(host.t)) {
+      std::copy(x.first->begin(), x.first->end(), host.image.begin() + at);
+      at += (x.first->size() + 31) & ~size_t(31);
+    }
   }
-  auto t = std::make_shared<RefTables>(*host);
-  const size_t size = ref_place(*t, nullptr);
+  auto t = std::make_shared<RefTables>(host.t);
+  const size_t bytes = host.image.size() * sizeof(double);
   double* base = nullptr;
   if (own) {
-    const hipError_t e = malloc_or_release((void**)&base, size * sizeof(double), dev);
+    const hipError_t e = malloc_or_release((void**)&base, bytes, dev);
     if (e != hipSuccess) {
       (void)hipGetLastError();
-      set_error("device allocation of %zu bytes failed: %s", size * sizeof(double), hipGetErrorString(e));
+      set_error("device allocation of %zu bytes failed: %s", bytes, hipGetErrorString(e));
       return AH_ENOMEM;
     }
     t->d_all = base;
-  } else {
-    AH_TRY(ar.get(&base, size));
-  }
-  ref_place(*t, base);
-  std::vector<double> all(size, 0.0);
-  for (auto& x : ref_parts(*t)) std::copy(x.first->begin(), x.first->end(), all.begin() + (*x.second - base));
-  if (own) {
-    AH_HIP(hipMemcpy(base, all.data(), size * sizeof(double), hipMemcpyHostToDevice));
+    ref_place(*t, base);
+    AH_HIP(hipMemcpy(base, host.image.data(), bytes, hipMemcpyHostToDevice));
     ref_cache()[dev * 16 + D * 4 + p] = t;
   } else {
-    AH_HIP(hipMemcpyAsync(base, all.data(), size * sizeof(double), hipMemcpyHostToDevice, ar.stream));
-    AH_HIP(hipStreamSynchronize(ar.stream));   // all goes away
+    lock.unlock();   // the allocator is the caller's code
+    AH_TRY(ar.get(&base, host.image.size()));
+    ref_place(*t, base);
+    AH_HIP(hipMemcpyAsync(base, host.image.data(), bytes, hipMemcpyHostToDevice, ar.stream));
   }
   out = t;
   return AH_OK;
